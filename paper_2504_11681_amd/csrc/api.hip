@@ -3,6 +3,7 @@
 #include "common.h"
 #include "fused1d.h"
 #include "fused2d.h"
+#include "matdft.h"
 #include "pruned1d.h"
 #include "staged.h"
 
@@ -193,7 +194,13 @@ tfno_status run(const Shape &req, Variant variant, const void *x, const void *W,
     c64 *yc = (c64 *)y;
     hipError_t e;
 
-    if (staged) {
+    const bool odd = !is_pow2(sh.N1) || !is_pow2(sh.N2);
+    if (staged && odd && !contraction_forced_f32() &&
+        matdft_workspace_bytes(B, C_in, C_out, sh.N1, sh.N2, sh.K1, sh.K2) <= workspace_for(req, (int)variant, B, C_in, C_out)) {
+        // a side that is no power of two: pruned transforms as contractions on the matrix pipe, within the workspace of
+        // the staged pipeline (whose direct sums over all N x N terms remain for batches of fewer than 128 points)
+        e = matdft_conv(xc, Wc, yc, B, C_in, C_out, sh.N1, sh.N2, sh.K1, sh.K2, (c64 *)ws, s);
+    } else if (staged) {
         e = staged_conv(dims, xc, Wc, yc, B, C_in, C_out, sh.N1, sh.N2, sh.K1, sh.K2, (c64 *)ws, s);
     } else if (variant == PRUNED) {
         e = pruned1d_launch(xc, Wc, yc, B, C_in, C_out, N, K, keep2, (c64 *)ws, s);

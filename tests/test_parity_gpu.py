@@ -245,6 +245,40 @@ def test_staged_lengths_that_are_not_powers_of_two(gpu, oracle_mod):
     check(run_gpu(gpu, "spectral_conv1d_auto", x, W, 40), want, "auto, N = 300")
 
 
+# the matrix transform that serves lengths with odd factors: remainders of its 16-element blocks on both sides (I, J % 16,
+# one step or two), edges of its 32-output tiles and of its groups of tiles per wave, pencil counts around 32 and around
+# the counts from which a wave takes more tiles, sums dealt out to 1, 4 and 8 waves, the direct sums of tiny fields.
+# (B, C_in, C_out, N, K)
+ODD_1D = [(1, 1, 1, 17, 17), (1, 2, 3, 127, 3), (2, 31, 33, 129, 31), (3, 11, 32, 144, 32), (1, 33, 1, 145, 33), (2, 5, 7, 257, 97),
+          (1, 40, 24, 271, 128), (2, 17, 9, 390, 129), (700, 16, 48, 136, 72), (1100, 32, 30, 40, 40), (1, 3, 2, 3000, 65),
+          (90, 3, 128, 100, 99), (4, 300, 5, 56, 8)]
+
+
+@pytest.mark.parametrize("shape", ODD_1D, ids=lambda s: "B%d_Ci%d_Co%d_N%d_K%d" % s)
+def test_1d_lengths_with_odd_factors(gpu, oracle_mod, shape):
+    B, Ci, Co, N, K = shape
+    say(f"[case] odd length {shape}")
+    x = inputs.make_x(1550 + N + K, B, Ci, (N,))
+    W = inputs.make_W(1550 + N + K, Ci, Co)
+    want, _ = oracle_mod.spectral_conv1d(x, W, K)
+    check(run_gpu(gpu, "spectral_conv1d_auto", x, W, K), want, "auto, odd length")
+
+
+# (B, C_in, C_out, N1, N2, K1, K2): odd sides on either axis or both, one side a power of two
+ODD_2D = [(2, 3, 2, 33, 31, 17, 16), (1, 2, 3, 3, 300, 2, 33), (2, 2, 2, 300, 5, 40, 5), (5, 7, 4, 64, 96, 64, 7), (3, 4, 5, 130, 32, 9, 32),
+          (9, 16, 16, 85, 85, 12, 12), (1, 1, 1, 9, 7, 9, 7)]
+
+
+@pytest.mark.parametrize("shape", ODD_2D, ids=lambda s: "B%d_Ci%d_Co%d_N%dx%d_K%dx%d" % s)
+def test_2d_sides_with_odd_factors(gpu, oracle_mod, shape):
+    B, Ci, Co, N1, N2, K1, K2 = shape
+    say(f"[case] odd sides {shape}")
+    x = inputs.make_x(1560 + N1 + K2, B, Ci, (N1, N2))
+    W = inputs.make_W(1560 + N1 + K2, Ci, Co)
+    want, _ = oracle_mod.spectral_conv2d_rect(x, W, K1, K2)
+    check(run_gpu_rect(gpu, "spectral_conv2d_rect_staged", x, W, K1, K2), want, "odd sides")
+
+
 def test_2d_staged_general_shape(gpu, oracle_mod):
     B, Ci, Co, N, K = 2, 3, 2, 32, 5
     x = inputs.make_x(9, B, Ci, (N, N))
