@@ -27,7 +27,7 @@ struct MatdftArgs {
 };
 
 // Which pairs of sides exist: ROWS -> SPEC, SPEC -> ROWS (1-D), ROWS -> ROWS (contiguous axis of a field),
-// STRIDED -> SPEC, SPEC -> STRIDED, STRIDED -> STRIDED (leading axis).
+// STRIDED -> SPEC, SPEC -> STRIDED (leading axis).
 hipError_t matdft_launch(MatdftSide in_side, MatdftSide out_side, MatdftArgs a, hipStream_t s);
 
 // The whole layer on fields N1 x N2 (1-D: N1 = K1 = 1) of any side lengths up to 4096: truncated transforms, the mode

@@ -55,7 +55,6 @@ hipError_t matdft_launch(MatdftSide in_side, MatdftSide out_side, MatdftArgs a, 
     case MD_SPEC * 4 + MD_ROWS: return pick_md<MD_SPEC, MD_ROWS>(a, s);
     case MD_STRIDED * 4 + MD_SPEC: return pick_md<MD_STRIDED, MD_SPEC>(a, s);
     case MD_SPEC * 4 + MD_STRIDED: return pick_md<MD_SPEC, MD_STRIDED>(a, s);
-    case MD_STRIDED * 4 + MD_STRIDED: return pick_md<MD_STRIDED, MD_STRIDED>(a, s);
     default: return hipErrorInvalidValue;
     }
 }

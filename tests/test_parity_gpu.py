@@ -348,6 +348,22 @@ def test_2d_strip_pipeline_on_request(gpu, oracle_mod, shape):
     check(run_gpu_rect(gpu, "spectral_conv2d_strips", x, W, K1, K2), want, "strips")
 
 
+# column kernels along the first axis: every length, mode counts at and one past the multiples of their first radix (8 for
+# 64 rows, else 16) where the pruned stage changes, the largest they take and one more (staged transform)
+COLS_2D = [(n1, k1) for n1, p in ((64, 8), (128, 16), (256, 16), (512, 16)) for k1 in (1, p, p + 1, 2 * p + 1, 4 * p + 1, 8 * p, 8 * p + 1)
+           if k1 <= n1]
+
+
+@pytest.mark.parametrize("shape", COLS_2D, ids=lambda s: "N%d_K%d" % s)
+def test_2d_strip_pipeline_column_kernels(gpu, oracle_mod, shape):
+    N1, K1 = shape
+    say(f"[case] column kernels {shape}")
+    x = inputs.make_x(460 + N1 + K1, 2, 3, (N1, 64))
+    W = inputs.make_W(460 + N1 + K1, 3, 2)
+    want, _ = oracle_mod.spectral_conv2d_rect(x, W, K1, 10)
+    check(run_gpu_rect(gpu, "spectral_conv2d_strips", x, W, K1, 10), want, "column kernels")
+
+
 @pytest.mark.parametrize("shape", RECT_STAGED_ONLY, ids=lambda s: "B%d_Ci%d_Co%d_N%dx%d_K%dx%d" % s)
 def test_2d_rect_staged_general_shapes(gpu, oracle_mod, shape):
     torch, binding = gpu
