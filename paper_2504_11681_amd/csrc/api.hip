@@ -218,9 +218,9 @@ tfno_status run(const Shape &req, Variant variant, const void *x, const void *W,
         a.Xh = (const c64 *)ws; a.Yh = (c64 *)ws;
         if (variant == FFT_GEMM) {
             e = fused1d_partial_launch(1, N, K, a, B, s);
-            if (e == hipSuccess) e = pruned1d_stages(PRUNED_INV, xc, Wc, yc, nullptr, (c64 *)ws, B, C_in, C_out, N, K, keep2, s);
+            if (e == hipSuccess) e = pruned1d_stages(PRUNED_INV, xc, Wc, yc, nullptr, (c64 *)ws, B, C_in, C_out, N, K, keep2, K, s);
         } else {
-            e = pruned1d_stages(PRUNED_FWD, xc, Wc, yc, (c64 *)ws, nullptr, B, C_in, C_out, N, K, keep2, s);
+            e = pruned1d_stages(PRUNED_FWD, xc, Wc, yc, (c64 *)ws, nullptr, B, C_in, C_out, N, K, keep2, K, s);
             if (e == hipSuccess) e = fused1d_partial_launch(2, N, K, a, B, s);
         }
     } else if (dims == 1) {
@@ -273,7 +273,7 @@ tfno_status run_permode(const Shape &req, const void *x, const void *W, void *y,
     if (st != TFNO_OK || empty) return st;
     Shape sh;                                               // the transform kernels' shape
     if (!kernel_shape(req, 6, &sh)) return TFNO_ERR_UNSUPPORTED;
-    const size_t pts = sh.pts(), M = sh.kpts();
+    const size_t pts = sh.pts();
     const size_t xb = sizeof(c64) * (size_t)B * C_in * pts, yb = sizeof(c64) * (size_t)B * C_out * pts;
     const size_t wb = sizeof(c64) * (size_t)C_in * C_out * req.kpts();
     void *wsp = nullptr;
@@ -285,21 +285,18 @@ tfno_status run_permode(const Shape &req, const void *x, const void *W, void *y,
     const float scale = 1.0f / ((float)sh.N1 * (float)sh.N2);
     hipError_t e;
     if (sh.dims == 1) {
-        const int N = sh.N2, K = sh.K2;
-        c64 *Yh = Xh + pruned1d_spectrum_elems(B, C_in, K);
-        const long long tiles = ((long long)B * K + 127) / 128;
-        e = pruned1d_stages(PRUNED_FWD, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, req.K2, s);
-        if (e == hipSuccess)
-            e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, K, tiles, K >= 128 ? K / 128 : 1, scale, K, 1, req.K2, s);
-        if (e == hipSuccess) e = pruned1d_stages(PRUNED_INV, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, K, s);
+        const int N = sh.N2, K = sh.K2, Mp = pruned1d_stride(N, req.K2);
+        c64 *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
+        e = pruned1d_stages(PRUNED_FWD, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, req.K2, Mp, s);
+        if (e == hipSuccess) e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, B, Mp, req.K2, scale, s);
+        if (e == hipSuccess) e = pruned1d_stages(PRUNED_INV, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, req.K2, Mp, s);
     } else {
-        c64 *Yh = Xh + (size_t)B * C_in * M;
+        const int Ma = req.K1 * req.K2, Mp = spectrum_stride(Ma);
+        c64 *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
         e = fused2d_images(-1, xc, Xh, (long long)B * C_in, C_in, sh.N1, sh.N2, sh.K1, sh.K2, req.K1, req.K2, false, 0, s);
+        if (e == hipSuccess) e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, B, Mp, Ma, scale, s);
         if (e == hipSuccess)
-            e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, (int)M, (long long)B * (long long)(M / 128), (int)(M / 128), scale,
-                                     sh.K2, req.K1, req.K2, s);
-        if (e == hipSuccess)
-            e = fused2d_images(+1, Yh, yc, (long long)B * C_out, C_out, sh.N1, sh.N2, sh.K1, sh.K2, sh.K1, sh.K2, false, 0, s);
+            e = fused2d_images(+1, Yh, yc, (long long)B * C_out, C_out, sh.N1, sh.N2, sh.K1, sh.K2, req.K1, req.K2, false, 0, s);
     }
     return e == hipSuccess ? TFNO_OK : TFNO_ERR_HIP;
 }
@@ -360,15 +357,13 @@ tfno_status run_fno2d(const void *x, const void *W, void *y, int B, int C_in, in
     tfno_status st = check_workspace(fused2d_workspace_bytes(B, C_in, C_out, K1, K2), x, xb, W, wb, y, yb, &wsp);
     if (st != TFNO_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    const size_t M = (size_t)K1 * K2;
-    c64 *Xh = (c64 *)wsp, *Yh = Xh + (size_t)B * C_in * M;
+    const int Ma = 2 * M1 * M2, Mp = spectrum_stride(Ma);
+    c64 *Xh = (c64 *)wsp, *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
     const float scale = 2.0f / ((float)N1 * (float)N2);     // C2R along the last axis: twice the real part
     hipError_t e = fused2d_images(-1, (const c64 *)x, Xh, (long long)B * C_in, C_in, N1, N2, K1, K2, 2 * M1, M2, true, M1, s);
+    if (e == hipSuccess) e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
     if (e == hipSuccess)
-        e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, (int)M, (long long)B * (long long)(M / 128),
-                                 (int)(M / 128), scale, K2, 2 * M1, M2, s);
-    if (e == hipSuccess)
-        e = fused2d_images(+1, Yh, (c64 *)y, (long long)B * C_out, C_out, N1, N2, K1, K2, K1, K2, true, M1, s);
+        e = fused2d_images(+1, Yh, (c64 *)y, (long long)B * C_out, C_out, N1, N2, K1, K2, 2 * M1, M2, true, M1, s);
     return e == hipSuccess ? TFNO_OK : TFNO_ERR_HIP;
 }
 
@@ -397,14 +392,12 @@ tfno_status run_fno1d(const void *x, const void *W, void *y, int B, int C_in, in
     tfno_status st = check_workspace(pruned1d_workspace_bytes(B, C_in, C_out, K), x, xb, W, wb, y, yb, &wsp);
     if (st != TFNO_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    c64 *Xh = (c64 *)wsp, *Yh = Xh + pruned1d_spectrum_elems(B, C_in, K);
-    const long long tiles = ((long long)B * K + 127) / 128;
-    hipError_t e = pruned1d_real_stages(PRUNED_FWD, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, M, s);
+    const int Mp = pruned1d_stride(N, M);
+    c64 *Xh = (c64 *)wsp, *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
+    hipError_t e = pruned1d_real_stages(PRUNED_FWD, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, M, Mp, s);
+    if (e == hipSuccess) e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, B, Mp, M, 2.0f / (float)N, s);
     if (e == hipSuccess)
-        e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, K, tiles, K >= 128 ? K / 128 : 1, 2.0f / (float)N, K,
-                                 1, M, s);
-    if (e == hipSuccess)
-        e = pruned1d_real_stages(PRUNED_INV, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, K, s);
+        e = pruned1d_real_stages(PRUNED_INV, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, M, Mp, s);
     return e == hipSuccess ? TFNO_OK : TFNO_ERR_HIP;
 }
 

@@ -6,36 +6,42 @@
 
 namespace tfno {
 
-hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, int M, long long num_tiles,
-                                int TPI, float scale, int K2p, int K1a, int K2a, hipStream_t s)
+template <int BT, int OT>
+static void launch_f32(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, long long B, int Mp, int Ma, float scale, hipStream_t s)
 {
-    if (num_tiles <= 0) return hipSuccess;
-    if (TPI < 1 || M < 1 || (long long)TPI * 128 > (long long)M + 127) return hipErrorInvalidValue;
-    if (K2p < 1 || M % K2p != 0 || K1a < 1 || K1a > M / K2p || K2a < 1 || K2a > K2p) return hipErrorInvalidValue;
-    const long long per = (num_tiles + TPI - 1) / TPI;      // tiles that hold the same modes
-    // Matrix-pipe kernel: whole 128-mode tiles per batch element, enough channels and batch elements to fill its
-    // 32 x 32 x 8-channel tiles; everything else (and TFNO_CONTRACTION=f32) keeps the FP32 kernel.
-    if (M % 128 == 0 && TPI == M / 128 && C_in >= 16 && C_out >= 16 && per >= 16 && !contraction_forced_f32() &&
-        (per + 31) / 32 <= 65535 && (C_out + 31) / 32 <= 65535) {
-        const dim3 grid((unsigned)(TPI * 16), (unsigned)((per + 31) / 32), (unsigned)((C_out + 31) / 32));
+    const unsigned long long threads = (unsigned long long)((B + BT - 1) / BT) * Ma;
+    const unsigned slabs = (unsigned)((C_out + OT - 1) / OT);
+    const dim3 grid((unsigned)((threads + 255) / 256 * slabs));
+    hipLaunchKernelGGL((k_cgemm_permode<BT, OT>), grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, slabs);
+}
+
+hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, long long B, int Mp, int Ma,
+                                float scale, hipStream_t s)
+{
+    if (B <= 0) return hipSuccess;
+    if (Ma < 1 || Mp < Ma || Mp % 8 != 0) return hipErrorInvalidValue;
+    // Matrix-pipe kernel from 48 workgroups' worth of results on (its time hardly falls below that: B 64, 128 modes, 64 x 64
+    // channels, 524288 results: 15 us against 17 for the FP32 kernel; B 64, 32 modes, 128 x 128 channels, 262144 results: 21
+    // against 18 us; B 32, 16 modes, 64 x 64 channels: 13 against 7 us), with enough channels, outputs and batch elements for
+    // its 32 x 32 x 8-channel tiles; everything else (and TFNO_CONTRACTION=f32) runs the FP32 kernel.
+    const long long gy = (B + 31) / 32, gz = (C_out + 31) / 32;
+    if (C_in >= 16 && C_out >= 16 && B >= 16 && B * Ma * C_out >= 48 * 8192 && !contraction_forced_f32() && gy <= 65535 && gz <= 65535) {
+        const dim3 grid((unsigned)(Mp / 8), (unsigned)gy, (unsigned)gz);
         // without masks where every tile is full and the extents a workgroup addresses with 32-bit offsets (32 batch
         // elements of Xh, all of W) stay below 2^31 bytes
-        const bool fits32 = 32LL * TPI * C_in * 1024 < (1LL << 31) && (long long)C_in * C_out * K1a * K2a * 8 < (1LL << 31);
-        if (per % 32 == 0 && C_out % 32 == 0 && C_in % 8 == 0 && fits32)
-            hipLaunchKernelGGL(k_cgemm_permode_mfma<true>, grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, M, num_tiles, TPI, scale, K2p, K1a, K2a);
+        const bool fits32 = (32LL * Mp + 256) * C_in * 8 < (1LL << 31) && (long long)C_in * C_out * Ma * 8 < (1LL << 31);
+        if (B % 32 == 0 && C_out % 32 == 0 && C_in % 8 == 0 && fits32)
+            hipLaunchKernelGGL(k_cgemm_permode_mfma<true>, grid, dim3(512), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale);
         else
-            hipLaunchKernelGGL(k_cgemm_permode_mfma<false>, grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, M, num_tiles, TPI, scale, K2p, K1a, K2a);
+            hipLaunchKernelGGL(k_cgemm_permode_mfma<false>, grid, dim3(512), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale);
         return hipGetLastError();
     }
-    constexpr int OT = 8;
-    const unsigned gy = (unsigned)((C_out + 2 * OT - 1) / (2 * OT));
-    if (per >= 8) {
-        const dim3 grid((unsigned)(TPI * ((per + 7) / 8)), gy);
-        hipLaunchKernelGGL((k_cgemm_permode<8, OT>), grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, M, num_tiles, TPI, scale, K2p, K1a, K2a);
-    } else {
-        const dim3 grid((unsigned)(TPI * ((per + 1) / 2)), gy);
-        hipLaunchKernelGGL((k_cgemm_permode<2, OT>), grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, M, num_tiles, TPI, scale, K2p, K1a, K2a);
-    }
+    // Batch elements x outputs per thread: more reuse of what is loaded where that still gives every SIMD a wave.
+    auto waves = [&](int bt, int ot) { return (B + bt - 1) / bt * Ma * ((C_out + ot - 1) / ot) / 64; };
+    if (waves(8, 8) >= 1024) launch_f32<8, 8>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
+    else if (waves(4, 4) >= 1024) launch_f32<4, 4>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
+    else if (waves(2, 2) >= 256) launch_f32<2, 2>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
+    else launch_f32<1, 1>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
     return hipGetLastError();
 }
 

@@ -2,50 +2,42 @@
 // the Fourier layer as the FNO model defines it, Sec. 1 / Sec. 2.1 step 3; Sec. 3.1 treats the case of one shared
 // matrix, which the MFMA kernels of cgemm_modes_kernel.h cover):
 //
-//   Yh[b, o, m] = scale * sum_c Xh[b, c, m] * W[c, o, m]
+//   Yh[b, o, m] = scale * sum_c Xh[b, c, m] * W[c, o, m],   m < Ma
 //
-// on spectra in the mode-tile-major layout ([tile][channel][128 modes]).  There is no matrix shared between modes,
-// so nothing maps onto an MFMA tile without gathering one mode's values across the batch; the kernel instead keeps
-// a thread per mode (all global accesses are 128 consecutive modes of one channel: coalesced for Xh, W and Yh) and
-// reuses registers: a thread accumulates BT batch elements x OT outputs, so every W value loaded is used BT times
-// and every Xh value OT times.  Tiles t with the same t % TPI hold the same modes (TPI = tiles per batch element,
-// or 1 when several batch elements share a tile), which is what lets one W value serve BT tiles.
-// W is [C_in, C_out, K1a, K2a] for the modes actually kept; the spectra may be laid out for more (see below).
+// Spectra are mode-tile major ([tile][channel][128]) over the joint mode b Mp + m, W is [C_in, C_out, Ma].  FP32 kernel
+// for products too small for the matrix pipe (cgemm_permode_mfma_kernel.h): a thread owns one mode of BT batch elements
+// and OT outputs, so a W value loaded is used BT times and an Xh value OT times; the threads of a wave own consecutive
+// modes (coalesced runs of Ma) and, where Ma is short, of consecutive batch groups.  Bound by the latency of the loads:
+// U channels are in flight, and BT and OT are chosen small enough to give the chip a wave per SIMD (B 32, 16 modes, 64 x 64
+// channels: 51 -> 7 us against 8 x 8 per thread, which made 8 workgroups).
 #pragma once
 #include "common.h"
+#include <type_traits>
 
 namespace tfno {
 
 template <int BT, int OT>
 __global__ void __launch_bounds__(256, 2)
 k_cgemm_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__restrict__ Yh, int C_in, int C_out,
-                int M, long long num_tiles, int TPI, float scale, int K2p, int K1a, int K2a)
+                long long B, int Mp, int Ma, float scale, unsigned slabs)
 {
-    const int tid = threadIdx.x, i = tid & 127, half = tid >> 7;
-    const int r = (int)(blockIdx.x % (unsigned)TPI);
-    const long long grp = blockIdx.x / (unsigned)TPI;
-    const int m = (r * 128 + i) % M;                        // the mode this thread owns in every tile it visits
-    // The spectra are laid out for K1p x K2p modes (M = K1p K2p, the built kernel sizes), W for the K1a x K2a modes
-    // actually kept.  Surplus modes hold zeros in Xh; they read a clamped (valid) weight.
-    const int k1 = m / K2p, k2 = m % K2p;
-    const int Ma = K1a * K2a;
-    const int wm = (k1 < K1a ? k1 : K1a - 1) * K2a + (k2 < K2a ? k2 : K2a - 1);
-    const int o0 = ((int)blockIdx.y * 2 + half) * OT;
+    constexpr int U = BT + OT <= 2 ? 16 : BT + OT <= 4 ? 8 : BT + OT <= 8 ? 4 : 2;
+    const unsigned long long f = blockIdx.x / slabs * 256ULL + threadIdx.x;      // (slabs of OT outputs innermost)
+    const long long grp = (long long)(f / (unsigned)Ma), b0 = grp * BT;
+    const int m = (int)(f % (unsigned)Ma);
+    const int o0 = (int)(blockIdx.x % slabs) * OT;
+    if (b0 >= B) return;
 
+    auto spec = [&](long long b, int C) __attribute__((always_inline)) {   // element (b, channel 0, m)
+        const long long j = b * Mp + m;
+        return (j >> 7) * C * 128 + (j & 127);
+    };
     const c64 *xp[BT];
-    bool tv[BT];
 #pragma unroll
-    for (int bi = 0; bi < BT; ++bi) {
-        const long long t = r + (long long)TPI * (grp * BT + bi);
-        tv[bi] = t < num_tiles;
-        xp[bi] = Xh + ((tv[bi] ? t : r) * C_in) * 128 + i;   // tile r exists and holds the same modes
-    }
+    for (int bi = 0; bi < BT; ++bi) xp[bi] = Xh + spec(b0 + bi < B ? b0 + bi : B - 1, C_in);
     const c64 *wp[OT];
 #pragma unroll
-    for (int oi = 0; oi < OT; ++oi) {
-        const int o = o0 + oi < C_out ? o0 + oi : C_out - 1;
-        wp[oi] = W + (long long)o * Ma + wm;
-    }
+    for (int oi = 0; oi < OT; ++oi) wp[oi] = W + (long long)(o0 + oi < C_out ? o0 + oi : C_out - 1) * Ma + m;
     const long long wstep = (long long)C_out * Ma;
 
     c64 acc[BT][OT];
@@ -54,24 +46,32 @@ k_cgemm_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__re
 #pragma unroll
         for (int oi = 0; oi < OT; ++oi) acc[bi][oi] = make_float2(0.f, 0.f);
 
-#pragma unroll 2
-    for (int c = 0; c < C_in; ++c) {
-        c64 xv[BT], wv[OT];
+    auto block = [&](int c0, auto count) __attribute__((always_inline)) {
+        constexpr int n = decltype(count)::value;
+        c64 xv[n][BT], wv[n][OT];
 #pragma unroll
-        for (int oi = 0; oi < OT; ++oi) wv[oi] = wp[oi][c * wstep];
+        for (int u = 0; u < n; ++u) {
 #pragma unroll
-        for (int bi = 0; bi < BT; ++bi) xv[bi] = xp[bi][(long long)c * 128];
+            for (int oi = 0; oi < OT; ++oi) wv[u][oi] = wp[oi][(c0 + u) * wstep];
 #pragma unroll
-        for (int bi = 0; bi < BT; ++bi)
+            for (int bi = 0; bi < BT; ++bi) xv[u][bi] = xp[bi][(long long)(c0 + u) * 128];
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int oi = 0; oi < OT; ++oi) acc[bi][oi] = cmac(acc[bi][oi], xv[bi], wv[oi]);
-    }
+        for (int u = 0; u < n; ++u)
+#pragma unroll
+            for (int bi = 0; bi < BT; ++bi)
+#pragma unroll
+                for (int oi = 0; oi < OT; ++oi) acc[bi][oi] = cmac(acc[bi][oi], xv[u][bi], wv[u][oi]);
+    };
+    int c = 0;
+    for (; c + U <= C_in; c += U) block(c, std::integral_constant<int, U>{});
+    for (; c < C_in; ++c) block(c, std::integral_constant<int, 1>{});
 
 #pragma unroll
     for (int bi = 0; bi < BT; ++bi) {
-        if (!tv[bi]) continue;
-        const long long t = r + (long long)TPI * (grp * BT + bi);
-        c64 *yp = Yh + (t * C_out) * 128 + i;
+        if (b0 + bi >= B) continue;
+        c64 *yp = Yh + spec(b0 + bi, C_out);
 #pragma unroll
         for (int oi = 0; oi < OT; ++oi)
             if (o0 + oi < C_out) yp[(long long)(o0 + oi) * 128] = make_float2(acc[bi][oi].x * scale, acc[bi][oi].y * scale);

@@ -13,7 +13,8 @@ size_t fused2d_workspace_bytes(long long B, int C_in, int C_out, int K1, int K2)
 hipError_t fused2d_launch(const c64 *x, const c64 *W, c64 *y, long long B, int C_in, int C_out, int N1, int N2,
                           int K1, int K2, int k1_keep, int k2_keep, c64 *ws, hipStream_t s);
 // One of the two image kernels: dir < 0 forward x[images, N1, N2] -> Xh (C = C_in), dir > 0 inverse Yh -> y (C = C_out).
-// k1_keep, k2_keep (forward only): modes at or past them are written as zeros.
+// Only the first k1_keep x k2_keep modes of the kernels' K1 x K2 exist in the spectra (the others are not stored and read
+// as zeros): mode m = k1 k2_keep + k2 of batch element b at joint mode b spectrum_stride(k1_keep k2_keep) + m.
 // fno: the real-field variants (x, y float32 images; first-axis frequencies -h1 .. K1-h1-1 at positions 0 .. K1-1;
 // R2C / C2R along the last axis, the caller's contraction carries the scale 2 / (N1 N2)); h1 is ignored otherwise.
 hipError_t fused2d_images(int dir, const c64 *in, c64 *out, long long images, int C, int N1, int N2, int K1, int K2,
@@ -34,10 +35,13 @@ TFNO_DECLARE_IMAGES(fused2d_fno_images_n256);
 hipError_t cgemm_modes_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, float scale, long long tiles,
                               hipStream_t s);
 
-// Yh[t][o][i] = scale * sum_c Xh[t][c][i] * W[c][o][k1][k2] with an own weight matrix per mode; tile t, lane i holds
-// mode m = ((t % TPI) * 128 + i) % M = k1 K2p + k2 of the M = K1p K2p modes the spectra are laid out for, W is
-// [C_in, C_out, K1a, K2a] for the modes kept (K1a <= K1p, K2a <= K2p; the surplus modes of Xh hold zeros).
-hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, int M, long long num_tiles,
-                                int TPI, float scale, int K2p, int K1a, int K2a, hipStream_t s);
+// Yh[b][o][m] = scale * sum_c Xh[b][c][m] * W[c][o][m], m < Ma, with an own weight matrix per mode: W is [C_in, C_out, Ma],
+// the spectra are mode-tile major over the joint mode b Mp + m (Mp >= Ma, a multiple of 8; results at m >= Ma are
+// unspecified).
+hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, long long B, int Mp, int Ma,
+                                float scale, hipStream_t s);
+
+// Modes per batch element in the joint mode index of a spectrum that keeps `modes` of them: 64-byte rows.
+inline int spectrum_stride(int modes) { return (modes + 7) & ~7; }
 
 }  // namespace tfno

@@ -64,13 +64,14 @@ hipError_t fused2d_images(int dir, const c64 *in, c64 *out, long long images, in
 hipError_t fused2d_launch(const c64 *x, const c64 *W, c64 *y, long long B, int C_in, int C_out, int N1, int N2,
                           int K1, int K2, int k1_keep, int k2_keep, c64 *ws, hipStream_t s)
 {
-    const int M = K1 * K2;                                  // a multiple of 128
-    c64 *Xh = ws, *Yh = ws + (size_t)B * C_in * M;
+    // joint modes b Mp + m in whole tiles of 128: at most the K1 x K2 (a multiple of 128) modes per element of the workspace
+    const long long tiles = (B * spectrum_stride(k1_keep * k2_keep) + 127) / 128;
+    c64 *Xh = ws, *Yh = ws + (size_t)tiles * 128 * C_in;
     hipError_t e = fused2d_images(-1, x, Xh, B * C_in, C_in, N1, N2, K1, K2, k1_keep, k2_keep, false, 0, s);
     if (e != hipSuccess) return e;
-    e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / ((float)N1 * (float)N2), B * (M / 128), s);
+    e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / ((float)N1 * (float)N2), tiles, s);
     if (e != hipSuccess) return e;
-    return fused2d_images(+1, Yh, y, B * C_out, C_out, N1, N2, K1, K2, K1, K2, false, 0, s);
+    return fused2d_images(+1, Yh, y, B * C_out, C_out, N1, N2, K1, K2, k1_keep, k2_keep, false, 0, s);
 }
 
 }  // namespace tfno

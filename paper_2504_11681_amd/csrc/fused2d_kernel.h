@@ -5,8 +5,8 @@
 //
 //   k_fwd2d   one workgroup per input image x[b, c]: truncated, output-pruned 2-D forward transform
 //             -> Xh[b, c, k1, k2], k1 < K1, k2 < K2                     (reads N1*N2, writes K1*K2)
-//             stored mode-tile major, [b][m / 128][c][m % 128] with m = k1 K2 + k2, so that the CGEMM streams
-//             one contiguous [C, 128] block per workgroup
+//             stored mode-tile major, [j / 128][c][j % 128] over the joint mode j = b Mp + k1 K2 + k2 (of the modes
+//             that are kept; Mp = their count rounded up to 8), so that the CGEMM streams contiguous [C, 128] blocks
 //   k_cgemm_modes   (cgemm_modes_kernel.h) Yh[b, o, m] = sum_c Xh[b, c, m] * W[c, o] / (N1 N2) over the K1*K2
 //             retained modes; one W for all modes (Sec. 3.1)
 //   k_inv2d   one workgroup per output image: zero-padded, input-pruned 2-D inverse -> y[b, o]
@@ -114,10 +114,12 @@ __device__ __forceinline__ Lds2d lds_setup(unsigned char *raw, int tid)
 }
 
 // ------------------------------------------------------------------------------------------------ forward
-// element offset of (channel c, mode m) of batch element b in a mode-tile-major spectrum buffer
-__device__ __forceinline__ long long spec_index(long long b, int c, int C, int m, int M)
+// element offset of (channel c, mode m) of batch element b in a mode-tile-major spectrum buffer with Mp modes per
+// batch element (128 consecutive joint modes b Mp + m make a tile)
+__device__ __forceinline__ long long spec_index(long long b, int c, int C, int m, int Mp)
 {
-    return ((b * (M / 128) + m / 128) * C + c) * 128 + m % 128;
+    const long long j = b * Mp + m;
+    return ((j >> 7) * C + c) * 128 + (j & 127);
 }
 
 // FNO (both kernels): the layer as FNO models apply it to real fields.  x and y are float32 images; the first axis
@@ -128,7 +130,7 @@ __device__ __forceinline__ long long spec_index(long long b, int c, int C, int m
 // zero-padded complex inverse once the k2 = 0 column is halved (done here, at the spectrum store).
 template <int N1, int N2, int K1, int K2, bool FNO = false>
 __global__ void __launch_bounds__((Cfg2d<N1, N2, K1, K2, N2 == 256>::NT), (Cfg2d<N1, N2, K1, K2, N2 == 256>::WG_PER_CU))
-k_fwd2d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C_in, int K1_keep, int K2_keep, int h1)
+k_fwd2d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C_in, int K1_keep, int K2_keep, int Mp, int h1)
 {
     using C = Cfg2d<N1, N2, K1, K2, N2 == 256>;
     constexpr int LPR = C::LPR, RPS = C::RPS, S = C::S, SWEEPS = C::SWEEPS, KH = C::KH, CPL = C::CPL;
@@ -283,10 +285,8 @@ k_fwd2d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C_in, int K1_keep, 
                 if constexpr (FNO) {
                     if (k2 == 0) val = make_float2(0.5f * val.x, 0.5f * val.y);
                 }
-                // (modes at or past K1_keep x K2_keep are written as zeros: truncation finer than the kernel's)
-                if (k1 < K1)
-                    Xh[spec_index(b, c, C_in, k1 * K2 + k2, K1 * K2)] =
-                        (k1 < K1_keep && k2 < K2_keep) ? val : make_float2(0.f, 0.f);
+                // (truncation finer than the kernel's: only the K1_keep x K2_keep block exists in the spectrum)
+                if (k1 < K1_keep && k2 < K2_keep) Xh[spec_index(b, c, C_in, k1 * K2_keep + k2, Mp)] = val;
             }
     }
 }
@@ -294,7 +294,7 @@ k_fwd2d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C_in, int K1_keep, 
 // ------------------------------------------------------------------------------------------------ inverse
 template <int N1, int N2, int K1, int K2, bool FNO = false>
 __global__ void __launch_bounds__((Cfg2d<N1, N2, K1, K2, false>::NT), (Cfg2d<N1, N2, K1, K2, false>::WG_PER_CU))
-k_inv2d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C_out, int h1)
+k_inv2d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C_out, int K1_keep, int K2_keep, int Mp, int h1)
 {
     using C = Cfg2d<N1, N2, K1, K2, false>;
     constexpr int LPR = C::LPR, RPS = C::RPS, S = C::S, SWEEPS = C::SWEEPS, KH = C::KH, CPL = C::CPL;
@@ -322,8 +322,8 @@ k_inv2d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C_out, int h1)
 #pragma unroll
             for (int ka = 0; ka < RPL; ++ka) {
                 const int k1 = FNO ? (ka + RPL * kb + h1) % RP + RP * m : ka + RPL * kb + RP * m;   // position in the block
-                const bool ok = col_on && k1 < K1;
-                c64 v = Yh[spec_index(b, o, C_out, ok ? k1 * K2 + k2 : 0, K1 * K2)];
+                const bool ok = k2 < K2_keep && k1 < K1_keep;
+                c64 v = Yh[spec_index(b, o, C_out, ok ? k1 * K2_keep + k2 : 0, Mp)];
                 Y[m * RPL + ka] = ok ? v : make_float2(0.f, 0.f);
             }
     }

@@ -51,14 +51,20 @@ size_t pruned1d_workspace_bytes(long long B, int C_in, int C_out, int K)
     return sizeof(c64) * (size_t)mode_tiles(B, K) * 128 * ((size_t)C_in + C_out);
 }
 
-size_t pruned1d_spectrum_elems(long long B, int C, int K) { return (size_t)mode_tiles(B, K) * 128 * (size_t)C; }
+size_t pruned1d_spectrum_elems(long long B, int C, int Mp) { return (size_t)mode_tiles(B, Mp) * 128 * (size_t)C; }
+
+int pruned1d_stride(int N, int K_keep)
+{
+    const int N1 = N / 256;                                 // long pencils: whole columns of the N1 x 256 array
+    return N >= 2048 ? (K_keep + N1 - 1) / N1 * N1 : spectrum_stride(K_keep);
+}
 
 template <int N, int K, bool REAL = false>
 static hipError_t launch_nk(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
-                            int C_out, int K_keep, hipStream_t s)
+                            int C_out, int K_keep, int Mp, hipStream_t s)
 {
     using Cf = CfgP1<N, K>;
-    const long long tiles = mode_tiles(B, K);
+    const long long tiles = mode_tiles(B, Mp);
     const long long pin = B * C_in, pout = B * C_out;
     const long long sin = (pin + Cf::PPS - 1) / Cf::PPS, sout = (pout + Cf::PPS - 1) / Cf::PPS;
     // a few sweeps per workgroup amortise the twiddle tables and keep a prefetch in flight
@@ -68,13 +74,37 @@ static hipError_t launch_nk(int stages, const c64 *x, const c64 *W, c64 *y, c64 
     const unsigned gout = REAL ? balanced_grid<&k_inv1d<N, K, REAL>>(sout, 256) : (unsigned)(sout < 1024 ? sout : 1024);
     hipError_t e = hipSuccess;
     if (stages & PRUNED_FWD) {
-        hipLaunchKernelGGL((k_fwd1d<N, K, REAL>), dim3(gin), dim3(256), 0, s, x, Xh, C_in, pin, K_keep);
+        hipLaunchKernelGGL((k_fwd1d<N, K, REAL>), dim3(gin), dim3(256), 0, s, x, Xh, C_in, pin, K_keep, Mp);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (stages & PRUNED_GEMM)
         if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / (float)N, tiles, s)) != hipSuccess) return e;
     if (stages & PRUNED_INV) {
-        hipLaunchKernelGGL((k_inv1d<N, K, REAL>), dim3(gout), dim3(256), 0, s, (const c64 *)Yh, y, C_out, pout);
+        hipLaunchKernelGGL((k_inv1d<N, K, REAL>), dim3(gout), dim3(256), 0, s, (const c64 *)Yh, y, C_out, pout, K_keep, Mp);
+        e = hipGetLastError();
+    }
+    return e;
+}
+
+template <int N1, int K2, bool ALL>
+static hipError_t launch_long(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
+                              int C_out, int K_keep, int Mp, hipStream_t s)
+{
+    using Cf = CfgLong<N1, K2>;
+    const long long tiles = mode_tiles(B, Mp);
+    const int K2k = Mp / N1;
+    const long long pin = B * C_in, pout = B * C_out;
+    const long long sin = (pin + Cf::G - 1) / Cf::G, sout = (pout + Cf::G - 1) / Cf::G;
+    const unsigned gin = balanced_grid<&k_fwd1d_long<N1, K2, ALL>>(sin, 256), gout = (unsigned)(sout < 2048 ? sout : 2048);
+    hipError_t e = hipSuccess;
+    if (stages & PRUNED_FWD) {
+        hipLaunchKernelGGL((k_fwd1d_long<N1, K2, ALL>), dim3(gin), dim3(256), 0, s, x, Xh, C_in, pin, K_keep, K2k);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (stages & PRUNED_GEMM)
+        if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / (float)Cf::N, tiles, s)) != hipSuccess) return e;
+    if (stages & PRUNED_INV) {
+        hipLaunchKernelGGL((k_inv1d_long<N1, K2, ALL>), dim3(gout), dim3(256), 0, s, (const c64 *)Yh, y, C_out, pout, K2k);
         e = hipGetLastError();
     }
     return e;
@@ -82,88 +112,74 @@ static hipError_t launch_nk(int stages, const c64 *x, const c64 *W, c64 *y, c64 
 
 template <int N1, int K2>
 static hipError_t launch_long(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
-                              int C_out, int K_keep, hipStream_t s)
+                              int C_out, int K_keep, int Mp, hipStream_t s)
 {
-    using Cf = CfgLong<N1, K2>;
-    const long long tiles = mode_tiles(B, Cf::K);
-    const long long pin = B * C_in, pout = B * C_out;
-    const long long sin = (pin + Cf::G - 1) / Cf::G, sout = (pout + Cf::G - 1) / Cf::G;
-    const unsigned gin = balanced_grid<&k_fwd1d_long<N1, K2>>(sin, 256), gout = (unsigned)(sout < 2048 ? sout : 2048);
-    hipError_t e = hipSuccess;
-    if (stages & PRUNED_FWD) {
-        hipLaunchKernelGGL((k_fwd1d_long<N1, K2>), dim3(gin), dim3(256), 0, s, x, Xh, C_in, pin, K_keep);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (stages & PRUNED_GEMM)
-        if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / (float)Cf::N, tiles, s)) != hipSuccess) return e;
-    if (stages & PRUNED_INV) {
-        hipLaunchKernelGGL((k_inv1d_long<N1, K2>), dim3(gout), dim3(256), 0, s, (const c64 *)Yh, y, C_out, pout);
-        e = hipGetLastError();
-    }
-    return e;
+    if (Mp == N1 * K2) return launch_long<N1, K2, true>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    return launch_long<N1, K2, false>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
 }
 
 template <int N1>
 static hipError_t launch_long_n(int K2, int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B,
-                                int C_in, int C_out, int K_keep, hipStream_t s)
+                                int C_in, int C_out, int K_keep, int Mp, hipStream_t s)
 {
     switch (K2) {
-    case 16: return launch_long<N1, 16>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 32: return launch_long<N1, 32>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 64: return launch_long<N1, 64>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 128: return launch_long<N1, 128>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 256: return launch_long<N1, 256>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
+    case 16: return launch_long<N1, 16>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 32: return launch_long<N1, 32>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 64: return launch_long<N1, 64>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 128: return launch_long<N1, 128>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 256: return launch_long<N1, 256>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 template <int N, bool REAL = false>
 static hipError_t launch_n(int K, int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B,
-                           int C_in, int C_out, int K_keep, hipStream_t s)
+                           int C_in, int C_out, int K_keep, int Mp, hipStream_t s)
 {
     constexpr int LPR = N / 16;
     switch (K) {
-    case 16: return launch_nk<N, 16, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 32: if constexpr (LPR >= 2) return launch_nk<N, 32, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s); break;
-    case 64: if constexpr (LPR >= 4) return launch_nk<N, 64, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s); break;
-    case 128: if constexpr (LPR >= 8) return launch_nk<N, 128, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s); break;
-    case 256: if constexpr (LPR >= 16) return launch_nk<N, 256, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s); break;
+    case 16: return launch_nk<N, 16, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 32: if constexpr (LPR >= 2) return launch_nk<N, 32, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s); break;
+    case 64: if constexpr (LPR >= 4) return launch_nk<N, 64, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s); break;
+    case 128: if constexpr (LPR >= 8) return launch_nk<N, 128, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s); break;
+    case 256: if constexpr (LPR >= 16) return launch_nk<N, 256, REAL>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s); break;
     default: break;
     }
     return hipErrorInvalidValue;
 }
 
 hipError_t pruned1d_stages(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
-                           int C_out, int N, int K, int K_keep, hipStream_t s)
+                           int C_out, int N, int K, int K_keep, int Mp, hipStream_t s)
 {
-    if (!pruned1d_supported(N, K) || K_keep < 1 || K_keep > K) return hipErrorInvalidValue;
+    if (!pruned1d_supported(N, K) || K_keep < 1 || K_keep > K || Mp > K || (Mp != K && Mp != pruned1d_stride(N, K_keep)))
+        return hipErrorInvalidValue;
     switch (N) {
-    case 64: return launch_n<64>(K, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 128: return launch_n<128>(K, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 256: return launch_n<256>(K, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
+    case 64: return launch_n<64>(K, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 128: return launch_n<128>(K, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 256: return launch_n<256>(K, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
     case 1024:
-        if (K == 64) return launch_nk<1024, 64>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-        return launch_nk<1024, 128>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 2048: return launch_long_n<8>(K / 8, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 4096: return launch_long_n<16>(K / 16, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, s);
+        if (K == 64) return launch_nk<1024, 64>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+        return launch_nk<1024, 128>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 2048: return launch_long_n<8>(K / 8, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 4096: return launch_long_n<16>(K / 16, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t pruned1d_real_stages(int stages, const float *x, float *y, c64 *Xh, c64 *Yh, long long B, int C_in, int C_out,
-                                int N, int K, int K_keep, hipStream_t s)
+                                int N, int K, int K_keep, int Mp, hipStream_t s)
 {
-    if (!pruned1d_supported(N, K) || N > 1024 || K_keep < 1 || K_keep > K || (stages & PRUNED_GEMM))
+    if (!pruned1d_supported(N, K) || N > 1024 || K_keep < 1 || K_keep > K || Mp > K || Mp < K_keep || (stages & PRUNED_GEMM))
         return hipErrorInvalidValue;
     const c64 *xc = reinterpret_cast<const c64 *>(x);
     c64 *yc = reinterpret_cast<c64 *>(y);
     switch (N) {
-    case 64: return launch_n<64, true>(K, stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 128: return launch_n<128, true>(K, stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, s);
-    case 256: return launch_n<256, true>(K, stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, s);
+    case 64: return launch_n<64, true>(K, stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 128: return launch_n<128, true>(K, stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    case 256: return launch_n<256, true>(K, stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
     case 1024:
-        if (K == 64) return launch_nk<1024, 64, true>(stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, s);
-        return launch_nk<1024, 128, true>(stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, s);
+        if (K == 64) return launch_nk<1024, 64, true>(stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+        return launch_nk<1024, 128, true>(stages, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -171,8 +187,9 @@ hipError_t pruned1d_real_stages(int stages, const float *x, float *y, c64 *Xh, c
 hipError_t pruned1d_launch(const c64 *x, const c64 *W, c64 *y, long long B, int C_in, int C_out, int N, int K,
                            int K_keep, c64 *ws, hipStream_t s)
 {
-    return pruned1d_stages(PRUNED_FWD | PRUNED_GEMM | PRUNED_INV, x, W, y, ws, ws + pruned1d_spectrum_elems(B, C_in, K),
-                           B, C_in, C_out, N, K, K_keep, s);
+    const int Mp = pruned1d_stride(N, K_keep);
+    return pruned1d_stages(PRUNED_FWD | PRUNED_GEMM | PRUNED_INV, x, W, y, ws, ws + pruned1d_spectrum_elems(B, C_in, Mp),
+                           B, C_in, C_out, N, K, K_keep, Mp, s);
 }
 
 }  // namespace tfno

@@ -83,14 +83,15 @@ __device__ __forceinline__ int p1_slot(int c, int p)
 }
 
 // ------------------------------------------------------------------------------------------------ forward
-// x: [npencils, N] contiguous (pencil q = b * C + c).  Xh: mode-tile major, joint mode m = b K + k.
+// x: [npencils, N] contiguous (pencil q = b * C + c).  Xh: mode-tile major, joint mode m = b Mp + k: bins below K_keep are
+// stored, bins K_keep .. Mp-1 are zeros, the kernel's bins from Mp on do not exist there.
 // REAL (both kernels): pencils of float32 values.  The forward transform of a real pencil is the complex one with a
 // zero imaginary part (its first K bins are the R2C bins); bin 0 is stored halved so that the inverse kernel, which
 // stores the real part of the zero-padded complex inverse, yields the C2R transform when the contraction in between
 // carries the scale 2 / N.
 template <int N, int K, bool REAL = false>
 __global__ void __launch_bounds__(256)
-k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npencils, int K_keep)
+k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npencils, int K_keep, int Mp)
 {
     using Cf = CfgP1<N, K>;
     constexpr int LPR = Cf::LPR, PPS = Cf::PPS, KH = Cf::KH, CPL = Cf::CPL, OPL = Cf::OPL;
@@ -154,12 +155,12 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
                 }, xo);
                 if (ok) {
 #pragma unroll
-                    for (int kh = 0; kh < KH; ++kh) {      // bins K_keep .. K-1: truncation finer than the kernel's K
+                    for (int kh = 0; kh < KH; ++kh) {      // bins K_keep .. Mp-1: zeros; from Mp on: not stored
                         c64 val = kl + 16 * kh < K_keep ? xo[kh] : make_float2(0.f, 0.f);
                         if constexpr (REAL) {
                             if (kl + 16 * kh == 0) val = make_float2(0.5f * val.x, 0.5f * val.y);
                         }
-                        Xh[spec1d_index(b * K + kl + 16 * kh, ch, C)] = val;
+                        if (kl + 16 * kh < Mp) Xh[spec1d_index(b * Mp + kl + 16 * kh, ch, C)] = val;
                     }
                 }
             }
@@ -198,7 +199,7 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
                     if constexpr (REAL) {
                         if (k == 0) val = make_float2(0.5f * val.x, 0.5f * val.y);
                     }
-                    Xh[spec1d_index(b * K + k, ch, C)] = val;
+                    if (k < Mp) Xh[spec1d_index(b * Mp + k, ch, C)] = val;
                 }
             }
         }
@@ -213,10 +214,10 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
 }
 
 // ------------------------------------------------------------------------------------------------ inverse
-// Yh: mode-tile major (joint mode m = b K + k, C channels).  y: [npencils, N] contiguous (pencil q = b * C + o).
+// Yh: mode-tile major (joint mode m = b Mp + k, C channels); bins from K_keep on are zeros.  y: [npencils, N] contiguous (pencil q = b * C + o).
 template <int N, int K, bool REAL = false>
 __global__ void __launch_bounds__(256)
-k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npencils)
+k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npencils, int K_keep, int Mp)
 {
     using Cf = CfgP1<N, K>;
     constexpr int LPR = Cf::LPR, PPS = Cf::PPS, KH = Cf::KH, CPL = Cf::CPL, NY = Cf::NY;
@@ -239,7 +240,9 @@ k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npenci
 #pragma unroll
             for (int kh = 0; kh < KH; ++kh) {
                 const int kl = WIDE ? kl_w : p + LPR * i;
-                yin[i * KH + kh] = Yh[spec1d_index(b * K + kl + 16 * kh, ch, C)];
+                const int k = kl + 16 * kh;
+                const c64 val = Yh[spec1d_index(b * Mp + (k < K_keep ? k : 0), ch, C)];
+                yin[i * KH + kh] = k < K_keep ? val : make_float2(0.f, 0.f);
             }
     };
     auto stage = [&](long long sweep, auto refill, long long next_sweep) __attribute__((always_inline)) {

@@ -17,8 +17,8 @@
 //            twiddle, transpose through a 16-lane patch, pruned 16-point DFT)
 //
 // A sweep of the workgroup is 16 rows: one pencil of 4096 points or two of 2048.  The inverse kernel runs the
-// transposed network.  Inside the truncated-spectrum buffers a pencil's K modes are stored in the order
-// k1 K2 + k2 (consecutive lanes then write consecutive addresses); the contraction shares one W across all modes
+// transposed network.  Inside the truncated-spectrum buffers a pencil's modes are stored in the order
+// k1 K2k + k2 (consecutive lanes then write consecutive addresses); the contraction shares one W across all modes
 // (Sec. 3.1), so any order works as long as both transforms agree.
 #pragma once
 #include "pruned1d_kernel.h"
@@ -45,11 +45,15 @@ __device__ __forceinline__ void long_setup(c64 *TW, c64 *tw0, int tid)
     tw0[0] = make_float2(1.f, 0.f);
 }
 
-// x: [npencils, N] contiguous (pencil q = b * C + c).  Xh: mode-tile major over the joint mode index b K + m.
-template <int N1, int K2>
+// x: [npencils, N] contiguous (pencil q = b * C + c).  Xh: mode-tile major over the joint mode index
+// b N1 K2k + k1 K2k + k2.
+// Only the first K2k of the K2 bins of every row exist in the spectra when fewer than K modes are kept (ALL: K2k = K2 as a
+// constant, which saves registers).
+template <int N1, int K2, bool ALL>
 __global__ void __launch_bounds__(256, 3)
-k_fwd1d_long(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npencils, int K_keep)
+k_fwd1d_long(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npencils, int K_keep, int K2k)
 {
+    const int K2_keep = ALL ? K2 : K2k;
     using Cf = CfgLong<N1, K2>;
     constexpr int N = Cf::N, K = Cf::K, G = Cf::G, KH = Cf::KH, RS = Cf::RS;
     // exchange buffer [16][RS]; its first 16 * 256 entries double as the 16 transpose patches of stage 2
@@ -106,9 +110,12 @@ k_fwd1d_long(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long n
             const long long b = q / C;
             const int ch = (int)(q % C);
 #pragma unroll
-            for (int kh = 0; kh < KH; ++kh)                // true bin k1 + N1 k2 at or past K_keep: finer truncation
-                Xh[spec1d_index(b * K + k1 * K2 + p + 16 * kh, ch, C)] =
-                    k1 + N1 * (p + 16 * kh) < K_keep ? xo[kh] : make_float2(0.f, 0.f);
+            for (int kh = 0; kh < KH; ++kh) {              // true bin k1 + N1 k2 at or past K_keep: finer truncation
+                const int k2 = p + 16 * kh;
+                if (ALL || k2 < K2_keep)
+                    Xh[spec1d_index(b * (N1 * K2_keep) + k1 * K2_keep + k2, ch, C)] =
+                        k1 + N1 * k2 < K_keep ? xo[kh] : make_float2(0.f, 0.f);
+            }
         }
     };
 
@@ -118,11 +125,12 @@ k_fwd1d_long(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long n
     stage(sweep, std::false_type{}, 0);
 }
 
-// Yh: mode-tile major (joint mode index b K + k1 K2 + k2, C channels).  y: [npencils, N] contiguous.
-template <int N1, int K2>
+// Yh: mode-tile major (joint mode index b N1 K2k + k1 K2k + k2, C channels; bins k2 from K2k on are zeros).  y: [npencils, N] contiguous.
+template <int N1, int K2, bool ALL>
 __global__ void __launch_bounds__(256, 3)
-k_inv1d_long(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npencils)
+k_inv1d_long(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npencils, int K2k)
 {
+    const int K2_keep = ALL ? K2 : K2k;
     using Cf = CfgLong<N1, K2>;
     constexpr int N = Cf::N, K = Cf::K, G = Cf::G, KH = Cf::KH, RS = Cf::RS;
     __shared__ __align__(16) c64 E[16 * RS];
@@ -143,7 +151,11 @@ k_inv1d_long(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long n
         const long long b = q / C;
         const int ch = (int)(q % C);
 #pragma unroll
-        for (int kh = 0; kh < KH; ++kh) yin[kh] = Yh[spec1d_index(b * K + k1 * K2 + p + 16 * kh, ch, C)];
+        for (int kh = 0; kh < KH; ++kh) {
+            const int k2 = p + 16 * kh;
+            const c64 val = Yh[spec1d_index(b * (N1 * K2_keep) + k1 * K2_keep + (ALL || k2 < K2_keep ? k2 : 0), ch, C)];
+            yin[kh] = ALL || k2 < K2_keep ? val : make_float2(0.f, 0.f);
+        }
     };
     auto stage = [&](long long sweep, auto refill, long long next_sweep) __attribute__((always_inline)) {
         constexpr bool REFILL = decltype(refill)::value;

@@ -392,7 +392,12 @@ PERMODE_1D = [(4, 16, 16, 64, 16), (19, 5, 7, 64, 64), (9, 33, 40, 128, 32), (3,
               # mode counts between the built sizes (weights hold exactly K matrices)
               (3, 5, 7, 64, 12), (9, 9, 4, 256, 100), (4, 6, 6, 1024, 72), (2, 3, 3, 128, 1),
               # batches and output counts that fill 64 x 64 tiles per mode (ragged last tiles, channel mask, surplus modes)
-              (250, 16, 128, 256, 128), (256, 9, 120, 256, 100)]
+              (250, 16, 128, 256, 128), (256, 9, 120, 256, 100),
+              # the contraction's kernels on both sides of the rules: matrix pipe with and without masks at fewer than 128
+              # modes and at counts that are no multiple of 8 (joint tiles shared by batch elements), FP32 with 8 x 8, 4 x 4,
+              # 2 x 2 and 1 x 1 results per thread, C_in not a multiple of the channels in flight
+              (96, 16, 64, 64, 64), (64, 24, 160, 128, 40), (71, 20, 50, 256, 117), (260, 9, 131, 256, 128), (33, 15, 65, 256, 33),
+              (5, 33, 9, 1024, 17), (2, 7, 3, 64, 3)]
 
 
 @pytest.mark.parametrize("shape", PERMODE_1D, ids=lambda s: "B%d_Ci%d_Co%d_N%d_K%d" % s)
@@ -413,7 +418,7 @@ def test_1d_permode(gpu, oracle_mod, shape):
 # (B, C_in, C_out, N1, N2, K1, K2)
 PERMODE_2D = [(2, 3, 5, 64, 64, 16, 16), (9, 5, 33, 128, 64, 32, 16), (1, 4, 3, 256, 256, 64, 64), (10, 2, 2, 64, 256, 16, 64),
               (3, 17, 9, 128, 128, 64, 32), (2, 3, 4, 64, 128, 12, 20), (9, 2, 3, 256, 64, 33, 5),
-              (120, 20, 112, 64, 64, 16, 16)]
+              (120, 20, 112, 64, 64, 16, 16), (40, 16, 33, 64, 64, 15, 21), (32, 32, 32, 64, 64, 24, 16)]
 
 
 @pytest.mark.parametrize("shape", PERMODE_2D, ids=lambda s: "B%d_Ci%d_Co%d_N%dx%d_K%dx%d" % s)
