@@ -490,4 +490,80 @@ k_cgemm_modes_small(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *
     });
 }
 
+// The same contraction without LDS and barriers: one mode tile and 32 outputs per workgroup, both operands straight from
+// memory (a wave splits its weights itself), the loads of 8 NSTEP channels issued at once and refilled step by step while
+// they are contracted.  The kernels above stage W for 64 outputs and walk tiles; with about a chip full of them or less their
+// time is that of one workgroup's chain of staging, tiles and steps.  25 tiles, C 40 -> 56: 13.4 -> 5.8 us; 32 tiles, C 64:
+// 15.2 -> 7.8 us; 64 tiles, C 128: 26 -> 17 us.  (64 outputs per workgroup measured 12 us at 32 tiles and no faster at 1024.)
+template <int NSTEP>
+__global__ void __launch_bounds__(256, 2)
+k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__restrict__ Yh, int C_in, int C_out, float scale)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 31, g = lane >> 5;
+    const int o0 = blockIdx.y * 32, o = o0 + col < C_out ? o0 + col : C_out - 1;
+    const c64 *__restrict__ xsrc = Xh + (long long)blockIdx.x * C_in * 128 + 32 * wave + col;
+
+    // (channels past C_in are read from channel 0 and meet zero weights; outputs past C_out are not stored)
+    c64 xq[NSTEP][4], wq[NSTEP][4];
+    auto load_step = [&](int c0, int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const int c = c0 + 8 * i + 4 * g + d, cc = c < C_in ? c : 0;
+            wq[i][d] = W[(long long)cc * C_out + o];
+            xq[i][d] = xsrc[cc * 128];
+        }
+    };
+    floatx16 acc_re, acc_im;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { acc_re[r] = 0.f; acc_im[r] = 0.f; }
+    auto block = [&](auto refill, int c0) __attribute__((always_inline)) {
+        static_for<0, NSTEP>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            uintx4 b[3], a_re[3], a_im[3];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const Split3 re = split3(xq[i][d].x), im = split3(xq[i][d].y);
+                b[0][d] = pack_bf16(re.t0, im.t0);
+                b[1][d] = pack_bf16(re.t1, im.t1);
+                b[2][d] = pack_bf16(re.t2, im.t2);
+                const float ws = c0 + 8 * i + 4 * g + d < C_in ? scale : 0.f;
+                const Split3 wr = split3(wq[i][d].x * ws), wi = split3(wq[i][d].y * ws);
+                a_re[0][d] = pack_bf16(wr.t0, wi.t0) ^ 0x80000000u;
+                a_re[1][d] = pack_bf16(wr.t1, wi.t1) ^ 0x80000000u;
+                a_re[2][d] = pack_bf16(wr.t2, wi.t2) ^ 0x80000000u;
+                a_im[0][d] = pack_bf16(wi.t0, wr.t0);
+                a_im[1][d] = pack_bf16(wi.t1, wr.t1);
+                a_im[2][d] = pack_bf16(wi.t2, wr.t2);
+            }
+            if constexpr (decltype(refill)::value) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_step(c0 + 8 * NSTEP, i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            constexpr int SA[6] = {2, 0, 1, 1, 0, 0}, SB[6] = {0, 2, 1, 0, 1, 0};   // smallest products first
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                const bf16x8 bb = __builtin_bit_cast(bf16x8, b[SB[k]]);
+                acc_re = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a_re[SA[k]]), bb, acc_re, 0, 0, 0);
+                acc_im = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a_im[SA[k]]), bb, acc_im, 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+#pragma unroll
+    for (int i = 0; i < NSTEP; ++i) load_step(0, i);
+    __builtin_amdgcn_sched_barrier(0);
+    int c0 = 0;
+    for (; c0 + 8 * NSTEP < C_in; c0 += 8 * NSTEP) block(std::true_type{}, c0);
+    block(std::false_type{}, c0);
+
+    c64 *__restrict__ Yb = Yh + (long long)blockIdx.x * C_out * 128 + 32 * wave + col;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int oo = o0 + 8 * (r / 4) + 4 * g + (r % 4);
+        if (oo < C_out) Yb[oo * 128] = make_float2(acc_re[r], acc_im[r]);
+    }
+}
+
 }  // namespace tfno

@@ -116,7 +116,11 @@ PRUNED_1D = [(4, 16, 16, 64, 16), (3, 5, 7, 64, 64), (2, 33, 40, 64, 32), (3, 9,
              # long pencils (N1 x 256 decomposition): odd pencil counts, K / N1 from 16 to 256, no truncation
              (2, 5, 7, 2048, 128), (3, 3, 5, 2048, 256), (1, 1, 1, 2048, 2048), (2, 8, 8, 2048, 1024),
              (2, 6, 9, 4096, 256), (1, 3, 2, 4096, 1024), (1, 2, 2, 4096, 4096), (2, 33, 70, 4096, 512),
-             (1, 4, 4, 2048, 512), (1, 2, 3, 4096, 2048)]
+             (1, 4, 4, 2048, 512), (1, 2, 3, 4096, 2048),
+             # the contraction's direct kernel (up to 512 workgroups or 32 outputs): channel counts around its steps and
+             # blocks, either side of both limits, and each of the kernels past them
+             (9, 8, 33, 256, 64), (9, 9, 31, 256, 64), (2, 17, 32, 128, 64), (3, 65, 40, 256, 128), (2, 129, 3, 256, 16),
+             (260, 4, 32, 256, 256), (256, 33, 64, 256, 128), (257, 33, 64, 256, 128), (300, 20, 40, 256, 128), (260, 130, 40, 256, 128)]
 
 
 @pytest.mark.parametrize("shape", PRUNED_1D, ids=lambda s: "B%d_Ci%d_Co%d_N%d_K%d" % s)
