@@ -4,8 +4,10 @@
 
 namespace tfno {
 
-// One transform out[q][j] = sum_{i < I} in[q][i] exp(dir 2 pi i (i j) / N),  j < J, of P pencils q.  I <= N and J <= N
-// prune the input (zero padding) and the output (truncation); nothing is scaled.  How a side is laid out:
+// One transform of P pencils q of N points that keeps K of its N bins:
+//   forward  out[q][k] = sum_{n < N} in[q][n] exp(-2 pi i n k / N),  k < K      (output pruned: truncation)
+//   inverse  out[q][n] = sum_{k < K} in[q][k] exp(+2 pi i n k / N),  n < N      (input pruned: zero padding; unscaled)
+// How a side is laid out:
 //   MD_ROWS     element e of pencil q at q * outer + e
 //   MD_STRIDED  element e at (q / inner) * outer + q % inner + e * inner: a leading axis of a row-major field, the
 //               `inner` pencils of an outer item being adjacent columns
@@ -16,19 +18,19 @@ enum MatdftSide { MD_ROWS = 0, MD_STRIDED = 1, MD_SPEC = 2 };
 struct MatdftArgs {
     const c64 *in;
     c64 *out;
-    int N, I, J;
+    int N, K;
     unsigned P;                     // pencils, below 2^31
     unsigned inner;
     long long in_outer, out_outer;  // MD_ROWS and MD_STRIDED sides
     int C;                          // MD_SPEC side
     long long M;
-    int dir;                        // -1 or +1
-    int jgroups;                    // filled in by the launcher
+    int groups;                     // filled in by the launcher
 };
 
-// Which pairs of sides exist: ROWS -> SPEC, SPEC -> ROWS (1-D), ROWS -> ROWS (contiguous axis of a field),
-// STRIDED -> SPEC, SPEC -> STRIDED (leading axis).
-hipError_t matdft_launch(MatdftSide in_side, MatdftSide out_side, MatdftArgs a, hipStream_t s);
+// Pairs of sides that exist: forward ROWS -> SPEC (1-D), ROWS -> ROWS (contiguous axis of a field), STRIDED -> SPEC (leading
+// axis); inverse SPEC -> ROWS, SPEC -> STRIDED, ROWS -> ROWS.
+hipError_t matdft_forward(MatdftSide in_side, MatdftSide out_side, MatdftArgs a, hipStream_t s);
+hipError_t matdft_inverse(MatdftSide in_side, MatdftSide out_side, MatdftArgs a, hipStream_t s);
 
 // The whole layer on fields N1 x N2 (1-D: N1 = K1 = 1) of any side lengths up to 4096: truncated transforms, the mode
 // contraction, zero-padded inverses.  Workspace: matdft_workspace_bytes.

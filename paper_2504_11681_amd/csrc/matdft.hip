@@ -4,59 +4,96 @@
 
 namespace tfno {
 
-template <int JT, int WI, int IN, int OUT>
-static hipError_t launch_md(MatdftArgs a, hipStream_t s)
+template <int JT, int WI, int NMAX, int IN, int OUT, bool VEC>
+static hipError_t launch_fwd(MatdftArgs a, hipStream_t s)
 {
+    using Cf = CfgMdF<JT, WI, NMAX>;
+    constexpr int nt = Cf::NT;
+    constexpr size_t lds = Cf::LDS;
     static LdsLimitOnce limit;
-    const hipError_t e = limit.set({reinterpret_cast<const void *>(&k_matdft<JT, WI, IN, OUT>)}, (int)CfgMd<JT, WI>::lds_bytes(4096));
+    const hipError_t e = limit.set({reinterpret_cast<const void *>(&k_matdft_fwd<JT, WI, NMAX, IN, OUT, VEC>)}, (int)lds);
     if (e != hipSuccess) return e;
-    a.jgroups = (a.J + 32 * JT - 1) / (32 * JT);
-    const unsigned long long items = (unsigned long long)((a.P + 31) / 32) * a.jgroups;
+    a.groups = (a.K + 32 * JT - 1) / (32 * JT);
+    const unsigned long long items = (unsigned long long)((a.P + 31) / 32) * a.groups;
     const unsigned long long blocks = WI > 1 ? items : (items + 3) / 4;
     if (blocks > 0x7fffffffULL) return hipErrorInvalidValue;
-    const size_t lds = CfgMd<JT, WI>::lds_bytes(a.N);
-    constexpr int nt = CfgMd<JT, WI>::NT;
-    hipLaunchKernelGGL((k_matdft<JT, WI, IN, OUT>), dim3((unsigned)blocks), dim3(nt), lds, s, a);
+    hipLaunchKernelGGL((k_matdft_fwd<JT, WI, NMAX, IN, OUT, VEC>), dim3((unsigned)blocks), dim3(nt), lds, s, a);
+    return hipGetLastError();
+}
+// (two sizes of the root table)
+template <int JT, int WI, int IN, int OUT, bool VEC>
+static hipError_t launch_fwd(const MatdftArgs &a, hipStream_t s)
+{
+    return a.N <= 1024 ? launch_fwd<JT, WI, 1024, IN, OUT, VEC>(a, s) : launch_fwd<JT, WI, 4096, IN, OUT, VEC>(a, s);
+}
+
+template <int IN, int OUT, bool VEC>
+static hipError_t pick_fwd(const MatdftArgs &a, hipStream_t s)
+{
+    const unsigned long long tiles = (a.P + 31) / 32;
+    const int kt = (a.K + 31) / 32;
+    // Output tiles per wave: the input is fetched, folded and split once per wave, so as many as divide the outputs best --
+    // unless that leaves the chip's 1024 SIMDs without a wave; then fewer, and the sum dealt out to 4 or 8 waves.
+    int w = 1;
+    for (int c = 2; c <= 4; ++c)
+        if ((kt + c - 1) / c * c <= (kt + w - 1) / w * w && tiles * ((kt + c - 1) / c) >= 1024) w = c;
+    const unsigned long long waves = tiles * ((kt + w - 1) / w);
+    const int parts = waves >= 1024 || a.N < 128 ? 1 : waves >= 256 || a.N < 256 ? 4 : 8;
+    switch (w) {
+    case 4: return launch_fwd<4, 1, IN, OUT, VEC>(a, s);
+    case 3: return launch_fwd<3, 1, IN, OUT, VEC>(a, s);
+    case 2: return launch_fwd<2, 1, IN, OUT, VEC>(a, s);
+    default:
+        return parts == 8 ? launch_fwd<1, 8, IN, OUT, VEC>(a, s) : parts == 4 ? launch_fwd<1, 4, IN, OUT, VEC>(a, s) : launch_fwd<1, 1, IN, OUT, VEC>(a, s);
+    }
+}
+
+template <int PT, int NMAX, int IN, int OUT>
+static hipError_t launch_inv(MatdftArgs a, hipStream_t s)
+{
+    constexpr size_t lds = MdRoots<NMAX>::BYTES;
+    static LdsLimitOnce limit;
+    const hipError_t e = limit.set({reinterpret_cast<const void *>(&k_matdft_inv<PT, NMAX, IN, OUT>)}, (int)lds);
+    if (e != hipSuccess) return e;
+    a.groups = (a.N / 2 + 32 * PT) / (32 * PT);             // output pairs 0 .. N/2
+    const unsigned long long blocks = ((unsigned long long)((a.P + 31) / 32) * a.groups + 3) / 4;
+    if (blocks > 0x7fffffffULL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_matdft_inv<PT, NMAX, IN, OUT>), dim3((unsigned)blocks), dim3(256), lds, s, a);
     return hipGetLastError();
 }
 
 template <int IN, int OUT>
-static hipError_t pick_md(const MatdftArgs &a, hipStream_t s)
+static hipError_t pick_inv(const MatdftArgs &a, hipStream_t s)
 {
+    // two tiles of output pairs per wave where they divide the pairs evenly and leave a wave for every SIMD
     const unsigned long long tiles = (a.P + 31) / 32;
-    const int jt = (a.J + 31) / 32;
-    // Output tiles per wave: the input is fetched and split once per wave, so as many as divide the outputs best -- unless
-    // that leaves the chip's 1024 SIMDs without a wave; then fewer, and the sum over the input dealt out to 4 or 8 waves.
-    // (three and four tiles between a spectrum and a leading axis spill)
-    constexpr int most = IN == MD_SPEC && OUT == MD_STRIDED ? 2 : 4;
-    int w = 1;
-    for (int c = 2; c <= most; ++c)
-        if ((jt + c - 1) / c * c <= (jt + w - 1) / w * w && tiles * ((jt + c - 1) / c) >= 1024) w = c;
-    const unsigned long long waves = tiles * ((jt + w - 1) / w);
-    const int parts = waves >= 1024 || a.I < 128 ? 1 : waves >= 256 || a.I < 256 ? 4 : 8;
-    if constexpr (most == 4) {
-        if (w == 4) return launch_md<4, 1, IN, OUT>(a, s);
-        if (w == 3) return launch_md<3, 1, IN, OUT>(a, s);
-    }
-    switch (w) {
-    case 2: return launch_md<2, 1, IN, OUT>(a, s);
-    default:
-        return parts == 8 ? launch_md<1, 8, IN, OUT>(a, s) : parts == 4 ? launch_md<1, 4, IN, OUT>(a, s) : launch_md<1, 1, IN, OUT>(a, s);
-    }
+    const int nt = (a.N / 2 + 32) / 32;
+    const bool two = nt % 2 == 0 && tiles * (nt / 2) >= 1024;
+    if (a.N <= 1024) return two ? launch_inv<2, 1024, IN, OUT>(a, s) : launch_inv<1, 1024, IN, OUT>(a, s);
+    return two ? launch_inv<2, 4096, IN, OUT>(a, s) : launch_inv<1, 4096, IN, OUT>(a, s);
 }
 
-hipError_t matdft_launch(MatdftSide in_side, MatdftSide out_side, MatdftArgs a, hipStream_t s)
+static bool args_ok(const MatdftArgs &a) { return a.N >= 2 && a.N <= 4096 && a.K >= 1 && a.K <= a.N && a.inner >= 1 && a.C >= 1; }
+
+hipError_t matdft_forward(MatdftSide in_side, MatdftSide out_side, MatdftArgs a, hipStream_t s)
 {
-    if (a.N < 1 || a.N > 4096 || a.I < 1 || a.I > a.N || a.J < 1 || a.J > a.N || a.inner < 1) return hipErrorInvalidValue;
+    if (!args_ok(a)) return hipErrorInvalidValue;
     if (a.P == 0) return hipSuccess;
-    switch (in_side * 4 + out_side) {
-    case MD_ROWS * 4 + MD_ROWS: return pick_md<MD_ROWS, MD_ROWS>(a, s);
-    case MD_ROWS * 4 + MD_SPEC: return pick_md<MD_ROWS, MD_SPEC>(a, s);
-    case MD_SPEC * 4 + MD_ROWS: return pick_md<MD_SPEC, MD_ROWS>(a, s);
-    case MD_STRIDED * 4 + MD_SPEC: return pick_md<MD_STRIDED, MD_SPEC>(a, s);
-    case MD_SPEC * 4 + MD_STRIDED: return pick_md<MD_SPEC, MD_STRIDED>(a, s);
-    default: return hipErrorInvalidValue;
-    }
+    const bool vec = a.N >= 40;
+    if (in_side == MD_ROWS && out_side == MD_SPEC) return vec ? pick_fwd<MD_ROWS, MD_SPEC, true>(a, s) : pick_fwd<MD_ROWS, MD_SPEC, false>(a, s);
+    if (in_side == MD_ROWS && out_side == MD_ROWS) return vec ? pick_fwd<MD_ROWS, MD_ROWS, true>(a, s) : pick_fwd<MD_ROWS, MD_ROWS, false>(a, s);
+    if (in_side == MD_STRIDED && out_side == MD_SPEC) return pick_fwd<MD_STRIDED, MD_SPEC, false>(a, s);
+    return hipErrorInvalidValue;
+}
+
+hipError_t matdft_inverse(MatdftSide in_side, MatdftSide out_side, MatdftArgs a, hipStream_t s)
+{
+    if (!args_ok(a)) return hipErrorInvalidValue;
+    if (a.P == 0) return hipSuccess;
+    if (in_side == MD_SPEC && out_side == MD_ROWS) return pick_inv<MD_SPEC, MD_ROWS>(a, s);
+    if (in_side == MD_SPEC && out_side == MD_STRIDED) return pick_inv<MD_SPEC, MD_STRIDED>(a, s);
+    if (in_side == MD_ROWS && out_side == MD_ROWS) return pick_inv<MD_ROWS, MD_ROWS>(a, s);
+    return hipErrorInvalidValue;
 }
 
 static long long mode_tiles(long long B, long long M) { return (B * M + 127) / 128; }
@@ -76,35 +113,31 @@ hipError_t matdft_conv(const c64 *x, const c64 *W, c64 *y, long long B, int C_in
 {
     const long long M = (long long)K1 * K2, tiles = mode_tiles(B, M);
     c64 *Xh = ws, *Yh = Xh + (size_t)tiles * 128 * C_in, *T = Yh + (size_t)tiles * 128 * C_out;
-    MatdftArgs f{}, g{};
+    MatdftArgs f{}, g{};                       // last axis, leading axis
+    f.N = N2; f.K = K2; f.inner = 1; f.M = M;
+    g.N = N1; g.K = K1; g.inner = (unsigned)K2; g.M = M;
     hipError_t e;
-    // last axis, truncated
-    f.in = x; f.N = N2; f.I = N2; f.J = K2; f.inner = 1; f.in_outer = N2; f.dir = -1;
-    f.P = (unsigned)(B * C_in * N1); f.C = C_in; f.M = M;
-    // leading axis
-    g.N = N1; g.inner = (unsigned)K2; g.M = M;
+    f.in = x; f.in_outer = N2; f.P = (unsigned)(B * C_in * N1); f.C = g.C = C_in;
     if (N1 == 1) {
         f.out = Xh;
-        e = matdft_launch(MD_ROWS, MD_SPEC, f, s);
+        e = matdft_forward(MD_ROWS, MD_SPEC, f, s);
     } else {
         f.out = T; f.out_outer = K2;
-        e = matdft_launch(MD_ROWS, MD_ROWS, f, s);
-        g.in = T; g.in_outer = (long long)N1 * K2; g.out = Xh; g.I = N1; g.J = K1; g.dir = -1;
-        g.P = (unsigned)(B * C_in * K2); g.C = C_in;
-        if (e == hipSuccess) e = matdft_launch(MD_STRIDED, MD_SPEC, g, s);
+        e = matdft_forward(MD_ROWS, MD_ROWS, f, s);
+        g.in = T; g.in_outer = (long long)N1 * K2; g.out = Xh; g.P = (unsigned)(B * C_in * K2);
+        if (e == hipSuccess) e = matdft_forward(MD_STRIDED, MD_SPEC, g, s);
     }
+    if (e == hipSuccess) e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / ((float)N1 * (float)N2), tiles, s);
     if (e != hipSuccess) return e;
-    if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / ((float)N1 * (float)N2), tiles, s)) != hipSuccess) return e;
-    f.dir = +1; f.I = K2; f.J = N2; f.C = C_out; f.P = (unsigned)(B * C_out * N1); f.out = y; f.out_outer = N2;
+    f.out = y; f.out_outer = N2; f.P = (unsigned)(B * C_out * N1); f.C = g.C = C_out;
     if (N1 == 1) {
         f.in = Yh;
-        return matdft_launch(MD_SPEC, MD_ROWS, f, s);
+        return matdft_inverse(MD_SPEC, MD_ROWS, f, s);
     }
-    g.in = Yh; g.out = T; g.out_outer = (long long)N1 * K2; g.I = K1; g.J = N1; g.dir = +1;
-    g.P = (unsigned)(B * C_out * K2); g.C = C_out;
-    if ((e = matdft_launch(MD_SPEC, MD_STRIDED, g, s)) != hipSuccess) return e;
+    g.in = Yh; g.out = T; g.out_outer = (long long)N1 * K2; g.P = (unsigned)(B * C_out * K2);
+    if ((e = matdft_inverse(MD_SPEC, MD_STRIDED, g, s)) != hipSuccess) return e;
     f.in = T; f.in_outer = K2;
-    return matdft_launch(MD_ROWS, MD_ROWS, f, s);
+    return matdft_inverse(MD_ROWS, MD_ROWS, f, s);
 }
 
 }  // namespace tfno
