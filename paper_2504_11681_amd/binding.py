@@ -7,6 +7,7 @@ no CPU fallback: if the library has not been built, loading raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -46,6 +47,56 @@ RECT_EXPORTS = EXPORTS[8:11]  # (x, W, y, B, C_in, C_out, N1, N2, K1, K2, stream
 
 _lib = None
 _workspace = None     # the torch tensor currently registered as workspace (kept alive here)
+
+# A small layer runs in a few microseconds on the device, so what a call costs on the host is its rate: torch, the entry
+# points and the current-stream query are looked up once, and the workspace size of a shape (a function of the sizes alone)
+# is kept for the most recent shapes (B 4, C 16, N 64: 8.4 -> 5.1 us per call, 3.2 of them the launch).
+_torch = None
+_raw_stream = None    # device index -> hipStream_t of the current stream
+
+
+def _load_torch():
+    global _torch, _raw_stream
+    import torch
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda index: torch.cuda.current_stream(index).cuda_stream)
+    _torch = torch
+    return torch
+
+
+@functools.lru_cache(maxsize=None)
+def _entry(name: str):
+    return getattr(lib(), name)
+
+
+@functools.lru_cache(maxsize=1024)
+def _need(query: str, *sizes) -> int:
+    return _entry(query)(*sizes)
+
+
+def _check_c64(x, W, y):
+    c64 = (_torch or _load_torch()).complex64
+    for t, name in ((x, "x"), (W, "W"), (y, "y")):
+        if t.dtype is not c64 or not t.is_contiguous() or not t.is_cuda:
+            raise TypeError(f"{name} must be a contiguous complex64 device tensor")
+
+
+def _check_real(x, W, y):
+    torch = _torch or _load_torch()
+    if x.dtype is not torch.float32 or y.dtype is not torch.float32 or W.dtype is not torch.complex64:
+        raise TypeError("x, y must be float32 and W complex64")
+    for t, name in ((x, "x"), (W, "W"), (y, "y")):
+        if not t.is_contiguous() or not t.is_cuda:
+            raise TypeError(f"{name} must be a contiguous device tensor")
+
+
+def _launch(name: str, x, W, y, sizes, stream):
+    if stream is None:
+        stream = _raw_stream(x.device.index)
+    st = _entry(name)(x.data_ptr(), W.data_ptr(), y.data_ptr(), *sizes, stream)
+    if st != OK:
+        raise TfnoError(st, name)
+    return y
 
 
 class TfnoError(RuntimeError):
@@ -144,32 +195,27 @@ def ensure_workspace(nbytes: int, device) -> None:
         set_workspace(torch.empty(nbytes, dtype=torch.uint8, device=device))
 
 
-def _call(name: str, dims: int, variant, x, W, y, K: int, stream):
-    import torch
-    for t, what in ((x, "x"), (W, "W"), (y, "y")):
-        if t.dtype != torch.complex64 or not t.is_contiguous() or not t.is_cuda:
-            raise TypeError(f"{what} must be a contiguous complex64 device tensor")
-    if x.dim() != 2 + dims or y.dim() != 2 + dims or W.dim() != 2:
+def _call(name: str, dims: int, variant: int, x, W, y, K: int, stream):
+    _check_c64(x, W, y)
+    xs, ws, ys = x.shape, W.shape, y.shape
+    if len(xs) != 2 + dims or len(ys) != 2 + dims or len(ws) != 2:
         raise ValueError("x, y must be [B, C, N] (1-D) or [B, C, N, N] (2-D); W must be [C_in, C_out]")
-    B, C_in, N = x.shape[0], x.shape[1], x.shape[2]
-    C_out = W.shape[1]
-    if W.shape[0] != C_in or tuple(y.shape) != (B, C_out) + tuple(x.shape[2:]) or any(s != N for s in x.shape[2:]):
+    B, C_in, N = xs[0], xs[1], xs[2]
+    C_out = ws[1]
+    if ws[0] != C_in or ys[0] != B or ys[1] != C_out or ys[2:] != xs[2:] or xs[-1] != N:
         raise ValueError("inconsistent tensor shapes")
-    ensure_workspace(workspace_bytes(dims, variant, B, C_in, C_out, N, K), x.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    st = getattr(lib(), name)(x.data_ptr(), W.data_ptr(), y.data_ptr(), B, C_in, C_out, N, K, stream)
-    if st != OK:
-        raise TfnoError(st, name)
-    return y
+    need = _need("tfno_workspace_bytes", dims, variant, B, C_in, C_out, N, K)
+    if need:
+        ensure_workspace(need, x.device)
+    return _launch(name, x, W, y, (B, C_in, C_out, N, K), stream)
 
 
 def spectral_conv1d(x, W, y, K: int, stream=None):
-    return _call("tfno_spectral_conv1d", 1, False, x, W, y, K, stream)
+    return _call("tfno_spectral_conv1d", 1, 0, x, W, y, K, stream)
 
 
 def spectral_conv2d(x, W, y, K: int, stream=None):
-    return _call("tfno_spectral_conv2d", 2, False, x, W, y, K, stream)
+    return _call("tfno_spectral_conv2d", 2, 0, x, W, y, K, stream)
 
 
 NOALLOC_SCRATCH_BYTES = 32 << 20     # TFNO_NOALLOC_SCRATCH_BYTES of the header
@@ -177,30 +223,22 @@ NOALLOC_SCRATCH_BYTES = 32 << 20     # TFNO_NOALLOC_SCRATCH_BYTES of the header
 
 def spectral_conv2d_noalloc(x, W, y, K: int, stream=None):
     """tfno_spectral_conv2d with the library's own scratch array: allocates nothing and registers no workspace."""
-    import torch
-    for t, what in ((x, "x"), (W, "W"), (y, "y")):
-        if t.dtype != torch.complex64 or not t.is_contiguous() or not t.is_cuda:
-            raise TypeError(f"{what} must be a contiguous complex64 device tensor")
+    _check_c64(x, W, y)
     if x.dim() != 4 or y.dim() != 4 or W.dim() != 2 or x.shape[2] != x.shape[3]:
         raise ValueError("x, y must be [B, C, N, N]; W must be [C_in, C_out]")
     B, C_in, N = x.shape[0], x.shape[1], x.shape[2]
     C_out = W.shape[1]
     if W.shape[0] != C_in or tuple(y.shape) != (B, C_out, N, N):
         raise ValueError("inconsistent tensor shapes")
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    st = lib().tfno_spectral_conv2d_noalloc(x.data_ptr(), W.data_ptr(), y.data_ptr(), B, C_in, C_out, N, K, stream)
-    if st != OK:
-        raise TfnoError(st, "tfno_spectral_conv2d_noalloc")
-    return y
+    return _launch("tfno_spectral_conv2d_noalloc", x, W, y, (B, C_in, C_out, N, K), stream)
 
 
 def spectral_conv1d_staged(x, W, y, K: int, stream=None):
-    return _call("tfno_spectral_conv1d_staged", 1, True, x, W, y, K, stream)
+    return _call("tfno_spectral_conv1d_staged", 1, 1, x, W, y, K, stream)
 
 
 def spectral_conv2d_staged(x, W, y, K: int, stream=None):
-    return _call("tfno_spectral_conv2d_staged", 2, True, x, W, y, K, stream)
+    return _call("tfno_spectral_conv2d_staged", 2, 1, x, W, y, K, stream)
 
 
 def spectral_conv1d_pruned(x, W, y, K: int, stream=None):
@@ -219,32 +257,27 @@ def spectral_conv1d_auto(x, W, y, K: int, stream=None):
     return _call("tfno_spectral_conv1d_auto", 1, 5, x, W, y, K, stream)
 
 
-def _call_rect(name: str, variant, x, W, y, K1: int, K2: int, stream):
-    import torch
-    for t, what in ((x, "x"), (W, "W"), (y, "y")):
-        if t.dtype != torch.complex64 or not t.is_contiguous() or not t.is_cuda:
-            raise TypeError(f"{what} must be a contiguous complex64 device tensor")
-    if x.dim() != 4 or y.dim() != 4 or W.dim() != 2:
+def _call_rect(name: str, variant: int, x, W, y, K1: int, K2: int, stream):
+    _check_c64(x, W, y)
+    xs, ws, ys = x.shape, W.shape, y.shape
+    if len(xs) != 4 or len(ys) != 4 or len(ws) != 2:
         raise ValueError("x, y must be [B, C, N1, N2]; W must be [C_in, C_out]")
-    B, C_in, N1, N2 = x.shape
-    C_out = W.shape[1]
-    if W.shape[0] != C_in or tuple(y.shape) != (B, C_out, N1, N2):
+    B, C_in, N1, N2 = xs
+    C_out = ws[1]
+    if ws[0] != C_in or ys[0] != B or ys[1] != C_out or ys[2:] != xs[2:]:
         raise ValueError("inconsistent tensor shapes")
-    ensure_workspace(workspace_bytes_2d(variant, B, C_in, C_out, N1, N2, K1, K2), x.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    st = getattr(lib(), name)(x.data_ptr(), W.data_ptr(), y.data_ptr(), B, C_in, C_out, N1, N2, K1, K2, stream)
-    if st != OK:
-        raise TfnoError(st, name)
-    return y
+    need = _need("tfno_workspace_bytes_2d", variant, B, C_in, C_out, N1, N2, K1, K2)
+    if need:
+        ensure_workspace(need, x.device)
+    return _launch(name, x, W, y, (B, C_in, C_out, N1, N2, K1, K2), stream)
 
 
 def spectral_conv2d_rect(x, W, y, K1: int, K2: int, stream=None):
-    return _call_rect("tfno_spectral_conv2d_rect", False, x, W, y, K1, K2, stream)
+    return _call_rect("tfno_spectral_conv2d_rect", 0, x, W, y, K1, K2, stream)
 
 
 def spectral_conv2d_rect_staged(x, W, y, K1: int, K2: int, stream=None):
-    return _call_rect("tfno_spectral_conv2d_rect_staged", True, x, W, y, K1, K2, stream)
+    return _call_rect("tfno_spectral_conv2d_rect_staged", 1, x, W, y, K1, K2, stream)
 
 
 def spectral_conv2d_strips(x, W, y, K1: int, K2: int, stream=None):
@@ -253,30 +286,23 @@ def spectral_conv2d_strips(x, W, y, K1: int, K2: int, stream=None):
 
 
 def _call_permode(name: str, dims: int, x, W, y, stream):
-    import torch
-    for t, what in ((x, "x"), (W, "W"), (y, "y")):
-        if t.dtype != torch.complex64 or not t.is_contiguous() or not t.is_cuda:
-            raise TypeError(f"{what} must be a contiguous complex64 device tensor")
-    if x.dim() != 2 + dims or y.dim() != 2 + dims or W.dim() != 2 + dims:
+    _check_c64(x, W, y)
+    xs, ws, ys = x.shape, W.shape, y.shape
+    if len(xs) != 2 + dims or len(ys) != 2 + dims or len(ws) != 2 + dims:
         raise ValueError("x, y must be [B, C, spatial...]; W must be [C_in, C_out, modes...]")
-    B, C_in = x.shape[0], x.shape[1]
-    C_out = W.shape[1]
-    if W.shape[0] != C_in or tuple(y.shape) != (B, C_out) + tuple(x.shape[2:]):
+    B, C_in = xs[0], xs[1]
+    C_out = ws[1]
+    if ws[0] != C_in or ys[0] != B or ys[1] != C_out or ys[2:] != xs[2:]:
         raise ValueError("inconsistent tensor shapes")
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
     if dims == 1:
-        N, K = x.shape[2], W.shape[2]
-        ensure_workspace(workspace_bytes(1, 6, B, C_in, C_out, N, K), x.device)
-        st = lib().tfno_spectral_conv1d_permode(x.data_ptr(), W.data_ptr(), y.data_ptr(), B, C_in, C_out, N, K, stream)
+        sizes = (B, C_in, C_out, xs[2], ws[2])
+        need = _need("tfno_workspace_bytes", 1, 6, *sizes)
     else:
-        N1, N2, K1, K2 = x.shape[2], x.shape[3], W.shape[2], W.shape[3]
-        ensure_workspace(workspace_bytes_2d(6, B, C_in, C_out, N1, N2, K1, K2), x.device)
-        st = lib().tfno_spectral_conv2d_permode(x.data_ptr(), W.data_ptr(), y.data_ptr(), B, C_in, C_out, N1, N2, K1, K2,
-                                                stream)
-    if st != OK:
-        raise TfnoError(st, name)
-    return y
+        sizes = (B, C_in, C_out, xs[2], xs[3], ws[2], ws[3])
+        need = _need("tfno_workspace_bytes_2d", 6, *sizes)
+    if need:
+        ensure_workspace(need, x.device)
+    return _launch(name, x, W, y, sizes, stream)
 
 
 def spectral_conv1d_permode(x, W, y, stream=None):
@@ -291,69 +317,48 @@ def spectral_conv2d_permode(x, W, y, stream=None):
 
 def spectral_conv1d_real(x, W, y, K: int, stream=None):
     """Real-valued layer: x [B, C_in, N] and y [B, C_out, N] float32 device tensors, W [C_in, C_out] complex64."""
-    import torch
-    if x.dtype != torch.float32 or y.dtype != torch.float32 or W.dtype != torch.complex64:
-        raise TypeError("x, y must be float32 and W complex64")
-    for t, what in ((x, "x"), (W, "W"), (y, "y")):
-        if not t.is_contiguous() or not t.is_cuda:
-            raise TypeError(f"{what} must be a contiguous device tensor")
-    if x.dim() != 3 or y.dim() != 3 or W.dim() != 2:
+    _check_real(x, W, y)
+    xs, ws, ys = x.shape, W.shape, y.shape
+    if len(xs) != 3 or len(ys) != 3 or len(ws) != 2:
         raise ValueError("x, y must be [B, C, N]; W must be [C_in, C_out]")
-    B, C_in, N = x.shape
-    C_out = W.shape[1]
-    if W.shape[0] != C_in or tuple(y.shape) != (B, C_out, N):
+    B, C_in, N = xs
+    C_out = ws[1]
+    if ws[0] != C_in or ys[0] != B or ys[1] != C_out or ys[2] != N:
         raise ValueError("inconsistent tensor shapes")
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    st = lib().tfno_spectral_conv1d_real(x.data_ptr(), W.data_ptr(), y.data_ptr(), B, C_in, C_out, N, K, stream)
-    if st != OK:
-        raise TfnoError(st, "tfno_spectral_conv1d_real")
-    return y
+    return _launch("tfno_spectral_conv1d_real", x, W, y, (B, C_in, C_out, N, K), stream)
 
 
 def fno2d_real(x, W, y, stream=None):
     """The 2-D Fourier layer of FNO models on real fields: x [B, C_in, N1, N2] and y [B, C_out, N1, N2] float32,
     W [C_in, C_out, 2*M1, M2] complex64 (first-axis frequencies -M1..M1-1, last-axis 0..M2-1)."""
-    import torch
-    if x.dtype != torch.float32 or y.dtype != torch.float32 or W.dtype != torch.complex64:
-        raise TypeError("x, y must be float32 and W complex64")
-    for t, what in ((x, "x"), (W, "W"), (y, "y")):
-        if not t.is_contiguous() or not t.is_cuda:
-            raise TypeError(f"{what} must be a contiguous device tensor")
-    if x.dim() != 4 or y.dim() != 4 or W.dim() != 4 or W.shape[2] % 2:
+    _check_real(x, W, y)
+    xs, ws, ys = x.shape, W.shape, y.shape
+    if len(xs) != 4 or len(ys) != 4 or len(ws) != 4 or ws[2] % 2:
         raise ValueError("x, y must be [B, C, N1, N2]; W must be [C_in, C_out, 2*M1, M2]")
-    B, C_in, N1, N2 = x.shape
-    C_out, M1, M2 = W.shape[1], W.shape[2] // 2, W.shape[3]
-    if W.shape[0] != C_in or tuple(y.shape) != (B, C_out, N1, N2):
+    B, C_in, N1, N2 = xs
+    C_out = ws[1]
+    if ws[0] != C_in or ys[0] != B or ys[1] != C_out or ys[2:] != xs[2:]:
         raise ValueError("inconsistent tensor shapes")
-    ensure_workspace(lib().tfno_fno2d_real_workspace_bytes(B, C_in, C_out, N1, N2, M1, M2), x.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    st = lib().tfno_fno2d_real(x.data_ptr(), W.data_ptr(), y.data_ptr(), B, C_in, C_out, N1, N2, M1, M2, stream)
-    if st != OK:
-        raise TfnoError(st, "tfno_fno2d_real")
-    return y
+    sizes = (B, C_in, C_out, N1, N2, ws[2] // 2, ws[3])
+    need = _need("tfno_fno2d_real_workspace_bytes", *sizes)
+    if need:
+        ensure_workspace(need, x.device)
+    return _launch("tfno_fno2d_real", x, W, y, sizes, stream)
 
 
 def fno1d_real(x, W, y, stream=None):
     """The 1-D Fourier layer of FNO models on real fields: x [B, C_in, N], y [B, C_out, N] float32,
     W [C_in, C_out, M] complex64 (one matrix per mode 0..M-1)."""
-    import torch
-    if x.dtype != torch.float32 or y.dtype != torch.float32 or W.dtype != torch.complex64:
-        raise TypeError("x, y must be float32 and W complex64")
-    for t, what in ((x, "x"), (W, "W"), (y, "y")):
-        if not t.is_contiguous() or not t.is_cuda:
-            raise TypeError(f"{what} must be a contiguous device tensor")
-    if x.dim() != 3 or y.dim() != 3 or W.dim() != 3:
+    _check_real(x, W, y)
+    xs, ws, ys = x.shape, W.shape, y.shape
+    if len(xs) != 3 or len(ys) != 3 or len(ws) != 3:
         raise ValueError("x, y must be [B, C, N]; W must be [C_in, C_out, M]")
-    B, C_in, N = x.shape
-    C_out, M = W.shape[1], W.shape[2]
-    if W.shape[0] != C_in or tuple(y.shape) != (B, C_out, N):
+    B, C_in, N = xs
+    C_out = ws[1]
+    if ws[0] != C_in or ys[0] != B or ys[1] != C_out or ys[2] != N:
         raise ValueError("inconsistent tensor shapes")
-    ensure_workspace(lib().tfno_fno1d_real_workspace_bytes(B, C_in, C_out, N, M), x.device)
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    st = lib().tfno_fno1d_real(x.data_ptr(), W.data_ptr(), y.data_ptr(), B, C_in, C_out, N, M, stream)
-    if st != OK:
-        raise TfnoError(st, "tfno_fno1d_real")
-    return y
+    sizes = (B, C_in, C_out, N, ws[2])
+    need = _need("tfno_fno1d_real_workspace_bytes", *sizes)
+    if need:
+        ensure_workspace(need, x.device)
+    return _launch("tfno_fno1d_real", x, W, y, sizes, stream)
