@@ -48,25 +48,36 @@ static hipError_t pick_fwd(const MatdftArgs &a, hipStream_t s)
     }
 }
 
-template <int PT, int NMAX, int IN, int OUT>
+template <int PT, int NMAX, int IN, int OUT, int G = 0>
 static hipError_t launch_inv(MatdftArgs a, hipStream_t s)
 {
-    constexpr size_t lds = MdRoots<NMAX>::BYTES;
+    // (G: the eight pencils that each of the 4 / G groups of waves puts together, N < 128 G points each)
+    constexpr size_t most = MdRoots<NMAX>::BYTES + 16 + (G ? sizeof(c64) * 4 / (G ? G : 1) * 8 * (128 * G - 1) : 0);
     static LdsLimitOnce limit;
-    const hipError_t e = limit.set({reinterpret_cast<const void *>(&k_matdft_inv<PT, NMAX, IN, OUT>)}, (int)lds);
+    const hipError_t e = limit.set({reinterpret_cast<const void *>(&k_matdft_inv<PT, NMAX, IN, OUT, G>)}, (int)most);
     if (e != hipSuccess) return e;
-    a.groups = (a.N / 2 + 32 * PT) / (32 * PT);             // output pairs 0 .. N/2
+    const size_t lds = MdRoots<NMAX>::BYTES + 16 + (G ? sizeof(c64) * 4 / (G ? G : 1) * 8 * a.N : 0);
+    a.groups = G ? G : (a.N / 2 + 32 * PT) / (32 * PT);     // output pairs 0 .. N/2
     const unsigned long long blocks = ((unsigned long long)((a.P + 31) / 32) * a.groups + 3) / 4;
     if (blocks > 0x7fffffffULL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_matdft_inv<PT, NMAX, IN, OUT>), dim3((unsigned)blocks), dim3(256), lds, s, a);
+    hipLaunchKernelGGL((k_matdft_inv<PT, NMAX, IN, OUT, G>), dim3((unsigned)blocks), dim3(256), lds, s, a);
     return hipGetLastError();
 }
 
 template <int IN, int OUT>
 static hipError_t pick_inv(const MatdftArgs &a, hipStream_t s)
 {
-    // two tiles of output pairs per wave where they divide the pairs evenly and leave a wave for every SIMD
     const unsigned long long tiles = (a.P + 31) / 32;
+    if constexpr (OUT == MD_ROWS) {
+        // Whole pencils per workgroup for outputs that the caches do not hold and that fill the chip this way (whole layer,
+        // 85 x 85, B 32, C 32: 62.3 -> 57.8 us; 200 x 200, B 16, C 16: 80 -> 68.5; N 500, B 300, C 64: 87 -> 80; below 64
+        // points half the output pairs would be padding: 48 x 60, B 64, C 32: 47 -> 50, not used).
+        if (a.N >= 64 && a.N < 512 && a.out_outer == a.N && (unsigned long long)a.P * a.N * sizeof(c64) >= (32ULL << 20) && tiles * ((a.N + 128) / 128) >= 1024) {
+            if (a.N < 128) return launch_inv<2, 1024, IN, OUT, 1>(a, s);
+            return a.N < 256 ? launch_inv<2, 1024, IN, OUT, 2>(a, s) : launch_inv<2, 1024, IN, OUT, 4>(a, s);
+        }
+    }
+    // two tiles of output pairs per wave where they divide the pairs evenly and leave a wave for every SIMD
     const int nt = (a.N / 2 + 32) / 32;
     const bool two = nt % 2 == 0 && tiles * (nt / 2) >= 1024;
     if (a.N <= 1024) return two ? launch_inv<2, 1024, IN, OUT>(a, s) : launch_inv<1, 1024, IN, OUT>(a, s);

@@ -69,6 +69,14 @@ struct MdRoots {
     }
 };
 
+// Orders this wave's LDS traffic (all lanes) without a workgroup barrier.
+__device__ __forceinline__ void wave_sync_md()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Position of a pencil on the strided and spectrum sides.
 struct MdPencil {
     long long strided;      // offset of element 0, strided side with `outer`
@@ -284,22 +292,28 @@ k_matdft_fwd(MatdftArgs a)
 }
 
 // ------------------------------------------------------------------------------------------------ inverse
-template <int PT, int NMAX, int IN, int OUT>
+// G (contiguous outputs only): G = 1, 2, 4 waves of the workgroup own whole pencils, N < 128 G.  They put eight of them at a
+// time together in LDS and store them as whole 128-byte lines past the caches.  A wave that stores its own 256-byte pieces
+// leaves partial lines, which only the caches can merge; of a large output these stay in the last-level cache as dirty lines,
+// and the next kernel's reads wait for their write-back (32 x 32 fields of 85 x 85: the next forward kernel takes 25 instead
+// of 18 us; with non-temporal stores of pieces it is the inverse kernel that doubles).  G = 0: every wave on its own.
+template <int PT, int NMAX, int IN, int OUT, int G>
 __global__ void __launch_bounds__(256, 2)
 k_matdft_inv(MatdftArgs a)
 {
     using Tab = MdRoots<NMAX>;
     constexpr bool COLQ = OUT == MD_STRIDED;
+    static_assert(G == 0 || (OUT == MD_ROWS && PT == 2), "whole pencils are contiguous ones");
     extern __shared__ __align__(16) unsigned char md_lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, h = lane >> 5;
     const int N = a.N, H = N / 2;                           // output pairs 0 .. H
     Tab::build(md_lds, N, tid, 256);
 
-    const unsigned item = blockIdx.x * 4 + wave;
+    const unsigned item = blockIdx.x * 4 + wave;            // (G: groups = G)
     const unsigned q0 = item / (unsigned)a.groups * 32;
     const int n0 = (int)(item % (unsigned)a.groups) * 32 * PT;
-    if (q0 >= a.P) return;
+    if (G == 0 && q0 >= a.P) return;
 
     const unsigned q = q0 + col < a.P ? q0 + col : a.P - 1;
     MdPencil pos{};
@@ -401,6 +415,37 @@ k_matdft_inv(MatdftArgs a)
     }
 
     // ---- stores: outputs n and N - n (0 and the middle of an even length have no partner)
+    if constexpr (G > 0) {
+        constexpr int T = 64 * G;                           // threads that store together
+        const int t = tid % T;
+        c64 *stage = reinterpret_cast<c64 *>(md_lds + Tab::BYTES / 16 * 16 + 16) + (tid / T) * (8 * N);
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {                    // pencils q0 + 8 rg .. + 7
+            if constexpr (G > 1) __syncthreads();
+            else wave_sync_md();
+#pragma unroll
+            for (int tt = 0; tt < PT; ++tt) {
+                const int n = n0 + 32 * tt + col;
+#pragma unroll
+                for (int r = 4 * rg; r < 4 * rg + 4; ++r) {
+                    c64 *row = stage + (4 * h + r % 4) * N;
+                    if (n <= H) row[n] = make_float2(cr[tt][r] - si[tt][r], ci[tt][r] + sr[tt][r]);
+                    if (n <= H && n && 2 * n != N) row[N - n] = make_float2(cr[tt][r] + si[tt][r], ci[tt][r] - sr[tt][r]);
+                }
+            }
+            if constexpr (G > 1) __syncthreads();
+            else wave_sync_md();
+            const unsigned p0 = q0 + 8 * rg;
+            if (p0 < a.P) {
+                const int count = (int)(a.P - p0 < 8 ? a.P - p0 : 8) * N;
+                c64 *dst = a.out + (long long)p0 * N;
+                const int lead = (int)(((unsigned long long)dst >> 3) & 15);       // elements since the last line boundary
+                for (int e = t - lead; e < count; e += T)
+                    if (e >= 0) store_nt(dst + e, stage[e]);
+            }
+        }
+        return;
+    }
     const int out_es = COLQ ? (int)a.inner : 1;
 #pragma unroll
     for (int t = 0; t < PT; ++t)
