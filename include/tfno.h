@@ -35,8 +35,9 @@
  *  - N must be a power of two, 2 <= N <= 4096; 1 <= K <= N; C_in, C_out >= 1.  The staged entry points (and
  *    tfno_spectral_conv1d_auto, which falls back to them) also take any other 2 <= N <= 4096.
  *  - Mode counts: the kernels are built for the power-of-two K that each entry point lists.  Every other K, down
- *    to 1, runs on the next built size K' >= K: the forward transform zeroes bins K .. K'-1 before the contraction,
- *    which is exactly the truncation to K (Sec. 3.3), so e.g. K = 12, 20 or 48 are served by the fused kernels; a
+ *    to 1, runs on the next built size K' >= K: the forward transform zeroes bins K .. K'-1 before the contraction, or,
+ *    where truncated spectra go through the workspace, stores only the K kept ones, which is exactly the truncation to
+ *    K (Sec. 3.3), so e.g. K = 12, 20 or 48 are served by the fused kernels; a
  *    call is TFNO_ERR_UNSUPPORTED only when no built size >= K exists for its N.  Workspace sizes follow K'.
  *  - Thread safety: entry points may be called concurrently from several host
  *    threads; tfno_set_workspace must not race with calls that use the workspace.
@@ -128,6 +129,11 @@ tfno_status tfno_spectral_conv2d_noalloc(const void *x, const void *W, void *y,
  * version transforms both axes with separate launches).  Same contract and same
  * result as the fused entry points; accepts every valid shape.  Needs
  * tfno_workspace_bytes(dims, 1, ...) bytes of workspace.
+ *
+ * With a side that is no power of two these entry points are the way to run the layer, not a baseline: they run
+ * pruned transforms as contractions with the kept columns of the DFT matrix around the mode CGEMM (three launches in
+ * 1-D, five in 2-D) inside the same workspace; batches so small that whole 128-mode tiles of spectrum do not fit it
+ * (fewer than 128 points) keep the five stages with direct sums.
  */
 tfno_status tfno_spectral_conv1d_staged(const void *x, const void *W, void *y,
                                         int B, int C_in, int C_out, int N, int K, void *stream);
