@@ -55,11 +55,17 @@ size_t pruned1d_spectrum_elems(long long B, int C, int Mp) { return (size_t)mode
 
 int pruned1d_stride(int N, int K_keep)
 {
-    const int N1 = N / 256;                                 // long pencils: whole columns of the N1 x 256 array
-    return N >= 2048 ? (K_keep + N1 - 1) / N1 * N1 : spectrum_stride(K_keep);
+    if (N < 2048) return spectrum_stride(K_keep);
+    // Long pencils: whole columns of the N1 x 256 array, and all of the kernel's K2 columns where less than an eighth
+    // of them would go: the masks then cost what the shorter spectra save (B 64, 128 x 128 channels, 2048 points: 63 of 64
+    // columns 95.8 us masked, 94.8 in full; 34 of 64 columns 88.7 against 92.6; B 32, 4096 points, 57 of 64: 99.0 both).
+    const int N1 = N / 256, cols = (K_keep + N1 - 1) / N1;
+    int K2 = 16;
+    while (K2 < cols) K2 *= 2;
+    return (8 * cols > 7 * K2 ? K2 : cols) * N1;
 }
 
-template <int N, int K, bool REAL = false>
+template <int N, int K, bool REAL, bool ALL>
 static hipError_t launch_nk(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
                             int C_out, int K_keep, int Mp, hipStream_t s)
 {
@@ -70,20 +76,28 @@ static hipError_t launch_nk(int stages, const c64 *x, const c64 *W, c64 *y, c64 
     // a few sweeps per workgroup amortise the twiddle tables and keep a prefetch in flight
     // (measured: the forward kernels gain 2 - 4 % and the real-valued inverse 13 % from the balanced grid; the complex
     // inverse kernels, which write twice the bytes, lose 4 % and keep the fixed grid)
-    const unsigned gin = balanced_grid<&k_fwd1d<N, K, REAL>>(sin, 256);
-    const unsigned gout = REAL ? balanced_grid<&k_inv1d<N, K, REAL>>(sout, 256) : (unsigned)(sout < 1024 ? sout : 1024);
+    const unsigned gin = balanced_grid<&k_fwd1d<N, K, REAL, ALL>>(sin, 256);
+    const unsigned gout = REAL ? balanced_grid<&k_inv1d<N, K, REAL, ALL>>(sout, 256) : (unsigned)(sout < 1024 ? sout : 1024);
     hipError_t e = hipSuccess;
     if (stages & PRUNED_FWD) {
-        hipLaunchKernelGGL((k_fwd1d<N, K, REAL>), dim3(gin), dim3(256), 0, s, x, Xh, C_in, pin, K_keep, Mp);
+        hipLaunchKernelGGL((k_fwd1d<N, K, REAL, ALL>), dim3(gin), dim3(256), 0, s, x, Xh, C_in, pin, K_keep, Mp);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (stages & PRUNED_GEMM)
         if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / (float)N, tiles, s)) != hipSuccess) return e;
     if (stages & PRUNED_INV) {
-        hipLaunchKernelGGL((k_inv1d<N, K, REAL>), dim3(gout), dim3(256), 0, s, (const c64 *)Yh, y, C_out, pout, K_keep, Mp);
+        hipLaunchKernelGGL((k_inv1d<N, K, REAL, ALL>), dim3(gout), dim3(256), 0, s, (const c64 *)Yh, y, C_out, pout, K_keep, Mp);
         e = hipGetLastError();
     }
     return e;
+}
+
+template <int N, int K, bool REAL = false>
+static hipError_t launch_nk(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
+                            int C_out, int K_keep, int Mp, hipStream_t s)
+{
+    if (K_keep == K && Mp == K) return launch_nk<N, K, REAL, true>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    return launch_nk<N, K, REAL, false>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
 }
 
 template <int N1, int K2, bool ALL>

@@ -153,14 +153,17 @@ k_inv1d_long(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long n
 #pragma unroll
         for (int kh = 0; kh < KH; ++kh) {
             const int k2 = p + 16 * kh;
-            const c64 val = Yh[spec1d_index(b * (N1 * K2_keep) + k1 * K2_keep + (ALL || k2 < K2_keep ? k2 : 0), ch, C)];
-            yin[kh] = ALL || k2 < K2_keep ? val : make_float2(0.f, 0.f);
+            yin[kh] = Yh[spec1d_index(b * (N1 * K2_keep) + k1 * K2_keep + (ALL || k2 < K2_keep ? k2 : 0), ch, C)];
         }
     };
     auto stage = [&](long long sweep, auto refill, long long next_sweep) __attribute__((always_inline)) {
         constexpr bool REFILL = decltype(refill)::value;
         // zero-padded, input-pruned 256-point inverse of row g (the stage of the short-pencil kernel)
-        dft_prune_in<16, KH, +1>(yin, [&](auto ppc, c64 val) __attribute__((always_inline)) {
+        // (bins that do not exist become zeros here and not beside the load, which would wait for the data at once)
+        c64 t[KH];
+#pragma unroll
+        for (int kh = 0; kh < KH; ++kh) t[kh] = ALL || p + 16 * kh < K2_keep ? yin[kh] : make_float2(0.f, 0.f);
+        dft_prune_in<16, KH, +1>(t, [&](auto ppc, c64 val) __attribute__((always_inline)) {
             constexpr int pp = decltype(ppc)::value;
             patch[p * 16 + (pp ^ p)] = val;
         });
