@@ -9,6 +9,9 @@
 // workgroups per CU (512 rows: 64 KB of LDS).  4 x 32 fields of 512 x 512 (268 MB), 64 modes: forward 61 us, inverse 63 us
 // = 5.0 and 4.8 TB/s (a radix-2 transform of the same columns in LDS: 397 and 323 us); 32 modes: 53 and 56 us.  The
 // tile's p rows are padded by 16 elements, so that the four p of a wave meet different bank halves.
+//
+// SPEC: the modes are the truncated spectrum of grids whose last axis has another transform, mode-tile major as the
+// contraction kernels take it (mode k of column n2 of field b C + c is mode b M + k N2 + n2), and N2 is any number of columns.
 #pragma once
 #include "common.h"
 #include "fft_regs.h"
@@ -34,9 +37,16 @@ __device__ __forceinline__ void col_twiddles(c64 *tw, int tid)
     for (int i = tid; i < P * T; i += CfgCol<P, T, Q>::NT) tw[i] = cis2pi(-(float)((i / P) * (i % P)), (float)(P * T));
 }
 
-template <int P, int T, int Q>
+// element `col` of row k of a mode-tile-major spectrum (see above)
+__device__ __forceinline__ long long col_spec(unsigned b, unsigned c, int C, long long M, int k, int N2, int col)
+{
+    const long long m = b * M + (long long)k * N2 + col;
+    return ((m >> 7) * C + c) * 128 + (m & 127);
+}
+
+template <int P, int T, int Q, bool SPEC>
 __global__ void __launch_bounds__((CfgCol<P, T, Q>::NT), (CfgCol<P, T, Q>::WG_PER_CU))
-k_colfft_fwd(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, unsigned groups)
+k_colfft_fwd(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, unsigned groups, int Cs, long long M)
 {
     using C = CfgCol<P, T, Q>;
     extern __shared__ __align__(16) unsigned char col_lds[];
@@ -44,14 +54,20 @@ k_colfft_fwd(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, 
     __shared__ c64 tw[P * T];                               // w_N1^(t p) at [t][p]
     const int tid = threadIdx.x, col = tid & 15, sub = tid >> 4;
     const unsigned field = blockIdx.x / groups, g = blockIdx.x % groups;
-    const c64 *__restrict__ src = in + (long long)field * C::N1 * N2 + 16 * g + col;
-    c64 *__restrict__ dst = out + (long long)field * K1 * N2 + 16 * g + col;
+    // (SPEC: columns past the last one read it again and are not stored)
+    const int n2 = (int)(16 * g) + col, n2_in = SPEC && n2 >= N2 ? N2 - 1 : n2;
+    const c64 *__restrict__ src = in + (long long)field * C::N1 * N2 + n2_in;
+    c64 *__restrict__ dst = out + (long long)field * K1 * N2 + n2;
+    const unsigned sb = SPEC ? field / (unsigned)Cs : 0, sc = SPEC ? field % (unsigned)Cs : 0;
 
     c64 v[C::TPT][P];
 #pragma unroll
     for (int i = 0; i < C::TPT; ++i)
 #pragma unroll
-        for (int j = 0; j < P; ++j) v[i][j] = load_nt(src + (long long)(sub + (C::NT / 16) * i + T * j) * N2);
+        for (int j = 0; j < P; ++j) {
+            const c64 *row = src + (long long)(sub + (C::NT / 16) * i + T * j) * N2;
+            v[i][j] = SPEC ? *row : load_nt(row);
+        }
     __builtin_amdgcn_sched_barrier(0);
     col_twiddles<P, T, Q>(tw, tid);                         // while the loads are in flight
     __syncthreads();
@@ -73,14 +89,20 @@ k_colfft_fwd(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, 
             return Z[p * C::PS + t * 16 + col];
         }, xo);
 #pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if (p + P * q < K1) dst[(long long)(p + P * q) * N2] = xo[q];
+        for (int q = 0; q < Q; ++q) {
+            const int k = p + P * q;
+            if constexpr (SPEC) {
+                if (k < K1 && n2 < N2) out[col_spec(sb, sc, Cs, M, k, N2, n2)] = xo[q];
+            } else {
+                if (k < K1) dst[(long long)k * N2] = xo[q];
+            }
+        }
     }
 }
 
-template <int P, int T, int Q>
+template <int P, int T, int Q, bool SPEC>
 __global__ void __launch_bounds__((CfgCol<P, T, Q>::NT), (CfgCol<P, T, Q>::WG_PER_CU))
-k_colfft_inv(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, unsigned groups)
+k_colfft_inv(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, unsigned groups, int Cs, long long M)
 {
     using C = CfgCol<P, T, Q>;
     extern __shared__ __align__(16) unsigned char col_lds[];
@@ -88,8 +110,10 @@ k_colfft_inv(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, 
     __shared__ c64 tw[P * T];
     const int tid = threadIdx.x, col = tid & 15, sub = tid >> 4;
     const unsigned field = blockIdx.x / groups, g = blockIdx.x % groups;
-    const c64 *__restrict__ src = in + (long long)field * K1 * N2 + 16 * g + col;
-    c64 *__restrict__ dst = out + (long long)field * C::N1 * N2 + 16 * g + col;
+    const int n2 = (int)(16 * g) + col, n2_in = SPEC && n2 >= N2 ? N2 - 1 : n2;
+    const c64 *__restrict__ src = in + (long long)field * K1 * N2 + n2;
+    c64 *__restrict__ dst = out + (long long)field * C::N1 * N2 + n2;
+    const unsigned sb = SPEC ? field / (unsigned)Cs : 0, sc = SPEC ? field % (unsigned)Cs : 0;
 
     c64 v[C::IPT][Q];
 #pragma unroll
@@ -97,7 +121,7 @@ k_colfft_inv(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, 
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int k = sub + (C::NT / 16) * i + P * q;
-            const c64 w = src[(long long)(k < K1 ? k : 0) * N2];
+            const c64 w = SPEC ? in[col_spec(sb, sc, Cs, M, k < K1 ? k : 0, N2, n2_in)] : src[(long long)(k < K1 ? k : 0) * N2];
             v[i][q] = k < K1 ? w : make_float2(0.f, 0.f);
         }
     __builtin_amdgcn_sched_barrier(0);
@@ -124,7 +148,13 @@ k_colfft_inv(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, 
         for (int p = 0; p < P; ++p) z[p] = Z[p * C::PS + t * 16 + col];
         RegFFT<P, +1, 1>::run(z, r);
 #pragma unroll
-        for (int j = 0; j < P; ++j) store_nt(dst + (long long)(t + T * j) * N2, r[j]);
+        for (int j = 0; j < P; ++j) {
+            if constexpr (SPEC) {           // (read again by the next kernel)
+                if (n2 < N2) dst[(long long)(t + T * j) * N2] = r[j];
+            } else {
+                store_nt(dst + (long long)(t + T * j) * N2, r[j]);
+            }
+        }
     }
 }
 

@@ -7,6 +7,8 @@ namespace tfno {
 // N in {64, 128, 256} with K a multiple of 16 such that K/16 divides N/16, N = 1024 with K in {64, 128}, or
 // N in {2048, 4096} with K / (N / 256) in {16, 32, 64, 128, 256}.
 bool pruned1d_supported(int N, int K);
+// The smallest built power of two >= K for pencils of N points; 0: none.
+int pruned1d_modes(int N, int K);
 // Workspace for the truncated spectra of input and output, padded to whole 128-mode tiles.
 size_t pruned1d_workspace_bytes(long long B, int C_in, int C_out, int K);
 // K_keep (1 .. K): bins K_keep .. K-1 of the forward transform are dropped, which truncates to K_keep modes.

@@ -23,6 +23,13 @@ bool pruned1d_supported(int N, int K)
     return (KH & (KH - 1)) == 0 && KH <= LPR;
 }
 
+int pruned1d_modes(int N, int K)
+{
+    for (int k = 16; k <= N; k <<= 1)
+        if (k >= K && pruned1d_supported(N, k)) return k;
+    return 0;
+}
+
 static long long mode_tiles(long long B, int K) { return (B * K + 127) / 128; }
 
 // Grid of a grid-stride transform kernel: as many workgroups as the chip holds at once (asked of the runtime once per

@@ -20,13 +20,21 @@ namespace tfno {
 // zero padding / truncation for the first axis of the 2-D pipeline.
 // in == out is allowed when both sides use the same strides (a workgroup reads all of its pencils
 // before it writes any).
+// SPEC: the forward transform writes (the inverse reads) a truncated spectrum, mode-tile major as the contraction kernels
+// take it, instead of strided pencils: element n of column r = q % inner_count of image q / inner_count = b spec_C + c is
+// mode m = b spec_M + n inner_count + r at ((m / 128) spec_C + c) 128 + m % 128.
 // ---------------------------------------------------------------------------------------------
-template <int DIR>
+template <int DIR, bool SPEC>
 __global__ void __launch_bounds__(256)
 k_staged_fft(const c64 *__restrict__ in, c64 *__restrict__ out, int N, int log2N, int PC,
              long long num_pencils, long long inner_count, long long in_outer_stride,
-             long long out_outer_stride, long long elem_stride, int n_in, int n_out, float scale)
+             long long out_outer_stride, long long elem_stride, int n_in, int n_out, float scale, int spec_C, long long spec_M)
 {
+    auto spec = [&](long long q, int n) __attribute__((always_inline)) {
+        const long long img = q / inner_count, b = img / spec_C;
+        const long long m = b * spec_M + n * inner_count + (q - img * inner_count);
+        return ((m >> 7) * spec_C + (img - b * spec_C)) * 128 + (m & 127);
+    };
     extern __shared__ float2 lds[];
     c64 *buf0 = lds;                  // [PC][N]
     c64 *buf1 = lds + (size_t)PC * N; // [PC][N]
@@ -38,7 +46,7 @@ k_staged_fft(const c64 *__restrict__ in, c64 *__restrict__ out, int N, int log2N
     for (int m = tid; m < N / 2; m += nth) tw[m] = cis2pi((float)(DIR * m), (float)N);
 
     const int total = PC * N;
-    if (elem_stride == 1) {
+    if (!SPEC && elem_stride == 1) {
         for (int i = tid; i < total; i += nth) {
             int j = i / N, n = i - j * N;
             long long q = q0 + j;
@@ -50,9 +58,12 @@ k_staged_fft(const c64 *__restrict__ in, c64 *__restrict__ out, int N, int log2N
         for (int i = tid; i < total; i += nth) {
             int n = i / PC, j = i - n * PC;
             long long q = q0 + j;
-            if (q < num_pencils)
-                buf0[j * N + n] = n < n_in ? in[(q / inner_count) * in_outer_stride + (q % inner_count) + n * elem_stride]
-                                           : make_float2(0.f, 0.f);
+            if (q < num_pencils) {
+                if constexpr (SPEC && DIR > 0) buf0[j * N + n] = n < n_in ? in[spec(q, n)] : make_float2(0.f, 0.f);
+                else
+                    buf0[j * N + n] = n < n_in ? in[(q / inner_count) * in_outer_stride + (q % inner_count) + n * elem_stride]
+                                               : make_float2(0.f, 0.f);
+            }
         }
     }
     __syncthreads();
@@ -75,7 +86,7 @@ k_staged_fft(const c64 *__restrict__ in, c64 *__restrict__ out, int N, int log2N
         c64 *tmp = src; src = dst; dst = tmp;
     }
 
-    if (elem_stride == 1) {
+    if (!SPEC && elem_stride == 1) {
         for (int i = tid; i < total; i += nth) {
             int j = i / N, n = i - j * N;
             long long q = q0 + j;
@@ -90,8 +101,10 @@ k_staged_fft(const c64 *__restrict__ in, c64 *__restrict__ out, int N, int log2N
             long long q = q0 + j;
             if (q < num_pencils && n < n_out) {
                 c64 v = src[j * N + n];
-                out[(q / inner_count) * out_outer_stride + (q % inner_count) + n * elem_stride] =
-                    make_float2(v.x * scale, v.y * scale);
+                if constexpr (SPEC && DIR < 0) out[spec(q, n)] = make_float2(v.x * scale, v.y * scale);
+                else
+                    out[(q / inner_count) * out_outer_stride + (q % inner_count) + n * elem_stride] =
+                        make_float2(v.x * scale, v.y * scale);
             }
         }
     }
@@ -193,12 +206,13 @@ hipError_t launch_axis_fft(int dir, const c64 *in, c64 *out, int N, long long nu
                            long long elem_stride, int n_in, int n_out, float scale, hipStream_t s)
 {
     static LdsLimitOnce fft_limit, dft_limit;
-    hipError_t e = fft_limit.set({reinterpret_cast<const void *>(&k_staged_fft<-1>),
-                                  reinterpret_cast<const void *>(&k_staged_fft<+1>)}, 96 * 1024);
+    hipError_t e = fft_limit.set({reinterpret_cast<const void *>(&k_staged_fft<-1, false>),
+                                  reinterpret_cast<const void *>(&k_staged_fft<+1, false>)}, 96 * 1024);
     if (e != hipSuccess) return e;
     if (num_pencils == 0) return hipSuccess;
     int PC = 4096 / N; if (PC > 16) PC = 16; if (PC < 1) PC = 1;
     if (inner_count > 1) { while (PC > 1 && inner_count % PC) PC >>= 1; }
+    while (num_pencils / PC >= (1 << 24) - 1 && PC * N <= 2048) PC <<= 1;      // (a launch has fewer than 2^32 threads)
     if ((N & (N - 1)) != 0) {                               // not a power of two: direct sum
         e = dft_limit.set({reinterpret_cast<const void *>(&k_staged_dft<-1>),
                            reinterpret_cast<const void *>(&k_staged_dft<+1>)}, 96 * 1024);
@@ -217,11 +231,34 @@ hipError_t launch_axis_fft(int dir, const c64 *in, c64 *out, int N, long long nu
     long long blocks = (num_pencils + PC - 1) / PC;
     int threads = 256;
     if (dir < 0)
-        hipLaunchKernelGGL(k_staged_fft<-1>, dim3((unsigned)blocks), dim3(threads), lds, s, in, out, N, ilog2(N), PC,
-                           num_pencils, inner_count, in_outer_stride, out_outer_stride, elem_stride, n_in, n_out, scale);
+        hipLaunchKernelGGL((k_staged_fft<-1, false>), dim3((unsigned)blocks), dim3(threads), lds, s, in, out, N, ilog2(N), PC,
+                           num_pencils, inner_count, in_outer_stride, out_outer_stride, elem_stride, n_in, n_out, scale, 1, 0LL);
     else
-        hipLaunchKernelGGL(k_staged_fft<+1>, dim3((unsigned)blocks), dim3(threads), lds, s, in, out, N, ilog2(N), PC,
-                           num_pencils, inner_count, in_outer_stride, out_outer_stride, elem_stride, n_in, n_out, scale);
+        hipLaunchKernelGGL((k_staged_fft<+1, false>), dim3((unsigned)blocks), dim3(threads), lds, s, in, out, N, ilog2(N), PC,
+                           num_pencils, inner_count, in_outer_stride, out_outer_stride, elem_stride, n_in, n_out, scale, 1, 0LL);
+    return hipGetLastError();
+}
+
+hipError_t launch_axis_fft_spec(int dir, const c64 *in, c64 *out, int N, int K, long long images, int cols, int C, long long M,
+                                hipStream_t s)
+{
+    static LdsLimitOnce limit;
+    hipError_t e = limit.set({reinterpret_cast<const void *>(&k_staged_fft<-1, true>),
+                              reinterpret_cast<const void *>(&k_staged_fft<+1, true>)}, 96 * 1024);
+    if (e != hipSuccess) return e;
+    if (images <= 0) return hipSuccess;
+    const long long pencils = images * cols;
+    int PC = N >= 4096 ? 1 : N > 256 ? 4096 / N : 16;       // (the columns of a workgroup may belong to several images)
+    while (pencils / PC >= (1 << 24) - 1 && PC * N <= 2048) PC <<= 1;          // (a launch has fewer than 2^32 threads)
+    while (pencils / PC < 512 && PC > 1) PC >>= 1;          // (few columns: two workgroups per CU before wide accesses)
+    const long long outer = (long long)N * cols, blocks = (pencils + PC - 1) / PC;
+    const size_t lds = ((size_t)2 * PC * N + N / 2) * sizeof(c64);
+    if (dir < 0)
+        hipLaunchKernelGGL((k_staged_fft<-1, true>), dim3((unsigned)blocks), dim3(256), lds, s, in, out, N, ilog2(N), PC, pencils,
+                           (long long)cols, outer, 0LL, (long long)cols, N, K, 1.f, C, M);
+    else
+        hipLaunchKernelGGL((k_staged_fft<+1, true>), dim3((unsigned)blocks), dim3(256), lds, s, in, out, N, ilog2(N), PC, pencils,
+                           (long long)cols, 0LL, outer, (long long)cols, K, N, 1.f, C, M);
     return hipGetLastError();
 }
 

@@ -28,13 +28,13 @@ def say(msg):
     sys.stdout.flush()
 
 
-def check(got: np.ndarray, want: np.ndarray, what=""):
+def check(got: np.ndarray, want: np.ndarray, what="", rel_l2=REL_L2):
     got = got.astype(np.complex128)
     err = got - want
     rel = np.linalg.norm(err.ravel()) / np.linalg.norm(want.ravel())
     mx = np.max(np.abs(err)) / np.max(np.abs(want))
     say(f"   {what}: rel_l2={rel:.3e} max_abs/max|y|={mx:.3e}")
-    assert rel <= REL_L2, f"{what}: relative L2 {rel:.3e}"
+    assert rel <= rel_l2, f"{what}: relative L2 {rel:.3e}"
     assert mx <= MAX_ABS, f"{what}: max abs {mx:.3e}"
 
 
@@ -289,6 +289,32 @@ def test_2d_sides_with_odd_factors(gpu, oracle_mod, shape):
     W = inputs.make_W(1560 + N1 + K2, Ci, Co)
     want, _ = oracle_mod.spectral_conv2d_rect(x, W, K1, K2)
     check(run_gpu_rect(gpu, "spectral_conv2d_rect_staged", x, W, K1, K2), want, "odd sides")
+
+
+# One side a power of two, the other with odd factors: every transform that a power of two can take on either axis (column
+# kernels with column counts around their 16, mode counts at and past what they take; pruned row kernels of every length
+# with whole and cut spectra; the radix-2 transform of the lengths that have neither).  (C_in, C_out, N1, N2, K1, K2)
+MIXED_2D = [(2, 3, 4096, 3, 4096, 3), (2, 3, 3, 4096, 3, 4096), (3, 2, 1024, 48, 1024, 48), (3, 2, 48, 1024, 48, 1024),
+            (2, 2, 2048, 7, 2048, 7), (2, 2, 7, 2048, 7, 2048), (2, 2, 5, 2048, 5, 17), (2, 2, 6, 4096, 3, 500),
+            (2, 2, 512, 13, 512, 6), (3, 3, 512, 33, 128, 33), (3, 3, 512, 31, 1, 15), (3, 3, 512, 48, 129, 20), (2, 2, 13, 512, 9, 300),
+            (4, 3, 256, 25, 128, 16), (4, 3, 256, 25, 17, 17), (4, 3, 256, 25, 129, 1), (4, 3, 25, 256, 20, 33), (4, 3, 25, 256, 25, 256),
+            (5, 4, 128, 100, 33, 48), (5, 4, 128, 9, 16, 9), (5, 4, 100, 128, 30, 20), (5, 4, 9, 128, 9, 128),
+            (5, 4, 64, 96, 64, 7), (5, 4, 64, 96, 8, 96), (5, 4, 96, 64, 7, 64), (5, 4, 96, 64, 50, 9), (5, 4, 60, 1024, 12, 100),
+            (5, 4, 16, 31, 16, 31), (5, 4, 31, 16, 31, 16), (5, 4, 2, 130, 1, 40), (5, 4, 130, 2, 40, 2), (3, 3, 32, 50, 20, 33)]
+
+
+@pytest.mark.parametrize("shape", MIXED_2D, ids=lambda s: "Ci%d_Co%d_N%dx%d_K%dx%d" % s)
+def test_2d_one_side_a_power_of_two(gpu, oracle_mod, shape):
+    """The side that is a power of two keeps the error of a butterfly network, which grows with the square root of its depth:
+    at most 12 steps each way of about 0.7 rounding units (2^-24), sqrt(24) 0.7 2^-24 = 2.0e-7, beside 1.5e-7 for the
+    short other side and 1e-7 for the contraction: 2.7e-7 together; the bound is half as much again.  (One 32-bit sum over
+    such a side gives 5e-7 at 1024 points and 1.1e-6 at 4096.)"""
+    Ci, Co, N1, N2, K1, K2 = shape
+    say(f"[case] mixed sides {shape}")
+    x = inputs.make_x(1570 + N1 + K2, 2, Ci, (N1, N2))
+    W = inputs.make_W(1570 + N1 + K2, Ci, Co)
+    want, _ = oracle_mod.spectral_conv2d_rect(x, W, K1, K2)
+    check(run_gpu_rect(gpu, "spectral_conv2d_rect_staged", x, W, K1, K2), want, "mixed sides", rel_l2=4e-7)
 
 
 def test_2d_staged_general_shape(gpu, oracle_mod):
