@@ -101,6 +101,11 @@ struct CfgMdF {
 };
 
 // VEC: contiguous pencils of at least 40 points, fetched 16 bytes at a time.
+//
+// ROWS -> ROWS (the first transform of a field): the matrix pipe rounds its sums downwards, not to nearest, so that all bins of
+// all rows carry an offset of the same sign.  The other axis adds the rows up, and bin 0 there collects the offsets while the
+// data add up like noise: 4096 x 3 points had 4.9e-7 of error in the bins of k1 = 0 against 1e-7 in the others.  Every
+// other pencil therefore goes through with its sign turned round, which moves the offsets to the highest frequency.
 template <int JT, int WI, int NMAX, int IN, int OUT, bool VEC>
 __global__ void __launch_bounds__((CfgMdF<JT, WI, NMAX>::NT), 2)
 k_matdft_fwd(MatdftArgs a)
@@ -113,6 +118,8 @@ k_matdft_fwd(MatdftArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, h = lane >> 5;
     const int N = a.N, H = N / 2;                           // slots 0 .. H: the pairs (n, N - n)
+    constexpr bool ALT = IN == MD_ROWS && OUT == MD_ROWS;   // (above)
+    const unsigned turn = (unsigned)(lane & 1) << 31;
     Tab::build(md_lds, N, tid, Cf::NT);
 
     const unsigned item = WI > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
@@ -208,7 +215,11 @@ k_matdft_fwd(MatdftArgs a)
             uintx4 re[2][3], im[2][3];                      // (s.re, d.im) and (s.im, -d.re) of the 8 pairs
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const c64 x = u[e], y = v[7 - e];
+                c64 x = u[e], y = v[7 - e];
+                if constexpr (ALT) {
+                    x = make_float2(__uint_as_float(__float_as_uint(x.x) ^ turn), __uint_as_float(__float_as_uint(x.y) ^ turn));
+                    y = make_float2(__uint_as_float(__float_as_uint(y.x) ^ turn), __uint_as_float(__float_as_uint(y.y) ^ turn));
+                }
                 const Split3 sr = split3(x.x + y.x), di = split3(x.y - y.y), si = split3(x.y + y.y), dr = split3(y.x - x.x);
                 re[e / 4][0][e % 4] = pack_bf16(sr.t0, di.t0);
                 re[e / 4][1][e % 4] = pack_bf16(sr.t1, di.t1);
@@ -249,6 +260,7 @@ k_matdft_fwd(MatdftArgs a)
         const int k = k0 + 32 * t + (COLQ ? row : col);
         const bool ok = k < a.K && q0 + (COLQ ? col : row) < a.P;
         if constexpr (OUT == MD_ROWS) {
+            if (ALT && (row & 1)) val = make_float2(-val.x, -val.y);
             if (ok) a.out[(long long)(q0 + row) * a.out_outer + k] = val;
         } else {
             long long m = pos.m;

@@ -317,6 +317,24 @@ def test_2d_one_side_a_power_of_two(gpu, oracle_mod, shape):
     check(run_gpu_rect(gpu, "spectral_conv2d_rect_staged", x, W, K1, K2), want, "mixed sides", rel_l2=4e-7)
 
 
+# (B, C_in, C_out, N1, N2, K1, K2): rows on the matrix pipe with one, four and eight waves to a sum and more tiles per wave
+@pytest.mark.parametrize("shape", [(2, 2, 8, 4096, 3, 9, 3), (2, 3, 8, 4096, 39, 8, 5), (2, 2, 8, 1024, 150, 8, 20), (1, 2, 8, 1024, 300, 6, 8),
+                                   (2, 8, 4, 4096, 70, 6, 40)], ids=lambda s: "B%d_Ci%d_Co%d_N%dx%d_K%dx%d" % s)
+def test_2d_rounding_offsets_do_not_gather_in_bin_zero(gpu, oracle_mod, shape):
+    """The error of the lowest bin of the first axis is like that of the other kept bins.  Each is a sum of rounding errors
+    over B C_out K2 >= 48 values: two such estimates differ by less than half; an offset common to all rows of a
+    field adds up over N1 rows while the data add up to sqrt(N1), and made it 3 to 5 times the others'."""
+    B, Ci, Co, N1, N2, K1, K2 = shape
+    say(f"[case] offsets {shape}")
+    x = inputs.make_x(1590 + N2, B, Ci, (N1, N2))
+    W = inputs.make_W(1590 + N2, Ci, Co)
+    want, _ = oracle_mod.spectral_conv2d_rect(x, W, K1, K2)
+    err = run_gpu_rect(gpu, "spectral_conv2d_rect_staged", x, W, K1, K2) - want
+    bins = np.sqrt(np.mean(np.abs(np.fft.fft(err, axis=2)[:, :, :K1]) ** 2, axis=(0, 1, 3)))
+    say(f"   bin 0 / others: {bins[0] / np.sqrt(np.mean(bins[1:] ** 2)):.2f}")
+    assert bins[0] <= 1.5 * np.sqrt(np.mean(bins[1:] ** 2)), shape
+
+
 def test_2d_staged_general_shape(gpu, oracle_mod):
     B, Ci, Co, N, K = 2, 3, 2, 32, 5
     x = inputs.make_x(9, B, Ci, (N, N))
