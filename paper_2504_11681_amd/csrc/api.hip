@@ -288,13 +288,13 @@ tfno_status run_permode(const Shape &req, const void *x, const void *W, void *y,
         const int N = sh.N2, K = sh.K2, Mp = pruned1d_stride(N, req.K2);
         c64 *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
         e = pruned1d_stages(PRUNED_FWD, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, req.K2, Mp, s);
-        if (e == hipSuccess) e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, B, Mp, req.K2, scale, s);
+        if (e == hipSuccess) e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, B, Mp, req.K2, Mp == K, scale, s);
         if (e == hipSuccess) e = pruned1d_stages(PRUNED_INV, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, req.K2, Mp, s);
     } else {
         const int Ma = req.K1 * req.K2, Mp = spectrum_stride(Ma);
         c64 *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
         e = fused2d_images(-1, xc, Xh, (long long)B * C_in, C_in, sh.N1, sh.N2, sh.K1, sh.K2, req.K1, req.K2, false, 0, s);
-        if (e == hipSuccess) e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, B, Mp, Ma, scale, s);
+        if (e == hipSuccess) e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, B, Mp, Ma, false, scale, s);
         if (e == hipSuccess)
             e = fused2d_images(+1, Yh, yc, (long long)B * C_out, C_out, sh.N1, sh.N2, sh.K1, sh.K2, req.K1, req.K2, false, 0, s);
     }
@@ -361,7 +361,7 @@ tfno_status run_fno2d(const void *x, const void *W, void *y, int B, int C_in, in
     c64 *Xh = (c64 *)wsp, *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
     const float scale = 2.0f / ((float)N1 * (float)N2);     // C2R along the last axis: twice the real part
     hipError_t e = fused2d_images(-1, (const c64 *)x, Xh, (long long)B * C_in, C_in, N1, N2, K1, K2, 2 * M1, M2, true, M1, s);
-    if (e == hipSuccess) e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
+    if (e == hipSuccess) e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, B, Mp, Ma, false, scale, s);
     if (e == hipSuccess)
         e = fused2d_images(+1, Yh, (c64 *)y, (long long)B * C_out, C_out, N1, N2, K1, K2, 2 * M1, M2, true, M1, s);
     return e == hipSuccess ? TFNO_OK : TFNO_ERR_HIP;
@@ -395,7 +395,7 @@ tfno_status run_fno1d(const void *x, const void *W, void *y, int B, int C_in, in
     const int Mp = pruned1d_stride(N, M);
     c64 *Xh = (c64 *)wsp, *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
     hipError_t e = pruned1d_real_stages(PRUNED_FWD, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, M, Mp, s);
-    if (e == hipSuccess) e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, B, Mp, M, 2.0f / (float)N, s);
+    if (e == hipSuccess) e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, B, Mp, M, Mp == K, 2.0f / (float)N, s);
     if (e == hipSuccess)
         e = pruned1d_real_stages(PRUNED_INV, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, M, Mp, s);
     return e == hipSuccess ? TFNO_OK : TFNO_ERR_HIP;

@@ -7,16 +7,17 @@
 namespace tfno {
 
 template <int BT, int OT>
-static void launch_f32(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, long long B, int Mp, int Ma, float scale, hipStream_t s)
+static void launch_f32(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, long long B, int Mp, int Ma, int Mc, float scale,
+                       hipStream_t s)
 {
-    const unsigned long long threads = (unsigned long long)((B + BT - 1) / BT) * Ma;
+    const unsigned long long threads = (unsigned long long)((B + BT - 1) / BT) * Mc;
     const unsigned slabs = (unsigned)((C_out + OT - 1) / OT);
     const dim3 grid((unsigned)((threads + 255) / 256 * slabs));
-    hipLaunchKernelGGL((k_cgemm_permode<BT, OT>), grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, slabs);
+    hipLaunchKernelGGL((k_cgemm_permode<BT, OT>), grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, slabs);
 }
 
 hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, long long B, int Mp, int Ma,
-                                float scale, hipStream_t s)
+                                bool zeros, float scale, hipStream_t s)
 {
     if (B <= 0) return hipSuccess;
     if (Ma < 1 || Mp < Ma || Mp % 8 != 0) return hipErrorInvalidValue;
@@ -36,12 +37,13 @@ hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, 
             hipLaunchKernelGGL(k_cgemm_permode_mfma<false>, grid, dim3(512), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale);
         return hipGetLastError();
     }
+    const int Mc = zeros ? Mp : Ma;
     // Batch elements x outputs per thread: more reuse of what is loaded where that still gives every SIMD a wave.
-    auto waves = [&](int bt, int ot) { return (B + bt - 1) / bt * Ma * ((C_out + ot - 1) / ot) / 64; };
-    if (waves(8, 8) >= 1024) launch_f32<8, 8>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
-    else if (waves(4, 4) >= 1024) launch_f32<4, 4>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
-    else if (waves(2, 2) >= 256) launch_f32<2, 2>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
-    else launch_f32<1, 1>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale, s);
+    auto waves = [&](int bt, int ot) { return (B + bt - 1) / bt * Mc * ((C_out + ot - 1) / ot) / 64; };
+    if (waves(8, 8) >= 1024) launch_f32<8, 8>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
+    else if (waves(4, 4) >= 1024) launch_f32<4, 4>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
+    else if (waves(2, 2) >= 256) launch_f32<2, 2>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
+    else launch_f32<1, 1>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
     return hipGetLastError();
 }
 

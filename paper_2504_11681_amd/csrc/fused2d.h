@@ -36,10 +36,10 @@ hipError_t cgemm_modes_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, in
                               hipStream_t s);
 
 // Yh[b][o][m] = scale * sum_c Xh[b][c][m] * W[c][o][m], m < Ma, with an own weight matrix per mode: W is [C_in, C_out, Ma],
-// the spectra are mode-tile major over the joint mode b Mp + m (Mp >= Ma, a multiple of 8; results at m >= Ma are
-// unspecified).
+// the spectra are mode-tile major over the joint mode b Mp + m (Mp >= Ma, a multiple of 8).  Results at m >= Ma: zeros if
+// `zeros` is set, which says that Xh holds zeros there, else unspecified.
 hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, long long B, int Mp, int Ma,
-                                float scale, hipStream_t s);
+                                bool zeros, float scale, hipStream_t s);
 
 // Modes per batch element in the joint mode index of a spectrum that keeps `modes` of them: 64-byte rows.
 inline int spectrum_stride(int modes) { return (modes + 7) & ~7; }

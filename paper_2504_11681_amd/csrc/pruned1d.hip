@@ -72,39 +72,46 @@ int pruned1d_stride(int N, int K_keep)
     return (8 * cols > 7 * K2 ? K2 : cols) * N1;
 }
 
-template <int N, int K, bool REAL, bool ALL>
-static hipError_t launch_nk(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
-                            int C_out, int K_keep, int Mp, hipStream_t s)
+template <int N, int K, bool REAL, int FORM>
+static hipError_t launch_fwd(const c64 *x, c64 *Xh, int C, long long pencils, int K_keep, int Mp, hipStream_t s)
 {
     using Cf = CfgP1<N, K>;
-    const long long tiles = mode_tiles(B, Mp);
-    const long long pin = B * C_in, pout = B * C_out;
-    const long long sin = (pin + Cf::PPS - 1) / Cf::PPS, sout = (pout + Cf::PPS - 1) / Cf::PPS;
     // a few sweeps per workgroup amortise the twiddle tables and keep a prefetch in flight
     // (measured: the forward kernels gain 2 - 4 % and the real-valued inverse 13 % from the balanced grid; the complex
     // inverse kernels, which write twice the bytes, lose 4 % and keep the fixed grid)
-    const unsigned gin = balanced_grid<&k_fwd1d<N, K, REAL, ALL>>(sin, 256);
-    const unsigned gout = REAL ? balanced_grid<&k_inv1d<N, K, REAL, ALL>>(sout, 256) : (unsigned)(sout < 1024 ? sout : 1024);
-    hipError_t e = hipSuccess;
-    if (stages & PRUNED_FWD) {
-        hipLaunchKernelGGL((k_fwd1d<N, K, REAL, ALL>), dim3(gin), dim3(256), 0, s, x, Xh, C_in, pin, K_keep, Mp);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (stages & PRUNED_GEMM)
-        if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / (float)N, tiles, s)) != hipSuccess) return e;
-    if (stages & PRUNED_INV) {
-        hipLaunchKernelGGL((k_inv1d<N, K, REAL, ALL>), dim3(gout), dim3(256), 0, s, (const c64 *)Yh, y, C_out, pout, K_keep, Mp);
-        e = hipGetLastError();
-    }
-    return e;
+    const unsigned grid = balanced_grid<&k_fwd1d<N, K, REAL, FORM>>((pencils + Cf::PPS - 1) / Cf::PPS, 256);
+    hipLaunchKernelGGL((k_fwd1d<N, K, REAL, FORM>), dim3(grid), dim3(256), 0, s, x, Xh, C, pencils, K_keep, Mp);
+    return hipGetLastError();
+}
+
+template <int N, int K, bool REAL, int FORM>
+static hipError_t launch_inv(const c64 *Yh, c64 *y, int C, long long pencils, int K_keep, int Mp, hipStream_t s)
+{
+    using Cf = CfgP1<N, K>;
+    const long long sweeps = (pencils + Cf::PPS - 1) / Cf::PPS;
+    const unsigned grid = REAL ? balanced_grid<&k_inv1d<N, K, REAL, FORM>>(sweeps, 256) : (unsigned)(sweeps < 1024 ? sweeps : 1024);
+    hipLaunchKernelGGL((k_inv1d<N, K, REAL, FORM>), dim3(grid), dim3(256), 0, s, Yh, y, C, pencils, K_keep, Mp);
+    return hipGetLastError();
 }
 
 template <int N, int K, bool REAL = false>
 static hipError_t launch_nk(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
                             int C_out, int K_keep, int Mp, hipStream_t s)
 {
-    if (K_keep == K && Mp == K) return launch_nk<N, K, REAL, true>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
-    return launch_nk<N, K, REAL, false>(stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);
+    const long long pin = B * C_in, pout = B * C_out;
+    hipError_t e = hipSuccess;
+    if (stages & PRUNED_FWD) {
+        e = Mp < K ? launch_fwd<N, K, REAL, P1_CUT>(x, Xh, C_in, pin, K_keep, Mp, s)
+            : K_keep < K ? launch_fwd<N, K, REAL, P1_FULL>(x, Xh, C_in, pin, K_keep, Mp, s)
+                         : launch_fwd<N, K, REAL, P1_ALL>(x, Xh, C_in, pin, K_keep, Mp, s);
+        if (e != hipSuccess) return e;
+    }
+    if (stages & PRUNED_GEMM)
+        if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, 1.0f / (float)N, mode_tiles(B, Mp), s)) != hipSuccess) return e;
+    if (stages & PRUNED_INV)
+        e = Mp < K ? launch_inv<N, K, REAL, P1_CUT>(Yh, y, C_out, pout, K_keep, Mp, s)
+                   : launch_inv<N, K, REAL, P1_ALL>(Yh, y, C_out, pout, K_keep, Mp, s);
+    return e;
 }
 
 template <int N1, int K2, bool ALL>

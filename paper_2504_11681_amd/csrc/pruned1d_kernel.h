@@ -89,14 +89,17 @@ __device__ __forceinline__ int p1_slot(int c, int p)
 // zero imaginary part (its first K bins are the R2C bins); bin 0 is stored halved so that the inverse kernel, which
 // stores the real part of the zero-padded complex inverse, yields the C2R transform when the contraction in between
 // carries the scale 2 / N.
-// ALL (both kernels): K_keep = Mp = K as constants; the masks of the general form cost registers (256 real points, 128
-// modes: 169 against 128, two waves per SIMD against four).  Per-mode layer around them, B 256, 1024 points, 128 real modes:
-// 128 channels 117 -> 108 us, 64 channels 59.8 -> 56.7 us with ALL and the inverse's zeros moved to their use.
-template <int N, int K, bool REAL, bool ALL>
+// FORM (both kernels): what of K_keep <= Mp <= K is constant; the masks of the general form cost registers (256 real points,
+// 128 modes: 169 against 128, two waves per SIMD against four).  Per-mode layer around them, B 256, 1024 points, 128 real
+// modes: 128 channels 117 -> 108 us, 64 channels 59.8 -> 56.7 us with P1_ALL and the inverse's zeros moved to their use.
+// With 127 modes kept: 118 -> 113 us with P1_FULL; CGEMM + iFFT variant, B 256, 128 channels, 128 points, 57 modes: 33.9 -> 31.7 us.
+// The inverse kernel knows P1_ALL and P1_CUT: a full spectrum holds zeros in the bins that are not kept.
+enum { P1_CUT = 0, P1_FULL = 1, P1_ALL = 2 };               // any Mp; Mp = K; K_keep = Mp = K
+template <int N, int K, bool REAL, int FORM>
 __global__ void __launch_bounds__(256)
 k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npencils, int K_keep_, int Mp_)
 {
-    const int K_keep = ALL ? K : K_keep_, Mp = ALL ? K : Mp_;
+    const int K_keep = FORM == P1_ALL ? K : K_keep_, Mp = FORM != P1_CUT ? K : Mp_;
     using Cf = CfgP1<N, K>;
     constexpr int LPR = Cf::LPR, PPS = Cf::PPS, KH = Cf::KH, CPL = Cf::CPL, OPL = Cf::OPL;
     constexpr bool WIDE = Cf::WIDE;
@@ -218,11 +221,14 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
 }
 
 // ------------------------------------------------------------------------------------------------ inverse
-// Yh: mode-tile major (joint mode m = b Mp + k, C channels); bins from K_keep on are zeros.  y: [npencils, N] contiguous (pencil q = b * C + o).
-template <int N, int K, bool REAL, bool ALL>
+// Yh: mode-tile major (joint mode m = b Mp + k, C channels); bins from K_keep on are taken as zeros (P1_ALL: they are stored
+// as zeros where there are any).  y: [npencils, N] contiguous (pencil q = b * C + o).
+template <int N, int K, bool REAL, int FORM>
 __global__ void __launch_bounds__(256)
 k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npencils, int K_keep_, int Mp_)
 {
+    static_assert(FORM != P1_FULL, "a full spectrum is read as it is");
+    constexpr bool ALL = FORM == P1_ALL;
     const int K_keep = ALL ? K : K_keep_, Mp = ALL ? K : Mp_;
     using Cf = CfgP1<N, K>;
     constexpr int LPR = Cf::LPR, PPS = Cf::PPS, KH = Cf::KH, CPL = Cf::CPL, NY = Cf::NY;

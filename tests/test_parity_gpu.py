@@ -492,6 +492,48 @@ def test_2d_permode(gpu, oracle_mod, shape):
     check(yd.cpu().numpy(), want, "permode 2d")
 
 
+# Layers whose truncated spectra pass through the workspace, with fewer modes than the kernels' (all bins stored, or only the
+# kept ones rounded up to 8), by the FP32 and the matrix-pipe contraction: modes that are not kept, and the rest of the last
+# 128-mode tile, hold whatever the workspace held unless a kernel writes them.  (entry, B, C_in, C_out, N, K)
+SURPLUS = [(e, B, ci, co, n, k) for e in ("spectral_conv1d_permode", "fno1d_real")
+           for B, ci, co, n, k in ((5, 7, 9, 256, 121), (5, 7, 9, 256, 100), (64, 32, 64, 256, 123), (64, 32, 64, 256, 99),
+                                   (3, 5, 6, 64, 9), (3, 5, 6, 64, 5), (2, 9, 4, 1024, 62), (3, 4, 4, 128, 60))] + [
+    (e, B, ci, co, n, k) for e in ("spectral_conv1d_pruned", "spectral_conv1d_fft_gemm", "spectral_conv1d_gemm_ifft")
+    for B, ci, co, n, k in ((5, 7, 9, 256, 121), (5, 7, 9, 256, 51), (9, 40, 33, 128, 57), (9, 40, 33, 128, 20))] + [
+    ("spectral_conv1d_pruned", 3, 4, 5, 2048, 150), ("spectral_conv1d_pruned", 3, 4, 5, 2048, 500), ("spectral_conv1d_pruned", 3, 4, 5, 1024, 127)]
+
+
+@pytest.mark.parametrize("case", SURPLUS, ids=lambda c: "%s-B%d_Ci%d_Co%d_N%d_K%d" % c)
+def test_what_the_workspace_held_does_not_matter(gpu, oracle_mod, case):
+    torch, binding = gpu
+    entry, B, Ci, Co, N, K = case
+    say(f"[case] surplus modes {case}")
+    real, per_mode = entry == "fno1d_real", entry in ("fno1d_real", "spectral_conv1d_permode")
+    x = inputs.make_x(1600 + N + K, B, Ci, (N,))
+    W = inputs.make_W(1600 + N + K, Ci, Co * K if per_mode else Co)
+    if real:
+        x = np.ascontiguousarray(x.real)
+    if per_mode:
+        W = W.reshape(Ci, Co, K)
+    f = np.exp(-2j * np.pi * np.outer(np.arange(N), np.arange(K)) / N)
+    X = x.astype(np.complex128) @ f
+    Y = np.einsum("bck,cok->bok", X, W) if per_mode else np.einsum("bck,co->bok", X, W)
+    if real:
+        Y[:, :, 0] *= 0.5
+    want = Y @ np.conj(f.T) / N
+    want = 2 * want.real if real else want
+    xd, Wd = torch.from_numpy(x).cuda(), torch.from_numpy(W).cuda()
+    yd = torch.full((B, Co, N), float("nan"), dtype=xd.dtype, device="cuda")
+    junk = torch.full((1 << 24,), 0xff, dtype=torch.uint8, device="cuda")       # NaN in every word
+    binding.set_workspace(junk)
+    try:
+        getattr(binding, entry)(xd, Wd, yd) if per_mode else getattr(binding, entry)(xd, Wd, yd, K)
+        torch.cuda.synchronize()
+    finally:
+        binding.set_workspace(None)
+    check(yd.cpu().numpy(), want, entry)
+
+
 def test_large_batch_uses_64_bit_offsets(gpu, oracle_mod):
     """B = 2^18 (1 GiB tensors, 2^18 workgroups): sampled batch elements against the oracle, including the last, whose
     byte offset is past 2^31; the rest of the batch is filled on the device and only checked to be written."""
