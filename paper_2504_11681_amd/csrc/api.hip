@@ -285,7 +285,7 @@ tfno_status run_permode(const Shape &req, const void *x, const void *W, void *y,
     const float scale = 1.0f / ((float)sh.N1 * (float)sh.N2);
     hipError_t e;
     if (sh.dims == 1) {
-        const int N = sh.N2, K = sh.K2, Mp = pruned1d_stride(N, req.K2);
+        const int N = sh.N2, K = sh.K2, Mp = pruned1d_stride(N, K, req.K2);
         c64 *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
         e = pruned1d_stages(PRUNED_FWD, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, req.K2, Mp, s);
         if (e == hipSuccess) e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, B, Mp, req.K2, Mp == K, scale, s);
@@ -392,7 +392,7 @@ tfno_status run_fno1d(const void *x, const void *W, void *y, int B, int C_in, in
     tfno_status st = check_workspace(pruned1d_workspace_bytes(B, C_in, C_out, K), x, xb, W, wb, y, yb, &wsp);
     if (st != TFNO_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    const int Mp = pruned1d_stride(N, M);
+    const int Mp = pruned1d_stride(N, K, M);
     c64 *Xh = (c64 *)wsp, *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
     hipError_t e = pruned1d_real_stages(PRUNED_FWD, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, M, Mp, s);
     if (e == hipSuccess) e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, B, Mp, M, Mp == K, 2.0f / (float)N, s);

@@ -119,7 +119,7 @@ static bool is_pow2(int n) { return (n & (n - 1)) == 0; }
 static int row_modes(int N2, int K2)
 {
     const int K = is_pow2(N2) ? pruned1d_modes(N2, K2) : 0;
-    return K ? pruned1d_stride(N2, K2) : K2;
+    return K ? pruned1d_stride(N2, K, K2) : K2;
 }
 
 // workspace: Xh, Yh in whole tiles of 128 modes; 2-D: the fields transformed along their last axis, [B, C, N1, cols],
