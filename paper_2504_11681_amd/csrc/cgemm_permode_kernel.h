@@ -58,12 +58,24 @@ k_cgemm_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__re
             for (int bi = 0; bi < BT; ++bi) xv[u][bi] = xp[bi][(long long)(c0 + u) * 128];
         }
         __builtin_amdgcn_sched_barrier(0);
+        // (a sum per block where there are few results per thread: one chain over all channels rounds more than the matrix
+        // pipe's sums do, which this kernel stands in for at small sizes)
+        constexpr bool SPLIT = BT * OT <= 4 && n > 1;
+        c64 part[BT][OT];
+#pragma unroll
+        for (int bi = 0; bi < BT; ++bi)
+#pragma unroll
+            for (int oi = 0; oi < OT; ++oi) part[bi][oi] = SPLIT ? make_float2(0.f, 0.f) : acc[bi][oi];
 #pragma unroll
         for (int u = 0; u < n; ++u)
 #pragma unroll
             for (int bi = 0; bi < BT; ++bi)
 #pragma unroll
-                for (int oi = 0; oi < OT; ++oi) acc[bi][oi] = cmac(acc[bi][oi], xv[u][bi], wv[u][oi]);
+                for (int oi = 0; oi < OT; ++oi) part[bi][oi] = cmac(part[bi][oi], xv[u][bi], wv[u][oi]);
+#pragma unroll
+        for (int bi = 0; bi < BT; ++bi)
+#pragma unroll
+            for (int oi = 0; oi < OT; ++oi) acc[bi][oi] = SPLIT ? cadd(acc[bi][oi], part[bi][oi]) : part[bi][oi];
     };
     int c = 0;
     for (; c + U <= C_in; c += U) block(c, std::integral_constant<int, U>{});

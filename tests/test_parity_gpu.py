@@ -492,6 +492,25 @@ def test_2d_permode(gpu, oracle_mod, shape):
     check(yd.cpu().numpy(), want, "permode 2d")
 
 
+@pytest.mark.parametrize("shape", [(16, 512, 64, 256, 128), (16, 300, 27, 256, 81), (3, 512, 5, 64, 16), (64, 512, 20, 64, 24)],
+                         ids=lambda s: "B%d_Ci%d_Co%d_N%d_K%d" % s)
+def test_permode_sums_over_many_channels(gpu, oracle_mod, shape):
+    """Small per-mode products on the FP32 kernel: sums of at most 16 channels are added up, so that the rounding grows with
+    sqrt(16) + sqrt(C / 16) terms' worth of 2^-24 / sqrt(6) each (about 2e-7 at 512 channels, beside 1.6e-7 for the two
+    transforms; the bound is half as much again) and not with sqrt(2 C), which measured 6e-7."""
+    B, Ci, Co, N, K = shape
+    say(f"[case] many channels {shape}")
+    x = inputs.make_x(1650 + Ci, B, Ci, (N,))
+    W = np.ascontiguousarray(inputs.make_W(1650 + Ci, Ci, Co * K).reshape(Ci, Co, K))
+    f = np.exp(-2j * np.pi * np.outer(np.arange(N), np.arange(K)) / N)
+    X = x.astype(np.complex128) @ f
+    want = np.matmul(X.transpose(2, 0, 1), W.astype(np.complex128).transpose(2, 0, 1)).transpose(1, 2, 0) @ np.conj(f.T) / N
+    torch, binding = gpu
+    yd = torch.full((B, Co, N), float("nan"), dtype=torch.complex64, device="cuda")
+    binding.spectral_conv1d_permode(torch.from_numpy(x).cuda(), torch.from_numpy(W).cuda(), yd)
+    check(yd.cpu().numpy(), want, "per mode", rel_l2=3.8e-7)
+
+
 # Layers whose truncated spectra pass through the workspace, with fewer modes than the kernels' (all bins stored, or only the
 # kept ones rounded up to 8), by the FP32 and the matrix-pipe contraction: modes that are not kept, and the rest of the last
 # 128-mode tile, hold whatever the workspace held unless a kernel writes them.  (entry, B, C_in, C_out, N, K)
