@@ -21,12 +21,14 @@ hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, 
 {
     if (B <= 0) return hipSuccess;
     if (Ma < 1 || Mp < Ma || Mp % 8 != 0) return hipErrorInvalidValue;
-    // Matrix-pipe kernel from 48 workgroups' worth of results on (its time hardly falls below that: B 64, 128 modes, 64 x 64
-    // channels, 524288 results: 15 us against 17 for the FP32 kernel; B 64, 32 modes, 128 x 128 channels, 262144 results: 21
-    // against 18 us; B 32, 16 modes, 64 x 64 channels: 13 against 7 us), with enough channels, outputs and batch elements for
-    // its 32 x 32 x 8-channel tiles; everything else (and TFNO_CONTRACTION=f32) runs the FP32 kernel.
+    // Matrix-pipe kernel from 36 workgroups' worth of results on (its time hardly falls below that: whole layers of 64 x 64
+    // channels, 256 points, with either kernel, FP32 first: 262144 results 22.1 and 22.6 us, 327680 results 29.9 and 24.9 us;
+    // 16 modes, B 64: 19.2 and 20.9 us), with enough channels, outputs and batch elements for its 32 x 32 x 8-channel
+    // tiles; everything else (and TFNO_CONTRACTION=f32) runs the FP32 kernel.  Below 32 channels its six products
+    // per value (bf16x3.h) lose more than the shorter sums gain (16 channels: 1.8e-7 against 1.7e-7 for a layer, 24: 1.9e-7 both), so
+    // few modes stay on the FP32 kernel there (B 64, 16 -> 256 channels, 60 modes: 23.6 against 22.4 us).
     const long long gy = (B + 31) / 32, gz = (C_out + 31) / 32;
-    if (C_in >= 16 && C_out >= 16 && B >= 16 && B * Ma * C_out >= 48 * 8192 && !contraction_forced_f32() && gy <= 65535 && gz <= 65535) {
+    if (C_in >= (Mp > 64 ? 16 : 32) && C_out >= 16 && B >= 16 && B * Ma * C_out >= 36 * 8192 && !contraction_forced_f32() && gy <= 65535 && gz <= 65535) {
         const dim3 grid((unsigned)(Mp / 8), (unsigned)gy, (unsigned)gz);
         // without masks where every tile is full and the extents a workgroup addresses with 32-bit offsets (32 batch
         // elements of Xh, all of W) stay below 2^31 bytes

@@ -1284,3 +1284,72 @@ def test_fp32_contraction_kernels_in_a_child_process(gpu, oracle_mod, tmp_path):
     check(got["y1"], oracle_mod.spectral_conv1d(x1, W1, 128)[0], "f32 1-D N=1024")
     x2 = inputs.make_x(32, 2, 5, (128, 128)); W2 = inputs.make_W(32, 5, 70)
     check(got["y2"], oracle_mod.spectral_conv2d(x2, W2, 32)[0], "f32 2-D 128x128")
+
+
+# (entry, sizes): the direct-sum transforms (long and short lengths, several pencils to a workgroup, columns of a grid), the
+# per-mode contraction with 8 x 8, 4 x 4 and fewer results per thread
+F32_LAYERS = [("staged1d", 2, 3, 4, 421, 50), ("staged1d", 3, 20, 9, 1000, 33), ("staged1d", 1, 2, 2, 4095, 100), ("staged1d", 7, 5, 6, 39, 39),
+              ("grid2d", 2, 3, 4, 85, 48, 12, 20), ("grid2d", 2, 2, 3, 48, 85, 48, 9), ("grid2d", 1, 3, 2, 421, 12, 30, 12),
+              ("permode1d", 128, 9, 128, 256, 256), ("permode1d", 100, 8, 100, 256, 128), ("permode1d", 60, 20, 70, 256, 100), ("permode1d", 6, 33, 7, 1024, 60),
+              ("permode1d", 64, 24, 128, 256, 60), ("permode1d", 64, 31, 100, 128, 50), ("permode1d", 64, 32, 128, 256, 60), ("permode1d", 64, 64, 64, 256, 73)]
+
+
+def f32_layer(torch, binding, layer):
+    """One layer of F32_LAYERS on the GPU: x, W, y as arrays."""
+    entry, B, Ci, Co, *dims = layer
+    n = len(dims) // 2
+    space, K = tuple(dims[:n]), dims[n:]
+    x = inputs.make_x(1700 + space[0], B, Ci, space)
+    W = inputs.make_W(1700 + space[0], Ci, Co * K[0] if entry == "permode1d" else Co)
+    if entry == "permode1d":
+        W = W.reshape(Ci, Co, K[0])
+    xd, Wd = torch.from_numpy(x).cuda(), torch.from_numpy(W).cuda()
+    yd = torch.full((B, Co) + space, float("nan"), dtype=torch.complex64, device="cuda")
+    if entry == "permode1d":
+        binding.spectral_conv1d_permode(xd, Wd, yd)
+    elif entry == "staged1d":
+        binding.spectral_conv1d_staged(xd, Wd, yd, K[0])
+    else:
+        binding.spectral_conv2d_rect_staged(xd, Wd, yd, *K)
+    torch.cuda.synchronize()
+    return x, W, yd.cpu().numpy()
+
+
+def test_fp32_general_layers_in_a_child_process(gpu, oracle_mod, tmp_path):
+    """TFNO_CONTRACTION=f32: lengths with odd factors by direct sums, the per-mode contraction on its FP32 kernel.  Per-mode
+    layers of fewer than 32 channels and at most 64 stored modes run that kernel by default as well (the six products of the
+    matrix pipe lose more there than its shorter sums gain), so their results are the same bits; with 32 channels, or more
+    than 64 modes, and 294912 results they are the matrix pipe's."""
+    import os
+    import subprocess
+    import textwrap
+    torch, binding = gpu
+    say("[case] TFNO_CONTRACTION=f32 child process, general layers")
+    out = str(tmp_path / "f32_general.npz")
+    code = textwrap.dedent(f"""
+        import sys
+        sys.path.insert(0, "tests")
+        import numpy as np, torch
+        from paper_2504_11681_amd import binding
+        from test_parity_gpu import F32_LAYERS, f32_layer
+        np.savez({out!r}, *[f32_layer(torch, binding, layer)[2] for layer in F32_LAYERS])
+    """)
+    env = dict(os.environ, TFNO_CONTRACTION="f32")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    subprocess.run([sys.executable, "-c", code], check=True, env=env, cwd=root, timeout=110)
+    got = np.load(out)
+    for i, layer in enumerate(F32_LAYERS):
+        entry, B, Ci, Co, *dims = layer
+        x, W, default = f32_layer(torch, binding, layer)
+        y = got["arr_%d" % i]
+        if entry == "permode1d":
+            N, K = dims
+            f = np.exp(-2j * np.pi * np.outer(np.arange(N), np.arange(K)) / N)
+            X = x.astype(np.complex128) @ f
+            want = np.matmul(X.transpose(2, 0, 1), W.astype(np.complex128).transpose(2, 0, 1)).transpose(1, 2, 0) @ np.conj(f.T) / N
+            same = np.array_equal(y.view(np.float32), default.view(np.float32))
+            matrix_pipe = B >= 16 and Co >= 16 and Ci >= (16 if K > 64 else 32) and B * K * Co >= 294912
+            assert same != matrix_pipe, (layer, same)
+        else:
+            want = (oracle_mod.spectral_conv1d if entry == "staged1d" else oracle_mod.spectral_conv2d_rect)(x, W, *dims[len(dims) // 2:])[0]
+        check(y, want, f"f32 {layer}")
