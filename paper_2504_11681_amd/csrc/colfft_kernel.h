@@ -84,7 +84,7 @@ k_colfft_fwd(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, 
     for (int i = 0; i < C::IPT; ++i) {
         const int p = sub + (C::NT / 16) * i;
         c64 xo[Q];
-        dft_prune_out<T, Q, -1>([&](auto tc) __attribute__((always_inline)) {
+        dft_prune_out_blocks<T, Q, -1>([&](auto tc) __attribute__((always_inline)) {
             constexpr int t = decltype(tc)::value;
             return Z[p * C::PS + t * 16 + col];
         }, xo);

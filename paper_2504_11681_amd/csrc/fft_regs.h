@@ -146,6 +146,40 @@ TFNO_HD void dft_prune_out(In &&in, c64 *out)
     });
 }
 
+// The same with the S-term sums added up four terms at a time: for few outputs of a long transform (Q much smaller than T) one
+// chain of S terms rounds more than a butterfly network would (32 terms: 1.06e-7 against 0.70e-7).
+template <int T, int Q, int DIR, class In>
+TFNO_HD void dft_prune_out_blocks(In &&in, c64 *out)
+{
+    constexpr int S = T / Q;
+    if constexpr (S <= 4) {
+        dft_prune_out<T, Q, DIR>(in, out);
+    } else {
+        static_for<0, S / 4>([&](auto bc) {
+            constexpr int b = decltype(bc)::value;
+            c64 part[Q];
+            static_for<4 * b, 4 * b + 4>([&](auto t1c) {
+                constexpr int t1 = decltype(t1c)::value;
+                c64 g[Q], F[Q];
+                static_for<0, Q>([&](auto t2c) {
+                    constexpr int t2 = decltype(t2c)::value;
+                    g[t2] = in(std::integral_constant<int, t1 + S * t2>{});
+                });
+                RegFFT<Q, DIR, 1>::run(g, F);
+                static_for<0, Q>([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    if constexpr (t1 == 4 * b) part[q] = mul_tw<T, DIR, t1 * q>(F[q]);
+                    else part[q] = mac_tw<T, DIR, t1 * q>(part[q], F[q]);
+                });
+            });
+            static_for<0, Q>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                out[q] = b == 0 ? part[q] : cadd(out[q], part[q]);
+            });
+        });
+    }
+}
+
 // emit(t, sum_{q<Q} in[q] exp(DIR 2 pi i t q / T)),  t < T.   (the transpose of the network above)
 // emit: callable (integral_constant t, c64); outputs are produced Q at a time.
 template <int T, int Q, int DIR, class Emit>

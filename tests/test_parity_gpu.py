@@ -420,6 +420,22 @@ def test_2d_strip_pipeline_column_kernels(gpu, oracle_mod, shape):
     check(run_gpu_rect(gpu, "spectral_conv2d_strips", x, W, K1, 10), want, "column kernels")
 
 
+@pytest.mark.parametrize("K1", [1, 2])
+def test_2d_strip_pipeline_few_modes_of_long_columns(gpu, oracle_mod, K1):
+    """The second stage of the column kernels sums 32 terms for one or two modes of 512 rows, 8 terms for 64 rows.  In one
+    chain these round by 1.06e-7 and 0.56e-7, in blocks of four by 0.70e-7 and 0.49e-7 (rms of such sums of normal
+    values); beside the rest of the layer, 1.5e-7, that is a ratio of 1.14 between the two column lengths, or 1.05."""
+    errs = []
+    for N1 in (64, 512):
+        x = inputs.make_x(490 + N1, 8, 16, (N1, 64))
+        W = inputs.make_W(490 + N1, 16, 16)
+        want, _ = oracle_mod.spectral_conv2d_rect(x, W, K1, 16)
+        got = run_gpu_rect(gpu, "spectral_conv2d_strips", x, W, K1, 16)
+        errs.append(np.linalg.norm(got - want) / np.linalg.norm(want))
+    say(f"   K1 = {K1}: 64 rows {errs[0]:.3e}, 512 rows {errs[1]:.3e}, ratio {errs[1] / errs[0]:.3f}")
+    assert errs[1] <= 1.1 * errs[0]
+
+
 @pytest.mark.parametrize("shape", RECT_STAGED_ONLY, ids=lambda s: "B%d_Ci%d_Co%d_N%dx%d_K%dx%d" % s)
 def test_2d_rect_staged_general_shapes(gpu, oracle_mod, shape):
     torch, binding = gpu
