@@ -595,6 +595,35 @@ def test_large_batch_uses_64_bit_offsets(gpu, oracle_mod):
     torch.cuda.empty_cache()
 
 
+def test_contraction_of_more_tiles_than_one_launch_takes(gpu):
+    """2^24 tiles of 128 modes: a launch has fewer than 2^32 threads, so one workgroup of 256 threads per tile is not possible
+    and the contraction has to take a kernel that walks several tiles.  All modes are kept and there is one channel, so
+    y = W x; 32-bit rounding of two transforms of 64 points leaves a few 1e-7."""
+    torch, binding = gpu
+    B = 1 << 25
+    say("[case] 2^24 contraction tiles, 69 GB")
+    if torch.cuda.mem_get_info()[0] < (80 << 30):
+        pytest.skip("needs 80 GB of free device memory")
+    binding.set_workspace(None)
+    block = torch.randn(1 << 16, 1, 64, dtype=torch.complex64, device="cuda")
+    x = block.repeat(B >> 16, 1, 1)
+    W = torch.full((1, 1), 0.75 - 0.5j, dtype=torch.complex64, device="cuda")
+    y = torch.empty_like(x)
+    try:
+        binding.spectral_conv1d_pruned(x, W, y, 64)
+        torch.cuda.synchronize()
+        want = block.to(torch.complex128) * (0.75 - 0.5j)
+        for first in (0, B // 2 - (1 << 15), B - (1 << 16)):
+            part = y[first:first + (1 << 16)].to(torch.complex128)
+            err = (part - want.roll(-(first & 0xffff), 0)).norm() / want.norm()
+            say(f"   rows from {first}: {err.item():.2e}")
+            assert err.item() <= 1e-6
+    finally:
+        binding.set_workspace(None)
+        del x, y
+        torch.cuda.empty_cache()
+
+
 def test_many_small_images_2d(gpu, oracle_mod):
     """32768 images of 64 x 64 (1 GiB): sampled batch elements against the oracle."""
     torch, binding = gpu
