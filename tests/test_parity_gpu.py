@@ -259,7 +259,7 @@ def test_staged_lengths_that_are_not_powers_of_two(gpu, oracle_mod):
 # (B, C_in, C_out, N, K)
 ODD_1D = [(1, 1, 1, 17, 17), (1, 2, 3, 127, 3), (2, 31, 33, 129, 31), (3, 11, 32, 144, 32), (1, 33, 1, 145, 33), (2, 5, 7, 257, 97),
           (1, 40, 24, 271, 128), (2, 17, 9, 390, 129), (700, 16, 48, 136, 72), (1100, 32, 30, 40, 40), (1, 3, 2, 3000, 65),
-          (90, 3, 128, 100, 99), (4, 300, 5, 56, 8), (3, 5, 6, 39, 39), (3, 5, 6, 41, 20),
+          (90, 3, 128, 100, 99), (2, 4, 4, 123, 123), (3, 20, 7, 64 + 1, 40), (2, 3, 3, 63, 63), (4, 300, 5, 56, 8), (3, 5, 6, 39, 39), (3, 5, 6, 41, 20),
           # outputs of 32 MB and more, stored as whole pencils by one, two or four waves (from 65 points; odd pencil counts, rows
           # that start anywhere in a line), and one length past the range on either side
           (700, 2, 97, 65, 9), (700, 2, 97, 63, 9), (513, 2, 73, 127, 20), (300, 2, 91, 129, 17), (257, 2, 65, 255, 30),
