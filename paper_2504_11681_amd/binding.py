@@ -69,9 +69,13 @@ def _entry(name: str):
     return getattr(lib(), name)
 
 
-@functools.lru_cache(maxsize=1024)
-def _need(query: str, *sizes) -> int:
+def _ask(query: str, *sizes) -> int:
     return _entry(query)(*sizes)
+
+
+# The sizes of the most recent calls, for plain ints only: a mode count may be anything that ctypes takes for an int, and a 0-d
+# array or tensor is not hashable, or compares by identity while its value changes (callers pick _ask for those).
+_need = functools.lru_cache(maxsize=1024)(_ask)
 
 
 def _check_c64(x, W, y):
@@ -204,7 +208,7 @@ def _call(name: str, dims: int, variant: int, x, W, y, K: int, stream):
     C_out = ws[1]
     if ws[0] != C_in or ys[0] != B or ys[1] != C_out or ys[2:] != xs[2:] or xs[-1] != N:
         raise ValueError("inconsistent tensor shapes")
-    need = _need("tfno_workspace_bytes", dims, variant, B, C_in, C_out, N, K)
+    need = (_need if type(K) is int else _ask)("tfno_workspace_bytes", dims, variant, B, C_in, C_out, N, K)
     if need:
         ensure_workspace(need, x.device)
     return _launch(name, x, W, y, (B, C_in, C_out, N, K), stream)
@@ -266,7 +270,7 @@ def _call_rect(name: str, variant: int, x, W, y, K1: int, K2: int, stream):
     C_out = ws[1]
     if ws[0] != C_in or ys[0] != B or ys[1] != C_out or ys[2:] != xs[2:]:
         raise ValueError("inconsistent tensor shapes")
-    need = _need("tfno_workspace_bytes_2d", variant, B, C_in, C_out, N1, N2, K1, K2)
+    need = (_need if type(K1) is type(K2) is int else _ask)("tfno_workspace_bytes_2d", variant, B, C_in, C_out, N1, N2, K1, K2)
     if need:
         ensure_workspace(need, x.device)
     return _launch(name, x, W, y, (B, C_in, C_out, N1, N2, K1, K2), stream)

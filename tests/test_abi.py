@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 from paper_2504_11681_amd import binding
@@ -259,3 +260,30 @@ def test_noalloc_entry_point_refuses_shapes_beyond_its_scratch_on_the_host(L):
     text = open(os.path.join(ROOT, "include", "tfno.h")).read()
     m = re.search(r"#define TFNO_NOALLOC_SCRATCH_BYTES \((\d+)u << (\d+)\)", text)
     assert m and int(m.group(1)) << int(m.group(2)) == binding.NOALLOC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("make", [lambda k: np.array(k), lambda k: np.int64(k), lambda k: __import__("torch").tensor(k)],
+                         ids=["array", "int64", "tensor"])
+def test_binding_takes_mode_counts_that_are_not_plain_ints(monkeypatch, make):
+    """Mode counts may be anything that converts to a C int.  The workspace size is looked up by value: an array or a tensor
+    whose value has changed since the last call gets the size of its new value."""
+    import torch
+    from paper_2504_11681_amd import binding
+    sizes, calls = [], []
+    monkeypatch.setattr(binding, "_check_c64", lambda *tensors: None)
+    monkeypatch.setattr(binding, "ensure_workspace", lambda n, device: sizes.append(n))
+    monkeypatch.setattr(binding, "_launch", lambda name, x, W, y, args, stream: calls.append(args))
+    x, W, y = torch.zeros(2, 3, 48), torch.zeros(3, 4), torch.zeros(2, 4, 48)
+    xg, yg = torch.zeros(2, 3, 48, 20), torch.zeros(2, 4, 48, 20)
+    K = make(5)
+    for value in (5, 40):
+        if isinstance(K, (np.ndarray, torch.Tensor)):
+            K[...] = value
+        else:
+            K = make(value)
+        for _ in range(2):
+            binding.spectral_conv1d_staged(x, W, y, K)
+            assert sizes[-1] == binding.workspace_bytes(1, 1, 2, 3, 4, 48, value)
+            binding.spectral_conv2d_rect_staged(xg, W, yg, K, 7)
+            assert sizes[-1] == binding.workspace_bytes_2d(1, 2, 3, 4, 48, 20, value, 7)
+    assert len(calls) == 8
