@@ -495,7 +495,11 @@ k_cgemm_modes_small(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *
 // they are contracted.  The kernels above stage W for 64 outputs and walk tiles; with about a chip full of them or less their
 // time is that of one workgroup's chain of staging, tiles and steps.  25 tiles, C 40 -> 56: 13.4 -> 5.8 us; 32 tiles, C 64:
 // 15.2 -> 7.8 us; 64 tiles, C 128: 26 -> 17 us.  (64 outputs per workgroup measured 12 us at 32 tiles and no faster at 1024.)
-template <int NSTEP>
+// NP: partial products of two three-term operands, smallest first.  Six leave out those of 2^-24 and below, which all have the
+// sign of the product: up to 16 channels, where little else rounds, that is a fifth of the error (16 channels, lengths of 3
+// to 25 points: whole layer 1.1e-7 - 2.1e-7 with six, 0.99e-7 - 1.8e-7 with eight, FP32 sums 1.3e-7 - 2.2e-7; 1 channel, 9 points, 2
+// modes: 1.22e-7, 0.96e-7, 1.03e-7).  The two more are lost in the latency of such short sums (8 channels, 7 points, B 4096: 16.2 and 16.1 us).
+template <int NSTEP, int NP>
 __global__ void __launch_bounds__(256, 2)
 k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__restrict__ Yh, int C_in, int C_out, float scale)
 {
@@ -541,9 +545,9 @@ k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 
                 load_step(c0 + 8 * NSTEP, i);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            constexpr int SA[6] = {2, 0, 1, 1, 0, 0}, SB[6] = {0, 2, 1, 0, 1, 0};   // smallest products first
+            constexpr int SA[8] = {2, 1, 2, 0, 1, 1, 0, 0}, SB[8] = {1, 2, 0, 2, 1, 0, 1, 0};
 #pragma unroll
-            for (int k = 0; k < 6; ++k) {
+            for (int k = 8 - NP; k < 8; ++k) {
                 const bf16x8 bb = __builtin_bit_cast(bf16x8, b[SB[k]]);
                 acc_re = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a_re[SA[k]]), bb, acc_re, 0, 0, 0);
                 acc_im = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a_im[SA[k]]), bb, acc_im, 0, 0, 0);

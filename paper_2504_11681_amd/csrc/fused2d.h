@@ -31,9 +31,10 @@ TFNO_DECLARE_IMAGES(fused2d_fno_images_n128);
 TFNO_DECLARE_IMAGES(fused2d_fno_images_n256);
 #undef TFNO_DECLARE_IMAGES
 
-// Yh = Xh . (scale W) over `tiles` tiles of 128 modes; both spectra mode-tile major ([tile][channel][128]).
+// Yh = Xh . (scale W) over `tiles` tiles of 128 modes; both spectra mode-tile major ([tile][channel][128]).  all_products: sums
+// over up to 16 channels as precise as FP32 ones, where the direct kernel runs.
 hipError_t cgemm_modes_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, float scale, long long tiles,
-                              hipStream_t s);
+                              hipStream_t s, bool all_products = false);
 
 // Yh[b][o][m] = scale * sum_c Xh[b][c][m] * W[c][o][m], m < Ma, with an own weight matrix per mode: W is [C_in, C_out, Ma],
 // the spectra are mode-tile major over the joint mode b Mp + m (Mp >= Ma, a multiple of 8).  Results at m >= Ma: zeros if

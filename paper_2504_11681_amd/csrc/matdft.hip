@@ -185,13 +185,13 @@ hipError_t matdft_conv(const c64 *x, const c64 *W, c64 *y, long long B, int C_in
         MatdftArgs a{};
         a.in = x; a.out = Xh; a.N = N2; a.K = K2; a.P = (unsigned)(B * C_in); a.inner = 1; a.in_outer = N2; a.C = C_in; a.M = g.M;
         if ((e = matdft_forward(MD_ROWS, MD_SPEC, a, s)) != hipSuccess) return e;
-        if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, scale, tiles, s)) != hipSuccess) return e;
+        if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, scale, tiles, s, true)) != hipSuccess) return e;
         a.in = Yh; a.out = y; a.P = (unsigned)(B * C_out); a.out_outer = N2; a.C = C_out;
         return matdft_inverse(MD_SPEC, MD_ROWS, a, s);
     }
     if ((e = last_axis(-1, g, x, T, B * C_in * N1)) != hipSuccess) return e;
     if ((e = first_axis(-1, g, T, Xh, B, C_in)) != hipSuccess) return e;
-    if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, scale, tiles, s)) != hipSuccess) return e;
+    if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, scale, tiles, s, true)) != hipSuccess) return e;
     if ((e = first_axis(+1, g, Yh, T, B, C_out)) != hipSuccess) return e;
     return last_axis(+1, g, T, y, B * C_out * N1);
 }

@@ -276,6 +276,22 @@ def test_1d_lengths_with_odd_factors(gpu, oracle_mod, shape):
     check(run_gpu(gpu, "spectral_conv1d_auto", x, W, K), want, "auto, odd length")
 
 
+@pytest.mark.parametrize("shape", [(1024, 2, 16, 3, 2), (1024, 1, 16, 9, 2), (1024, 4, 16, 9, 2), (512, 9, 16, 7, 2)],
+                         ids=lambda s: "B%d_Ci%d_Co%d_N%d_K%d" % s)
+def test_1d_short_odd_lengths_and_few_channels(gpu, oracle_mod, shape):
+    """Hardly anything rounds here but the last step of each transform and every step of 8 channels of the contraction, 0.8 units
+    of 2^-24 each when rounded downwards, and the roots and weights, 0.5 units each: 0.98e-7 up to 8 channels, 1.08e-7 up to 16;
+    the bound is an eighth above that.  Leaving out the smallest partial products of the contraction, all of one sign,
+    adds 2^-24.5 to the value itself: 1.2e-7 to 1.4e-7."""
+    B, Ci, Co, N, K = shape
+    say(f"[case] short odd length {shape}")
+    x = inputs.make_x(1580 + N, B, Ci, (N,))
+    W = inputs.make_W(1580 + N, Ci, Co)
+    want, _ = oracle_mod.spectral_conv1d(x, W, K)
+    check(run_gpu(gpu, "spectral_conv1d_auto", x, W, K), want, "short odd length",
+          rel_l2=1.125 * 2.0 ** -24 * np.sqrt((2 + (Ci + 7) // 8) * 0.64 + 3 * 0.25))
+
+
 # (B, C_in, C_out, N1, N2, K1, K2): odd sides on either axis or both, one side a power of two
 ODD_2D = [(2, 3, 2, 33, 31, 17, 16), (1, 2, 3, 3, 300, 2, 33), (2, 2, 2, 300, 5, 40, 5), (5, 7, 4, 64, 96, 64, 7), (3, 4, 5, 130, 32, 9, 32),
           (9, 16, 16, 85, 85, 12, 12), (1, 1, 1, 9, 7, 9, 7)]
