@@ -40,6 +40,8 @@ static hipError_t pick_fwd(const MatdftArgs &a, hipStream_t s)
     int w = 1;
     for (int c = 2; c <= 4; ++c)
         if ((kt + c - 1) / c * c <= (kt + w - 1) / w * w && tiles * ((kt + c - 1) / c) >= 1024) w = c;
+    if constexpr (IN == MD_ROWS && !VEC)                    // (fewer than 40 points: one wave to a sum, at most two tiles)
+        return w == 2 ? launch_fwd<2, 1, 1024, IN, OUT, VEC>(a, s) : launch_fwd<1, 1, 1024, IN, OUT, VEC>(a, s);
     const unsigned long long waves = tiles * ((kt + w - 1) / w);
     // (64 to 127 points have 3 or 4 blocks of 16 slots to deal out, worth it while most of the chip is idle: 8 fields of 123 x 3
     // points, all modes, whole layer 32.5 -> 28.5 us, 28.5 us with direct sums)

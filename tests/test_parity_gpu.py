@@ -253,9 +253,9 @@ def test_staged_lengths_that_are_not_powers_of_two(gpu, oracle_mod):
     check(run_gpu(gpu, "spectral_conv1d_auto", x, W, 40), want, "auto, N = 300")
 
 
-# the matrix transform that serves lengths with odd factors: remainders of its 16-element blocks on both sides (I, J % 16,
-# one step or two), edges of its 32-output tiles and of its groups of tiles per wave, pencil counts around 32 and around
-# the counts from which a wave takes more tiles, sums dealt out to 1, 4 and 8 waves, the direct sums of tiny fields.
+# the matrix transform that serves lengths with odd factors: remainders of its 16-element blocks, edges of its 32-output
+# tiles, pencil counts around 32, sums dealt out to 1, 4 and 8 waves, the direct sums of fields that do not fit (its other
+# forms: MATDFT_FORMS below).
 # (B, C_in, C_out, N, K)
 ODD_1D = [(1, 1, 1, 17, 17), (1, 2, 3, 127, 3), (2, 31, 33, 129, 31), (3, 11, 32, 144, 32), (1, 33, 1, 145, 33), (2, 5, 7, 257, 97),
           (1, 40, 24, 271, 128), (2, 17, 9, 390, 129), (700, 16, 48, 136, 72), (1100, 32, 30, 40, 40), (1, 3, 2, 3000, 65),
@@ -305,6 +305,60 @@ def test_2d_sides_with_odd_factors(gpu, oracle_mod, shape):
     W = inputs.make_W(1560 + N1 + K2, Ci, Co)
     want, _ = oracle_mod.spectral_conv2d_rect(x, W, K1, K2)
     check(run_gpu_rect(gpu, "spectral_conv2d_rect_staged", x, W, K1, K2), want, "odd sides")
+
+
+# Every form of the matrix transform, by the sides it reads and writes.  (B, C_in, C_out, N1, N2, K1, K2); N1 = 1: 1-D
+MATDFT_FORMS = {
+    "1-D, two output tiles per wave": (328, 100, 2, 1, 140, 1, 40), "1-D, three": (328, 100, 2, 1, 141, 1, 70), "1-D, four": (328, 100, 2, 1, 140, 1, 100),
+    "1-D, long, two": (330, 100, 2, 1, 1030, 1, 64), "1-D, long, three": (330, 100, 2, 1, 1031, 1, 96), "1-D, long, four": (330, 100, 2, 1, 1030, 1, 128),
+    "1-D, few points, two": (330, 100, 2, 1, 39, 1, 39), "1-D, inverse with two tiles": (330, 2, 100, 1, 100, 1, 30),
+    "1-D, long, inverse with two tiles": (28, 2, 100, 1, 1500, 1, 40), "1-D, long, four waves": (8, 40, 8, 1, 1500, 1, 40), "1-D, long, eight waves": (1, 40, 8, 1, 1500, 1, 40),
+    "rows, two": (8, 63, 2, 66, 140, 5, 40), "rows, three": (8, 63, 2, 66, 141, 5, 70), "rows, four": (8, 63, 2, 66, 140, 5, 100),
+    "rows, four waves": (2, 40, 3, 90, 140, 5, 20), "rows, eight waves": (2, 3, 4, 90, 300, 5, 20), "rows, few points, two": (8, 63, 2, 66, 39, 5, 39),
+    "rows, long": (8, 49, 3, 21, 1500, 9, 20), "rows, long, two": (33, 100, 2, 10, 1100, 3, 50), "rows, long, four waves": (4, 49, 3, 21, 1500, 9, 20), "rows, long, eight waves": (1, 4, 3, 21, 1500, 9, 20),
+    "rows, inverse in pieces, two tiles": (8, 2, 64, 65, 100, 7, 30), "rows, long, inverse, two tiles": (8, 2, 49, 9, 1500, 4, 20), "rows, long, inverse": (1, 2, 3, 9, 1500, 4, 20),
+    "rows, inverse in whole pencils by one wave": (8, 2, 73, 85, 85, 12, 12), "by two waves": (8, 2, 61, 61, 200, 9, 10), "by two waves, just past 128": (8, 2, 61, 90, 130, 9, 10),
+    "by four waves": (4, 2, 61, 61, 300, 9, 10), "by four waves, just past 256": (4, 2, 61, 70, 257, 9, 10), "by four waves, odd counts": (5, 2, 33, 67, 499, 5, 33),
+    "columns, two": (28, 100, 2, 141, 13, 40, 12), "columns, three": (28, 100, 2, 141, 13, 70, 12), "columns, four": (28, 100, 2, 140, 13, 100, 12),
+    "columns, four waves": (4, 50, 3, 141, 50, 20, 10), "columns, eight waves": (2, 3, 3, 301, 13, 20, 12), "columns, long": (33, 90, 3, 1050, 13, 20, 11),
+    "columns, long, two": (33, 90, 2, 1050, 13, 50, 12), "columns, long, four waves": (8, 60, 3, 1500, 13, 20, 11), "columns, long, eight waves": (1, 6, 3, 1500, 13, 20, 11),
+    "columns, inverse with two tiles": (28, 2, 100, 100, 12, 30, 12), "columns, long, inverse, two tiles": (8, 2, 49, 1500, 9, 20, 9)}
+
+
+def exact_layer(torch, x, W, K1, K2):
+    """The definition in float64 on the GPU, shared weights, as plain matrix products: x [B, C_in, N1, N2]."""
+    B, Ci, N1, N2 = x.shape
+    f1 = torch.from_numpy(np.exp(-2j * np.pi * (np.outer(np.arange(N1), np.arange(K1)) % N1) / N1)).cuda()
+    f2 = torch.from_numpy(np.exp(-2j * np.pi * (np.outer(np.arange(N2), np.arange(K2)) % N2) / N2)).cuda()
+    X = x.to(torch.complex128).reshape(-1, N2) @ f2
+    X = X.reshape(B * Ci, N1, K2).transpose(1, 2).reshape(-1, N1) @ f1                                  # [B Ci K2, K1]
+    Y = X.reshape(B, Ci, K2 * K1).transpose(1, 2).reshape(-1, Ci) @ W.to(torch.complex128)               # [B K2 K1, Co]
+    Y = Y.reshape(B, K2, K1, -1).permute(0, 3, 1, 2).reshape(-1, K1) @ f1.conj().T.contiguous()         # [B Co K2, N1]
+    y = Y.reshape(-1, K2, N1).transpose(1, 2).reshape(-1, K2) @ f2.conj().T.contiguous()
+    return y.reshape(B, -1, N1, N2) / (N1 * N2)
+
+
+@pytest.mark.parametrize("form", MATDFT_FORMS)
+def test_forms_of_the_matrix_transform(gpu, form):
+    """Tolerance: four times what 32-bit sums over these lengths measure (2.6e-7 at 1000 points, growing with the length)."""
+    torch, binding = gpu
+    B, Ci, Co, N1, N2, K1, K2 = MATDFT_FORMS[form]
+    say(f"[case] matrix transform: {form} {MATDFT_FORMS[form]}")
+    gen = torch.Generator(device="cuda").manual_seed(1800 + N1 + N2)
+    x = torch.view_as_complex(torch.randn((B, Ci, N1, N2, 2), generator=gen, device="cuda"))
+    W = torch.view_as_complex(torch.randn((Ci, Co, 2), generator=gen, device="cuda")) / Ci ** 0.5
+    y = torch.full((B, Co, N1, N2), float("nan"), dtype=torch.complex64, device="cuda")
+    if N1 == 1:
+        binding.spectral_conv1d_auto(x.reshape(B, Ci, N2), W, y.view(B, Co, N2), K2)
+    else:
+        binding.spectral_conv2d_rect_staged(x, W, y, K1, K2)
+    want = exact_layer(torch, x, W, K1, K2)
+    rel = ((y - want).norm() / want.norm()).item()
+    say(f"   rel_l2={rel:.3e}")
+    assert rel <= 1e-6 * max(1.0, max(N1, N2) / 1000)
+    assert (y - want).abs().max().item() <= 1e-5 * want.abs().max().item()
+    del x, y, want
+    torch.cuda.empty_cache()
 
 
 # One side a power of two, the other with odd factors: every transform that a power of two can take on either axis (column
@@ -1139,18 +1193,32 @@ def test_empty_batch_and_error_paths(gpu):
 # path that mixed scaled and unscaled quantities, would show here.
 @pytest.mark.parametrize("entry,shape", [("spectral_conv1d", (3, 24, 40, 1024, 128)), ("spectral_conv1d", (5, 32, 64, 256, 128)),
                                          ("spectral_conv1d", (4, 64, 256, 256, 64)), ("spectral_conv1d_pruned", (3, 70, 65, 256, 64)),
-                                         ("spectral_conv2d", (2, 8, 8, 64, 16))],
+                                         ("spectral_conv2d", (2, 8, 8, 64, 16)), ("spectral_conv2d", (1, 4, 3, 512, 40)),
+                                         ("spectral_conv1d_auto", (3, 24, 40, 1000, 50)), ("spectral_conv1d_auto", (9, 5, 40, 39, 20)),
+                                         ("spectral_conv2d_staged", (2, 8, 8, 85, 12)),
+                                         ("spectral_conv1d_permode", (16, 24, 33, 256, 100)), ("spectral_conv1d_permode", (64, 40, 64, 256, 100)),
+                                         ("spectral_conv1d_permode", (3, 20, 7, 64, 12))],
                          ids=lambda v: v if isinstance(v, str) else "x".join(map(str, v)))
 def test_power_of_two_scaling_is_exact(gpu, entry, shape):
+    torch, binding = gpu
     B, Ci, Co, N, K = shape
     say(f"[case] scaling {entry} {shape}")
-    dims = (N, N) if entry.endswith("2d") else (N,)
+    dims = (N, N) if "2d" in entry else (N,)
     x = inputs.make_x(4242, B, Ci, dims)
-    W = inputs.make_W(4242, Ci, Co)
-    base = run_gpu(gpu, entry, x, W, K)
+    per_mode = entry.endswith("permode")
+    W = inputs.make_W(4242, Ci, Co * K if per_mode else Co)
+
+    def run(x, W):
+        if not per_mode:
+            return run_gpu(gpu, entry, x, W, K)
+        y = torch.full((B, Co, N), float("nan"), dtype=torch.complex64, device="cuda")
+        getattr(binding, entry)(torch.from_numpy(x).cuda(), torch.from_numpy(W.reshape(Ci, Co, K)).cuda(), y)
+        return y.cpu().numpy()
+
+    base = run(x, W)
     assert np.isfinite(base.view(np.float32)).all()
     for ex, ew in ((30, 0), (-30, 0), (0, 25), (-20, -20), (40, -45)):
-        got = run_gpu(gpu, entry, x * np.float32(2.0 ** ex), W * np.float32(2.0 ** ew), K)
+        got = run(x * np.float32(2.0 ** ex), W * np.float32(2.0 ** ew))
         want = base * np.float32(2.0 ** (ex + ew))
         assert np.array_equal(got.view(np.float32), want.view(np.float32)), (entry, shape, ex, ew)
 
