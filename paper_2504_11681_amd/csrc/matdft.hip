@@ -76,12 +76,16 @@ static hipError_t pick_inv(const MatdftArgs &a, hipStream_t s)
 {
     const unsigned long long tiles = (a.P + 31) / 32;
     if constexpr (OUT == MD_ROWS) {
-        // Whole pencils per workgroup for outputs that the caches do not hold and that fill the chip this way (whole layer,
-        // 85 x 85, B 32, C 32: 62.3 -> 57.8 us; 200 x 200, B 16, C 16: 80 -> 68.5; N 500, B 300, C 64: 87 -> 80; below 64
-        // points half the output pairs would be padding: 48 x 60, B 64, C 32: 47 -> 50, not used).
-        if (a.N >= 64 && a.N < 512 && a.out_outer == a.N && (unsigned long long)a.P * a.N * sizeof(c64) >= (32ULL << 20) && tiles * ((a.N + 128) / 128) >= 1024) {
-            if (a.N < 128) return launch_inv<2, 1024, IN, OUT, 1>(a, s);
-            return a.N < 256 ? launch_inv<2, 1024, IN, OUT, 2>(a, s) : launch_inv<2, 1024, IN, OUT, 4>(a, s);
+        // Whole pencils per workgroup for outputs that the caches do not hold and that fill the chip this way: layers whose
+        // buffers change from call to call, outputs of 40, 80, 160 MB: 85 points 40.6 -> 39.8, 74.0 -> 63.9, 122.8 -> 113.4 us,
+        // 200 points 40.3 -> 40.2, 72.8 -> 60.7, 120.8 -> 112.5 us, 500 points 41.8 -> 41.3, 71.4 -> 61.2, 134.1 -> 115.1 us.
+        // Where more than 3/8 of the pairs that the waves cover are padding, only larger outputs gain (257 points, 16 -> 16
+        // channels: 39.7 -> 45.0, 75.0 -> 66.1, 113.6 -> 112.1 us; 4 -> 16: 32.2 -> 38.4, 49.8 -> 50.8, 77.3 -> 72.4 us).  Below 64 points half the pairs would be padding: 48 x 60 points 47 -> 50 us.
+        const int G = a.N < 128 ? 1 : a.N < 256 ? 2 : 4;
+        const unsigned long long bytes = (unsigned long long)a.P * a.N * sizeof(c64), least = 8 * (a.N / 2 + 1) < 5 * 64 * G ? 64ULL << 20 : 32ULL << 20;
+        if (a.N >= 64 && a.N < 512 && a.out_outer == a.N && bytes >= least && tiles * G >= 1024) {
+            if (G == 1) return launch_inv<2, 1024, IN, OUT, 1>(a, s);
+            return G == 2 ? launch_inv<2, 1024, IN, OUT, 2>(a, s) : launch_inv<2, 1024, IN, OUT, 4>(a, s);
         }
     }
     // two tiles of output pairs per wave where they divide the pairs evenly and leave a wave for every SIMD

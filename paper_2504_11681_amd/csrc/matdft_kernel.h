@@ -305,7 +305,8 @@ k_matdft_fwd(MatdftArgs a)
 
 // ------------------------------------------------------------------------------------------------ inverse
 // G (contiguous outputs only): G = 1, 2, 4 waves of the workgroup own whole pencils, N < 128 G.  They put eight of them at a
-// time together in LDS and store them as whole 128-byte lines past the caches.  A wave that stores its own 256-byte pieces
+// time together in LDS and store them as whole 128-byte lines past the caches (for odd N every other boundary between two
+// eights splits a line).  A wave that stores its own 256-byte pieces
 // leaves partial lines, which only the caches can merge; of a large output these stay in the last-level cache as dirty lines,
 // and the next kernel's reads wait for their write-back (32 x 32 fields of 85 x 85: the next forward kernel takes 25 instead
 // of 18 us; with non-temporal stores of pieces it is the inverse kernel that doubles).  G = 0: every wave on its own.
@@ -365,8 +366,9 @@ k_matdft_inv(MatdftArgs a)
 
     c64 u[8];
     fetch(u, 0);
+    const int modes = G > 0 && n0 > H ? 0 : a.K;            // (a wave past the last pair only helps to store)
 #pragma unroll 1
-    for (int i0 = 0; i0 < a.K; i0 += 16) {
+    for (int i0 = 0; i0 < modes; i0 += 16) {
         if (i0 + 16 > a.K) {
 #pragma unroll
             for (int e = 0; e < 8; ++e)
