@@ -109,7 +109,9 @@ size_t workspace_for(const Shape &sh, int variant, int B, int C_in, int C_out);
 
 
 // Mode counts between the built kernel sizes: the request runs on the next power of two K' >= K for which a kernel
-// exists and the forward side zeroes bins K .. K'-1 before the contraction (exactly the truncation to K).
+// exists, which is exactly the truncation to K.  The fused kernels write zeros for bins K .. K'-1 into their operand
+// tiles.  Spectra in the workspace hold the kept modes only, or all K' bins of the 1-D kernels with zeros past K; what their
+// strides leave over is unspecified, and the inverse kernels do not take it in.
 template <class Pred>
 int round_modes(int N, int K, Pred pred)
 {
@@ -198,8 +200,12 @@ tfno_status run(const Shape &req, Variant variant, const void *x, const void *W,
     const bool odd = !is_pow2(sh.N1) || !is_pow2(sh.N2);
     if (staged && odd && !contraction_forced_f32() &&
         matdft_workspace_bytes(B, C_in, C_out, sh.N1, sh.N2, sh.K1, sh.K2) <= workspace_for(req, (int)variant, B, C_in, C_out)) {
-        // a side that is no power of two: pruned transforms as contractions on the matrix pipe, within the workspace of
-        // the staged pipeline (whose direct sums over all N x N terms remain for batches of fewer than 128 points)
+        // a side that is no power of two: pruned transforms, along that side as contractions on the matrix pipe, within the
+        // workspace that the staged pipeline has always asked for.  They do not fit where the whole 128-mode tiles of the two
+        // spectra, and in 2-D the fields transformed along their last axis (B N1 K2 max(C_in, C_out)), take more than its four
+        // arrays: few points (one field of up to 126 points in 1-D, of up to 252 in 2-D with 32 channels each), or unequal
+        // channel counts with all modes of the last axis kept (64 -> 1 channels, 83 x 97 points, 4 x 97 modes).  Those
+        // calls keep the direct sums.
         e = matdft_conv(xc, Wc, yc, B, C_in, C_out, sh.N1, sh.N2, sh.K1, sh.K2, (c64 *)ws, s);
     } else if (staged) {
         e = staged_conv(dims, xc, Wc, yc, B, C_in, C_out, sh.N1, sh.N2, sh.K1, sh.K2, (c64 *)ws, s);
@@ -285,7 +291,7 @@ tfno_status run_permode(const Shape &req, const void *x, const void *W, void *y,
     const float scale = 1.0f / ((float)sh.N1 * (float)sh.N2);
     hipError_t e;
     if (sh.dims == 1) {
-        const int N = sh.N2, K = sh.K2, Mp = pruned1d_stride(N, K, req.K2);
+        const int N = sh.N2, K = sh.K2, Mp = pruned1d_stride(N, K, req.K2, true);
         c64 *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
         e = pruned1d_stages(PRUNED_FWD, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, req.K2, Mp, s);
         if (e == hipSuccess) e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, B, Mp, req.K2, Mp == K, scale, s);
@@ -392,7 +398,7 @@ tfno_status run_fno1d(const void *x, const void *W, void *y, int B, int C_in, in
     tfno_status st = check_workspace(pruned1d_workspace_bytes(B, C_in, C_out, K), x, xb, W, wb, y, yb, &wsp);
     if (st != TFNO_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    const int Mp = pruned1d_stride(N, K, M);
+    const int Mp = pruned1d_stride(N, K, M, true);
     c64 *Xh = (c64 *)wsp, *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
     hipError_t e = pruned1d_real_stages(PRUNED_FWD, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, M, Mp, s);
     if (e == hipSuccess) e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, B, Mp, M, Mp == K, 2.0f / (float)N, s);

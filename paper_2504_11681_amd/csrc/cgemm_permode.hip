@@ -13,7 +13,8 @@ static void launch_f32(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out
     const unsigned long long threads = (unsigned long long)((B + BT - 1) / BT) * Mc;
     const unsigned slabs = (unsigned)((C_out + OT - 1) / OT);
     const dim3 grid((unsigned)((threads + 255) / 256 * slabs));
-    hipLaunchKernelGGL((k_cgemm_permode<BT, OT>), grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, slabs);
+    auto run = Mc > Ma ? &k_cgemm_permode<BT, OT, true> : &k_cgemm_permode<BT, OT, false>;
+    hipLaunchKernelGGL(run, grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, slabs);
 }
 
 hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, long long B, int Mp, int Ma,
@@ -21,27 +22,26 @@ hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, 
 {
     if (B <= 0) return hipSuccess;
     if (Ma < 1 || Mp < Ma || Mp % 8 != 0) return hipErrorInvalidValue;
-    // Matrix-pipe kernel from 36 workgroups' worth of results on (its time hardly falls below that: whole layers of 64 x 64
+    // Matrix-pipe kernel from 36 workgroups' worth of results on, 48 below 32 channels (its time hardly falls below that: whole layers of 64 x 64
     // channels, 256 points, with either kernel, FP32 first: 262144 results 22.1 and 22.6 us, 327680 results 29.9 and 24.9 us;
-    // 16 modes, B 64: 19.2 and 20.9 us), with enough channels, outputs and batch elements for its 32 x 32 x 8-channel
-    // tiles; everything else (and TFNO_CONTRACTION=f32) runs the FP32 kernel.  Below 32 channels its six products
-    // per value (bf16x3.h) lose more than the shorter sums gain (16 channels: 1.8e-7 against 1.7e-7 for a layer, 24: 1.9e-7 both), so
-    // few modes stay on the FP32 kernel there (B 64, 16 -> 256 channels, 60 modes: 23.6 against 22.4 us).
+    // 16 modes, B 64: 19.2 and 20.9 us; 18 -> 256 channels, 327680 results: 19.2 and 22.4 us), with enough channels, outputs and batch elements for its 32 x 32 x 8-channel
+    // tiles; everything else (and TFNO_CONTRACTION=f32) runs the FP32 kernel.
     const long long gy = (B + 31) / 32, gz = (C_out + 31) / 32;
-    if (C_in >= (Mp > 64 ? 16 : 32) && C_out >= 16 && B >= 16 && B * Ma * C_out >= 36 * 8192 && !contraction_forced_f32() && gy <= 65535 && gz <= 65535) {
+    if (C_in >= 16 && C_out >= 16 && B >= 16 && B * Ma * C_out >= (C_in < 32 ? 48 : 36) * 8192 && !contraction_forced_f32() && gy <= 65535 && gz <= 65535) {
         const dim3 grid((unsigned)(Mp / 8), (unsigned)gy, (unsigned)gz);
         // without masks where every tile is full and the extents a workgroup addresses with 32-bit offsets (32 batch
         // elements of Xh, all of W) stay below 2^31 bytes
         const bool fits32 = (32LL * Mp + 256) * C_in * 8 < (1LL << 31) && (long long)C_in * C_out * Ma * 8 < (1LL << 31);
-        if (B % 32 == 0 && C_out % 32 == 0 && C_in % 8 == 0 && fits32)
-            hipLaunchKernelGGL(k_cgemm_permode_mfma<true>, grid, dim3(512), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale);
-        else
-            hipLaunchKernelGGL(k_cgemm_permode_mfma<false>, grid, dim3(512), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale);
+        const bool full = B % 32 == 0 && C_out % 32 == 0 && C_in % 8 == 0 && fits32;
+        // (eight partial products below 32 channels where they are hidden: with more than 64 modes they take up to 9 %)
+        auto run = C_in < 32 && Mp <= 64 ? (full ? &k_cgemm_permode_mfma<true, 8> : &k_cgemm_permode_mfma<false, 8>)
+                                         : (full ? &k_cgemm_permode_mfma<true, 6> : &k_cgemm_permode_mfma<false, 6>);
+        hipLaunchKernelGGL(run, grid, dim3(512), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, scale);
         return hipGetLastError();
     }
     const int Mc = zeros ? Mp : Ma;
     // Batch elements x outputs per thread: more reuse of what is loaded where that still gives every SIMD a wave.
-    auto waves = [&](int bt, int ot) { return (B + bt - 1) / bt * Mc * ((C_out + ot - 1) / ot) / 64; };
+    auto waves = [&](int bt, int ot) { return (B + bt - 1) / bt * Ma * ((C_out + ot - 1) / ot) / 64; };
     if (waves(8, 8) >= 1024) launch_f32<8, 8>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
     else if (waves(4, 4) >= 1024) launch_f32<4, 4>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
     else if (waves(2, 2) >= 256) launch_f32<2, 2>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);

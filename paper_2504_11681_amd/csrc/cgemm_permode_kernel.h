@@ -2,13 +2,13 @@
 // the Fourier layer as the FNO model defines it, Sec. 1 / Sec. 2.1 step 3; Sec. 3.1 treats the case of one shared
 // matrix, which the MFMA kernels of cgemm_modes_kernel.h cover):
 //
-//   Yh[b, o, m] = scale * sum_c Xh[b, c, m] * W[c, o, min(m, Ma - 1)],   m < Mc
+//   Yh[b, o, m] = scale * sum_c Xh[b, c, m] * W[c, o, m],   m < Ma;     0,   Ma <= m < Mc
 //
 // Spectra are mode-tile major ([tile][channel][128]) over the joint mode b Mp + m, W is [C_in, C_out, Ma]; Mc is
-// Ma, or Mp where surplus modes that hold zeros have to come out as zeros.  FP32 kernel
+// Ma, or Mp where the surplus modes have to be zeros (ZEROS: the last threads store them).  FP32 kernel
 // for products too small for the matrix pipe (cgemm_permode_mfma_kernel.h): a thread owns one mode of BT batch elements
 // and OT outputs, so a W value loaded is used BT times and an Xh value OT times; the threads of a wave own consecutive
-// modes (coalesced runs of Mc) and, where Mc is short, of consecutive batch groups.  Bound by the latency of the loads:
+// modes (coalesced runs of Ma) and, where Ma is short, of consecutive batch groups.  Bound by the latency of the loads:
 // U channels are in flight, and BT and OT are chosen small enough to give the chip a wave per SIMD (B 32, 16 modes, 64 x 64
 // channels: 51 -> 7 us against 8 x 8 per thread, which made 8 workgroups).
 #pragma once
@@ -17,28 +17,39 @@
 
 namespace tfno {
 
-template <int BT, int OT>
+template <int BT, int OT, bool ZEROS>
 __global__ void __launch_bounds__(256, 2)
 k_cgemm_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__restrict__ Yh, int C_in, int C_out,
                 long long B, int Mp, int Ma, int Mc, float scale, unsigned slabs)
 {
     constexpr int U = BT + OT <= 2 ? 16 : BT + OT <= 4 ? 8 : BT + OT <= 8 ? 4 : 2;
     const unsigned long long f = blockIdx.x / slabs * 256ULL + threadIdx.x;      // (slabs of OT outputs innermost)
-    const long long grp = (long long)(f / (unsigned)Mc), b0 = grp * BT;
-    const int m = (int)(f % (unsigned)Mc), wm = m < Ma ? m : Ma - 1;
     const int o0 = (int)(blockIdx.x % slabs) * OT;
-    if (b0 >= B) return;
-
-    auto spec = [&](long long b, int C) __attribute__((always_inline)) {   // element (b, channel 0, m)
+    auto spec = [&](long long b, int m, int C) __attribute__((always_inline)) {   // element (b, channel 0, m)
         const long long j = b * Mp + m;
         return (j >> 7) * C * 128 + (j & 127);
     };
+    if constexpr (ZEROS) {                                  // (a branch of their own: in the sums' loops they cost 0.4 us)
+        const unsigned long long sums = (unsigned long long)((B + BT - 1) / BT) * (unsigned)Ma;      // threads that have a sum
+        if (f >= sums) {
+            const unsigned extra = (unsigned)(Mc - Ma);
+            const long long z0 = (long long)((f - sums) / extra) * BT;
+            const int m = Ma + (int)((f - sums) % extra);
+            for (long long b = z0; b < z0 + BT && b < B; ++b)
+                for (int o = o0; o < o0 + OT && o < C_out; ++o) Yh[spec(b, m, C_out) + (long long)o * 128] = make_float2(0.f, 0.f);
+            return;
+        }
+    }
+    const long long grp = (long long)(f / (unsigned)Ma), b0 = grp * BT;
+    const int m = (int)(f % (unsigned)Ma);
+    if (b0 >= B) return;
+
     const c64 *xp[BT];
 #pragma unroll
-    for (int bi = 0; bi < BT; ++bi) xp[bi] = Xh + spec(b0 + bi < B ? b0 + bi : B - 1, C_in);
+    for (int bi = 0; bi < BT; ++bi) xp[bi] = Xh + spec(b0 + bi < B ? b0 + bi : B - 1, m, C_in);
     const c64 *wp[OT];
 #pragma unroll
-    for (int oi = 0; oi < OT; ++oi) wp[oi] = W + (long long)(o0 + oi < C_out ? o0 + oi : C_out - 1) * Ma + wm;
+    for (int oi = 0; oi < OT; ++oi) wp[oi] = W + (long long)(o0 + oi < C_out ? o0 + oi : C_out - 1) * Ma + m;
     const long long wstep = (long long)C_out * Ma;
 
     c64 acc[BT][OT];
@@ -84,7 +95,7 @@ k_cgemm_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__re
 #pragma unroll
     for (int bi = 0; bi < BT; ++bi) {
         if (b0 + bi >= B) continue;
-        c64 *yp = Yh + spec(b0 + bi, C_out);
+        c64 *yp = Yh + spec(b0 + bi, m, C_out);
 #pragma unroll
         for (int oi = 0; oi < OT; ++oi)
             if (o0 + oi < C_out) yp[(long long)(o0 + oi) * 128] = make_float2(acc[bi][oi].x * scale, acc[bi][oi].y * scale);

@@ -21,7 +21,7 @@ enum { PRUNED_FWD = 1, PRUNED_GEMM = 2, PRUNED_INV = 4 };
 size_t pruned1d_spectrum_elems(long long B, int C, int Mp);
 // Modes per pencil in the joint mode index of the spectra when K_keep of the kernel's K bins are kept (at most K): the
 // bins past it are neither stored nor contracted (N 2048, K 316 of 512: 320; K 500 of 512: 512).
-int pruned1d_stride(int N, int K, int K_keep);
+int pruned1d_stride(int N, int K, int K_keep, bool per_mode = false);
 // Mp: pruned1d_stride(N, K, K_keep), or K with N <= 1024 for the partially fused kernels, which read and write all K.  With
 // Mp = K the forward transform writes zeros to the bins that are not kept and the inverse expects zeros there.
 hipError_t pruned1d_stages(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,

@@ -60,16 +60,16 @@ size_t pruned1d_workspace_bytes(long long B, int C_in, int C_out, int K)
 
 size_t pruned1d_spectrum_elems(long long B, int C, int Mp) { return (size_t)mode_tiles(B, Mp) * 128 * (size_t)C; }
 
-int pruned1d_stride(int N, int K, int K_keep)
+int pruned1d_stride(int N, int K, int K_keep, bool per_mode)
 {
     if (N < 2048) {
         // The kept bins in 64-byte rows, or all of the kernel's where the masks of cut spectra cost more than the shorter
-        // spectra save: past 7/8 of them for kernels that keep all N bins, whose contraction weighs most (B 512, 128 channels,
-        // 128 points: 112 modes 93.4 us cut and 97 in full, 120 modes 100.6 and 96.6), past 3/4 for the others (B 256: 1024
-        // real points, 128 channels, own weights, 100 modes 113 us cut and 106 in full; 256 points, 64 channels, 100 modes
-        // 35.9 and 32.8).
+        // spectra save: past 7/8 of them where the contraction weighs most, in kernels that keep all N bins (B 512, 128 channels, 128
+        // points: 112 modes 93.4 us cut and 97 in full, 120 modes 100.6 and 96.6) and with own weights per mode up to 256 points (B 64,
+        // 28 -> 256 channels, 256 points, 100 modes 28.1 and 29.9); past 3/4 in the others (B 256: 1024 real points, 128 channels,
+        // own weights, 100 modes 113 and 106; 256 points, 64 channels, shared weights, 100 modes 35.9 and 32.8).
         const int s = spectrum_stride(K_keep);
-        return (K == N ? 8 * s > 7 * K : 4 * s > 3 * K) ? K : s;
+        return (K == N || (per_mode && N <= 256) ? 8 * s > 7 * K : 4 * s > 3 * K) ? K : s;
     }
     // Long pencils: whole columns of the N1 x 256 array, and all of the kernel's K2 columns where less than an eighth
     // of them would go: the masks then cost what the shorter spectra save (B 64, 128 x 128 channels, 2048 points: 63 of 64
@@ -187,7 +187,7 @@ static hipError_t launch_n(int K, int stages, const c64 *x, const c64 *W, c64 *y
 hipError_t pruned1d_stages(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
                            int C_out, int N, int K, int K_keep, int Mp, hipStream_t s)
 {
-    if (!pruned1d_supported(N, K) || K_keep < 1 || K_keep > K || Mp > K || (Mp != K && Mp != pruned1d_stride(N, K, K_keep)))
+    if (!pruned1d_supported(N, K) || K_keep < 1 || K_keep > K || Mp > K || Mp < K_keep || (N < 2048 ? Mp % 8 : Mp % (N / 256)) != 0)
         return hipErrorInvalidValue;
     switch (N) {
     case 64: return launch_n<64>(K, stages, x, W, y, Xh, Yh, B, C_in, C_out, K_keep, Mp, s);

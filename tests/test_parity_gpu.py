@@ -207,7 +207,7 @@ def test_1d_pruned_unsupported_shapes(gpu):
 
 STAGED_ONLY_1D = [(2, 3, 4, 2, 1), (2, 3, 4, 4, 3), (3, 6, 5, 32, 5), (2, 4, 4, 2048, 100), (1, 2, 3, 4096, 4096),
                   (2, 5, 3, 256, 48),
-                  # lengths that are not powers of two (direct-sum transform)
+                  # lengths that are not powers of two (matrix transform; the shortest, which does not fit, direct sums)
                   (2, 3, 4, 3, 2), (3, 5, 4, 48, 12), (2, 4, 6, 421, 24), (1, 3, 2, 1000, 1000), (2, 2, 2, 85, 85),
                   (1, 2, 2, 4095, 7)]
 
@@ -1418,9 +1418,11 @@ def test_fp32_contraction_kernels_in_a_child_process(gpu, oracle_mod, tmp_path):
 # (entry, sizes): the direct-sum transforms (long and short lengths, several pencils to a workgroup, columns of a grid), the
 # per-mode contraction with 8 x 8, 4 x 4 and fewer results per thread
 F32_LAYERS = [("staged1d", 2, 3, 4, 421, 50), ("staged1d", 3, 20, 9, 1000, 33), ("staged1d", 1, 2, 2, 4095, 100), ("staged1d", 7, 5, 6, 39, 39),
+              # (of these two the first does not fit the workspace with the matrix transform, the second just does)
+              ("grid2d", 1, 64, 1, 83, 97, 4, 97), ("grid2d", 1, 64, 1, 83, 97, 4, 90), ("staged1d", 1, 3, 4, 127, 127), ("staged1d", 1, 3, 4, 63, 63),
               ("grid2d", 2, 3, 4, 85, 48, 12, 20), ("grid2d", 2, 2, 3, 48, 85, 48, 9), ("grid2d", 1, 3, 2, 421, 12, 30, 12),
               ("permode1d", 128, 9, 128, 256, 256), ("permode1d", 100, 8, 100, 256, 128), ("permode1d", 60, 20, 70, 256, 100), ("permode1d", 6, 33, 7, 1024, 60),
-              ("permode1d", 64, 24, 128, 256, 60), ("permode1d", 64, 31, 100, 128, 50), ("permode1d", 64, 32, 128, 256, 60), ("permode1d", 64, 64, 64, 256, 73)]
+              ("permode1d", 128, 24, 128, 256, 64), ("permode1d", 128, 16, 129, 256, 64), ("permode1d", 64, 31, 100, 128, 50), ("permode1d", 64, 32, 128, 256, 60), ("permode1d", 64, 64, 64, 256, 73)]
 
 
 def f32_layer(torch, binding, layer):
@@ -1445,10 +1447,11 @@ def f32_layer(torch, binding, layer):
 
 
 def test_fp32_general_layers_in_a_child_process(gpu, oracle_mod, tmp_path):
-    """TFNO_CONTRACTION=f32: lengths with odd factors by direct sums, the per-mode contraction on its FP32 kernel.  Per-mode
-    layers of fewer than 32 channels and at most 64 stored modes run that kernel by default as well (the six products of the
-    matrix pipe lose more there than its shorter sums gain), so their results are the same bits; with 32 channels, or more
-    than 64 modes, and 294912 results they are the matrix pipe's."""
+    """TFNO_CONTRACTION=f32: lengths with odd factors by direct sums, the per-mode contraction on its FP32 kernel.  By default the
+    direct sums run where whole tiles of spectra and the half-transformed fields do not fit the workspace (same bits).  Per-mode
+    layers run that kernel by default as well below 294912 results (393216 below 32 channels) or 16 channels, outputs or
+    batch elements (same bits); the others run on the matrix pipe, with the error of the FP32 sums (which depends on the results
+    per thread) or less, also with few channels: leaving out the smallest products would make it 4 % more at 16 of them."""
     import os
     import subprocess
     import textwrap
@@ -1477,8 +1480,16 @@ def test_fp32_general_layers_in_a_child_process(gpu, oracle_mod, tmp_path):
             X = x.astype(np.complex128) @ f
             want = np.matmul(X.transpose(2, 0, 1), W.astype(np.complex128).transpose(2, 0, 1)).transpose(1, 2, 0) @ np.conj(f.T) / N
             same = np.array_equal(y.view(np.float32), default.view(np.float32))
-            matrix_pipe = B >= 16 and Co >= 16 and Ci >= (16 if K > 64 else 32) and B * K * Co >= 294912
+            matrix_pipe = B >= 16 and Co >= 16 and Ci >= 16 and B * K * Co >= (393216 if Ci < 32 else 294912)
             assert same != matrix_pipe, (layer, same)
+            errs = [np.linalg.norm(v - want) / np.linalg.norm(want) for v in (default, y)]
+            say(f"   default {errs[0]:.3e}, FP32 {errs[1]:.3e}")
+            assert not matrix_pipe or K > 64 or Ci >= 32 or errs[0] <= 1.03 * errs[1], layer
         else:
+            N1, N2, K1, K2 = dims if entry == "grid2d" else (1, dims[0], 1, dims[1])
+            if N2 & (N2 - 1):                             # (powers of two: K2 may be rounded up)
+                need = -(-B * K1 * K2 // 128) * 128 * (Ci + Co) + (B * N1 * K2 * max(Ci, Co) if N1 > 1 else 0)
+                fits = need <= B * (Ci + Co) * (N1 * N2 + K1 * K2)
+                assert np.array_equal(y.view(np.float32), default.view(np.float32)) != fits, (layer, fits)
             want = (oracle_mod.spectral_conv1d if entry == "staged1d" else oracle_mod.spectral_conv2d_rect)(x, W, *dims[len(dims) // 2:])[0]
         check(y, want, f"f32 {layer}")
