@@ -122,12 +122,13 @@ static long long mode_tiles(long long B, long long M) { return (B * M + 127) / 1
 
 static bool is_pow2(int n) { return (n & (n - 1)) == 0; }
 
-// 2-D: columns of the fields transformed along their last axis, K2 or, from the pruned kernels of powers of two, their
-// stride (bins past K2 are zeros there)
+// 2-D: columns of the fields transformed along their last axis, K2 or, from the row kernels of powers of two, their
+// stride (its bins past K2 are zeros)
 static int row_modes(int N2, int K2)
 {
     const int K = is_pow2(N2) ? pruned1d_modes(N2, K2) : 0;
-    return K ? pruned1d_stride(N2, K, K2) : K2;
+    const int rows = K ? 0 : pruned1d_row_stride(N2, K2);
+    return K ? pruned1d_stride(N2, K, K2) : rows ? rows : K2;
 }
 
 // workspace: Xh, Yh in whole tiles of 128 modes; 2-D: the fields transformed along their last axis, [B, C, N1, cols],
@@ -154,6 +155,7 @@ hipError_t last_axis(int dir, const Grid &g, const c64 *in, c64 *out, long long 
         // (the spectrum of one channel is [rows, cols])
         if (K && dir < 0) return pruned1d_stages(PRUNED_FWD, in, nullptr, nullptr, out, nullptr, rows, 1, 1, g.N2, K, g.K2, g.cols, g.s);
         if (K) return pruned1d_stages(PRUNED_INV, nullptr, nullptr, out, nullptr, const_cast<c64 *>(in), rows, 1, 1, g.N2, K, g.K2, g.cols, g.s);
+        if (pruned1d_row_stride(g.N2, g.K2)) return pruned1d_rows(dir, in, out, rows, g.N2, g.K2, g.s);
         if (dir < 0) return launch_axis_fft(-1, in, out, g.N2, rows, 1, g.N2, g.cols, 1, g.N2, g.K2, 1.f, g.s);
         return launch_axis_fft(+1, in, out, g.N2, rows, 1, g.cols, g.N2, 1, g.K2, g.N2, 1.f, g.s);
     }

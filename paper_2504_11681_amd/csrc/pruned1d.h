@@ -27,6 +27,11 @@ int pruned1d_stride(int N, int K, int K_keep, bool per_mode = false);
 hipError_t pruned1d_stages(int stages, const c64 *x, const c64 *W, c64 *y, c64 *Xh, c64 *Yh, long long B, int C_in,
                            int C_out, int N, int K, int K_keep, int Mp, hipStream_t s);
 
+// Rows of 512 or 1024 points by the long-pencil kernels: dir < 0 [rows, N] -> [rows, stride], K_keep bins in an order of their
+// own and zeros; dir > 0 the unscaled zero-padded inverse, which takes all `stride` of them.  stride 0: other lengths.
+int pruned1d_row_stride(int N, int K_keep);
+hipError_t pruned1d_rows(int dir, const c64 *in, c64 *out, long long rows, int N, int K_keep, hipStream_t s);
+
 // Real pencils (x, y float32; N <= 1024): PRUNED_FWD writes the R2C bins with bin 0 halved, PRUNED_INV stores the real
 // part of the zero-padded inverse; the contraction between them (not run here) carries the scale 2 / N.
 hipError_t pruned1d_real_stages(int stages, const float *x, float *y, c64 *Xh, c64 *Yh, long long B, int C_in, int C_out,

@@ -31,7 +31,7 @@ struct CfgLong {
     static constexpr int G = 16 / N1;           // pencils per sweep
     static constexpr int KH = K2 / 16;          // retained outputs per column of the 256-point transform
     static constexpr int RS = 272;              // row stride of the exchange buffer: rows g, g + 1 start 32 banks apart
-    static_assert(N1 == 8 || N1 == 16, "N in {2048, 4096}");
+    static_assert(N1 == 2 || N1 == 4 || N1 == 8 || N1 == 16, "N in {512, 1024, 2048, 4096}");
     static_assert(K2 % 16 == 0 && KH >= 1 && KH <= 16 && (KH & (KH - 1)) == 0, "K / N1 in {16, 32, 64, 128, 256}");
 };
 

@@ -370,7 +370,8 @@ MIXED_2D = [(2, 3, 4096, 3, 4096, 3), (2, 3, 3, 4096, 3, 4096), (3, 2, 1024, 48,
             (4, 3, 256, 25, 128, 16), (4, 3, 256, 25, 17, 17), (4, 3, 256, 25, 129, 1), (4, 3, 25, 256, 20, 33), (4, 3, 25, 256, 25, 256),
             (5, 4, 128, 100, 33, 48), (5, 4, 128, 9, 16, 9), (5, 4, 100, 128, 30, 20), (5, 4, 9, 128, 9, 128),
             (5, 4, 64, 96, 64, 7), (5, 4, 64, 96, 8, 96), (5, 4, 96, 64, 7, 64), (5, 4, 96, 64, 50, 9), (5, 4, 60, 1024, 12, 100),
-            (5, 4, 16, 31, 16, 31), (5, 4, 31, 16, 31, 16), (5, 4, 2, 130, 1, 40), (5, 4, 130, 2, 40, 2), (3, 3, 32, 50, 20, 33)]
+            (5, 4, 16, 31, 16, 31), (5, 4, 31, 16, 31, 16), (3, 2, 31, 512, 5, 20), (2, 2, 9, 512, 9, 512), (2, 3, 7, 512, 3, 65),
+            (2, 3, 7, 1024, 7, 129), (2, 2, 6, 1024, 3, 500), (5, 4, 2, 130, 1, 40), (5, 4, 130, 2, 40, 2), (3, 3, 32, 50, 20, 33)]
 
 
 @pytest.mark.parametrize("shape", MIXED_2D, ids=lambda s: "Ci%d_Co%d_N%dx%d_K%dx%d" % s)
