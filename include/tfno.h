@@ -131,9 +131,13 @@ tfno_status tfno_spectral_conv2d_noalloc(const void *x, const void *W, void *y,
  * tfno_workspace_bytes(dims, 1, ...) bytes of workspace.
  *
  * With a side that is no power of two these entry points are the way to run the layer, not a baseline: they run
- * pruned transforms as contractions with the kept columns of the DFT matrix around the mode CGEMM (three launches in
- * 1-D, five in 2-D) inside the same workspace; batches so small that whole 128-mode tiles of spectrum do not fit it
- * (fewer than 128 points) keep the five stages with direct sums.
+ * pruned transforms around the mode CGEMM (three launches in 1-D, five in 2-D) inside the same workspace, along that side
+ * as contractions with the kept columns of the DFT matrix, along a side that is a power of two by butterflies.  Calls for
+ * which this does not fit the workspace keep the five stages with direct sums.  In complex elements it takes
+ *   ceil(B K1 K / 128) 128 (C_in + C_out) + B N1 K max(C_in, C_out)        (1-D: K1 = 1, without the second term)
+ * where K is K2, or what K2 is rounded up to by the row kernels of a last axis that is a power of two; the workspace
+ * has B (C_in + C_out) (N1 N2 + K1 K2).  So small batches do not fit, and grids with unequal channel counts that keep
+ * nearly all modes of the last axis.
  */
 tfno_status tfno_spectral_conv1d_staged(const void *x, const void *W, void *y,
                                         int B, int C_in, int C_out, int N, int K, void *stream);

@@ -49,6 +49,8 @@ hipError_t launch(int dir, int N1, const Cols &a, hipStream_t s)
 }
 }  // namespace
 
+// (1024 rows of 16 columns would take 131 KB of LDS: one workgroup per CU and nothing beside it to cover its load and store
+// phases; fewer columns touch parts of lines.  Not built; such columns run the radix-2 transform.)
 bool colfft_supported(int N1, int K1)
 {
     return (N1 == 64 || N1 == 128 || N1 == 256 || N1 == 512) && K1 >= 1 && K1 <= 8 * stage_a_points(N1) && K1 <= N1;

@@ -5,8 +5,8 @@
 //   k_cgemm_modes (fused2d_kernel.h)  Yh[b, o, k] = sum_c Xh[b, c, k] W[c, o] / N         (BF16x3 or FP32 MFMA)
 //   k_inv1d   zero-padded, input-pruned inverse Yh[b, o, k] -> y[b, o, :]                  (reads K, writes N)
 //
-// The spectra are stored mode-tile major over the joint mode index m = b K + k ([m / 128][channel][m % 128]), the
-// layout the mode CGEMM streams.  Only the truncated spectra cross global memory: 2 K / N of the tensor bytes
+// The spectra are stored mode-tile major over the joint mode index m = b Mp + k ([m / 128][channel][m % 128];
+// Mp: the kept modes rounded up to 8, or all K), the layout the mode CGEMM streams.  Only the truncated spectra cross global memory: 2 K / N of the tensor bytes
 // extra, against the fused kernel's none; in exchange the transforms run at high occupancy and the contraction
 // runs on the matrix pipe alone, which wins where the fused kernel is bound by its FP32 contraction.
 //

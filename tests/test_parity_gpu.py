@@ -752,6 +752,47 @@ def test_entry_points_replay_from_a_hip_graph(gpu):
         assert torch.equal(torch.view_as_real(y2), torch.view_as_real(want2))
 
 
+def test_general_layers_replay_from_a_hip_graph(gpu):
+    """The same for odd lengths, odd and mixed grids, the column kernels and the per-mode layers: captured after one eager
+    call each, replayed three times with eager work between, results the same bits."""
+    torch, binding = gpu
+    say("[case] HIP graph capture of odd lengths, mixed grids, column kernels, per-mode layers")
+    layers = []
+    for name, B, Ci, Co, dims, K in (("spectral_conv1d_auto", 9, 24, 40, (1000,), (50,)), ("spectral_conv2d_rect_staged", 2, 5, 6, (85, 90), (12, 9)),
+                                     ("spectral_conv2d_rect_staged", 2, 5, 6, (85, 64), (12, 9)), ("spectral_conv2d_rect_staged", 2, 5, 6, (30, 512), (12, 40)),
+                                     ("spectral_conv2d_rect_staged", 2, 5, 6, (128, 25), (12, 9)), ("spectral_conv2d_rect_staged", 2, 5, 6, (1024, 9), (12, 9)),
+                                     ("spectral_conv2d_strips", 2, 5, 6, (512, 64), (12, 9)), ("spectral_conv1d_permode", 6, 5, 6, (256,), (121,)),
+                                     ("spectral_conv1d_permode", 64, 20, 70, (256,), (100,))):
+        per_mode = name.endswith("permode")
+        x = torch.from_numpy(inputs.make_x(13, B, Ci, dims)).cuda()
+        W = torch.from_numpy(inputs.make_W(13, Ci, Co * K[0] if per_mode else Co)).cuda()
+        y = torch.zeros((B, Co) + dims, dtype=torch.complex64, device="cuda")
+        layers.append((getattr(binding, name), x, W.reshape(Ci, Co, -1) if per_mode else W, y, () if per_mode else K))
+    for _ in range(2):                                      # (the workspace reaches its largest size in the first round)
+        for fn, x, W, y, K in layers:
+            fn(x, W, y, *K)
+    torch.cuda.synchronize()
+    want = [y.clone() for _, _, _, y, _ in layers]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            for fn, x, W, y, K in layers:
+                fn(x, W, y, *K)
+    torch.cuda.current_stream().wait_stream(side)
+    for _ in range(3):
+        for _, _, _, y, _ in layers:
+            y.zero_()
+        layers[0][0](layers[0][1], layers[0][2], layers[0][3], *layers[0][4])
+        layers[0][3].zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for (_, _, _, y, _), w in zip(layers, want):
+            assert torch.equal(torch.view_as_real(y), torch.view_as_real(w))
+
+
 # real-valued layer (B, C_in, C_out, N, K): every N of the fused kernel, ragged channels, K = N/2
 REAL_1D = [(4, 16, 16, 64, 16), (3, 5, 7, 64, 8), (2, 33, 40, 64, 32), (3, 9, 70, 128, 32), (2, 37, 17, 128, 64),
            (64, 64, 64, 256, 64), (5, 19, 130, 256, 32), (2, 40, 33, 256, 16), (3, 24, 96, 256, 128), (2, 17, 9, 512, 32),
