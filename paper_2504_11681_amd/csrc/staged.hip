@@ -30,10 +30,19 @@ k_staged_fft(const c64 *__restrict__ in, c64 *__restrict__ out, int N, int log2N
              long long num_pencils, long long inner_count, long long in_outer_stride,
              long long out_outer_stride, long long elem_stride, int n_in, int n_out, float scale, int spec_C, long long spec_M)
 {
+    // (SPEC: fewer than 2^31 pencils, so that 32-bit divisions do)
     auto spec = [&](long long q, int n) __attribute__((always_inline)) {
-        const long long img = q / inner_count, b = img / spec_C;
-        const long long m = b * spec_M + n * inner_count + (q - img * inner_count);
-        return ((m >> 7) * spec_C + (img - b * spec_C)) * 128 + (m & 127);
+        const unsigned cols = (unsigned)inner_count, img = (unsigned)q / cols, b = img / (unsigned)spec_C;
+        const long long m = b * spec_M + (long long)n * cols + ((unsigned)q - img * cols);
+        return ((m >> 7) * spec_C + (img - b * (unsigned)spec_C)) * 128 + (m & 127);
+    };
+    auto strided = [&](long long q, int n, long long outer) __attribute__((always_inline)) {
+        if constexpr (SPEC) {
+            const unsigned cols = (unsigned)inner_count, img = (unsigned)q / cols;
+            return img * outer + ((unsigned)q - img * cols) + (long long)n * cols;
+        } else {
+            return (q / inner_count) * outer + (q % inner_count) + n * elem_stride;
+        }
     };
     extern __shared__ float2 lds[];
     c64 *buf0 = lds;                  // [PC][N]
@@ -60,9 +69,7 @@ k_staged_fft(const c64 *__restrict__ in, c64 *__restrict__ out, int N, int log2N
             long long q = q0 + j;
             if (q < num_pencils) {
                 if constexpr (SPEC && DIR > 0) buf0[j * N + n] = n < n_in ? in[spec(q, n)] : make_float2(0.f, 0.f);
-                else
-                    buf0[j * N + n] = n < n_in ? in[(q / inner_count) * in_outer_stride + (q % inner_count) + n * elem_stride]
-                                               : make_float2(0.f, 0.f);
+                else buf0[j * N + n] = n < n_in ? in[strided(q, n, in_outer_stride)] : make_float2(0.f, 0.f);
             }
         }
     }
@@ -102,9 +109,7 @@ k_staged_fft(const c64 *__restrict__ in, c64 *__restrict__ out, int N, int log2N
             if (q < num_pencils && n < n_out) {
                 c64 v = src[j * N + n];
                 if constexpr (SPEC && DIR < 0) out[spec(q, n)] = make_float2(v.x * scale, v.y * scale);
-                else
-                    out[(q / inner_count) * out_outer_stride + (q % inner_count) + n * elem_stride] =
-                        make_float2(v.x * scale, v.y * scale);
+                else out[strided(q, n, out_outer_stride)] = make_float2(v.x * scale, v.y * scale);
             }
         }
     }
@@ -248,6 +253,7 @@ hipError_t launch_axis_fft_spec(int dir, const c64 *in, c64 *out, int N, int K, 
     if (e != hipSuccess) return e;
     if (images <= 0) return hipSuccess;
     const long long pencils = images * cols;
+    if (pencils > 0x7fffffffLL) return hipErrorInvalidValue;
     int PC = N >= 4096 ? 1 : N > 256 ? 4096 / N : 16;       // (the columns of a workgroup may belong to several images)
     while (pencils / PC >= (1 << 24) - 1 && PC * N <= 2048) PC <<= 1;          // (a launch has fewer than 2^32 threads)
     while (pencils / PC < 512 && PC > 1) PC >>= 1;          // (few columns: two workgroups per CU before wide accesses)
