@@ -21,11 +21,13 @@ hipError_t cgemm_modes_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, in
                               hipStream_t s, bool all_products)
 {
     // The direct kernel up to two workgroups per CU (at 512 of them 13.4 against 15.1 us with 64 channels and 20 against 27 us
-    // with 128; at 800 and 1024 it loses, 23 against 18 us and 37 against 29 us), and for up to 32 outputs, where the others
+    // with 128; at 800 and 1024 it loses, 23 against 18 us and 37 against 29 us), one per CU with more than 128 channels, whose
+    // weights every wave splits again (whole layers, 256 points, 128 modes, 384 -> 64 channels, 160 and 280 workgroups: 50.1
+    // against 69.9 us and 84.4 against 82.2 us), and for up to 32 outputs, where the others
     // would contract half a slab of padding (1024 tiles, C 64 -> 24: 22 against 25 us; 2048 tiles, C 32: 25 against 31 us).
-    // (Layers of up to 32 outputs were measured over 1 to 512 channels and up to 2048 tiles: none slower than with the others.)
+    // (Up to 32 outputs: measured over 1 to 512 channels and up to 2048 tiles, 1.2 to 1.6 times the others' speed.)
     // A tile is a workgroup there, and a launch has fewer than 2^32 threads.
-    if (!contraction_forced_f32() && (C_out <= 32 || tiles * ((C_out + 31) / 32) <= 512) && tiles < (1LL << 24)) {
+    if (!contraction_forced_f32() && (C_out <= 32 || tiles * ((C_out + 31) / 32) <= (C_in <= 128 ? 512 : 256)) && tiles < (1LL << 24)) {
         const dim3 gd((unsigned)tiles, (unsigned)((C_out + 31) / 32));
         if (C_in <= 16 && all_products) hipLaunchKernelGGL((k_cgemm_modes_direct<2, 8>), gd, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, scale);
         else if (C_in <= 16) hipLaunchKernelGGL((k_cgemm_modes_direct<2, 6>), gd, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, scale);

@@ -121,6 +121,7 @@ PRUNED_1D = [(4, 16, 16, 64, 16), (3, 5, 7, 64, 64), (2, 33, 40, 64, 32), (3, 9,
              # blocks, either side of both limits, and each of the kernels past them
              (9, 8, 33, 256, 64), (9, 9, 31, 256, 64), (2, 17, 32, 128, 64), (3, 65, 40, 256, 128), (2, 129, 3, 256, 16),
              (260, 4, 32, 256, 256), (256, 33, 64, 256, 128), (257, 33, 64, 256, 128), (300, 20, 40, 256, 128), (260, 130, 40, 256, 128),
+             (128, 129, 64, 256, 128), (129, 129, 64, 256, 128), (129, 128, 64, 256, 128),
              # fewer modes than the kernel's: cut spectra with several sweeps per workgroup, either side of the rule that
              # keeps all columns of a long pencil
              (600, 20, 40, 256, 100), (300, 17, 33, 1024, 100), (150, 9, 30, 2048, 150), (2, 5, 6, 2048, 448),
