@@ -48,6 +48,9 @@ __device__ __forceinline__ c64 load_nt(const c64 *p)
     return make_float2(t.x, t.y);
 }
 
+// Four floats in one access of tensors that are aligned to 8 bytes.
+typedef float tfno_vf4 __attribute__((ext_vector_type(4), aligned(8)));
+
 // Workgroup ids are dealt round-robin to the 8 XCDs (id % 8).  This maps a launch index to a work item so that the
 // workgroups resident on one XCD own a CONTIGUOUS range of items instead of every eighth one.  With items that are
 // 0.5-1 MiB apart in memory (batch rows, images), every eighth item shares the address bits that select the

@@ -6,6 +6,8 @@
 //                        feeds retained modes, Sec. 3.3 "FFT pruning")
 //  dft_prune_in<T,Q>     T-point DFT of an input whose bins Q..T-1 are zero (input pruning: the inverse
 //                        transform of a zero-padded spectrum, Sec. 3.3)
+//  dft_prune_out_sym<T,Q>, dft_prune_in_sym<T,Q>   the same for the 2 Q bins -Q..Q-1
+//  real_dft16, hermitian_dft16   16-point DFT of real values (bins 0..8), and its mirror: real results from bins 0..8
 // DIR = -1: exp(-2 pi i k n / L) (forward);  DIR = +1: inverse, unscaled.
 #pragma once
 #include "common.h"
@@ -200,5 +202,115 @@ TFNO_HD void dft_prune_in(const c64 *in, Emit &&emit)
         });
     });
 }
+
+// Both pruned networks for the bins q = -Q..Q-1 (2 Q | T), slot r < 2 Q holding bin r or, from Q on, r - 2 Q: with the 2 Q-point
+// transforms of the decimated input only the twiddle exponents of the upper slots differ.
+template <int T, int Q, int DIR, class In>
+TFNO_HD void dft_prune_out_sym(In &&in, c64 *out)
+{
+    constexpr int M = 2 * Q, S = T / M;
+    static_for<0, S>([&](auto t1c) {
+        constexpr int t1 = decltype(t1c)::value;
+        c64 g[M], F[M];
+        static_for<0, M>([&](auto t2c) {
+            constexpr int t2 = decltype(t2c)::value;
+            g[t2] = in(std::integral_constant<int, t1 + S * t2>{});
+        });
+        RegFFT<M, DIR, 1>::run(g, F);
+        static_for<0, M>([&](auto rc) {
+            constexpr int r = decltype(rc)::value, q = r < Q ? r : r - M;
+            if constexpr (t1 == 0) out[r] = F[r];
+            else out[r] = mac_tw<T, DIR, t1 * q>(out[r], F[r]);
+        });
+    });
+}
+
+template <int T, int Q, int DIR, class Emit>
+TFNO_HD void dft_prune_in_sym(const c64 *in, Emit &&emit)
+{
+    constexpr int M = 2 * Q, S = T / M;
+    static_for<0, S>([&](auto t1c) {
+        constexpr int t1 = decltype(t1c)::value;
+        c64 g[M], G[M];
+        static_for<0, M>([&](auto rc) {
+            constexpr int r = decltype(rc)::value, q = r < Q ? r : r - M;
+            g[r] = mul_tw<T, DIR, t1 * q>(in[r]);
+        });
+        RegFFT<M, DIR, 1>::run(g, G);
+        static_for<0, M>([&](auto t2c) {
+            constexpr int t2 = decltype(t2c)::value;
+            emit(std::integral_constant<int, t1 + S * t2>{}, G[t2]);
+        });
+    });
+}
+
+// Real decimation in time: a[i * STRIDE], i < L, are real -> bins 0..L/2 (the others are their conjugates; bins 0 and L/2 are
+// real).  Its last level has radix 2 over pairs (x[i], x[i + L/2]) of the whole transform, so it starts from the sums and
+// differences of those: s[i], d[i], i < LT/2, LT the whole length.
+template <int L, int STRIDE>
+struct RealFFT {
+    TFNO_HD static void run(const float *s, const float *d, c64 *z)
+    {
+        c64 e[L / 4 + 1], o[L / 4 + 1];
+        RealFFT<L / 2, 2 * STRIDE>::run(s, d, e);
+        RealFFT<L / 2, 2 * STRIDE>::run(s + STRIDE, d + STRIDE, o);
+        z[0] = make_float2(e[0].x + o[0].x, 0.f);
+        z[L / 2] = make_float2(e[0].x - o[0].x, 0.f);
+        static_for<1, L / 4>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            // (both results as sums of their own: the difference as 2 e - lo, two instructions less, doubles its rounding error)
+            constexpr int m = k * (32 / L);
+            constexpr float c = cos32(m), s1 = sin32(m);
+            z[k] = make_float2(fmaf(o[k].y, s1, fmaf(o[k].x, c, e[k].x)), fmaf(-o[k].x, s1, fmaf(o[k].y, c, e[k].y)));
+            z[L / 2 - k] = make_float2(fmaf(-o[k].y, s1, fmaf(-o[k].x, c, e[k].x)), -fmaf(o[k].x, s1, fmaf(-o[k].y, c, e[k].y)));
+        });
+        z[L / 4] = make_float2(e[L / 4].x, -o[L / 4].x);
+    }
+};
+template <int STRIDE>
+struct RealFFT<2, STRIDE> {
+    TFNO_HD static void run(const float *s, const float *d, c64 *z)
+    {
+        z[0] = make_float2(s[0], 0.f);
+        z[1] = make_float2(d[0], 0.f);
+    }
+};
+// First level of the real 16-point transform (afterwards v is dead and can be refilled), and the rest of it: 60 additions and
+// multiply-adds in all against 168 of the complex network.
+TFNO_HD void real_first_level16(const float *v, float *s, float *d)
+{
+    static_for<0, 8>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        s[i] = v[i] + v[i + 8];
+        d[i] = v[i] - v[i + 8];
+    });
+}
+TFNO_HD void real_dft16(const float *s, const float *d, c64 *z) { RealFFT<16, 1>::run(s, d, z); }
+
+// Mirror image: out[j] = h0 + (-1)^j hn + Re sum_{0 < c < L/2} h[c] exp(2 pi i c j / L), j < L; out[j * STRIDE].
+template <int L, int STRIDE>
+struct HermitianFFT {
+    TFNO_HD static void run(float h0, float hn, const c64 *h, float *out)
+    {
+        c64 a[L / 4 + 1], b[L / 4 + 1];
+        static_for<1, L / 4>([&](auto cc) {
+            constexpr int c = decltype(cc)::value;
+            const c64 u = h[c], v = h[L / 2 - c];
+            a[c] = make_float2(u.x + v.x, u.y - v.y);
+            b[c] = mul_tw<L, +1, c>(make_float2(u.x - v.x, u.y + v.y));
+        });
+        HermitianFFT<L / 2, 2 * STRIDE>::run(h0 + hn, h[L / 4].x, a, out);
+        HermitianFFT<L / 2, 2 * STRIDE>::run(h0 - hn, -h[L / 4].y, b, out + STRIDE);
+    }
+};
+template <int STRIDE>
+struct HermitianFFT<2, STRIDE> {
+    TFNO_HD static void run(float h0, float hn, const c64 *, float *out)
+    {
+        out[0] = h0 + hn;
+        out[STRIDE] = h0 - hn;
+    }
+};
+TFNO_HD void hermitian_dft16(float h0, float h8, const c64 *h, float *out) { HermitianFFT<16, 1>::run(h0, h8, h, out); }
 
 }  // namespace tfno

@@ -910,6 +910,28 @@ def test_fno2d_real_layer(gpu, oracle_mod, shape):
     assert rel <= REL_L2 and mx <= MAX_ABS
 
 
+# Row stage of real images: every number of lanes per row (N2 / 16) with every number of bins per column (K2 / 16), one mode,
+# the last mode, and one to many images per batch; tensors that are aligned to 8 bytes only (16-byte accesses in the kernels).
+@pytest.mark.parametrize("N1,N2", [(64, 64), (64, 128), (128, 256), (256, 64), (256, 256)])
+def test_fno2d_rows_of_every_width(gpu, oracle_mod, N1, N2):
+    torch, binding = gpu
+    for M2 in sorted({1, 7, 8, 9, 16, 17, min(64, N2 // 2)}):
+        for shift in (0, 2):
+            B, Ci, Co, M1 = 2, 3, 5, 5 + M2 % 4
+            say(f"[case] fno2d rows {(N1, N2, M1, M2, shift)}")
+            x = np.ascontiguousarray(inputs.make_x(1350 + N1 + M2, B, Ci, (N1, N2)).real)
+            W = np.ascontiguousarray(inputs.make_W(1350 + N2 + M2, Ci, Co * 2 * M1 * M2).reshape(Ci, Co, 2 * M1, M2))
+            want, _ = oracle_mod.fno2d_real(x, W)
+            xd = torch.empty(x.size + 4, dtype=torch.float32, device="cuda")[shift:shift + x.size].view(B, Ci, N1, N2)
+            xd.copy_(torch.from_numpy(x))
+            whole = torch.full((want.size + 8,), float("nan"), dtype=torch.float32, device="cuda")
+            yd = whole[shift:shift + want.size].view(B, Co, N1, N2)
+            binding.fno2d_real(xd, torch.from_numpy(W).cuda(), yd)
+            torch.cuda.synchronize()
+            close(yd.cpu().numpy().astype(np.float64), want, ("fno2d rows", N1, N2, M1, M2, shift))
+            assert bool(torch.isnan(whole[:shift]).all()) and bool(torch.isnan(whole[shift + want.size:]).all())
+
+
 # the 1-D FNO layer on real fields (B, C_in, C_out, N, M)
 FNO_1D = [(4, 16, 16, 64, 16), (3, 5, 7, 64, 12), (9, 33, 40, 128, 20), (17, 6, 18, 256, 128), (2, 20, 30, 1024, 64),
           (11, 13, 17, 1024, 100), (2, 3, 3, 128, 1), (8, 3, 2, 256, 33)]
