@@ -6,14 +6,15 @@
 
 namespace tfno {
 
-template <int BT, int OT>
+template <int BT, int OT, int KS>
 static void launch_f32(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, long long B, int Mp, int Ma, int Mc, float scale,
                        hipStream_t s)
 {
     const unsigned long long threads = (unsigned long long)((B + BT - 1) / BT) * Mc;
     const unsigned slabs = (unsigned)((C_out + OT - 1) / OT);
-    const dim3 grid((unsigned)((threads + 255) / 256 * slabs));
-    auto run = Mc > Ma ? &k_cgemm_permode<BT, OT, true> : &k_cgemm_permode<BT, OT, false>;
+    constexpr unsigned RESULTS = 256 / KS;
+    const dim3 grid((unsigned)((threads + RESULTS - 1) / RESULTS * slabs));
+    auto run = Mc > Ma ? &k_cgemm_permode<BT, OT, true, KS> : &k_cgemm_permode<BT, OT, false, KS>;
     hipLaunchKernelGGL(run, grid, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, slabs);
 }
 
@@ -42,10 +43,15 @@ hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, 
     const int Mc = zeros ? Mp : Ma;
     // Batch elements x outputs per thread: more reuse of what is loaded where that still gives every SIMD a wave.
     auto waves = [&](int bt, int ot) { return (B + bt - 1) / bt * Ma * ((C_out + ot - 1) / ot) / 64; };
-    if (waves(8, 8) >= 1024) launch_f32<8, 8>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
-    else if (waves(4, 4) >= 1024) launch_f32<4, 4>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
-    else if (waves(2, 2) >= 256) launch_f32<2, 2>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
-    else launch_f32<1, 1>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
+    if (waves(8, 8) >= 1024) launch_f32<8, 8, 1>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
+    else if (waves(4, 4) >= 1024) launch_f32<4, 4, 1>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
+    else if (waves(2, 2) >= 256) {
+        if (C_in > 8) launch_f32<2, 2, 4>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);     // more than one block of channels
+        else launch_f32<2, 2, 1>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
+    } else {
+        if (C_in > 16) launch_f32<1, 1, 4>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
+        else launch_f32<1, 1, 1>(Xh, W, Yh, C_in, C_out, B, Mp, Ma, Mc, scale, s);
+    }
     return hipGetLastError();
 }
 

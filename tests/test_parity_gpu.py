@@ -932,6 +932,22 @@ def test_fno2d_rows_of_every_width(gpu, oracle_mod, N1, N2):
             assert bool(torch.isnan(whole[:shift]).all()) and bool(torch.isnan(whole[shift + want.size:]).all())
 
 
+# Channel counts around the blocks of the per-mode FP32 kernel (16 with one result per thread, 8 with four; four waves share a
+# result's blocks): below one block, one to five blocks, every remainder's halves, batches that leave the last workgroup ragged.
+@pytest.mark.parametrize("B,Co,M", [(3, 5, 9), (5, 33, 57)], ids=["one", "four"])
+def test_permode_channel_blocks(gpu, oracle_mod, B, Co, M):
+    torch, binding = gpu
+    for Ci in (1, 7, 8, 9, 15, 16, 17, 23, 24, 31, 32, 33, 47, 64, 65, 79, 130):
+        say(f"[case] permode channel blocks {(B, Ci, Co, M)}")
+        x = np.ascontiguousarray(inputs.make_x(1370 + Ci, B, Ci, (128,)).real)
+        W = np.ascontiguousarray(inputs.make_W(1370 + Ci, Ci, Co * M).reshape(Ci, Co, M))
+        want, _ = oracle_mod.fno1d_real(x, W)
+        yd = torch.full((B, Co, 128), float("nan"), dtype=torch.float32, device="cuda")
+        binding.fno1d_real(torch.from_numpy(x).cuda(), torch.from_numpy(W).cuda(), yd)
+        torch.cuda.synchronize()
+        close(yd.cpu().numpy().astype(np.float64), want, ("permode channel blocks", B, Ci, Co, M))
+
+
 # the 1-D FNO layer on real fields (B, C_in, C_out, N, M)
 FNO_1D = [(4, 16, 16, 64, 16), (3, 5, 7, 64, 12), (9, 33, 40, 128, 20), (17, 6, 18, 256, 128), (2, 20, 30, 1024, 64),
           (11, 13, 17, 1024, 100), (2, 3, 3, 128, 1), (8, 3, 2, 256, 33)]
