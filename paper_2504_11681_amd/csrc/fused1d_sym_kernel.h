@@ -58,10 +58,13 @@ __device__ __forceinline__ float sym_quad_perm(float v)
 
 // EVEN: C_in is a multiple of 8 and C_out a multiple of 128 (no masks).  DEEP: the number of 8-channel blocks
 // is even and at least four; the k-loop then keeps two blocks of loads in flight per wave.
-// REAL: the real-valued layer.  a.x and a.y point to float32 tensors (strides in floats); the forward transform of
-// a real pencil is the complex one with a zero imaginary part, whose first K bins are the R2C bins; the C2R inverse of
-// the zero-padded half spectrum is (2/N) Re( sum_k Y'[k] e^(+2 pi i k n / N) ) with Y'[0] = Y[0]/2, so bin 0 is halved
-// on its way into the operand tile, the caller passes scale = 2/N, and only real parts are stored.
+// REAL: the real-valued layer.  a.x and a.y point to float32 tensors (strides in floats); the first K bins of a real pencil
+// are the R2C bins; the C2R inverse of the zero-padded half spectrum is (2/N) Re( sum_k Y'[k] e^(+2 pi i k n / N) ) with
+// Y'[0] = Y[0]/2, so bin 0 is halved on its way into the operand tile, the caller passes scale = 2/N, and only real parts are
+// stored.  The 16-point transforms of the rows are real ones: forward, columns 9..15 are the conjugates of 7..1 before the
+// twiddle; inverse, columns c and 16 - c are folded into one since only the real part of their sum counts.  Bound by vector
+// instructions and LDS (each two thirds of the time, eight waves per CU); B 256, 128 -> 128 channels, 128 modes, complex row networks on
+// real values and these: 28.1 and 26.1 million vector instructions, 75.9 and 74.1 us; 64 modes 69.2 and 66.9 us.
 template <int K, bool EVEN, bool DEEP, bool REAL = false>
 __global__ void __launch_bounds__(512)
 k_fused1d_sym(Fused1dArgs a)
@@ -104,11 +107,12 @@ k_fused1d_sym(Fused1dArgs a)
 #pragma unroll
         for (int r = 0; r < 16; ++r) { acc_re[i][r] = 0.f; acc_im[i][r] = 0.f; }
 
-    c64 va[16], vb[16];         // the next two pencils of this wave: block b lives in buffer b & 1
+    using VT = std::conditional_t<REAL, float, c64>;
+    VT va[16], vb[16];          // the next two pencils of this wave: block b lives in buffer b & 1
     c64 wraw[4];                // W[c0 + 4g + d][o_lane], d < 4, of the next block
     uintx4 a_re[3], a_im[3];    // split A operands of the current block
 
-    auto load_pencil = [&](c64 *v, int c0) __attribute__((always_inline)) {
+    auto load_pencil = [&](VT *v, int c0) __attribute__((always_inline)) {
         const int c = c0 + wave;
         if constexpr (REAL) {
             const bool ok = EVEN || c < a.C_in;
@@ -116,7 +120,7 @@ k_fused1d_sym(Fused1dArgs a)
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 const float val = __builtin_nontemporal_load(src + 64 * j);
-                v[j] = make_float2(ok ? val : 0.f, 0.f);
+                v[j] = ok ? val : 0.f;
             }
         } else if constexpr (EVEN) {
             const c64 *src = xb + (long long)c * a.x_chan_stride + p;
@@ -162,26 +166,45 @@ k_fused1d_sym(Fused1dArgs a)
     // registers (after the patch writes): two blocks of loads per wave, 128 KB per CU, are then in flight, which
     // the loaded HBM latency needs; one block (64 KB) leaves the k-loop waiting for memory.
     // REFILL, not DEEP: v is reloaded with the next block right after the first butterfly level.
-    auto row_stage = [&](c64 *v, int buf, auto refill, int refill_c0, auto &&hook) __attribute__((always_inline)) {
+    auto row_stage = [&](VT *v, int buf, auto refill, int refill_c0, auto &&hook) __attribute__((always_inline)) {
         constexpr bool REFILL = decltype(refill)::value;
         hook(std::integral_constant<int, 0>{});
         {
-            c64 ea[8], eb[8], za[8], zo[8];
-            dif_first_level<16, -1>(v, ea, eb);
-            if constexpr (REFILL && !DEEP) {
-                __builtin_amdgcn_sched_barrier(0);
-                load_pencil(v, refill_c0);
-                __builtin_amdgcn_sched_barrier(0);
+            c64 za[8], zo[8];
+            if constexpr (REAL) {
+                float vs[8], vd[8];
+                c64 z[9];
+                real_first_level16(v, vs, vd);
+                if constexpr (REFILL && !DEEP) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_pencil(v, refill_c0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                real_dft16(vs, vd, z);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    za[k] = k <= 4 ? z[2 * k] : make_float2(z[16 - 2 * k].x, -z[16 - 2 * k].y);
+                    zo[k] = k < 4 ? z[2 * k + 1] : make_float2(z[15 - 2 * k].x, -z[15 - 2 * k].y);
+                }
+            } else {
+                c64 ea[8], eb[8];
+                dif_first_level<16, -1>(v, ea, eb);
+                if constexpr (REFILL && !DEEP) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_pencil(v, refill_c0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                RegFFT<8, -1, 1>::run(ea, za);
+                RegFFT<8, -1, 1>::run(eb, zo);
             }
-            RegFFT<8, -1, 1>::run(ea, za);
-            RegFFT<8, -1, 1>::run(eb, zo);
             hook(std::integral_constant<int, 10>{});
             wave_sync();                                    // the previous pencil's patch reads are done
             hook(std::integral_constant<int, 1>{});
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const int c0 = 2 * k, c1 = 2 * k + 1;       // z[2k] = za[k], z[2k+1] = zo[k]
-                const c64 t0 = c0 == 0 ? za[0] : cmul(za[k], TW[c0 * 64 + p]);
+                const c64 w0 = TW[c0 * 64 + p];
+                const c64 t0 = c0 == 0 ? za[0] : REAL && c0 == 8 ? make_float2(za[4].x * w0.x, za[4].x * w0.y) : cmul(za[k], w0);
                 const c64 t1 = cmul(zo[k], TW[c1 * 64 + p]);
                 patch[c0 * 64 + (p ^ (4 * (c0 & 7)))] = t0;
                 patch[c1 * 64 + (p ^ (4 * (c1 & 7)))] = t1;
@@ -269,8 +292,9 @@ k_fused1d_sym(Fused1dArgs a)
     // together after the barrier, so without the pattern the matrix pipe runs while the vector ALU idles and vice
     // versa.  (Contraction first: it does not depend on the loads in flight, so the row stage, which starts by
     // waiting for them, still meets them as late as possible.)
+    constexpr int P0 = REAL ? 1 : 2;                        // products beside the first stretch (a real one is half as long)
     auto no_hook = [](auto) __attribute__((always_inline)) {};
-    auto body = [&](int it, c64 *v, auto refill) __attribute__((always_inline)) {
+    auto body = [&](int it, VT *v, auto refill) __attribute__((always_inline)) {
         load_w((it + 1) * PPI);
         const unsigned *src = XS + (it & 1) * C::XS_BUF + (g * KT + tile0) * C::XT + nn;
         uintx4 b[TPW][3];
@@ -301,17 +325,17 @@ k_fused1d_sym(Fused1dArgs a)
                         const unsigned *q = src + t * 2 * KT * C::XT + i * C::XT;
                         b[i][t] = uintx4{q[0], q[32], q[64], q[96]};        // the four channel slots of mode nn
                     }
-                products(0, 2);
+                products(0, P0);
             } else if constexpr (R == 10) {
-                pattern(std::integral_constant<int, 4 * TPW>{}, std::integral_constant<int, 20>{});
+                pattern(std::integral_constant<int, 2 * P0 * TPW>{}, std::integral_constant<int, 20>{});
             } else if constexpr (R == 1) {
-                products(2, 3);
+                products(P0, P0 + 1);
             } else if constexpr (R == 11) {
                 pattern(std::integral_constant<int, 2 * TPW>{}, std::integral_constant<int, 20>{});
             } else if constexpr (R == 2) {
-                products(3, 6);
+                products(P0 + 1, 6);
             } else if constexpr (R == 12) {
-                pattern(std::integral_constant<int, 6 * TPW>{}, std::integral_constant<int, 18>{});
+                pattern(std::integral_constant<int, (10 - 2 * P0) * TPW>{}, std::integral_constant<int, 18>{});
             }
         });
         split_w();
@@ -388,7 +412,8 @@ k_fused1d_sym(Fused1dArgs a)
             patch[kl * 64 + ((qa + 4 * pp) ^ swz)] = val;
         });
         wave_sync();
-        c64 z[16], res[16];
+        c64 z[16];
+        VT res[16];
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
             c64 t = patch[c * 64 + (p ^ (4 * (c & 7)))];
@@ -398,13 +423,20 @@ k_fused1d_sym(Fused1dArgs a)
             }
             z[c] = t;
         }
-        RegFFT<16, +1, 1>::run(z, res);
+        if constexpr (REAL) {
+            c64 h[8];
+#pragma unroll
+            for (int c = 1; c < 8; ++c) h[c] = make_float2(z[c].x + z[16 - c].x, z[c].y - z[16 - c].y);
+            hermitian_dft16(z[0].x, z[8].x, h, res);
+        } else {
+            RegFFT<16, +1, 1>::run(z, res);
+        }
         const int o = o_base + 32 * (wave >> 1) + 8 * (r / 4) + 4 * (wave & 1) + (r % 4);
         if (EVEN || o < a.C_out) {
             if constexpr (REAL) {
                 float *dst = ybr + (long long)o * a.y_chan_stride + p;
 #pragma unroll
-                for (int j = 0; j < 16; ++j) __builtin_nontemporal_store(res[j].x, dst + 64 * j);
+                for (int j = 0; j < 16; ++j) __builtin_nontemporal_store(res[j], dst + 64 * j);
             } else {
                 c64 *dst = yb + (long long)o * a.y_chan_stride + p;
 #pragma unroll
