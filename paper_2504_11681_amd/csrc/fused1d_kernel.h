@@ -214,6 +214,16 @@ k_fused1d(Fused1dArgs a)
     const int o_lane = o_base + 32 * ot_w + (lane & 31);   // the output channel whose W this lane feeds
     const bool hi = lane >= 32;
     const int n_it = (a.C_in + PPI - 1) / PPI;
+    // ROT: the blocks of channels, and the output slabs, are taken in an order that starts elsewhere in neighbouring workgroups of an
+    // XCD.  Batch rows are a multiple of 256 KB apart, so workgroups that start together and walk their rows in the same order
+    // ask the same few memory channels all the time (B 512, 256 -> 256 channels, 128 modes 259 -> 252 us; B 256 138 -> 131 us; B 200,
+    // 100 -> 250 channels 87 -> 72 us; with neighbouring rows on one XCD instead 274 and 131 us).
+    constexpr bool ROT = C::WIDE && OT == 8;
+    const int rot = ROT ? (bb >> 3) % n_it : 0;
+    auto channel = [&](int it) __attribute__((always_inline)) {         // first channel of the block of iteration `it`
+        if constexpr (ROT) return (it + rot < n_it ? it + rot : it + rot - n_it) * PPI;
+        else return it * PPI;
+    };
 
     c64 v[P];       // the pencil slice this lane transforms next
     // W[c][o_lane] for the channels of the iteration whose MFMAs run next: all PPI of them (FP32 MFMA), or, for
@@ -421,13 +431,13 @@ k_fused1d(Fused1dArgs a)
         constexpr bool DO_A = decltype(do_a)::value, DO_LOAD = decltype(do_load)::value;
         // (scheduling fences: left alone, the compiler sinks stage A into the MFMA sequence and the pencil loads
         // behind the closing barrier, which leaves them one stage B to arrive instead of a whole contraction)
-        load_w(wv, it * PPI);
+        load_w(wv, channel(it));
         stage_b(0);
         wave_sync();
         __syncthreads();
         if constexpr (DO_A) { stage_a(); wave_sync(); }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (DO_LOAD) load_pencil((it + 2) * PPI);
+        if constexpr (DO_LOAD) load_pencil(channel(it + 2));
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (ALLT) mfma_block_wide();
         else if (has_tiles) mfma_block_wide();
@@ -459,11 +469,11 @@ k_fused1d(Fused1dArgs a)
 
     // ------------------------------------------------------------------ k-loop over input channels
     if constexpr (C::WIDE) {
-        load_pencil(0);
+        load_pencil(channel(0));
         build_twiddles();
         stage_a();
         wave_sync();
-        if (n_it > 1) load_pencil(PPI);
+        if (n_it > 1) load_pencil(channel(1));
         int it = 0;
         for (; it + 2 < n_it; ++it) wide_step(yes, yes, it);
         if (it + 1 < n_it) { wide_step(yes, no, it); ++it; }
@@ -623,7 +633,8 @@ k_fused1d(Fused1dArgs a)
         }
     } else {
         __syncthreads();   // every wave is done reading XH, which YH aliases
-        for (int ot = 0; ot < OT; ++ot) {
+        for (int slab = 0; slab < OT; ++slab) {
+            const int ot = ROT ? (slab + (bb >> 3)) % OT : slab;
             // accumulator layout of the 32x32 MFMA: register r of lane l holds
             //   row (output)  8*(r/4) + 4*(l/32) + r%4,   column (mode) l%32
             if constexpr (C::YH_TURNS) {
