@@ -1574,3 +1574,36 @@ def test_fp32_general_layers_in_a_child_process(gpu, oracle_mod, tmp_path):
                 assert np.array_equal(y.view(np.float32), default.view(np.float32)) != fits, (layer, fits)
             want = (oracle_mod.spectral_conv1d if entry == "staged1d" else oracle_mod.spectral_conv2d_rect)(x, W, *dims[len(dims) // 2:])[0]
         check(y, want, f"f32 {layer}")
+
+
+# Column kernels whose XCDs take neighbouring columns (fields past 192 MB; truncated spectra of more than 16 columns): numbers of
+# workgroups that the eight XCDs do not share evenly.  The large field is checked against float64 sums over its kept modes.
+@pytest.mark.parametrize("shape", [(1, 3, 2, 64, 90, 24, 20), (3, 1, 1, 128, 300, 10, 50), (13, 8, 1, 512, 512, 3, 5)],
+                         ids=lambda s: "B%d_%d_%d_%dx%d_K%dx%d" % s)
+def test_column_kernels_with_neighbouring_columns(gpu, oracle_mod, shape):
+    torch, binding = gpu
+    B, Ci, Co, N1, N2, K1, K2 = shape
+    say(f"[case] columns {shape}")
+    x = torch.view_as_complex(torch.randn(B, Ci, N1, N2, 2, generator=torch.Generator().manual_seed(N1 + N2)))
+    W = torch.from_numpy(inputs.make_W(1390 + N1, Ci, Co))
+    y = torch.full((B, Co, N1, N2), float("nan"), dtype=torch.complex64, device="cuda")
+    call = binding.spectral_conv2d_rect if N2 % 16 == 0 and not N2 & (N2 - 1) else binding.spectral_conv2d_rect_staged
+    call(x.cuda(), W.cuda(), y, K1, K2)
+    torch.cuda.synchronize()
+    f1 = np.exp(-2j * np.pi * np.outer(np.arange(K1), np.arange(N1)) / N1)
+    f2 = np.exp(-2j * np.pi * np.outer(np.arange(N2), np.arange(K2)) / N2)
+    X = f1 @ (x.numpy().astype(np.complex128) @ f2)                             # [B, Ci, K1, K2]
+    Y = np.tensordot(X, W.numpy().astype(np.complex128), axes=([1], [0]))       # [B, K1, K2, Co]
+    want = f1.conj().T @ np.moveaxis(Y, -1, 1) @ f2.conj().T / (N1 * N2)
+    close(y.cpu().numpy().astype(np.complex128), want, ("columns", shape))
+
+
+# The 256-output kernel takes its blocks of 32 channels and its slabs in rotated order: fewer blocks than starts, one block, a ragged
+# last one, ragged outputs.
+@pytest.mark.parametrize("Ci,Co", [(1, 129), (32, 256), (33, 160), (70, 250), (256, 256)])
+def test_rotated_channel_blocks(gpu, oracle_mod, Ci, Co):
+    B, N, K = 200, 256, 128
+    x, W = inputs.make_x(2400 + Ci, B, Ci, (N,)), inputs.make_W(2400 + Ci, Ci, Co)
+    say(f"[case] rotated blocks {(B, Ci, Co, N, K)}")
+    want, _ = oracle_mod.spectral_conv1d(x, W, K)
+    check(run_gpu(gpu, "spectral_conv1d", x, W, K), want, "256-output kernel")
