@@ -218,7 +218,10 @@ k_fused1d(Fused1dArgs a)
     // XCD.  Batch rows are a multiple of 256 KB apart, so workgroups that start together and walk their rows in the same order
     // ask the same few memory channels all the time (B 512, 256 -> 256 channels, 128 modes 259 -> 252 us; B 256 138 -> 131 us; B 200,
     // 100 -> 250 channels 87 -> 72 us; with neighbouring rows on one XCD instead 274 and 131 us).
-    constexpr bool ROT = C::WIDE && OT == 8;
+    // Also with the masked forms of 128 outputs (B 300, 130 -> 130 channels, N 128 70 -> 63 us; B 400, 50 -> 70, N 256, 100 modes 42 -> 38 us;
+    // B 100, 100 -> 100, N 1024, 32 modes 62.5 -> 60 us).  Narrower slabs, which small batches get, and real fields lose 1 - 2 %, unmasked
+    // forms 0 - 1 %.
+    constexpr bool ROT = (C::WIDE && OT == 8) || (!EVEN && MODE == 0 && !REAL && (OT == 4 || N == 1024));
     const int rot = ROT ? (bb >> 3) % n_it : 0;
     auto channel = [&](int it) __attribute__((always_inline)) {         // first channel of the block of iteration `it`
         if constexpr (ROT) return (it + rot < n_it ? it + rot : it + rot - n_it) * PPI;
@@ -452,12 +455,12 @@ k_fused1d(Fused1dArgs a)
         constexpr bool DO_B = decltype(do_b)::value, DO_A = decltype(do_a)::value, DO_LOAD = decltype(do_load)::value;
         const int cur = it & 1;
         c64 wn[NWV];
-        if constexpr (DO_B) load_w(wn, (it + 1) * PPI);
+        if constexpr (DO_B) load_w(wn, channel(it + 1));
         if constexpr (ALLT) mfma_block(cur);
         else if (has_tiles) mfma_block(cur);
         if constexpr (DO_B) { stage_b(cur ^ 1); wave_sync(); }
         if constexpr (DO_A) { stage_a(); wave_sync(); }
-        if constexpr (DO_LOAD) load_pencil((it + 3) * PPI);
+        if constexpr (DO_LOAD) load_pencil(channel(it + 3));
         if constexpr (DO_B) {
 #pragma unroll
             for (int jc = 0; jc < NWV; ++jc) wv[jc] = wn[jc];
@@ -479,18 +482,18 @@ k_fused1d(Fused1dArgs a)
         if (it + 1 < n_it) { wide_step(yes, no, it); ++it; }
         wide_step(no, no, it);
     } else if constexpr (MODE != 2) {
-        load_pencil(0);
-        load_w(wv, 0);
+        load_pencil(channel(0));
+        load_w(wv, channel(0));
         build_twiddles();
         stage_a();
         wave_sync();
-        if (n_it > 1) load_pencil(PPI);
+        if (n_it > 1) load_pencil(channel(1));
         stage_b(0);
         wave_sync();
         if (n_it > 1) {
             stage_a();
             wave_sync();
-            if (n_it > 2) load_pencil(2 * PPI);
+            if (n_it > 2) load_pencil(channel(2));
         }
         __syncthreads();
         {
