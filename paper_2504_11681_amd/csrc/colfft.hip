@@ -20,13 +20,14 @@ hipError_t launch_pq(int dir, const Cols &a, hipStream_t s)
     const unsigned groups = (unsigned)((a.N2 + 15) / 16);
     const dim3 grid((unsigned)(a.fields * groups));
     constexpr int nt = C::NT;
-    // Neighbouring columns per XCD for fields that the last-level cache does not hold, with rows of 1 KB and more (every eighth line
-    // and neighbouring ones, whole layers, us): 268 MB, 512 x 512 134.5 and 130.9, 512 x 256 118.2 and 113.1, 512 x 128 112.9 and 110.2, but
-    // 512 x 64 111 and 120; 134 MB, 512 x 512 72.0 and 73.7; 67 MB, 512 x 256 38.1 and 40.1.  The few columns of truncated spectra gain at any size
-    // (256 x 360, 24 x 24 modes 63.6 and 62.0; 128 x 300, 24 x 50 modes 51.0 and 47.0) unless they are one group of 16.
-    const bool contiguous = SPEC ? groups > 1 : a.N2 >= 128 && a.fields * C::N1 * a.N2 * (long long)sizeof(c64) > 192LL << 20;
+    // Neighbouring columns per XCD for fields that the last-level cache does not hold, with rows of 1 KB and more, in the forward
+    // kernel (whole layers, every eighth line / neighbouring ones / those in both kernels, us): 268 MB, 512 x 512 134.1, 129.5, 131.0,
+    // 512 x 256 118.0, 112.4, 113.5, 512 x 128 112.5, 108.7, 110.3, 512 MB, 512 x 512 233, 223, 219, but in both kernels 512 x 64 111 and 120; 134 MB,
+    // 512 x 512 72.0 and 73.7; 67 MB, 512 x 256 38.1 and 40.1.  The columns of truncated spectra gain in both kernels (256 x 360, 24 x 24 modes
+    // 63.8, 64.0, 62.3; 128 x 300, 24 x 50 modes 51.4, 49.9, 47.3) from a workgroup per CU on, unless they are one group of 16.
+    const bool contiguous = SPEC ? groups > 1 && a.fields * groups >= 256 : a.N2 >= 128 && a.fields * C::N1 * a.N2 * (long long)sizeof(c64) > 192LL << 20;
     if (dir < 0) hipLaunchKernelGGL((k_colfft_fwd<P, T, Q, SPEC>), grid, dim3(nt), C::LDS, s, a.in, a.out, a.N2, a.K1, groups, contiguous, a.C, a.M);
-    else hipLaunchKernelGGL((k_colfft_inv<P, T, Q, SPEC>), grid, dim3(nt), C::LDS, s, a.in, a.out, a.N2, a.K1, groups, contiguous, a.C, a.M);
+    else hipLaunchKernelGGL((k_colfft_inv<P, T, Q, SPEC>), grid, dim3(nt), C::LDS, s, a.in, a.out, a.N2, a.K1, groups, SPEC && contiguous, a.C, a.M);
     return hipGetLastError();
 }
 
