@@ -136,17 +136,10 @@ __device__ __forceinline__ void lds_tables(const Lds2d &l, int tid)
 }
 
 // ------------------------------------------------------------------------------------------------ forward
-// element offset of (channel c, mode m) of batch element b in a mode-tile-major spectrum buffer with Mp modes per
-// batch element (128 consecutive joint modes b Mp + m make a tile)
-__device__ __forceinline__ long long spec_index(long long b, int c, int C, int m, int Mp)
-{
-    const long long j = b * Mp + m;
-    return ((j >> 7) * C + c) * 128 + (j & 127);
-}
-
-// The same for the modes of one image: first tile of the batch element and the position of its mode 0 in it, once per
-// workgroup (uniform), so that a mode costs a shift, a mask and a multiply-add (with spec_index, eight modes of a lane took
-// 200 instructions of 64-bit arithmetic).
+// Element offsets of the modes m of one image (channel c of batch element b) in a mode-tile-major spectrum buffer with Mp modes per
+// batch element (128 consecutive joint modes b Mp + m make a tile): the first tile and the position of mode 0 in it once per
+// workgroup (uniform), so that a mode costs a shift, a mask and a multiply-add (in 64-bit arithmetic of its own, eight modes of a lane
+// took 200 instructions).
 struct SpecImage {
     long long base;
     int pos;
