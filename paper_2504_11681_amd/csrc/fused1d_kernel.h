@@ -213,20 +213,11 @@ k_fused1d(Fused1dArgs a)
 
     const int o_lane = o_base + 32 * ot_w + (lane & 31);   // the output channel whose W this lane feeds
     const bool hi = lane >= 32;
+    // Blocks of channels are summed in the same order everywhere: equal rows of a batch give equal bits wherever they stand.  (A start that
+    // differs between workgroups keeps them from asking for the same memory at the same time, but then a row's sum depends on its
+    // place: B 512, 256 -> 256 channels, N 256, 128 modes 245 and 240 us, B 200, 100 -> 250 channels 88 and 76, B 300, 130 -> 130, N 128 75 and 68; a
+    // different order of the output slabs alone, 244, 95 and 76.)
     const int n_it = (a.C_in + PPI - 1) / PPI;
-    // ROT: the blocks of channels, and the output slabs, are taken in an order that starts elsewhere in neighbouring workgroups of an
-    // XCD.  Batch rows are a multiple of 256 KB apart, so workgroups that start together and walk their rows in the same order
-    // ask the same few memory channels all the time (B 512, 256 -> 256 channels, 128 modes 259 -> 252 us; B 256 138 -> 131 us; B 200,
-    // 100 -> 250 channels 87 -> 72 us; with neighbouring rows on one XCD instead 274 and 131 us).
-    // Also with the masked forms of 128 outputs (B 300, 130 -> 130 channels, N 128 70 -> 63 us; B 400, 50 -> 70, N 256, 100 modes 42 -> 38 us;
-    // B 100, 100 -> 100, N 1024, 32 modes 62.5 -> 60 us).  Narrower slabs, which small batches get, and real fields lose 1 - 2 %, unmasked
-    // forms 0 - 1 %.
-    constexpr bool ROT = (C::WIDE && OT == 8) || (!EVEN && MODE == 0 && !REAL && (OT == 4 || N == 1024));
-    const int rot = ROT ? (bb >> 3) % n_it : 0;
-    auto channel = [&](int it) __attribute__((always_inline)) {         // first channel of the block of iteration `it`
-        if constexpr (ROT) return (it + rot < n_it ? it + rot : it + rot - n_it) * PPI;
-        else return it * PPI;
-    };
 
     c64 v[P];       // the pencil slice this lane transforms next
     // W[c][o_lane] for the channels of the iteration whose MFMAs run next: all PPI of them (FP32 MFMA), or, for
@@ -434,13 +425,13 @@ k_fused1d(Fused1dArgs a)
         constexpr bool DO_A = decltype(do_a)::value, DO_LOAD = decltype(do_load)::value;
         // (scheduling fences: left alone, the compiler sinks stage A into the MFMA sequence and the pencil loads
         // behind the closing barrier, which leaves them one stage B to arrive instead of a whole contraction)
-        load_w(wv, channel(it));
+        load_w(wv, it * PPI);
         stage_b(0);
         wave_sync();
         __syncthreads();
         if constexpr (DO_A) { stage_a(); wave_sync(); }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (DO_LOAD) load_pencil(channel(it + 2));
+        if constexpr (DO_LOAD) load_pencil((it + 2) * PPI);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (ALLT) mfma_block_wide();
         else if (has_tiles) mfma_block_wide();
@@ -455,12 +446,12 @@ k_fused1d(Fused1dArgs a)
         constexpr bool DO_B = decltype(do_b)::value, DO_A = decltype(do_a)::value, DO_LOAD = decltype(do_load)::value;
         const int cur = it & 1;
         c64 wn[NWV];
-        if constexpr (DO_B) load_w(wn, channel(it + 1));
+        if constexpr (DO_B) load_w(wn, (it + 1) * PPI);
         if constexpr (ALLT) mfma_block(cur);
         else if (has_tiles) mfma_block(cur);
         if constexpr (DO_B) { stage_b(cur ^ 1); wave_sync(); }
         if constexpr (DO_A) { stage_a(); wave_sync(); }
-        if constexpr (DO_LOAD) load_pencil(channel(it + 3));
+        if constexpr (DO_LOAD) load_pencil((it + 3) * PPI);
         if constexpr (DO_B) {
 #pragma unroll
             for (int jc = 0; jc < NWV; ++jc) wv[jc] = wn[jc];
@@ -472,28 +463,28 @@ k_fused1d(Fused1dArgs a)
 
     // ------------------------------------------------------------------ k-loop over input channels
     if constexpr (C::WIDE) {
-        load_pencil(channel(0));
+        load_pencil(0);
         build_twiddles();
         stage_a();
         wave_sync();
-        if (n_it > 1) load_pencil(channel(1));
+        if (n_it > 1) load_pencil(PPI);
         int it = 0;
         for (; it + 2 < n_it; ++it) wide_step(yes, yes, it);
         if (it + 1 < n_it) { wide_step(yes, no, it); ++it; }
         wide_step(no, no, it);
     } else if constexpr (MODE != 2) {
-        load_pencil(channel(0));
-        load_w(wv, channel(0));
+        load_pencil(0);
+        load_w(wv, 0);
         build_twiddles();
         stage_a();
         wave_sync();
-        if (n_it > 1) load_pencil(channel(1));
+        if (n_it > 1) load_pencil(PPI);
         stage_b(0);
         wave_sync();
         if (n_it > 1) {
             stage_a();
             wave_sync();
-            if (n_it > 2) load_pencil(channel(2));
+            if (n_it > 2) load_pencil(2 * PPI);
         }
         __syncthreads();
         {
@@ -636,8 +627,7 @@ k_fused1d(Fused1dArgs a)
         }
     } else {
         __syncthreads();   // every wave is done reading XH, which YH aliases
-        for (int slab = 0; slab < OT; ++slab) {
-            const int ot = ROT ? (slab + (bb >> 3)) % OT : slab;
+        for (int ot = 0; ot < OT; ++ot) {
             // accumulator layout of the 32x32 MFMA: register r of lane l holds
             //   row (output)  8*(r/4) + 4*(l/32) + r%4,   column (mode) l%32
             if constexpr (C::YH_TURNS) {

@@ -1598,12 +1598,38 @@ def test_column_kernels_with_neighbouring_columns(gpu, oracle_mod, shape):
     close(y.cpu().numpy().astype(np.complex128), want, ("columns", shape))
 
 
-# The 256-output kernel takes its blocks of 32 channels and its slabs in rotated order: fewer blocks than starts, one block, a ragged
-# last one, ragged outputs.
+# The 256-output kernel: one block of 32 channels, whole blocks, a ragged last one, ragged outputs.
 @pytest.mark.parametrize("Ci,Co", [(1, 129), (32, 256), (33, 160), (70, 250), (256, 256)])
-def test_rotated_channel_blocks(gpu, oracle_mod, Ci, Co):
+def test_channel_blocks_of_the_256_output_kernel(gpu, oracle_mod, Ci, Co):
     B, N, K = 200, 256, 128
     x, W = inputs.make_x(2400 + Ci, B, Ci, (N,)), inputs.make_W(2400 + Ci, Ci, Co)
-    say(f"[case] rotated blocks {(B, Ci, Co, N, K)}")
+    say(f"[case] channel blocks {(B, Ci, Co, N, K)}")
     want, _ = oracle_mod.spectral_conv1d(x, W, K)
     check(run_gpu(gpu, "spectral_conv1d", x, W, K), want, "256-output kernel")
+
+
+# Fused 1-D kernels with four and more blocks of channels, the last one ragged, and more workgroups than the eight XCDs hold at a
+# time: a batch whose rows are all equal gives the same bits in every row, and different rows agree with the oracle.
+# (B, C_in, C_out, N, K)
+MANY_BLOCKS = [
+    (300, 130, 130, 128, 64), (300, 70, 70, 256, 128), (400, 50, 70, 256, 100), (520, 130, 70, 64, 16),     # single operand tile, 128 outputs
+    (140, 70, 100, 256, 64), (140, 70, 100, 512, 64), (132, 41, 100, 1024, 32), (300, 33, 45, 1024, 64),    # double-buffered
+    (200, 100, 250, 256, 128), (200, 256, 256, 256, 128), (200, 70, 200, 256, 64),                          # 256 outputs
+]
+
+
+@pytest.mark.parametrize("shape", MANY_BLOCKS, ids=lambda s: "B%d_Ci%d_Co%d_N%d_K%d" % s)
+def test_equal_rows_give_equal_bits(gpu, oracle_mod, shape):
+    torch, binding = gpu
+    B, Ci, Co, N, K = shape
+    say(f"[case] equal rows {shape}")
+    x, W = inputs.make_x(2450 + Ci, B, Ci, (N,)), inputs.make_W(2450 + Ci, Ci, Co)
+    want, _ = oracle_mod.spectral_conv1d(x, W, K)
+    check(run_gpu(gpu, "spectral_conv1d", x, W, K), want, "different rows")
+    row = torch.from_numpy(x[7:8]).cuda()
+    y = torch.empty((B, Co, N), dtype=torch.complex64, device="cuda")
+    binding.spectral_conv1d(row.expand(B, Ci, N).contiguous(), torch.from_numpy(W).cuda(), y, K)
+    torch.cuda.synchronize()
+    close(y[0].cpu().numpy().astype(np.complex128), want[7], ("equal rows", shape))
+    bits = torch.view_as_real(y).view(torch.int32)
+    assert bool((bits == bits[:1]).all()), "rows differ"
