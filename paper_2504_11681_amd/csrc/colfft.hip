@@ -20,12 +20,16 @@ hipError_t launch_pq(int dir, const Cols &a, hipStream_t s)
     const unsigned groups = (unsigned)((a.N2 + 15) / 16);
     const dim3 grid((unsigned)(a.fields * groups));
     constexpr int nt = C::NT;
-    // Neighbouring columns per XCD for fields that the last-level cache does not hold, with rows of 1 KB and more, in the forward
-    // kernel (whole layers, every eighth line / neighbouring ones / those in both kernels, us): 268 MB, 512 x 512 134.1, 129.5, 131.0,
-    // 512 x 256 118.0, 112.4, 113.5, 512 x 128 112.5, 108.7, 110.3, 512 MB, 512 x 512 233, 223, 219, but in both kernels 512 x 64 111 and 120; 134 MB,
-    // 512 x 512 72.0 and 73.7; 67 MB, 512 x 256 38.1 and 40.1.  The columns of truncated spectra gain in both kernels (256 x 360, 24 x 24 modes
-    // 63.8, 64.0, 62.3; 128 x 300, 24 x 50 modes 51.4, 49.9, 47.3) from a workgroup per CU on, unless they are one group of 16.
-    const bool contiguous = SPEC ? groups > 1 && a.fields * groups >= 256 : a.N2 >= 128 && a.fields * C::N1 * a.N2 * (long long)sizeof(c64) > 192LL << 20;
+    // Neighbouring columns per XCD in the forward kernel for fields one and a half times the last-level cache and larger, with rows of
+    // 1 KB and more.  Whole layers, every eighth line and neighbouring ones (us), on fields that the program has just written / that no cache
+    // holds / pass after pass over the same three: 512 x 512, 268 MB 142 151 / 147 141 / 134 130, 335 MB 181 190 / 194 186 / 175 168, 403 MB
+    // 211 209 / 226 216 / 204 196, 470 MB 244 234 / 262 251 / 235 231; 512 x 256, 335 MB 171 176 / 180 175 / 163 157, 403 MB 202 195 / 212 204 / 193 185;
+    // 512 x 128, 403 MB 202 198 / 215 208 / 195 186.  Smaller fields lose where they were just written, the usual case.  (In the inverse kernel as
+    // well 512 x 512 gains another 1 - 4 % and 512 x 256 and 512 x 128 lose up to 3 %; 512 x 64 in both kernels 111 and 120.)
+    // The columns of truncated spectra gain in both kernels (256 x 360, 24 x 24 modes, 8 x 16 fields 79 77 / 83 82 / 65 62; 128 x 300, 24 x 50
+    // modes, 32 x 32 fields 304 299 / 308 300 / 277 261; 64 to 256 rows of 200, 16 x 32 modes: equal within 1 %) from a workgroup per CU on, unless
+    // they are one group of 16.
+    const bool contiguous = SPEC ? groups > 1 && a.fields * groups >= 256 : a.N2 >= 128 && a.fields * C::N1 * a.N2 * (long long)sizeof(c64) >= 384LL << 20;
     if (dir < 0) hipLaunchKernelGGL((k_colfft_fwd<P, T, Q, SPEC>), grid, dim3(nt), C::LDS, s, a.in, a.out, a.N2, a.K1, groups, contiguous, a.C, a.M);
     else hipLaunchKernelGGL((k_colfft_inv<P, T, Q, SPEC>), grid, dim3(nt), C::LDS, s, a.in, a.out, a.N2, a.K1, groups, SPEC && contiguous, a.C, a.M);
     return hipGetLastError();

@@ -1576,9 +1576,11 @@ def test_fp32_general_layers_in_a_child_process(gpu, oracle_mod, tmp_path):
         check(y, want, f"f32 {layer}")
 
 
-# Column kernels whose XCDs take neighbouring columns (fields past 192 MB; truncated spectra of more than 16 columns from 256 workgroups
-# on) with numbers of workgroups that the eight XCDs do not share evenly, and one below; against float64 sums over the kept modes.
-@pytest.mark.parametrize("shape", [(43, 3, 3, 64, 90, 9, 20), (65, 2, 1, 128, 300, 10, 50), (3, 2, 1, 128, 300, 10, 50), (13, 8, 1, 512, 512, 3, 5)],
+# Column kernels on both sides of the rules by which an XCD takes neighbouring columns: truncated spectra of more than 16 columns from 256
+# workgroups on (258, 520 and 260 of them, 258 and 260 not shared evenly by the eight XCDs, and 24), whole fields from 403 MB on (200 fields of
+# 512 x 512 points, 419 MB, and 104, 218 MB; their workgroups are always a multiple of eight); against float64 sums over the kept modes.
+@pytest.mark.parametrize("shape", [(43, 3, 3, 64, 90, 9, 20), (65, 2, 1, 128, 300, 10, 50), (3, 2, 1, 128, 300, 10, 50), (13, 8, 1, 512, 512, 3, 5),
+                                   (25, 8, 1, 512, 512, 3, 5)],
                          ids=lambda s: "B%d_%d_%d_%dx%d_K%dx%d" % s)
 def test_column_kernels_with_neighbouring_columns(gpu, oracle_mod, shape):
     torch, binding = gpu
