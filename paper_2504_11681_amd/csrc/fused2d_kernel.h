@@ -219,17 +219,24 @@ k_fwd2d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C_in, int K1_keep, 
     // workgroup id) therefore start at different passes so that together they use all channels.
     const int r_rot = (int)(blockIdx.x >> 3);
     const RowPieces<C> pieces(L.scr, tid);
-    using VT = std::conditional_t<FNO, tfno_vf4, c64>;
-    constexpr int NV = FNO ? 4 : 16;
+    // (real rows with more than 32 modes are loaded by the lanes that transform them: kernel alone, through the patch and so, 128 x 128, 1024
+    // images 25.8 and 23.7 us, 64 x 256, 256 images 9.4 and 8.7 us, larger fields equal)
+    constexpr bool PIECES = FNO && KH <= 2;
+    using VT = std::conditional_t<PIECES, tfno_vf4, std::conditional_t<FNO, float, c64>>;
+    constexpr int NV = PIECES ? 4 : 16;
     auto load_rows = [&](VT *v, int sweep) __attribute__((always_inline)) {
         const int r = (sweep / SWEEPS + r_rot) & (S - 1), s = (sweep % SWEEPS) * RPS + g;
         if (row_on) {
-            if constexpr (FNO) {
+            if constexpr (PIECES) {
                 // (s: the wave's first row here)
                 const XT *src = img + (long long)(r + S * (s - (tid & 63) / LPR + pieces.row)) * N2 + pieces.col;
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     v[j] = __builtin_nontemporal_load(reinterpret_cast<const tfno_vf4 *>(src + j * pieces.ROWS * S * N2));
+            } else if constexpr (FNO) {
+                const XT *src = img + (long long)(r + S * s) * N2 + p;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) v[j] = LPR >= 16 ? __builtin_nontemporal_load(src + LPR * j) : src[LPR * j];
             } else {
                 const XT *src = img + (long long)(r + S * s) * N2 + p;
 #pragma unroll
@@ -251,18 +258,26 @@ k_fwd2d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C_in, int K1_keep, 
         c64 *tile = L.tile + ((sweep / SWEEPS) % NBUF) * (RP * TS);
         c64 z[C::COLS];
         if constexpr (FNO) {
-            const float *flat = reinterpret_cast<const float *>(L.scr + (tid >> 6) * C::WREG) + (tid & 63) / LPR * C::FP;
-            float u[16], vs[8], vd[8];
-            wave_sync();                                    // the previous sweep's patch reads are done
+            float vs[8], vd[8];
+            if constexpr (PIECES) {
+                const float *flat = reinterpret_cast<const float *>(L.scr + (tid >> 6) * C::WREG) + (tid & 63) / LPR * C::FP;
+                float u[16];
+                wave_sync();                                // the previous sweep's patch reads are done
 #pragma unroll
-            for (int j = 0; j < 4; ++j) *pieces.at(j) = v[j];
-            wave_sync();
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (REFILL) load_rows(v, next_sweep);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int j = 0; j < 4; ++j) *pieces.at(j) = v[j];
+                wave_sync();
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (REFILL) load_rows(v, next_sweep);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) u[j] = flat[p + LPR * j];
-            real_first_level16(u, vs, vd);
+                for (int j = 0; j < 16; ++j) u[j] = flat[p + LPR * j];
+                real_first_level16(u, vs, vd);
+            } else {
+                real_first_level16(v, vs, vd);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (REFILL) load_rows(v, next_sweep);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             real_dft16(vs, vd, z);
         } else {
             c64 ea[8], eb[8], za[8], zo[8];
@@ -300,6 +315,11 @@ k_fwd2d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C_in, int K1_keep, 
         wave_sync();
         if constexpr (FNO) {
             c64 *row = tile + s * TS;
+            c64 c8[LPR];                                    // column 8, read beside the others by all lanes though one transforms it
+            if constexpr (LPR < 16) {
+#pragma unroll
+                for (int pp = 0; pp < LPR; ++pp) c8[pp] = scr[8 * LPR + pp];
+            }
             static_for<0, (LPR < 16 ? 8 / LPR : 1)>([&](auto ic) __attribute__((always_inline)) {
                 const int kl = p + LPR * decltype(ic)::value;   // kl % LPR == p
                 if (LPR < 16 || kl < 9) {
@@ -321,7 +341,7 @@ k_fwd2d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C_in, int K1_keep, 
                     c64 xo[KH];
                     dft_prune_out<LPR, KH, -1>([&](auto ppc) __attribute__((always_inline)) {
                         constexpr int pp = decltype(ppc)::value;
-                        return scr[8 * LPR + pp];
+                        return c8[pp];
                     }, xo);
 #pragma unroll
                     for (int kh = 0; kh < KH; ++kh) row[8 + 16 * kh] = xo[kh];
@@ -488,14 +508,26 @@ k_inv2d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C_out, int K1_keep,
         if (!col_on) return;
         const int r = (i + r_rot) & (S - 1);
         c64 *tile = L.tile + (i % NBUF) * (RP * TS);
-        c64 G[RPL], f[RPL];
+        auto pass_twiddle = [&](int ka, int m) __attribute__((always_inline)) {
+            const int k1 = FNO ? (ka + RPL * kb + h1) % RP + RP * m - h1 : ka + RPL * kb + RP * m;     // frequency
+            return L.twn[(r * k1) & (N1 - 1)];
+        };
+        // Real fields: all read before their first use.  The kernel's LDS holds four workgroups per CU there, so the compiler saves
+        // registers and reads, waits and multiplies one at a time (256 x 256, 64 x 64 modes, 256 images: 30.4 and 26.8 us).
+        c64 G[RPL], f[RPL], w1[FNO ? C::NACC : 1];
+        if constexpr (FNO) {
+#pragma unroll
+            for (int ka = 0; ka < RPL; ++ka)
+#pragma unroll
+                for (int m = 0; m < MREP; ++m) w1[m * RPL + ka] = pass_twiddle(ka, m);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int ka = 0; ka < RPL; ++ka) {
             c64 t = make_float2(0.f, 0.f);
 #pragma unroll
             for (int m = 0; m < MREP; ++m) {
-                const int k1 = FNO ? (ka + RPL * kb + h1) % RP + RP * m - h1 : ka + RPL * kb + RP * m;     // frequency
-                const c64 w = L.twn[(r * k1) & (N1 - 1)];
+                const c64 w = FNO ? w1[FNO ? m * RPL + ka : 0] : pass_twiddle(ka, m);
                 t = cmac(t, Y[m * RPL + ka], make_float2(w.x, -w.y));
             }
             t = quad_dft4_inv(t, q4);

@@ -915,7 +915,7 @@ def test_fno2d_real_layer(gpu, oracle_mod, shape):
 @pytest.mark.parametrize("N1,N2", [(64, 64), (64, 128), (128, 256), (256, 64), (256, 256)])
 def test_fno2d_rows_of_every_width(gpu, oracle_mod, N1, N2):
     torch, binding = gpu
-    for M2 in sorted({1, 7, 8, 9, 16, 17, min(64, N2 // 2)}):
+    for M2 in [m for m in (1, 7, 8, 9, 16, 17, 32, 33, 64) if 2 * m <= N2]:    # (more than 32: rows that skip the patch on their way in)
         for shift in (0, 2):
             B, Ci, Co, M1 = 2, 3, 5, 5 + M2 % 4
             say(f"[case] fno2d rows {(N1, N2, M1, M2, shift)}")
