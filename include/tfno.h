@@ -28,7 +28,7 @@
  *    keep it alive and unmodified until the stream has passed the call.
  *  - y must not overlap x or W (checked on address ranges: TFNO_ERR_ALIAS).
  *  - x, W and y must be aligned to 8 bytes (TFNO_ERR_ALIGN), the float32 tensors of the real-valued entry points
- *    included: complex64 elements move as 8-byte words and the real-valued kernels move pairs of floats.
+ *    included: complex64 elements move as 8-byte words, and kernels for real fields move up to four floats at a time.
  *  - Argument errors are detected on the host before anything is launched, so a
  *    failed call has no effect on y.  B == 0 is a valid empty call (TFNO_OK,
  *    nothing launched, pointers may be NULL).

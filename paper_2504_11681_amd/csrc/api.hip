@@ -70,7 +70,8 @@ bool sizes_ok(const Shape &sh, int B, int C_in, int C_out, bool any_n = false)
            (sh.dims == 1 || axis_ok(sh.N1, sh.K1, any_n));
 }
 
-// complex64 elements are read and written as 8-byte words, and the real-valued kernels move pairs of floats
+// complex64 elements are read and written as 8-byte words, and the image kernels for real fields move four floats at a time in
+// accesses that need 8-byte alignment
 bool aligned8(const void *a, const void *b, const void *c)
 {
     return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 7u) == 0;

@@ -347,20 +347,18 @@ k_fwd2d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C_in, int K1_keep, 
                     for (int kh = 0; kh < KH; ++kh) row[8 + 16 * kh] = xo[kh];
                 }
             }
-            return;
-        }
-        if constexpr (!FNO) {
+        } else {
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-            const int kl = p + LPR * i;                     // kl % LPR == p
-            c64 xo[KH];
-            dft_prune_out<LPR, KH, -1>([&](auto ppc) __attribute__((always_inline)) {
-                constexpr int pp = decltype(ppc)::value;
-                return scr[kl * LPR + (pp ^ p)];
-            }, xo);
+            for (int i = 0; i < CPL; ++i) {
+                const int kl = p + LPR * i;                     // kl % LPR == p
+                c64 xo[KH];
+                dft_prune_out<LPR, KH, -1>([&](auto ppc) __attribute__((always_inline)) {
+                    constexpr int pp = decltype(ppc)::value;
+                    return scr[kl * LPR + (pp ^ p)];
+                }, xo);
 #pragma unroll
-            for (int kh = 0; kh < KH; ++kh) tile[s * TS + kl + 16 * kh] = xo[kh];
-        }
+                for (int kh = 0; kh < KH; ++kh) tile[s * TS + kl + 16 * kh] = xo[kh];
+            }
         }
     };
     // RP-point transform of the tile columns of pass `i` (rows r + S s), accumulated with the pass twiddle
@@ -587,32 +585,30 @@ k_inv2d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C_out, int K1_keep,
             }
             const c64 t8 = scr[8 * LPR + (p ^ (8 % LPR))], w8 = L.tw[8 * LPR + p];
             hermitian_dft16(scr[p].x, fmaf(t8.x, w8.x, t8.y * w8.y), h, out);
-            return;
-        }
-        if constexpr (!FNO) {
+        } else {
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-            const int kl = p + LPR * i;
-            c64 yin[KH];
+            for (int i = 0; i < CPL; ++i) {
+                const int kl = p + LPR * i;
+                c64 yin[KH];
 #pragma unroll
-            for (int kh = 0; kh < KH; ++kh) yin[kh] = tile[s * TS + kl + 16 * kh];
-            dft_prune_in<LPR, KH, +1>(yin, [&](auto ppc, c64 val) __attribute__((always_inline)) {
-                constexpr int pp = decltype(ppc)::value;
-                scr[kl * LPR + (pp ^ p)] = val;
-            });
-        }
-        wave_sync();
-        c64 z[16];
-#pragma unroll
-        for (int kl = 0; kl < 16; ++kl) {
-            c64 t = scr[kl * LPR + (p ^ (kl % LPR))];
-            if (kl != 0) {
-                const c64 w = L.tw[kl * LPR + p];
-                t = cmul(t, make_float2(w.x, -w.y));
+                for (int kh = 0; kh < KH; ++kh) yin[kh] = tile[s * TS + kl + 16 * kh];
+                dft_prune_in<LPR, KH, +1>(yin, [&](auto ppc, c64 val) __attribute__((always_inline)) {
+                    constexpr int pp = decltype(ppc)::value;
+                    scr[kl * LPR + (pp ^ p)] = val;
+                });
             }
-            z[kl] = t;
-        }
-        RegFFT<16, +1, 1>::run(z, out);
+            wave_sync();
+            c64 z[16];
+#pragma unroll
+            for (int kl = 0; kl < 16; ++kl) {
+                c64 t = scr[kl * LPR + (p ^ (kl % LPR))];
+                if (kl != 0) {
+                    const c64 w = L.tw[kl * LPR + p];
+                    t = cmul(t, make_float2(w.x, -w.y));
+                }
+                z[kl] = t;
+            }
+            RegFFT<16, +1, 1>::run(z, out);
         }
     };
     auto store_rows = [&](const XT *out, int sweep) __attribute__((always_inline)) {
@@ -637,8 +633,8 @@ k_inv2d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C_out, int K1_keep,
             for (int j = 0; j < 16; ++j) {
                 // non-temporal only where the LPR lanes of a row write whole 128-byte lines: with narrower rows every
                 // store instruction leaves half or quarter lines, which cost up to 40 % of the kernel time when they
-                // bypass the cache that would have merged them.  (Pairing complex elements between neighbouring
-                // lanes as above, 16 bytes per lane, measured no faster for 64- and 128-point rows.)
+                // bypass the cache that would have merged them.  (Lanes that swap halves with their neighbour and
+                // write two complex elements each measured no faster for 64- and 128-point rows.)
                 if constexpr (LPR >= 16) store_nt(dst + LPR * j, out[j]);
                 else dst[LPR * j] = out[j];
             }
