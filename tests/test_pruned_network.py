@@ -82,6 +82,39 @@ def test_pruned_networks_execute_the_operation_counts_the_paper_prints(tmp_path)
     assert counts["inv_4_2"] == (8, 0) and counts["inv_4_1"] == (0, 0)
 
 
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc to compile fft_regs.h for gfx950")
+def test_real_networks_execute_the_operation_counts_that_the_source_states(tmp_path):
+    """16-point transform of real values, its mirror, and the complex network: the numbers in the comment at real_first_level16."""
+    counts = real_op_counts(tmp_path, textwrap.dedent("""
+        extern "C" __global__ void real_16(const float *in, c64 *out)
+        {
+            float v[16], s[8], d[8];
+            c64 z[9];
+            for (int i = 0; i < 16; ++i) v[i] = in[i];
+            real_first_level16(v, s, d);
+            real_dft16(s, d, z);
+            for (int i = 0; i < 9; ++i) out[i] = z[i];
+        }
+        extern "C" __global__ void hermitian_16(const c64 *in, float *out)
+        {
+            c64 h[8];
+            float o[16];
+            for (int i = 1; i < 8; ++i) h[i] = in[i];
+            hermitian_dft16(in[0].x, in[8].x, h, o);
+            for (int i = 0; i < 16; ++i) out[i] = o[i];
+        }
+        extern "C" __global__ void complex_16(const c64 *in, c64 *out)
+        {
+            c64 v[16], z[16];
+            for (int i = 0; i < 16; ++i) v[i] = in[i];
+            RegFFT<16, -1, 1>::run(v, z);
+            for (int i = 0; i < 16; ++i) out[i] = z[i];
+        }"""))
+    text = open(os.path.join(CSRC, "fft_regs.h")).read()
+    real, mirror, full = map(int, re.search(r"(\d+) additions and\n// multiply-adds in all, hermitian_dft16 (\d+), RegFFT<16> of complex values (\d+)", text).groups())
+    assert (sum(counts["real_16"]), sum(counts["hermitian_16"]), sum(counts["complex_16"])) == (real, mirror, full)
+
+
 def test_forward_kernel_writes_a_quarter_of_the_spectrum_for_64_of_256():
     """Sec. 3.3: keeping 64 of 256 bins removes 75 % of the forward transform's global writes.  The forward kernel of
     the CGEMM + iFFT variant writes exactly the buffer tfno_workspace_bytes(1, 4, ...) describes."""
