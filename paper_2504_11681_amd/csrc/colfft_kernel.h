@@ -6,8 +6,8 @@
 //   stage B   thread (column, p): T-point transform over t, pruned to the Q outputs that are modes p + P q < P Q
 // through one LDS tile [p][t][column]; the inverse runs the transposed network with the missing modes as zeros.  Bound:
 // HBM (about 30 vector instructions per element); all rows of the 16 columns are in flight at once, two or more
-// workgroups per CU (512 rows: 64 KB of LDS).  4 x 32 fields of 512 x 512 (268 MB), 64 modes: forward 61 us, inverse 63 us
-// = 5.0 and 4.8 TB/s (a radix-2 transform of the same columns in LDS: 397 and 323 us); 32 modes: 53 and 56 us.  The
+// workgroups per CU (512 rows: 64 KB of LDS).  4 x 32 fields of 512 x 512 (268 MB), 64 modes: forward 59 us, inverse 57 us
+// = 5.1 and 5.3 TB/s (a radix-2 transform of the same columns in LDS: 397 and 323 us); 32 modes: 54 us each.  The
 // tile's p rows are padded by 16 elements, so that the four p of a wave meet different bank halves.
 //
 // `contiguous`: the workgroups of an XCD take neighbouring columns and fields (see xcd_contiguous) instead of every eighth line of

@@ -130,7 +130,7 @@ def test_real_layer_argument_checks(L):
     # float tensors: y right behind x (4 B per element) does not overlap, y inside x does
     assert f(x, W, x + 4 * 2 * 4 * 64 - 4, 2, 4, 4, 64, 16, None) == binding.ERR_ALIAS
     assert f(x, W, W, 2, 4, 4, 64, 16, None) == binding.ERR_ALIAS
-    # the real-valued kernels move pairs of floats
+    # the kernels for real fields move up to four floats at a time
     assert f(x + 4, W, y, 2, 4, 4, 64, 16, None) == binding.ERR_ALIGN
     assert f(x, W, y + 4, 2, 4, 4, 64, 16, None) == binding.ERR_ALIGN
     assert f(None, None, None, 0, 4, 4, 64, 16, None) == binding.OK
