@@ -2,6 +2,7 @@
 #include "matdft_kernel.h"
 #include "colfft.h"
 #include "fused2d.h"          // cgemm_modes_launch
+#include "matgrid.h"
 #include "pruned1d.h"
 #include "staged.h"           // launch_axis_fft
 
@@ -197,9 +198,15 @@ hipError_t matdft_conv(const c64 *x, const c64 *W, c64 *y, long long B, int C_in
         a.in = Yh; a.out = y; a.P = (unsigned)(B * C_out); a.out_outer = N2; a.C = C_out;
         return matdft_inverse(MD_SPEC, MD_ROWS, a, s);
     }
-    if ((e = last_axis(-1, g, x, T, B * C_in * N1)) != hipSuccess) return e;
-    if ((e = first_axis(-1, g, T, Xh, B, C_in)) != hipSuccess) return e;
+    const bool odd = !is_pow2(N1) && !is_pow2(N2);
+    if (odd && matgrid_supported(-1, B * C_in, N1, N2, K1, K2)) {
+        if ((e = matgrid_launch(-1, x, Xh, B * C_in, C_in, N1, N2, K1, K2, s)) != hipSuccess) return e;
+    } else {
+        if ((e = last_axis(-1, g, x, T, B * C_in * N1)) != hipSuccess) return e;
+        if ((e = first_axis(-1, g, T, Xh, B, C_in)) != hipSuccess) return e;
+    }
     if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, scale, tiles, s, true)) != hipSuccess) return e;
+    if (odd && matgrid_supported(+1, B * C_out, N1, N2, K1, K2)) return matgrid_launch(+1, Yh, y, B * C_out, C_out, N1, N2, K1, K2, s);
     if ((e = first_axis(+1, g, Yh, T, B, C_out)) != hipSuccess) return e;
     return last_axis(+1, g, T, y, B * C_out * N1);
 }

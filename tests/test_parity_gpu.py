@@ -308,6 +308,38 @@ def test_2d_sides_with_odd_factors(gpu, oracle_mod, shape):
     check(run_gpu_rect(gpu, "spectral_conv2d_rect_staged", x, W, K1, K2), want, "odd sides")
 
 
+# Both sides odd: a workgroup per field.  (B, C_in, C_out, N1, N2, K1, K2), with 256 fields and more each way unless noted: the shortest
+# sides, both parities, one and two sixteens of modes on either axis, all parts of a sum and sets of waves, the last columns' tile full, with one
+# column, with two; sides of equal length (one root table); long sums on either axis; and one step outside (the kernel per axis)
+FIELD_2D = [(32, 8, 8, 30, 30, 1, 1), (32, 8, 8, 31, 33, 15, 16), (32, 8, 9, 33, 34, 16, 17), (16, 17, 16, 33, 65, 17, 16), (32, 8, 8, 50, 66, 32, 32),
+            (2, 3, 5, 85, 85, 12, 12), (8, 9, 40, 85, 85, 12, 12), (1, 2, 3, 60, 50, 9, 9), (1, 3, 2, 45, 97, 10, 11), (33, 32, 32, 40, 96, 8, 9),
+            (8, 32, 33, 97, 129, 16, 20), (8, 32, 33, 63, 160, 17, 9), (4, 64, 65, 62, 255, 30, 31), (4, 64, 64, 36, 249, 9, 12), (16, 16, 16, 511, 41, 13, 9),
+            (2, 128, 128, 500, 33, 32, 8), (2, 130, 128, 300, 130, 20, 21), (4, 33, 2, 194, 67, 16, 13),
+            (32, 8, 8, 29, 33, 9, 9), (32, 8, 8, 33, 29, 9, 9), (32, 8, 8, 45, 45, 33, 9), (32, 8, 8, 45, 45, 9, 33), (16, 16, 16, 33, 257, 9, 9), (16, 16, 16, 513, 33, 9, 9),
+            # (the inverse rows kernel in whole pencils by one and two waves, which odd grids of these sizes no longer run)
+            (8, 2, 61, 128, 85, 12, 12), (8, 2, 61, 64, 200, 9, 10), (8, 2, 61, 64, 130, 9, 10)]
+
+
+@pytest.mark.parametrize("shape", FIELD_2D, ids=lambda s: "B%d_Ci%d_Co%d_N%dx%d_K%dx%d" % s)
+def test_fields_with_odd_sides(gpu, shape):
+    """Bound: four sums on the matrix pipe (two axes, two directions), each with the rounding of its operands' sums and differences and
+    of its own additions in blocks of 32 slots, at most 3 units of 2^-24 between them, and the contraction with 2: sqrt(4 9 + 4) 2^-24 = 3.8e-7."""
+    torch, binding = gpu
+    B, Ci, Co, N1, N2, K1, K2 = shape
+    say(f"[case] field {shape}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1610 + N1 + K2)
+    x = torch.randn((B, Ci, N1, N2), dtype=torch.complex64, device="cuda", generator=g)
+    W = torch.randn((Ci, Co), dtype=torch.complex64, device="cuda", generator=g) / Ci ** 0.5
+    y = torch.full((B, Co, N1, N2), float("nan"), dtype=torch.complex64, device="cuda")
+    binding.spectral_conv2d_rect_staged(x, W, y, K1, K2)
+    want = exact_layer(torch, x, W, K1, K2)
+    rel = float((y - want).norm() / want.norm())
+    worst = float((y - want).abs().max() / want.abs().max())
+    say(f"   rel {rel:.2e}, max {worst:.2e}")
+    assert rel <= 3.8e-7 and worst <= 4e-6, shape
+
+
 # Every form of the matrix transform, by the sides it reads and writes.  (B, C_in, C_out, N1, N2, K1, K2); N1 = 1: 1-D
 MATDFT_FORMS = {
     "1-D, two output tiles per wave": (328, 100, 2, 1, 140, 1, 40), "1-D, three": (328, 100, 2, 1, 141, 1, 70), "1-D, four": (328, 100, 2, 1, 140, 1, 100),
