@@ -3,6 +3,7 @@
 #include "colfft.h"
 #include "fused2d.h"          // cgemm_modes_launch
 #include "matgrid.h"
+#include "matrow.h"
 #include "pruned1d.h"
 #include "staged.h"           // launch_axis_fft
 
@@ -193,7 +194,10 @@ hipError_t matdft_conv(const c64 *x, const c64 *W, c64 *y, long long B, int C_in
     if (N1 == 1) {
         MatdftArgs a{};
         a.in = x; a.out = Xh; a.N = N2; a.K = K2; a.P = (unsigned)(B * C_in); a.inner = 1; a.in_outer = N2; a.C = C_in; a.M = g.M;
-        if ((e = matdft_forward(MD_ROWS, MD_SPEC, a, s)) != hipSuccess) return e;
+        const MatrowArgs r{x, W, Xh, y, (int)B, C_in, C_out, N2, K2, scale, 0, 0};
+        e = matrow_forward_supported(B, C_in, N2, K2) ? matrow_forward(r, s) : matdft_forward(MD_ROWS, MD_SPEC, a, s);
+        if (e != hipSuccess) return e;
+        if (matrow_inverse_supported(B, C_in, C_out, N2, K2)) return matrow_inverse(r, s);
         if ((e = cgemm_modes_launch(Xh, W, Yh, C_in, C_out, scale, tiles, s, true)) != hipSuccess) return e;
         a.in = Yh; a.out = y; a.P = (unsigned)(B * C_out); a.out_outer = N2; a.C = C_out;
         return matdft_inverse(MD_SPEC, MD_ROWS, a, s);

@@ -78,14 +78,14 @@ __device__ __forceinline__ void mg_mend(c64 *u, c64 *v, int n, int H, int N)
 // Sums over the slots of blocks part, part + parts, ... of CT tiles of 16 pencils: 16 KT modes.  A lane owns pencil lane % 16 of each
 // tile and the slots 4 (lane / 16) .. + 3 of every 16.  COLQ: the pencils are the columns of the product, and those of odd tiles go
 // through with their sign turned round (below).  fetch(u, v, n): raw elements of the slots n .. n + 3, every address valid; begin()
-// runs once the first ones are on their way.
+// runs once the first ones are on their way.  ROW: slot 0's partners come one element early.  Modes k0 .. k0 + 16 KT - 1.
 template <int CT, int KT>
 struct MgSums { md_floatx4 re[CT][KT], im[CT][KT]; };
 // LONG: the matrix pipe cuts off what a sum cannot hold, always in one direction, so that the offset grows with the number of
 // products added up; every other block the sums go into others by rounded additions (443 x 302 points: 3.7e-7 -> 2.4e-7 of the
 // whole layer).
-template <int CT, int KT, bool COLQ, bool LONG, class Fetch, class Begin>
-__device__ __forceinline__ void mg_sum(MgSums<CT, KT> &acc, const unsigned char *tab, int N, int K, int part, int parts, Fetch fetch, Begin begin)
+template <int CT, int KT, bool COLQ, bool LONG, bool ROW = false, class Fetch, class Begin>
+__device__ __forceinline__ void mg_sum(MgSums<CT, KT> &acc, const unsigned char *tab, int N, int K, int part, int parts, Fetch fetch, Begin begin, int k0 = 0)
 {
     const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4, H = N / 2, nblk = H / 16 + 1;
 #pragma unroll
@@ -104,7 +104,7 @@ __device__ __forceinline__ void mg_sum(MgSums<CT, KT> &acc, const unsigned char 
     unsigned idx[KT], step[KT], skip[KT];
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
-        const unsigned k = 16 * t + col < K ? (unsigned)(16 * t + col) : 0u;               // (past K: not stored)
+        const unsigned k = k0 + 16 * t + col < K ? (unsigned)(k0 + 16 * t + col) : 0u;     // (past K: not stored)
         idx[t] = MG_ROOT * (k * (unsigned)(16 * part + 4 * g) % (unsigned)N);
         skip[t] = MG_ROOT * (k * (unsigned)(16 * parts - 4) % (unsigned)N);
         step[t] = MG_ROOT * k;
@@ -128,6 +128,9 @@ __device__ __forceinline__ void mg_sum(MgSums<CT, KT> &acc, const unsigned char 
         uintx4 w[KT][3];
         roots(w);
         if (blk == 0 || blk == nblk - 1) {
+            if constexpr (ROW) {
+                if (blk == 0 && g == 0) v[0][2] = v[0][3];
+            }
 #pragma unroll
             for (int c = 0; c < CT; ++c) mg_mend(u[c], v[c], 16 * blk + 4 * g, H, N);
         }

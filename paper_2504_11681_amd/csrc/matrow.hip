@@ -1,0 +1,108 @@
+// Launcher of the 1-D layer's kernels for lengths that are no powers of two.
+#include "matrow_kernel.h"
+
+namespace tfno {
+
+namespace {
+constexpr size_t MOST_LDS = 160 * 1024;
+typedef void (*Kernel)(MatrowArgs);
+
+int forward_parts(int N) { return N / 32 + 1 < MR_WAVES ? N / 32 + 1 : MR_WAVES; }
+// sixteens of modes per wave: as few groups of at most four as there can be, of equal size; groups of at most two while most of the chip
+// is idle (1 x 4 pencils of 3000 points, 200 modes: 43.4 -> 35.37 us the layer)
+int forward_tiles(long long P, int K)
+{
+    const int all = (K + 15) / 16, most = (P + 15) / 16 * ((all + 1) / 2) <= 128 ? 2 : 4, groups = (all + most - 1) / most;
+    return (all + groups - 1) / groups;
+}
+size_t forward_lds(long long P, int N, int K) { return MG_ROOT * (size_t)N + sizeof(c64) * forward_parts(N) * 256 * forward_tiles(P, K); }
+
+struct Inverse { int waves, parts, groups; size_t lds; };
+Inverse inverse_plan(long long B, int C_in, int C_out, int N, int K)
+{
+    Inverse p{};
+    const int tiles = N / 64 + 1, mt = (K + 31) / 32, steps = (C_in + 7) / 8;
+    const long long slabs = B * ((C_out + 31) / 32);
+    // eight waves, or with two workgroups for every CU and few outputs as many as have a tile of them
+    p.waves = slabs < 512 || tiles >= MR_WAVES ? MR_WAVES : tiles > mt ? tiles : mt;
+    p.parts = p.waves / mt < steps ? p.waves / mt : steps;
+    const int most = (tiles + p.waves - 1) / p.waves;
+    p.groups = (int)(slabs * most <= 512 ? most : slabs >= 512 ? 1 : 512 / slabs);
+    p.lds = MG_ROOT * (size_t)N + 16 * 64 * 6 * (size_t)mr_steps(K) + sizeof(c64) * p.parts * 32 * mr_pitch(K);
+    return p;
+}
+
+template <bool LONG>
+Kernel pick_fwd(int KT)
+{
+    switch (KT) {
+    case 1: return k_matrow_fwd<1, LONG>;
+    case 2: return k_matrow_fwd<2, LONG>;
+    case 3: return k_matrow_fwd<3, LONG>;
+    default: return k_matrow_fwd<4, LONG>;
+    }
+}
+}  // namespace
+
+bool matrow_forward_supported(long long B, int C_in, int N, int K)
+{
+    // (few pencils: with 16384 of them and more the transform of one sum per wave has the chip full, 256 x 64 pencils of 500 points, 60 modes
+    // 25 against 30 us; 64 x 128 of 500 points, 64 modes 16.0 -> 15.4, 64 x 40 of 1000, 50 modes 12.7 -> 11.1, 5 x 71 of 162, 9 modes 5.9 -> 4.0)
+    // Short sums, which a wave gets through by itself, lose earlier (700 x 20 pencils of 130 points, 60 modes: the layer 45.6 -> 52.2; 64 x 128 of 50
+    // points, 12 modes 22.6 -> 11.8), and earlier still with more than 64 modes: those are several groups of waves, each of which fetches and folds
+    // the pencils again (33 x 128 of 130 points, 96 modes: 31.4 -> 35.9).
+    const long long most = N >= 256 ? 16383 : K <= 64 ? 8192 : 4096;
+    return N >= 32 && N <= 4096 && B * C_in <= most && forward_lds(B * C_in, N, K) <= MOST_LDS;
+}
+
+hipError_t matrow_forward(const MatrowArgs &args, hipStream_t s)
+{
+    if (!matrow_forward_supported(args.B, args.C_in, args.N, args.K)) return hipErrorInvalidValue;
+    static LdsLimitOnce limit;
+    const hipError_t e = limit.set({reinterpret_cast<const void *>(&k_matrow_fwd<1, false>), reinterpret_cast<const void *>(&k_matrow_fwd<2, false>),
+                                    reinterpret_cast<const void *>(&k_matrow_fwd<3, false>), reinterpret_cast<const void *>(&k_matrow_fwd<4, false>),
+                                    reinterpret_cast<const void *>(&k_matrow_fwd<1, true>), reinterpret_cast<const void *>(&k_matrow_fwd<2, true>),
+                                    reinterpret_cast<const void *>(&k_matrow_fwd<3, true>), reinterpret_cast<const void *>(&k_matrow_fwd<4, true>)},
+                                   (int)MOST_LDS);
+    if (e != hipSuccess) return e;
+    MatrowArgs a = args;
+    a.parts = forward_parts(a.N);
+    const int KT = forward_tiles((long long)a.B * a.C_in, a.K);
+    const dim3 grid((unsigned)(((long long)a.B * a.C_in + 15) / 16), (unsigned)((a.K + 16 * KT - 1) / (16 * KT)));
+    const Kernel kernel = a.N / 32 + 1 > 4 * a.parts ? pick_fwd<true>(KT) : pick_fwd<false>(KT);
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * a.parts), forward_lds((long long)a.B * a.C_in, a.N, a.K), s, a);
+    return hipGetLastError();
+}
+
+bool matrow_inverse_supported(long long B, int C_in, int C_out, int N, int K)
+{
+    if (N < 32 || N > 4096 || K > 32 * MR_WAVES) return false;
+    if ((long long)C_in * C_out >= (1LL << 28) || (long long)C_in * 128 >= (1LL << 28) || B * C_out >= (1LL << 31) / 32) return false;
+    // Many modes leave two waves or one to a sum over the channels, and one workgroup to a CU: with many channels then a contraction for
+    // all workgroups is ahead (B 64, C 128, N 1000, K 100: 51.5 against 58 us; B 16, C 200, N 500, K 200: 37 against 42; but 16 -> 128
+    // channels, N 700, K 90: 34 against 29)
+    if (K > 64 && C_in > 64 && (C_in > 128 || B * ((C_out + 31) / 32) > 128)) return false;
+    // Slabs of 32 outputs that are a quarter padding and more, four to a CU and more (B 2048, C 16, N 200, K 20: the layer 37.2 -> 42.6; B 512,
+    // C 64, N 100, K 20: 29.8 -> 26.0)
+    const long long slabs = (C_out + 31) / 32;
+    if (B * slabs >= 1024 && 4 * C_out < 3 * 32 * slabs) return false;
+    return inverse_plan(B, C_in, C_out, N, K).lds <= MOST_LDS;
+}
+
+hipError_t matrow_inverse(const MatrowArgs &args, hipStream_t s)
+{
+    if (!matrow_inverse_supported(args.B, args.C_in, args.C_out, args.N, args.K)) return hipErrorInvalidValue;
+    static LdsLimitOnce limit;
+    const hipError_t e = limit.set({reinterpret_cast<const void *>(&k_matrow_inv<6>), reinterpret_cast<const void *>(&k_matrow_inv<8>)}, (int)MOST_LDS);
+    if (e != hipSuccess) return e;
+    MatrowArgs a = args;
+    const Inverse p = inverse_plan(a.B, a.C_in, a.C_out, a.N, a.K);
+    a.parts = p.parts;
+    a.groups = p.groups;
+    const long long blocks = (long long)a.B * ((a.C_out + 31) / 32) * a.groups;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((a.C_in <= 16 ? k_matrow_inv<8> : k_matrow_inv<6>), dim3((unsigned)blocks), dim3(64 * p.waves), p.lds, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace tfno

@@ -340,6 +340,39 @@ def test_fields_with_odd_sides(gpu, shape):
     assert rel <= 3.8e-7 and worst <= 4e-6, shape
 
 
+# 1-D, few pencils: the forward kernel with 1 to 4 sixteens of modes per wave and several groups of them, one to eight waves to a sum, long sums,
+# a last tile of pencils with one; the kernel that contracts and transforms back: channels past a step of eight, modes past a tile, one to eight
+# tiles of modes (and shares of the channels), last slabs with one output and none missing, outputs in one group of workgroups and in
+# several, as many waves as tiles of outputs (512 slabs and more); and one step outside each.  (B, C_in, C_out, N, K)
+ROW_1D = [(2, 3, 4, 33, 1), (3, 5, 33, 33, 33), (1, 17, 32, 34, 16), (3, 16, 31, 47, 17), (2, 9, 64, 63, 32), (5, 8, 65, 65, 33), (1, 1, 1, 66, 48), (3, 24, 40, 95, 49),
+          (2, 40, 33, 97, 64), (2, 64, 32, 129, 65), (1, 65, 5, 255, 96), (2, 33, 40, 257, 97), (2, 64, 7, 300, 128), (1, 20, 12, 511, 160), (2, 3, 5, 600, 256), (2, 3, 5, 600, 257),
+          (64, 40, 56, 1000, 50), (2, 15, 70, 1025, 12), (1, 128, 128, 1900, 20), (1, 4, 6, 4095, 7), (1, 4, 6, 3000, 200), (255, 64, 4, 90, 10), (256, 64, 4, 90, 10),
+          (300, 9, 40, 33, 9), (512, 8, 32, 100, 20), (1024, 8, 24, 50, 9), (1024, 8, 23, 50, 9), (600, 4, 8, 50, 40), (530, 5, 30, 520, 9), (64, 64, 20, 200, 70), (65, 64, 20, 200, 70),
+          (2, 129, 30, 130, 66), (129, 65, 32, 60, 33), (2, 4, 5, 31, 9)]
+
+
+@pytest.mark.parametrize("shape", ROW_1D, ids=lambda s: "B%d_Ci%d_Co%d_N%d_K%d" % s)
+def test_rows_with_odd_lengths(gpu, shape):
+    """Bound: a sum on the matrix pipe each way, each with the rounding of its operands' sums and differences and of its own additions (those
+    of the kernels beside these grow with the length: 3 units of 2^-24 and a sixteenth of one per block of 16 pairs), and the contraction with 3
+    and one per 32 channels (single fields of few points, which run on direct sums: 2.8e-7 of 3.1e-7)."""
+    torch, binding = gpu
+    B, Ci, Co, N, K = shape
+    say(f"[case] row {shape}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1620 + N + K)
+    x = torch.randn((B, Ci, N), dtype=torch.complex64, device="cuda", generator=g)
+    W = torch.randn((Ci, Co), dtype=torch.complex64, device="cuda", generator=g) / Ci ** 0.5
+    y = torch.full((B, Co, N), float("nan"), dtype=torch.complex64, device="cuda")
+    binding.spectral_conv1d_auto(x, W, y, K)
+    want = exact_layer(torch, x[:, :, None], W, 1, K)[:, :, 0]
+    rel = float((y - want).norm() / want.norm())
+    worst = float((y - want).abs().max() / want.abs().max())
+    bound = 2.0 ** -24 * np.sqrt(2 * (3 + N / 512) ** 2 + (3 + Ci / 32) ** 2)
+    say(f"   rel {rel:.2e} of {bound:.2e}, max {worst:.2e}")
+    assert rel <= bound and worst <= 10 * bound, shape
+
+
 # Every form of the matrix transform, by the sides it reads and writes.  (B, C_in, C_out, N1, N2, K1, K2); N1 = 1: 1-D
 MATDFT_FORMS = {
     "1-D, two output tiles per wave": (328, 100, 2, 1, 140, 1, 40), "1-D, three": (328, 100, 2, 1, 141, 1, 70), "1-D, four": (328, 100, 2, 1, 140, 1, 100),
