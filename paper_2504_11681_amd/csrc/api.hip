@@ -295,6 +295,10 @@ tfno_status run_permode(const Shape &req, const void *x, const void *W, void *y,
         const int N = sh.N2, K = sh.K2, Mp = pruned1d_stride(N, K, req.K2, true);
         c64 *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
         e = pruned1d_stages(PRUNED_FWD, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, req.K2, Mp, s);
+        if (pruned1d_permode_fused(B, C_in, C_out, N, K, req.K2) && !contraction_forced_f32()) {
+            if (e == hipSuccess) e = pruned1d_permode_inverse(false, Xh, Wc, yc, B, C_in, C_out, N, K, req.K2, Mp, scale, s);
+            return e == hipSuccess ? TFNO_OK : TFNO_ERR_HIP;
+        }
         if (e == hipSuccess) e = cgemm_permode_launch(Xh, Wc, Yh, C_in, C_out, B, Mp, req.K2, Mp == K, scale, s);
         if (e == hipSuccess) e = pruned1d_stages(PRUNED_INV, xc, nullptr, yc, Xh, Yh, B, C_in, C_out, N, K, req.K2, Mp, s);
     } else {
@@ -402,6 +406,10 @@ tfno_status run_fno1d(const void *x, const void *W, void *y, int B, int C_in, in
     const int Mp = pruned1d_stride(N, K, M, true);
     c64 *Xh = (c64 *)wsp, *Yh = Xh + pruned1d_spectrum_elems(B, C_in, Mp);
     hipError_t e = pruned1d_real_stages(PRUNED_FWD, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, M, Mp, s);
+    if (pruned1d_permode_fused(B, C_in, C_out, N, K, M) && !contraction_forced_f32()) {
+        if (e == hipSuccess) e = pruned1d_permode_inverse(true, Xh, (const c64 *)W, (c64 *)y, B, C_in, C_out, N, K, M, Mp, 2.0f / (float)N, s);
+        return e == hipSuccess ? TFNO_OK : TFNO_ERR_HIP;
+    }
     if (e == hipSuccess) e = cgemm_permode_launch(Xh, (const c64 *)W, Yh, C_in, C_out, B, Mp, M, Mp == K, 2.0f / (float)N, s);
     if (e == hipSuccess)
         e = pruned1d_real_stages(PRUNED_INV, (const float *)x, (float *)y, Xh, Yh, B, C_in, C_out, N, K, M, Mp, s);

@@ -37,4 +37,10 @@ hipError_t pruned1d_rows(int dir, const c64 *in, c64 *out, long long rows, int N
 hipError_t pruned1d_real_stages(int stages, const float *x, float *y, c64 *Xh, c64 *Yh, long long B, int C_in, int C_out,
                                 int N, int K, int K_keep, int Mp, hipStream_t s);
 
+// Contraction with own weights per mode (W [C_in, C_out, Ma], times scale) and zero-padded inverse in one kernel: Xh -> y, for
+// small layers.  real: y float32, as pruned1d_real_stages.
+bool pruned1d_permode_fused(long long B, int C_in, int C_out, int N, int K, int Ma);
+hipError_t pruned1d_permode_inverse(bool real, const c64 *Xh, const c64 *W, c64 *y, long long B, int C_in, int C_out, int N, int K, int Ma,
+                                    int Mp, float scale, hipStream_t s);
+
 }  // namespace tfno

@@ -228,4 +228,66 @@ hipError_t pruned1d_launch(const c64 *x, const c64 *W, c64 *y, long long B, int 
                            B, C_in, C_out, N, K, K_keep, Mp, s);
 }
 
+// Outputs per workgroup: results for at most two lanes' worth of a wave, but workgroups for every CU.
+static int permode_outputs(long long B, int C_out, int N, int Ma)
+{
+    const int pencils = 4096 / N;                           // that 256 lanes transform
+    int G = pencils < 16 ? pencils : 16;
+    while (G > 1 && (G * Ma > 128 || B * ((C_out + G - 1) / G) < 256)) G /= 2;
+    return G;
+}
+
+// Every batch element reads the weights again, and every workgroup sets up its twiddles: up to 20 MB of the one and three of the other for every CU the
+// launch and the latency that are saved weigh more (whole layers, two kernels after the forward transform against one: B 32, 64 x 64 channels, N 1024, 16
+// modes, 16.8 MB, 512 workgroups 13.6 and 11.5 us; B 15, 22 -> 41, N 64, 13 modes 11.6 and 8.7; B 11, 82 -> 72, N 128, 39 modes, 20.3 MB 11.9 and 13.1; B 8,
+// 15 -> 98, N 256, 79 modes, 784 workgroups 11.5 and 11.9; B 182, 13 -> 32, N 128, 16 modes, 728 workgroups 11.5 and 8.8; B 54, 62 -> 96, N 256, 45 modes, 116 MB 19.9 and 31.4).
+bool pruned1d_permode_fused(long long B, int C_in, int C_out, int N, int K, int Ma)
+{
+    if (N > 1024 || !pruned1d_supported(N, K) || Ma > 256) return false;
+    if (B > 768 || B * C_out > (1LL << 24) || B * C_in * C_out * (long long)Ma * (long long)sizeof(c64) > 20000000) return false;
+    const int G = permode_outputs(B, C_out, N, Ma);
+    return B * ((C_out + G - 1) / G) <= 768;
+}
+
+template <int N, int K, bool REAL>
+static hipError_t launch_permode(const c64 *Xh, const c64 *W, c64 *y, long long B, int C_in, int C_out, int Ma, int Mp, float scale, hipStream_t s)
+{
+    const int G = permode_outputs(B, C_out, N, Ma), slabs = (C_out + G - 1) / G;
+    hipLaunchKernelGGL((k_inv1d_permode<N, K, REAL>), dim3((unsigned)(B * slabs)), dim3(256), 0, s, Xh, W, y, C_in, C_out, Mp, Ma, G, slabs, scale);
+    return hipGetLastError();
+}
+
+template <int N, bool REAL>
+static hipError_t permode_k(int K, const c64 *Xh, const c64 *W, c64 *y, long long B, int C_in, int C_out, int Ma, int Mp, float scale, hipStream_t s)
+{
+    switch (K) {
+    case 16: if constexpr (N <= 256) return launch_permode<N, 16, REAL>(Xh, W, y, B, C_in, C_out, Ma, Mp, scale, s); break;
+    case 32: if constexpr (N <= 256) return launch_permode<N, 32, REAL>(Xh, W, y, B, C_in, C_out, Ma, Mp, scale, s); break;
+    case 64: return launch_permode<N, 64, REAL>(Xh, W, y, B, C_in, C_out, Ma, Mp, scale, s);
+    case 128: if constexpr (N >= 128) return launch_permode<N, 128, REAL>(Xh, W, y, B, C_in, C_out, Ma, Mp, scale, s); break;
+    case 256: if constexpr (N == 256) return launch_permode<N, 256, REAL>(Xh, W, y, B, C_in, C_out, Ma, Mp, scale, s); break;
+    default: break;
+    }
+    return hipErrorInvalidValue;
+}
+
+template <bool REAL>
+static hipError_t permode_n(const c64 *Xh, const c64 *W, c64 *y, long long B, int C_in, int C_out, int N, int K, int Ma, int Mp, float scale, hipStream_t s)
+{
+    switch (N) {
+    case 64: return permode_k<64, REAL>(K, Xh, W, y, B, C_in, C_out, Ma, Mp, scale, s);
+    case 128: return permode_k<128, REAL>(K, Xh, W, y, B, C_in, C_out, Ma, Mp, scale, s);
+    case 256: return permode_k<256, REAL>(K, Xh, W, y, B, C_in, C_out, Ma, Mp, scale, s);
+    case 1024: return permode_k<1024, REAL>(K, Xh, W, y, B, C_in, C_out, Ma, Mp, scale, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t pruned1d_permode_inverse(bool real, const c64 *Xh, const c64 *W, c64 *y, long long B, int C_in, int C_out, int N, int K, int Ma,
+                                    int Mp, float scale, hipStream_t s)
+{
+    if (Ma < 1 || Ma > K || Mp < Ma || !pruned1d_permode_fused(B, C_in, C_out, N, K, Ma)) return hipErrorInvalidValue;
+    return real ? permode_n<true>(Xh, W, y, B, C_in, C_out, N, K, Ma, Mp, scale, s) : permode_n<false>(Xh, W, y, B, C_in, C_out, N, K, Ma, Mp, scale, s);
+}
+
 }  // namespace tfno

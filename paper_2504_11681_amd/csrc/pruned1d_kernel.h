@@ -221,6 +221,79 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
 }
 
 // ------------------------------------------------------------------------------------------------ inverse
+// Zero-padded inverse of one pencil per LPR lanes, from its kept bins kept(i, kh) of column p + LPR i (wide path: of the lane's column) to
+// y[q]; refill() runs when these are no longer needed.
+template <int N, int K, bool REAL, class Kept, class Refill>
+__device__ __forceinline__ void p1_inverse(const LdsP1<N, K> &L, int tid, Kept kept, Refill refill, c64 *__restrict__ y, long long q, bool ok)
+{
+    using Cf = CfgP1<N, K>;
+    constexpr int LPR = Cf::LPR, KH = Cf::KH, CPL = Cf::CPL;
+    constexpr bool WIDE = Cf::WIDE;
+    const int p = tid % LPR, kl_w = (tid & 63) >> 2, qa = tid & 3;
+    wave_sync();                                            // the previous sweep's patch reads are done
+    if constexpr (!WIDE) {
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) {
+            const int kl = p + LPR * i;
+            c64 t[KH];
+#pragma unroll
+            for (int kh = 0; kh < KH; ++kh) t[kh] = kept(i, kh);
+            dft_prune_in<LPR, KH, +1>(t, [&](auto ppc, c64 val) __attribute__((always_inline)) {
+                constexpr int pp = decltype(ppc)::value;
+                L.patch[kl * LPR + (pp ^ p)] = val;
+            });
+        }
+    } else {
+        const int swz = 4 * (kl_w & 3);
+        c64 t[KH];
+#pragma unroll
+        for (int kh = 0; kh < KH; ++kh) {
+            t[kh] = kept(0, kh);
+            if (kh != 0) {
+                const c64 w = L.tw64[qa * kh];
+                t[kh] = cmul(t[kh], make_float2(w.x, -w.y));
+            }
+        }
+        dft_prune_in<16, KH, +1>(t, [&](auto ppc, c64 val) __attribute__((always_inline)) {
+            constexpr int pp = decltype(ppc)::value;
+            L.patch[kl_w * 64 + ((qa + 4 * pp) ^ swz)] = val;
+        });
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    refill();
+    __builtin_amdgcn_sched_barrier(0);
+    wave_sync();
+    c64 z[16], res[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+        c64 t = L.patch[p1_slot<LPR>(c, p)];
+        if (c != 0) {
+            const c64 w = L.tw[c * LPR + p];
+            t = cmul(t, make_float2(w.x, -w.y));
+        }
+        z[c] = t;
+    }
+    RegFFT<16, +1, 1>::run(z, res);
+    if (ok) {
+        if constexpr (REAL) {
+            float *dst = reinterpret_cast<float *>(y) + q * N + p;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                if constexpr (LPR >= 32) __builtin_nontemporal_store(res[j].x, dst + LPR * j);
+                else dst[LPR * j] = res[j].x;
+            }
+        } else {
+            // (non-temporal only where the lanes of a pencil write whole 128-byte lines)
+            c64 *dst = y + q * N + p;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                if constexpr (LPR >= 16) store_nt(dst + LPR * j, res[j]);
+                else dst[LPR * j] = res[j];
+            }
+        }
+    }
+}
+
 // Yh: mode-tile major (joint mode m = b Mp + k, C channels); bins from K_keep on are taken as zeros (P1_ALL: they are stored
 // as zeros where there are any).  y: [npencils, N] contiguous (pencil q = b * C + o).
 template <int N, int K, bool REAL, int FORM>
@@ -263,70 +336,10 @@ k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npenci
         return ALL || k < K_keep ? yin[i * KH + kh] : make_float2(0.f, 0.f);
     };
     auto stage = [&](long long sweep, auto refill, long long next_sweep) __attribute__((always_inline)) {
-        constexpr bool REFILL = decltype(refill)::value;
-        wave_sync();                                        // the previous sweep's patch reads are done
-        if constexpr (!WIDE) {
-#pragma unroll
-            for (int i = 0; i < CPL; ++i) {
-                const int kl = p + LPR * i;
-                c64 t[KH];
-#pragma unroll
-                for (int kh = 0; kh < KH; ++kh) t[kh] = kept(i, kh);
-                dft_prune_in<LPR, KH, +1>(t, [&](auto ppc, c64 val) __attribute__((always_inline)) {
-                    constexpr int pp = decltype(ppc)::value;
-                    L.patch[kl * LPR + (pp ^ p)] = val;
-                });
-            }
-        } else {
-            const int swz = 4 * (kl_w & 3);
-            c64 t[KH];
-#pragma unroll
-            for (int kh = 0; kh < KH; ++kh) {
-                t[kh] = kept(0, kh);
-                if (kh != 0) {
-                    const c64 w = L.tw64[qa * kh];
-                    t[kh] = cmul(t[kh], make_float2(w.x, -w.y));
-                }
-            }
-            dft_prune_in<16, KH, +1>(t, [&](auto ppc, c64 val) __attribute__((always_inline)) {
-                constexpr int pp = decltype(ppc)::value;
-                L.patch[kl_w * 64 + ((qa + 4 * pp) ^ swz)] = val;
-            });
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (REFILL) load_spectrum(next_sweep);    // yin is free: in flight during the row transform
-        __builtin_amdgcn_sched_barrier(0);
-        wave_sync();
-        c64 z[16], res[16];
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            c64 t = L.patch[p1_slot<LPR>(c, p)];
-            if (c != 0) {
-                const c64 w = L.tw[c * LPR + p];
-                t = cmul(t, make_float2(w.x, -w.y));
-            }
-            z[c] = t;
-        }
-        RegFFT<16, +1, 1>::run(z, res);
         const long long q = sweep * PPS + g;
-        if (q < npencils) {
-            if constexpr (REAL) {
-                float *dst = reinterpret_cast<float *>(y) + q * N + p;
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    if constexpr (LPR >= 32) __builtin_nontemporal_store(res[j].x, dst + LPR * j);
-                    else dst[LPR * j] = res[j].x;
-                }
-            } else {
-                // (non-temporal only where the lanes of a pencil write whole 128-byte lines)
-                c64 *dst = y + q * N + p;
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    if constexpr (LPR >= 16) store_nt(dst + LPR * j, res[j]);
-                    else dst[LPR * j] = res[j];
-                }
-            }
-        }
+        p1_inverse<N, K, REAL>(L, tid, kept, [&]() __attribute__((always_inline)) {
+            if constexpr (decltype(refill)::value) load_spectrum(next_sweep);       // yin is free: in flight during the row transform
+        }, y, q, q < npencils);
     };
 
     if ((long long)blockIdx.x >= nsweeps) return;
@@ -335,6 +348,89 @@ k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npenci
     long long sweep = blockIdx.x;
     for (; sweep + gridDim.x < nsweeps; sweep += gridDim.x) stage(sweep, std::true_type{}, sweep + gridDim.x);
     stage(sweep, std::false_type{}, 0);
+}
+
+// Contraction with an own weight matrix per mode and inverse transform in one kernel, for layers so small that a launch and the latency
+// behind it are most of a kernel's time.  A workgroup takes one batch element and G outputs, a lane one (output, mode) pair or two, whose
+// weights are consecutive in memory, and the four waves every fourth block of channels; the sums meet in LDS, in the place the inverse
+// transform reads its bins from.  Every batch element reads all weights again, from the caches.
+// Xh: joint mode b Mp + k.  W: [C_in, C_out, Ma].  G Ma <= 256 results and G LPR <= 256 lanes to a workgroup.
+template <int N, int K, bool REAL>
+__global__ void __launch_bounds__(256)
+k_inv1d_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__restrict__ y, int C_in, int C_out, int Mp, int Ma, int G, int slabs, float scale)
+{
+    using Cf = CfgP1<N, K>;
+    constexpr int LPR = Cf::LPR;
+    __shared__ __align__(16) unsigned char raw[Cf::LDS_BYTES];
+    __shared__ c64 sums[4][256];
+    const int tid = threadIdx.x, lane = tid & 63, part = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = (int)(blockIdx.x / (unsigned)slabs), o0 = (int)(blockIdx.x % (unsigned)slabs) * G;
+    const int results = min(G, C_out - o0) * Ma;
+
+    const c64 *__restrict__ wsrc = W + (long long)o0 * Ma;
+    const unsigned wstep = (unsigned)C_out * (unsigned)Ma;
+    auto column = [&](int r) __attribute__((always_inline)) {
+        const long long m = (long long)b * Mp + r % Ma;
+        return Xh + (m >> 7) * C_in * 128 + (m & 127);
+    };
+    // R results per lane, U channels in flight; a block's sum first, as in k_cgemm_permode
+    auto contract = [&](auto rc, auto uc, int r0) __attribute__((always_inline)) {
+        constexpr int R = decltype(rc)::value, U = decltype(uc)::value;
+        const c64 *xs[R];
+        unsigned r[R];
+        c64 acc[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            r[i] = (unsigned)min(r0 + 64 * i + lane, results - 1);
+            xs[i] = column((int)r[i]);
+            acc[i] = make_float2(0.f, 0.f);
+        }
+        for (int c0 = part * U; c0 < C_in; c0 += 4 * U) {
+            c64 xv[U][R], wv[U][R];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const unsigned c = (unsigned)min(c0 + u, C_in - 1);
+                    wv[u][i] = wsrc[(unsigned long long)c * wstep + r[i]];
+                    xv[u][i] = xs[i][c * 128u];
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            c64 sum[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) sum[i] = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (c0 + u < C_in) {                        // (uniform)
+#pragma unroll
+                    for (int i = 0; i < R; ++i) sum[i] = cmac(sum[i], xv[u][i], wv[u][i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < R; ++i) acc[i] = cadd(acc[i], sum[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i) sums[part][r0 + 64 * i + lane] = acc[i];
+    };
+    if (results <= 64) contract(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{}, 0);
+    else
+        for (int r0 = 0; r0 < results; r0 += 128) contract(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{}, r0);
+    const LdsP1<N, K> L = p1_setup<N, K>(raw, tid);
+    __syncthreads();                                        // (twiddle tables too)
+    {
+        c64 s = sums[0][tid];
+#pragma unroll
+        for (int i = 1; i < 4; ++i) s = cadd(s, sums[i][tid]);
+        sums[0][tid] = make_float2(s.x * scale, s.y * scale);
+    }
+    __syncthreads();
+    const int g = tid / LPR;
+    if (g >= G) return;                                     // (no barrier follows; a wave's lanes of other pencils go on)
+    const int o = o0 + g;
+    p1_inverse<N, K, REAL>(L, tid, [&](int i, int kh) __attribute__((always_inline)) {
+        const int k = (Cf::WIDE ? (tid & 63) >> 2 : tid % LPR + LPR * i) + 16 * kh;
+        return k < Ma && o < C_out ? sums[0][min(g * Ma + k, 255)] : make_float2(0.f, 0.f);
+    }, [] {}, y, (long long)b * C_out + o, o < C_out);
 }
 
 }  // namespace tfno

@@ -1013,6 +1013,43 @@ def test_permode_channel_blocks(gpu, oracle_mod, B, Co, M):
         close(yd.cpu().numpy().astype(np.float64), want, ("permode channel blocks", B, Ci, Co, M))
 
 
+# The same blocks through the 2-D layer, whose small contractions the FP32 kernel runs (those of small 1-D layers are in the inverse kernel).
+@pytest.mark.parametrize("B,Co,K1,K2", [(3, 5, 3, 3), (5, 33, 3, 19)], ids=["one", "four"])
+def test_permode_channel_blocks_2d(gpu, oracle_mod, B, Co, K1, K2):
+    torch, binding = gpu
+    for Ci in (1, 7, 8, 9, 15, 16, 17, 23, 31, 33, 47, 65, 79):
+        say(f"[case] permode channel blocks, 2-D {(B, Ci, Co, K1, K2)}")
+        x = inputs.make_x(1375 + Ci, B, Ci, (64, 64))
+        W = np.ascontiguousarray(inputs.make_W(1375 + Ci, Ci, Co * K1 * K2).reshape(Ci, Co, K1, K2))
+        want, _ = oracle_mod.spectral_conv2d_permode(x, W)
+        yd = torch.full((B, Co, 64, 64), float("nan"), dtype=torch.complex64, device="cuda")
+        binding.spectral_conv2d_permode(torch.from_numpy(x).cuda(), torch.from_numpy(W).cuda(), yd)
+        torch.cuda.synchronize()
+        close(yd.cpu().numpy(), want, ("permode channel blocks, 2-D", B, Ci, Co, K1, K2))
+
+
+# Small per-mode layers, contraction and inverse in one kernel: every length and mode count it is built for, real and complex; one and two results per
+# lane, one and several rounds of them, one output per workgroup up to 16, a last workgroup with one output, channels around the blocks of
+# 8 and 16 and a round of four of them; and the limits of the rule (20 MB of weights read, 768 workgroups).
+@pytest.mark.parametrize("N,K", [(64, 9), (64, 32), (64, 40), (128, 7), (128, 32), (128, 63), (128, 100), (256, 16), (256, 20), (256, 64), (256, 128), (256, 200),
+                                 (1024, 16), (1024, 64), (1024, 127)], ids=lambda v: str(v))
+def test_small_permode_layers(gpu, oracle_mod, N, K):
+    torch, binding = gpu
+    for B, Ci, Co in ((1, 1, 1), (2, 8, 17), (3, 33, 5), (2, 65, 9), (70, 3, 17), (300, 2, 3)) + (((384, 3, 2), (385, 3, 2)) if N == 256 else ()):
+        say(f"[case] small permode {(B, Ci, Co, N, K)}")
+        x = inputs.make_x(1385 + Ci, B, Ci, (N,))
+        W = np.ascontiguousarray(inputs.make_W(1385 + Ci, Ci, Co * K).reshape(Ci, Co, K))
+        yd = torch.full((B, Co, N), float("nan"), dtype=torch.complex64, device="cuda")
+        binding.spectral_conv1d_permode(torch.from_numpy(x).cuda(), torch.from_numpy(W).cuda(), yd)
+        close(yd.cpu().numpy(), oracle_mod.spectral_conv1d_permode(x, W)[0], ("small permode", B, Ci, Co, N, K))
+        if 2 * K > N:
+            continue
+        xr = np.ascontiguousarray(x.real)
+        yr = torch.full((B, Co, N), float("nan"), dtype=torch.float32, device="cuda")
+        binding.fno1d_real(torch.from_numpy(xr).cuda(), torch.from_numpy(W).cuda(), yr)
+        close(yr.cpu().numpy().astype(np.float64), oracle_mod.fno1d_real(xr, W)[0], ("small fno1d", B, Ci, Co, N, K))
+
+
 # the 1-D FNO layer on real fields (B, C_in, C_out, N, M)
 FNO_1D = [(4, 16, 16, 64, 16), (3, 5, 7, 64, 12), (9, 33, 40, 128, 20), (17, 6, 18, 256, 128), (2, 20, 30, 1024, 64),
           (11, 13, 17, 1024, 100), (2, 3, 3, 128, 1), (8, 3, 2, 256, 33)]
