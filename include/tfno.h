@@ -27,6 +27,7 @@
  *  - Ownership: the caller owns every buffer (including the workspace) and must
  *    keep it alive and unmodified until the stream has passed the call.
  *  - y must not overlap x or W (checked on address ranges: TFNO_ERR_ALIAS).
+ *  - y may hold intermediates of a call before its result.
  *  - x, W and y must be aligned to 8 bytes (TFNO_ERR_ALIGN), the float32 tensors of the real-valued entry points
  *    included: complex64 elements move as 8-byte words, and kernels for real fields move up to four floats at a time.
  *  - Argument errors are detected on the host before anything is launched, so a

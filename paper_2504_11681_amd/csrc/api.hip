@@ -168,6 +168,48 @@ tfno_status check_workspace(size_t need, const void *x, size_t xb, const void *W
 
 enum Variant { FUSED = 0, STAGED = 1, PRUNED = 2, FFT_GEMM = 3, GEMM_IFFT = 4, STRIPS = 7 };
 
+// Fused kernel along the last axis on the K1 retained rows of every batch element; strides of channels and batch elements.
+Fused1dArgs strip_rows(const c64 *T1, const c64 *W, c64 *T2, int B, int C_in, int C_out, int N1, int N, int K1, int keep2, long long x_chan,
+                       long long x_batch, long long y_chan, long long y_batch)
+{
+    Fused1dArgs a{};
+    a.x = T1; a.W = W; a.y = T2; a.C_in = C_in; a.C_out = C_out;
+    a.inner_count = K1;
+    a.x_outer_stride = x_batch; a.x_inner_stride = N; a.x_chan_stride = x_chan;
+    a.y_outer_stride = y_batch; a.y_inner_stride = N; a.y_chan_stride = y_chan;
+    a.scale = 1.0f / ((float)N1 * (float)N);
+    a.K_keep = keep2;
+    return a;
+}
+
+// The strip pipeline on grids that the image kernels cover, for few images: an image is one workgroup there, which walks through its N1 rows, while
+// the column kernels have N2 / 16 workgroups to an image.  Both half-transformed fields are held in y, so that the call needs no more
+// workspace than the image kernels: the K1 rows of an output image are its own first rows, which the column kernel has read when it
+// writes to them; the K1 rows of `g` input images follow in the g parts of an output image.  Returns g; 0: image kernels.
+// Whole layers, image kernels and strips (us): 256 x 256, K 64 x 64, B 1, C 16 64.8 and 16.3; B 4, C 32 70 and 50; B 4, C 64 77 and 83; 256 x 64, K 32 x 16,
+// B 4, C 64 38 and 22; 128 x 128, K 16 x 16, B 4, C 64 30 and 24, B 8 37 and 41; 64 x 64, K 16 x 16, B 8, C 64 22 and 18; 64 x 256, K 16 x 64, B 4, C 32 24 and 19,
+// C 64 27 and 31: up to about 72000 rows' worth of images x N2, 100000 with the longer walk of 256 rows.
+int strip_channels_per_field(const Shape &req, int B, int C_in, int C_out)
+{
+    if (!colfft_supported(req.N1, req.K1) || !round_modes(req.N2, req.K2, fused1d_supported) || generic_kernels_forced() || contraction_forced_f32()) return 0;
+    if ((double)B * ((double)C_in + C_out) * req.N2 > (req.N1 >= 256 ? 100000.0 : 72000.0)) return 0;
+    int g = 1;
+    while (g * (long long)C_out < C_in) g *= 2;
+    return 2 * req.K1 * g <= req.N1 ? g : 0;
+}
+
+hipError_t strips_in_y(const Shape &req, const c64 *x, const c64 *W, c64 *y, int B, int C_in, int C_out, int g, hipStream_t s)
+{
+    const int N1 = req.N1, N = req.N2, K1 = req.K1;
+    const long long NN = (long long)N1 * N, chan = NN / g;
+    c64 *T1 = y + (long long)K1 * N;
+    hipError_t e = colfft_launch(-1, x, T1, (long long)B * C_in, N1, N, K1, ColRows{C_in, C_out * NN, chan}, s);
+    if (e != hipSuccess) return e;
+    e = fused1d_launch(N, round_modes(N, req.K2, fused1d_supported), strip_rows(T1, W, y, B, C_in, C_out, N1, N, K1, req.K2, chan, C_out * NN, NN, C_out * NN), (long long)B * K1, s);
+    if (e != hipSuccess) return e;
+    return colfft_launch(+1, y, y, (long long)B * C_out, N1, N, K1, ColRows{1, NN, 0}, s);
+}
+
 // own_scratch: the intermediates go to the library's static scratch array instead of the registered workspace
 tfno_status run(const Shape &req, Variant variant, const void *x, const void *W, void *y, int B, int C_in, int C_out,
                 void *stream, bool own_scratch = false)
@@ -240,8 +282,10 @@ tfno_status run(const Shape &req, Variant variant, const void *x, const void *W,
         a.K_keep = keep2;
         e = fused1d_launch(N, K, a, B, s);
     } else if (variant != STRIPS && sh.image_kernels()) {
-        // image kernels: only the truncated K1 x K2 spectra cross global memory
-        e = fused2d_launch(xc, Wc, yc, B, C_in, C_out, sh.N1, sh.N2, sh.K1, sh.K2, keep1, keep2, (c64 *)ws, s);
+        // image kernels: only the truncated K1 x K2 spectra cross global memory.  Few images: strips, held in y
+        const int share = strip_channels_per_field(req, B, C_in, C_out);
+        e = share ? strips_in_y(req, xc, Wc, yc, B, C_in, C_out, share, s)
+                  : fused2d_launch(xc, Wc, yc, B, C_in, C_out, sh.N1, sh.N2, sh.K1, sh.K2, keep1, keep2, (c64 *)ws, s);
     } else {
         // strip pipeline (Sec. 3.2 / 3.3), for shapes the image kernels do not cover: truncated forward transform
         // along the first axis, fused kernel along the last axis on the K1 retained rows, zero-padded inverse along
@@ -253,20 +297,11 @@ tfno_status run(const Shape &req, Variant variant, const void *x, const void *W,
         // The first axis: column kernels where they exist (4 x 32 fields of 512 x 512, K1 64: 61 + 63 us against 397 + 323 us
         // for the staged transform), the staged transform for other lengths and for more modes.
         const bool cols = colfft_supported(N1, K1);
-        e = cols ? colfft_launch(-1, xc, T1, (long long)B * C_in, N1, N, K1, s)
+        e = cols ? colfft_launch(-1, xc, T1, (long long)B * C_in, N1, N, K1, ColRows{1, KN, 0}, s)
                  : launch_axis_fft(-1, xc, T1, N1, (long long)B * C_in * N, N, NN, KN, N, N1, K1, 1.f, s);
-        if (e == hipSuccess) {
-            Fused1dArgs a{};
-            a.x = T1; a.W = Wc; a.y = T2; a.C_in = C_in; a.C_out = C_out;
-            a.inner_count = K1;
-            a.x_outer_stride = (long long)C_in * KN;  a.x_inner_stride = N; a.x_chan_stride = KN;
-            a.y_outer_stride = (long long)C_out * KN; a.y_inner_stride = N; a.y_chan_stride = KN;
-            a.scale = 1.0f / ((float)N1 * (float)N);
-            a.K_keep = keep2;
-            e = fused1d_launch(N, K, a, (long long)B * K1, s);
-        }
+        if (e == hipSuccess) e = fused1d_launch(N, K, strip_rows(T1, Wc, T2, B, C_in, C_out, N1, N, K1, keep2, KN, C_in * KN, KN, C_out * KN), (long long)B * K1, s);
         if (e == hipSuccess)
-            e = cols ? colfft_launch(+1, T2, yc, (long long)B * C_out, N1, N, K1, s)
+            e = cols ? colfft_launch(+1, T2, yc, (long long)B * C_out, N1, N, K1, ColRows{1, KN, 0}, s)
                      : launch_axis_fft(+1, T2, yc, N1, (long long)B * C_out * N, N, KN, NN, N, K1, N1, 1.f, s);
     }
     return e == hipSuccess ? TFNO_OK : TFNO_ERR_HIP;

@@ -7,7 +7,7 @@ namespace tfno {
 namespace {
 int stage_a_points(int N1) { return N1 == 64 ? 8 : 16; }
 
-struct Cols { const c64 *in; c64 *out; long long fields; int N2, K1, C; long long M; };
+struct Cols { const c64 *in; c64 *out; long long fields; int N2, K1, C; long long M, channel; };
 
 template <int P, int T, int Q, bool SPEC>
 hipError_t launch_pq(int dir, const Cols &a, hipStream_t s)
@@ -30,7 +30,7 @@ hipError_t launch_pq(int dir, const Cols &a, hipStream_t s)
     // modes, 32 x 32 fields 304 299 / 308 300 / 277 261; 64 to 256 rows of 200, 16 x 32 modes: equal within 1 %) from a workgroup per CU on, unless
     // they are one group of 16.
     const bool contiguous = SPEC ? groups > 1 && a.fields * groups >= 256 : a.N2 >= 128 && a.fields * C::N1 * a.N2 * (long long)sizeof(c64) >= 384LL << 20;
-    if (dir < 0) hipLaunchKernelGGL((k_colfft_fwd<P, T, Q, SPEC>), grid, dim3(nt), C::LDS, s, a.in, a.out, a.N2, a.K1, groups, contiguous, a.C, a.M);
+    if (dir < 0) hipLaunchKernelGGL((k_colfft_fwd<P, T, Q, SPEC>), grid, dim3(nt), C::LDS, s, a.in, a.out, a.N2, a.K1, groups, contiguous, a.C, a.M, a.channel);
     else hipLaunchKernelGGL((k_colfft_inv<P, T, Q, SPEC>), grid, dim3(nt), C::LDS, s, a.in, a.out, a.N2, a.K1, groups, SPEC && contiguous, a.C, a.M);
     return hipGetLastError();
 }
@@ -66,16 +66,16 @@ bool colfft_supported(int N1, int K1)
     return (N1 == 64 || N1 == 128 || N1 == 256 || N1 == 512) && K1 >= 1 && K1 <= 8 * stage_a_points(N1) && K1 <= N1;
 }
 
-hipError_t colfft_launch(int dir, const c64 *in, c64 *out, long long fields, int N1, int N2, int K1, hipStream_t s)
+hipError_t colfft_launch(int dir, const c64 *in, c64 *out, long long fields, int N1, int N2, int K1, ColRows rows, hipStream_t s)
 {
-    if (N2 < 16 || N2 % 16 != 0) return hipErrorInvalidValue;
-    return launch<false>(dir, N1, Cols{in, out, fields, N2, K1, 1, 0}, s);
+    if (N2 < 16 || N2 % 16 != 0 || rows.channels < 1 || (dir > 0 && rows.channels != 1)) return hipErrorInvalidValue;
+    return launch<false>(dir, N1, Cols{in, out, fields, N2, K1, rows.channels, rows.outer, rows.inner}, s);
 }
 
 hipError_t colfft_spec_launch(int dir, const c64 *in, c64 *out, long long fields, int N1, int N2, int K1, int C, long long M, hipStream_t s)
 {
     if (N2 < 1 || C < 1) return hipErrorInvalidValue;
-    return launch<true>(dir, N1, Cols{in, out, fields, N2, K1, C, M}, s);
+    return launch<true>(dir, N1, Cols{in, out, fields, N2, K1, C, M, 0}, s);
 }
 
 }  // namespace tfno

@@ -49,7 +49,7 @@ __device__ __forceinline__ long long col_spec(unsigned b, unsigned c, int C, lon
 
 template <int P, int T, int Q, bool SPEC>
 __global__ void __launch_bounds__((CfgCol<P, T, Q>::NT), (CfgCol<P, T, Q>::WG_PER_CU))
-k_colfft_fwd(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, unsigned groups, bool contiguous, int Cs, long long M)
+k_colfft_fwd(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, unsigned groups, bool contiguous, int Cs, long long M, long long channel)
 {
     using C = CfgCol<P, T, Q>;
     extern __shared__ __align__(16) unsigned char col_lds[];
@@ -60,8 +60,8 @@ k_colfft_fwd(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, 
     // (SPEC: columns past the last one read it again and are not stored)
     const int n2 = (int)(16 * g) + col, n2_in = SPEC && n2 >= N2 ? N2 - 1 : n2;
     const c64 *__restrict__ src = in + (long long)field * C::N1 * N2 + n2_in;
-    c64 *__restrict__ dst = out + (long long)field * K1 * N2 + n2;
-    const unsigned sb = SPEC ? field / (unsigned)Cs : 0, sc = SPEC ? field % (unsigned)Cs : 0;
+    const unsigned sb = field / (unsigned)Cs, sc = field - sb * (unsigned)Cs;
+    c64 *__restrict__ dst = out + (SPEC ? 0 : (long long)sb * M + (long long)sc * channel) + n2;
 
     c64 v[C::TPT][P];
 #pragma unroll
@@ -105,7 +105,7 @@ k_colfft_fwd(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, 
 
 template <int P, int T, int Q, bool SPEC>
 __global__ void __launch_bounds__((CfgCol<P, T, Q>::NT), (CfgCol<P, T, Q>::WG_PER_CU))
-k_colfft_inv(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, unsigned groups, bool contiguous, int Cs, long long M)
+k_colfft_inv(const c64 *in, c64 *out, int N2, int K1, unsigned groups, bool contiguous, int Cs, long long M)
 {
     using C = CfgCol<P, T, Q>;
     extern __shared__ __align__(16) unsigned char col_lds[];
@@ -114,8 +114,9 @@ k_colfft_inv(const c64 *__restrict__ in, c64 *__restrict__ out, int N2, int K1, 
     const int tid = threadIdx.x, col = tid & 15, sub = tid >> 4;
     const unsigned wg = contiguous ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, field = wg / groups, g = wg % groups;
     const int n2 = (int)(16 * g) + col, n2_in = SPEC && n2 >= N2 ? N2 - 1 : n2;
-    const c64 *__restrict__ src = in + (long long)field * K1 * N2 + n2;
-    c64 *__restrict__ dst = out + (long long)field * C::N1 * N2 + n2;
+    // (the modes of a field may lie in its own rows: a workgroup has read its columns when it first writes to them)
+    const c64 *src = in + (SPEC ? 0 : (long long)field * M) + n2;
+    c64 *dst = out + (long long)field * C::N1 * N2 + n2;
     const unsigned sb = SPEC ? field / (unsigned)Cs : 0, sc = SPEC ? field % (unsigned)Cs : 0;
 
     c64 v[C::IPT][Q];

@@ -373,6 +373,40 @@ def test_rows_with_odd_lengths(gpu, shape):
     assert rel <= bound and worst <= 10 * bound, shape
 
 
+# Grids of powers of two with few images, whose strips are held in y: every pair of sides, one, two, four and eight input images to an output
+# image's field (the last with rows to spare, and with none), ragged and whole slabs, the largest and smallest mode counts, and one step outside
+# (no room for the input rows; more images than that: the image kernels).  (B, C_in, C_out, N1, N2, K1, K2)
+FEW_IMAGES = [(2, 3, 5, 64, 64, 32, 32), (2, 5, 3, 64, 64, 16, 64), (1, 9, 4, 64, 128, 8, 9), (3, 7, 1, 64, 256, 4, 20), (1, 8, 1, 64, 64, 4, 16), (2, 9, 1, 64, 64, 4, 16),
+              (2, 4, 3, 64, 64, 17, 12), (2, 33, 17, 128, 64, 32, 31), (2, 16, 4, 128, 128, 16, 64), (1, 17, 33, 128, 256, 64, 33), (2, 7, 2, 128, 64, 1, 1),
+              (1, 16, 16, 256, 256, 64, 64), (2, 31, 4, 256, 64, 16, 16), (1, 5, 40, 256, 128, 33, 64), (1, 3, 2, 256, 256, 65, 40), (1, 2, 2, 256, 64, 128, 9), (1, 2, 2, 64, 64, 33, 9),
+              (25, 22, 23, 64, 64, 9, 9), (26, 22, 23, 64, 64, 9, 9), (11, 17, 18, 256, 256, 9, 17), (12, 17, 18, 256, 256, 9, 17), (20, 14, 15, 128, 128, 30, 20), (10, 16, 13, 64, 256, 9, 60),
+              (17, 35, 35, 64, 64, 16, 32), (10, 30, 30, 128, 128, 64, 64), (6, 40, 40, 256, 128, 32, 16), (40, 20, 20, 256, 64, 64, 32)]
+
+
+@pytest.mark.parametrize("shape", FEW_IMAGES, ids=lambda s: "B%d_Ci%d_Co%d_N%dx%d_K%dx%d" % s)
+def test_2d_few_and_many_images(gpu, shape):
+    """Bound: up to 8 steps of butterflies along an axis, two axes, two directions, of about 0.7 units of 2^-24 each, and the contraction with
+    3: sqrt(32 0.5 + 9) 2^-24 = 3.0e-7.  y begins 8 bytes past a line, between guards."""
+    torch, binding = gpu
+    B, Ci, Co, N1, N2, K1, K2 = shape
+    say(f"[case] images {shape}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1630 + N1 + K2)
+    x = torch.randn((B, Ci, N1, N2), dtype=torch.complex64, device="cuda", generator=g)
+    W = torch.randn((Ci, Co), dtype=torch.complex64, device="cuda", generator=g) / Ci ** 0.5
+    n = B * Co * N1 * N2
+    whole = torch.full((n + 2,), float("nan"), dtype=torch.complex64, device="cuda")
+    y = whole[1:1 + n].view(B, Co, N1, N2)
+    want = exact_layer(torch, x, W, K1, K2)
+    for turn in range(2):                                   # (y holds the first call's result in the second)
+        binding.spectral_conv2d_rect(x, W, y, K1, K2)
+        rel = float((y - want).norm() / want.norm())
+        worst = float((y - want).abs().max() / want.abs().max())
+        say(f"   rel {rel:.2e}, max {worst:.2e}")
+        assert rel <= 3.0e-7 and worst <= 3e-6, shape
+    assert bool(torch.isnan(whole[:1].real).all()) and bool(torch.isnan(whole[n + 1:].real).all())
+
+
 # Every form of the matrix transform, by the sides it reads and writes.  (B, C_in, C_out, N1, N2, K1, K2); N1 = 1: 1-D
 MATDFT_FORMS = {
     "1-D, two output tiles per wave": (328, 100, 2, 1, 140, 1, 40), "1-D, three": (328, 100, 2, 1, 141, 1, 70), "1-D, four": (328, 100, 2, 1, 140, 1, 100),
