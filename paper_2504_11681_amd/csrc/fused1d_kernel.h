@@ -77,6 +77,9 @@ struct FusedCfg {
     static constexpr int TPW = KS > 1 ? 1 : (TILES + NW - 1) / NW;     // 32x32 complex tiles per wave
     static constexpr bool ALLT = KS > 1 ? TILES * KS == NW : TILES % NW == 0;   // every wave owns exactly TPW tiles
     static constexpr bool DIRECT = KS == 1 && P == 32 && OT == NW && TPW == KT;   // wave w owns output slab w entirely
+    // The same with two lanes to a column, N = 128 and 256.  Not where it measured slower: N = 256 with up to 64 modes (B 512, C 128: 59.2 and 61.1 us),
+    // whose four waves share the way through the slabs among them, and the three workgroups per CU of N = 128, K = 32 (254 and 261 us).
+    static constexpr bool DIRECT16 = KS == 1 && P == 16 && OT == NW && TPW == KT && (N == 128 ? K >= 64 || (K == 32 && XB == 2) : K == 128);
     static constexpr int RPA = 32 / T;              // direct epilogue: stage-B' rounds per stage-A' round
     static constexpr int ZROW = T + 1;
     static constexpr int ZS = P * ZROW + (T == 8 ? 8 - (P * ZROW) % 16 + ((P * ZROW) % 16 > 8 ? 16 : 0) : 0);
@@ -623,6 +626,40 @@ k_fused1d(Fused1dArgs a)
             wave_sync();
             const int r2 = rr + jw / 2;
             ifft_store(o_base + 32 * wave + 8 * (r2 / 4) + 4 * (jw % 2) + (r2 % 4));
+            wave_sync();
+        }
+    } else if constexpr (C::DIRECT16 && MODE == 0) {
+        // Wave w owns outputs o_base + 32 w .. +31 for every mode.  Register r of lane l of tile i holds Yh[o][32 i + l % 32]: a column p = l % 16
+        // has its even q = 2 i in the lanes of even sixteens and its odd q in those of odd ones.  Swapping the odd sixteens of register r with
+        // the even ones of register r + 1 gives every lane all Q modes of its column of one pencil: the even sixteens that of r, the odd ones
+        // that of r + 1.  Nothing goes through the workgroup's LDS, and no barrier holds seven waves up while the one that owns a slab
+        // writes it there.  (B 512, N 256, 128 modes: 256 channels 242.0 ->
+        // 233.6 us, 128 channels 78.5 -> 76.0; N 128, B 1024, C 128, 64 modes 83.7 -> 79.1, real rows 86.0 -> 76.3; the CGEMM + iFFT kernel, which has less to do
+        // before it: B 512, 200 -> 256, N 128, 32 modes 101.1 -> 103.1, not used.)
+        constexpr int RPA = PPW / 4;                        // pairs of registers to a round: PPW pencils, four at a time
+        const int p = lane & 15, slot = (lane >> 5) * 2 + ((lane >> 4) & 1);
+        for (int rr = 0; rr < 16; rr += 2 * RPA) {
+#pragma unroll
+            for (int sub = 0; sub < RPA; ++sub) {
+                const int r = rr + 2 * sub;
+                c64 yin[Q];
+                static_for<0, 8>([&](auto rc) {
+                    constexpr int R = 2 * decltype(rc)::value;
+                    if (r == R) {
+#pragma unroll
+                        for (int i = 0; i < KT; ++i) {
+                            const auto re = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc_re[i][R]), __float_as_uint(acc_re[i][R + 1]), false, false);
+                            const auto im = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc_im[i][R]), __float_as_uint(acc_im[i][R + 1]), false, false);
+                            yin[2 * i] = make_float2(__uint_as_float(re[0]), __uint_as_float(im[0]));
+                            yin[2 * i + 1] = make_float2(__uint_as_float(re[1]), __uint_as_float(im[1]));
+                        }
+                    }
+                });
+                stage_b_inv(yin, 4 * sub + slot, p);
+            }
+            wave_sync();
+            const int r2 = rr + 2 * (jw / 4);
+            ifft_store(o_base + 32 * wave + 8 * (r2 / 4) + 4 * ((jw % 4) / 2) + (r2 % 4) + (jw % 2));
             wave_sync();
         }
     } else {

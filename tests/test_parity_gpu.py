@@ -407,6 +407,32 @@ def test_2d_few_and_many_images(gpu, shape):
     assert bool(torch.isnan(whole[:1].real).all()) and bool(torch.isnan(whole[n + 1:].real).all())
 
 
+# Fused layers whose waves invert the slab they have accumulated without the workgroup's LDS (every wave a slab of 32 outputs and all modes): N 128
+# and 256, four and eight waves, complex and real rows, whole and ragged slabs, a last one with one output, modes cut inside a built size.
+# (entry, B, C_in, C_out, N, K)
+OWN_SLABS = [("spectral_conv1d", 3, 32, 128, 128, 32), ("spectral_conv1d", 2, 33, 97, 128, 20), ("spectral_conv1d", 2, 64, 128, 128, 64), ("spectral_conv1d", 2, 20, 129, 128, 40),
+             ("spectral_conv1d", 2, 32, 128, 128, 128), ("spectral_conv1d", 300, 33, 65, 128, 64), ("spectral_conv1d", 300, 32, 128, 128, 100), ("spectral_conv1d", 2, 32, 128, 256, 128),
+             ("spectral_conv1d", 300, 17, 100, 256, 128), ("spectral_conv1d", 300, 16, 128, 256, 90), ("spectral_conv1d", 192, 32, 256, 256, 128), ("spectral_conv1d", 193, 40, 250, 256, 100),
+             ("spectral_conv1d", 200, 9, 129, 256, 128), ("spectral_conv1d_real", 3, 32, 128, 128, 32), ("spectral_conv1d_real", 150, 21, 97, 128, 64),
+             ("spectral_conv1d_real", 150, 32, 128, 256, 128), ("spectral_conv1d_real", 150, 9, 66, 256, 70)]
+
+
+@pytest.mark.parametrize("case", OWN_SLABS, ids=lambda c: "%s_B%d_Ci%d_Co%d_N%d_K%d" % c)
+def test_waves_that_own_their_slab(gpu, oracle_mod, case):
+    torch, binding = gpu
+    entry, B, Ci, Co, N, K = case
+    say(f"[case] own slab {case}")
+    x = inputs.make_x(1640 + N + K, B, Ci, (N,))
+    W = inputs.make_W(1640 + N + K, Ci, Co)
+    if entry == "spectral_conv1d":
+        check(run_gpu(gpu, entry, x, W, K), oracle_mod.spectral_conv1d(x, W, K)[0], "own slab")
+        return
+    xr = np.ascontiguousarray(x.real)
+    yd = torch.full((B, Co, N), float("nan"), dtype=torch.float32, device="cuda")
+    binding.spectral_conv1d_real(torch.from_numpy(xr).cuda(), torch.from_numpy(W).cuda(), yd, K)
+    close(yd.cpu().numpy().astype(np.float64), oracle_mod.spectral_conv1d_real(xr, W, K)[0], case)
+
+
 # Every form of the matrix transform, by the sides it reads and writes.  (B, C_in, C_out, N1, N2, K1, K2); N1 = 1: 1-D
 MATDFT_FORMS = {
     "1-D, two output tiles per wave": (328, 100, 2, 1, 140, 1, 40), "1-D, three": (328, 100, 2, 1, 141, 1, 70), "1-D, four": (328, 100, 2, 1, 140, 1, 100),
