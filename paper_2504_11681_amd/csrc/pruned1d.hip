@@ -239,7 +239,7 @@ static int permode_outputs(long long B, int C_out, int N, int Ma)
 
 // Every batch element reads the weights again, and every workgroup sets up its twiddles: up to 20 MB of the one and three of the other for every CU the
 // launch and the latency that are saved weigh more (whole layers, two kernels after the forward transform against one: B 32, 64 x 64 channels, N 1024, 16
-// modes, 16.8 MB, 512 workgroups 13.6 and 11.5 us; B 15, 22 -> 41, N 64, 13 modes 11.6 and 8.7; B 11, 82 -> 72, N 128, 39 modes, 20.3 MB 11.9 and 13.1; B 8,
+// modes, 16.8 MB, 512 workgroups 13.6 and 10.9 us; B 15, 22 -> 41, N 64, 13 modes 11.6 and 8.7; B 11, 82 -> 72, N 128, 39 modes, 20.3 MB 11.9 and 13.1; B 8,
 // 15 -> 98, N 256, 79 modes, 784 workgroups 11.5 and 11.9; B 182, 13 -> 32, N 128, 16 modes, 728 workgroups 11.5 and 8.8; B 54, 62 -> 96, N 256, 45 modes, 116 MB 19.9 and 31.4).
 bool pruned1d_permode_fused(long long B, int C_in, int C_out, int N, int K, int Ma)
 {

@@ -69,9 +69,18 @@ __device__ __forceinline__ LdsP1<N, K> p1_setup(unsigned char *raw, int tid)
     l.patch = base + (tid / C::LPR) * C::GS;
     l.tw = base + C::PPS * C::GS;
     l.tw64 = l.tw + N;
-    for (int i = tid; i < N; i += C::NT) l.tw[i] = cis2pi(-(float)((i / C::LPR) * (i % C::LPR)), (float)N);
-    if (tid < 64) l.tw64[tid] = cis2pi(-(float)tid, 64.f);
     return l;
+}
+
+// The twiddle tables, to be built while the first loads are on their way (about 1 us for 1024 points).
+template <int N, int K>
+__device__ __forceinline__ void p1_tables(const LdsP1<N, K> &l, int tid)
+{
+    using C = CfgP1<N, K>;
+    __builtin_amdgcn_sched_barrier(0);
+    for (int i = tid; i < N; i += C::NT) l.tw[i] = cis2pi(-(float)((i / C::LPR) * (i % C::LPR)), (float)N);
+    if (C::WIDE && tid < 64) l.tw64[tid] = cis2pi(-(float)tid, 64.f);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // patch slot of entry (column c, position p)
@@ -214,7 +223,8 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
 
     if ((long long)blockIdx.x >= nsweeps) return;           // uniform per workgroup; no barrier has been reached
     load_pencil(blockIdx.x);
-    __syncthreads();                                        // twiddle tables are ready
+    p1_tables(L, tid);
+    __syncthreads();
     long long sweep = blockIdx.x;
     for (; sweep + gridDim.x < nsweeps; sweep += gridDim.x) stage(sweep, std::true_type{}, sweep + gridDim.x);
     stage(sweep, std::false_type{}, 0);
@@ -344,7 +354,8 @@ k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npenci
 
     if ((long long)blockIdx.x >= nsweeps) return;
     load_spectrum(blockIdx.x);
-    __syncthreads();                                        // twiddle tables are ready
+    p1_tables(L, tid);
+    __syncthreads();
     long long sweep = blockIdx.x;
     for (; sweep + gridDim.x < nsweeps; sweep += gridDim.x) stage(sweep, std::true_type{}, sweep + gridDim.x);
     stage(sweep, std::false_type{}, 0);
@@ -374,6 +385,8 @@ k_inv1d_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__re
         return Xh + (m >> 7) * C_in * 128 + (m & 127);
     };
     // R results per lane, U channels in flight; a block's sum first, as in k_cgemm_permode
+    const LdsP1<N, K> L = p1_setup<N, K>(raw, tid);
+    bool tables = false;
     auto contract = [&](auto rc, auto uc, int r0) __attribute__((always_inline)) {
         constexpr int R = decltype(rc)::value, U = decltype(uc)::value;
         const c64 *xs[R];
@@ -396,6 +409,10 @@ k_inv1d_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__re
                     xv[u][i] = xs[i][c * 128u];
                 }
             __builtin_amdgcn_sched_barrier(0);
+            if (!tables) {
+                p1_tables(L, tid);
+                tables = true;
+            }
             c64 sum[R];
 #pragma unroll
             for (int i = 0; i < R; ++i) sum[i] = make_float2(0.f, 0.f);
@@ -415,8 +432,8 @@ k_inv1d_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__re
     if (results <= 64) contract(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{}, 0);
     else
         for (int r0 = 0; r0 < results; r0 += 128) contract(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{}, r0);
-    const LdsP1<N, K> L = p1_setup<N, K>(raw, tid);
-    __syncthreads();                                        // (twiddle tables too)
+    if (!tables) p1_tables(L, tid);                         // (a wave without channels)
+    __syncthreads();
     {
         c64 s = sums[0][tid];
 #pragma unroll
