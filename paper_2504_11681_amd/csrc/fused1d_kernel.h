@@ -153,7 +153,7 @@ __global__ void __launch_bounds__((FusedCfg<N, K, OT, BF, NW, XB, KS>::NT), (Fus
 k_fused1d(Fused1dArgs a)
 {
     using C = FusedCfg<N, K, OT, BF, NW, XB, KS>;
-    static_assert(!C::WIDE || (MODE == 0 && !REAL), "the eight-wave kernel is the fully fused complex layer only");
+    static_assert(!C::WIDE || MODE == 0, "the eight-wave kernel is the fully fused layer only");
     static_assert(KS == 1 || MODE != 1, "partial accumulators meet in the inverse transform's LDS tile");
     static_assert(C::FITS, "LDS budget of one gfx950 CU");
     constexpr int NWV = C::NWV;
@@ -170,6 +170,7 @@ k_fused1d(Fused1dArgs a)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     // (N = 1024 only: one workgroup per CU and 1 MiB rows; with several small workgroups per CU the mapping measured
     // up to 10 % slower)
     const int bb = N == 1024 ? (int)xcd_contiguous(blockIdx.x, gridDim.x) : (int)blockIdx.x;
@@ -230,12 +231,24 @@ k_fused1d(Fused1dArgs a)
         return BF ? 8 * ((i / 4) * KS + part) + 4 * (lane >> 5) + (i % 4) : i;
     };
 
+    // The last block with channels missing: what a wave or a step of the contraction has none for is left out (complex rows, N 256: B 300, 100 -> 250,
+    // 128 modes 178 -> 126 us; N 128: B 300, 130 -> 130, 64 modes 72.6 -> 62.5, B 163, 86 -> 10, 16 modes 10.0 -> 8.7; real rows, whose small layers
+    // wait for one workgroup's chain, 3 to 7 % slower: only the steps are left out there).
+    constexpr bool SKIP = !EVEN && BF && !REAL;
     auto load_pencil = [&](int c0) __attribute__((always_inline)) {
         const int c = c0 + ja;
         if constexpr (EVEN) {
             const XT *src = xb + (long long)c * a.x_chan_stride + t;
 #pragma unroll
             for (int jj = 0; jj < P; ++jj) v[jj] = widen(fetch(src + T * jj));
+        } else if constexpr (SKIP) {
+            // Channels past C_in meet zero weights: the lanes of a wave that has some of both read channel 0 (finite wherever the result
+            // is), a wave that has none loads nothing.
+            if (c0 + wave_u * PPW < a.C_in) {
+                const XT *src = xb + (long long)(c < a.C_in ? c : 0) * a.x_chan_stride + t;
+#pragma unroll
+                for (int jj = 0; jj < P; ++jj) v[jj] = widen(fetch(src + T * jj));
+            }
         } else {
             const bool ok = c < a.C_in;
             const XT *src = xb + (long long)(ok ? c : 0) * a.x_chan_stride + t;
@@ -278,15 +291,27 @@ k_fused1d(Fused1dArgs a)
         }
     };
     // stage A: P-point transform of the slice in v, written transposed into the wave's Z tile
-    auto stage_a = [&]() __attribute__((always_inline)) {
+    // (with channels that leave a wave without any in the last block, that wave skips its transforms and puts zeros into the operand tile)
+    auto has_pencils = [&](int blk) __attribute__((always_inline)) { return !SKIP || blk * PPI + wave_u * PPW < a.C_in; };
+    auto stage_a = [&](int blk) __attribute__((always_inline)) {
+        if (!has_pencils(blk)) return;
         c64 z[P];
         RegFFT<P, -1, 1>::run(v, z);
 #pragma unroll
         for (int p = 0; p < P; ++p) Zw[jw * ZS + p * ZROW + t] = z[p];
     };
     // stage B: twiddle, T-point transform pruned to the Q retained outputs of each column, into XH[buf]
-    auto stage_b = [&](int buf) __attribute__((always_inline)) {
+    auto stage_b = [&](int buf, int blk) __attribute__((always_inline)) {
         float *XHb = XH + buf * C::XH_BUF;
+        if (!has_pencils(blk)) {
+#pragma unroll
+            for (int cc = 0; cc < CPL; ++cc) {
+                const int item = lane + 64 * cc;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) put_operand(XHb, wave * PPW + item / P, item % P + P * q, make_float2(0.f, 0.f));
+            }
+            return;
+        }
 #pragma unroll
         for (int cc = 0; cc < CPL; ++cc) {
             const int item = lane + 64 * cc;
@@ -328,7 +353,9 @@ k_fused1d(Fused1dArgs a)
         }
     };
     // complex MAC on the matrix cores (channels past C_in carry zero spectra and zero weights)
-    auto mfma_block = [&](int buf) __attribute__((always_inline)) {
+    // (the last block leaves out its steps past C_in)
+    auto mfma_block = [&](int buf, auto last, int blk) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last)::value && !EVEN;
         const float *XHb = XH + buf * C::XH_BUF;
         if constexpr (BF) {
             // 8 channels per v_mfma_f32_32x32x16_bf16: lanes 0-31 carry channels 0-3 of the step, lanes 32-63
@@ -337,6 +364,7 @@ k_fused1d(Fused1dArgs a)
             const unsigned *XS = reinterpret_cast<const unsigned *>(XHb) + (hi ? 1 : 0) * (KT * 128) + kt0 * 128 + (lane & 31) * 4;
 #pragma unroll
             for (int s = 0; s < PPI / 8 / KS; ++s) {
+                if (LAST && blk * PPI + 8 * (s * KS + __builtin_amdgcn_readfirstlane(part)) >= a.C_in) break;
                 uintx4 a_re[3], a_im[3];
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
@@ -383,7 +411,8 @@ k_fused1d(Fused1dArgs a)
     // wv.  Global loads complete in issue order, so a wait for a weight that was fetched after a block of pencil loads
     // would also wait for those pencils (HBM latency): the weights of a block are therefore fetched at the start of
     // its stage B, BEFORE the pencil loads that are issued next, and every wait meets loads a whole phase old.
-    auto mfma_block_wide = [&]() __attribute__((always_inline)) {
+    auto mfma_block_wide = [&](auto last, int blk) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last)::value && !EVEN;
         const unsigned *XS = reinterpret_cast<const unsigned *>(XH) + (hi ? 1 : 0) * (KT * 128) + kt0 * 128 + (lane & 31) * 4;
         // tile-step n = (8-channel step n / TPW, tile n % TPW): its three B operands are read from LDS while the MFMAs
         // of tile-step n-1 run
@@ -396,6 +425,7 @@ k_fused1d(Fused1dArgs a)
         read_b(b[0], 0);
 #pragma unroll
         for (int s = 0; s < PPI / 8 / KS; ++s) {
+            if (LAST && blk * PPI + 8 * (s * KS + __builtin_amdgcn_readfirstlane(part)) >= a.C_in) break;
             uintx4 a_re[3], a_im[3];
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
@@ -429,15 +459,16 @@ k_fused1d(Fused1dArgs a)
         // (scheduling fences: left alone, the compiler sinks stage A into the MFMA sequence and the pencil loads
         // behind the closing barrier, which leaves them one stage B to arrive instead of a whole contraction)
         load_w(wv, it * PPI);
-        stage_b(0);
+        stage_b(0, it);
         wave_sync();
         __syncthreads();
-        if constexpr (DO_A) { stage_a(); wave_sync(); }
+        if constexpr (DO_A) { stage_a(it + 1); wave_sync(); }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (DO_LOAD) load_pencil((it + 2) * PPI);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (ALLT) mfma_block_wide();
-        else if (has_tiles) mfma_block_wide();
+        constexpr std::integral_constant<bool, !DO_A> last{};
+        if constexpr (ALLT) mfma_block_wide(last, it);
+        else if (has_tiles) mfma_block_wide(last, it);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (DO_A) __syncthreads();
     };
@@ -450,10 +481,11 @@ k_fused1d(Fused1dArgs a)
         const int cur = it & 1;
         c64 wn[NWV];
         if constexpr (DO_B) load_w(wn, (it + 1) * PPI);
-        if constexpr (ALLT) mfma_block(cur);
-        else if (has_tiles) mfma_block(cur);
-        if constexpr (DO_B) { stage_b(cur ^ 1); wave_sync(); }
-        if constexpr (DO_A) { stage_a(); wave_sync(); }
+        constexpr std::integral_constant<bool, !DO_B> last{};
+        if constexpr (ALLT) mfma_block(cur, last, it);
+        else if (has_tiles) mfma_block(cur, last, it);
+        if constexpr (DO_B) { stage_b(cur ^ 1, it + 1); wave_sync(); }
+        if constexpr (DO_A) { stage_a(it + 2); wave_sync(); }
         if constexpr (DO_LOAD) load_pencil((it + 3) * PPI);
         if constexpr (DO_B) {
 #pragma unroll
@@ -468,7 +500,7 @@ k_fused1d(Fused1dArgs a)
     if constexpr (C::WIDE) {
         load_pencil(0);
         build_twiddles();
-        stage_a();
+        stage_a(0);
         wave_sync();
         if (n_it > 1) load_pencil(PPI);
         int it = 0;
@@ -479,13 +511,13 @@ k_fused1d(Fused1dArgs a)
         load_pencil(0);
         load_w(wv, 0);
         build_twiddles();
-        stage_a();
+        stage_a(0);
         wave_sync();
         if (n_it > 1) load_pencil(PPI);
-        stage_b(0);
+        stage_b(0, 0);
         wave_sync();
         if (n_it > 1) {
-            stage_a();
+            stage_a(1);
             wave_sync();
             if (n_it > 2) load_pencil(2 * PPI);
         }
@@ -532,8 +564,9 @@ k_fused1d(Fused1dArgs a)
             constexpr bool DO_PUT = decltype(do_put)::value, DO_LOAD = decltype(do_load)::value;
             c64 wn[NWV];
             if constexpr (DO_PUT) load_w(wn, (it + 1) * PPI);
-            if constexpr (ALLT) mfma_block(it & 1);
-            else if (has_tiles) mfma_block(it & 1);
+            constexpr std::integral_constant<bool, !DO_PUT> last{};
+            if constexpr (ALLT) mfma_block(it & 1, last, it);
+            else if (has_tiles) mfma_block(it & 1, last, it);
             if constexpr (DO_PUT) put_spec((it & 1) ^ 1);
             if constexpr (DO_LOAD) load_spec((it + 2) * PPI);
             if constexpr (DO_PUT) {
