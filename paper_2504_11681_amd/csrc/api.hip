@@ -210,9 +210,10 @@ hipError_t strips_in_y(const Shape &req, const c64 *x, const c64 *W, c64 *y, int
     return colfft_launch(+1, y, y, (long long)B * C_out, N1, N, K1, ColRows{1, NN, 0}, s);
 }
 
-// own_scratch: the intermediates go to the library's static scratch array instead of the registered workspace
+// own_scratch: the intermediates go to the library's static scratch array instead of the registered workspace.  by_shape: the fused variant may
+// be replaced by three kernels that need no workspace
 tfno_status run(const Shape &req, Variant variant, const void *x, const void *W, void *y, int B, int C_in, int C_out,
-                void *stream, bool own_scratch = false)
+                void *stream, bool own_scratch = false, bool by_shape = false)
 {
     const bool staged = variant == STAGED;
     bool empty;
@@ -272,6 +273,8 @@ tfno_status run(const Shape &req, Variant variant, const void *x, const void *W,
             e = pruned1d_stages(PRUNED_FWD, xc, Wc, yc, (c64 *)ws, nullptr, B, C_in, C_out, N, K, keep2, K, s);
             if (e == hipSuccess) e = fused1d_partial_launch(2, N, K, a, B, s);
         }
+    } else if (dims == 1 && by_shape && default_kernels() && pruned1d_in_y_supported(false, B, C_in, C_out, N, keep2)) {
+        e = pruned1d_in_y(false, xc, Wc, yc, B, C_in, C_out, N, keep2, s);
     } else if (dims == 1) {
         Fused1dArgs a{};
         a.x = xc; a.W = Wc; a.y = yc; a.C_in = C_in; a.C_out = C_out;
@@ -362,6 +365,8 @@ tfno_status run_real1d(const void *x, const void *W, void *y, int B, int C_in, i
     if (!aligned8(x, W, y)) return TFNO_ERR_ALIGN;
     const int Kk = round_modes(N, K, fused1d_real_supported);       // the kernel's K; bins K .. Kk-1 are zeroed
     if (!Kk) return TFNO_ERR_UNSUPPORTED;
+    if (default_kernels() && pruned1d_in_y_supported(true, B, C_in, C_out, N, K))
+        return pruned1d_in_y(true, x, (const c64 *)W, y, B, C_in, C_out, N, K, (hipStream_t)stream) == hipSuccess ? TFNO_OK : TFNO_ERR_HIP;
     Fused1dArgs a{};
     a.x = (const c64 *)x; a.W = (const c64 *)W; a.y = (c64 *)y; a.C_in = C_in; a.C_out = C_out;   // x, y: float tensors
     a.K_keep = K;
@@ -552,6 +557,7 @@ static int kernel_choice()
 }
 
 bool generic_kernels_forced() { return kernel_choice() == 2; }
+bool default_kernels() { return kernel_choice() == 0 && !contraction_forced_f32(); }
 
 hipError_t fused1d_launch(int N, int K, const Fused1dArgs &a, long long rows, hipStream_t s)
 {
@@ -653,7 +659,7 @@ tfno_status tfno_spectral_conv1d_gemm_ifft(const void *x, const void *W, void *y
 tfno_status tfno_spectral_conv1d_auto(const void *x, const void *W, void *y, int B, int C_in, int C_out, int N, int K,
                                       void *stream)
 {
-    return run(shape1d(N, K), choose_variant(N, K, C_out), x, W, y, B, C_in, C_out, stream);
+    return run(shape1d(N, K), choose_variant(N, K, C_out), x, W, y, B, C_in, C_out, stream, false, true);
 }
 
 tfno_status tfno_spectral_conv1d_staged(const void *x, const void *W, void *y, int B, int C_in, int C_out, int N,

@@ -499,14 +499,18 @@ k_cgemm_modes_small(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *
 // sign of the product: up to 16 channels, where little else rounds, that is a fifth of the error (16 channels, lengths of 3
 // to 25 points: whole layer 1.1e-7 - 2.1e-7 with six, 0.99e-7 - 1.8e-7 with eight, FP32 sums 1.3e-7 - 2.2e-7; 1 channel, 9 points, 2
 // modes: 1.22e-7, 0.96e-7, 1.03e-7).  The two more are lost in the latency of such short sums (8 channels, 7 points, B 4096: 16.2 and 16.1 us).
-template <int NSTEP, int NP>
+// ROWS: the spectra are rows of up to 128 modes, channel c of batch element blockIdx.x at blockIdx.x batch + c channel; a wave for
+// every 32 modes.
+struct ModeRows { long long x_batch, y_batch; int x_channel, y_channel; };
+template <int NSTEP, int NP, bool ROWS = false>
 __global__ void __launch_bounds__(256, 2)
-k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__restrict__ Yh, int C_in, int C_out, float scale)
+k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__restrict__ Yh, int C_in, int C_out, float scale, ModeRows rows)
 {
+    const int x_channel = ROWS ? rows.x_channel : 128, y_channel = ROWS ? rows.y_channel : 128;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, g = lane >> 5;
     const int o0 = blockIdx.y * 32, o = o0 + col < C_out ? o0 + col : C_out - 1;
-    const c64 *__restrict__ xsrc = Xh + (long long)blockIdx.x * C_in * 128 + 32 * wave + col;
+    const c64 *__restrict__ xsrc = Xh + (ROWS ? blockIdx.x * rows.x_batch : (long long)blockIdx.x * C_in * 128) + 32 * wave + col;
 
     // (channels past C_in are read from channel 0 and meet zero weights; outputs past C_out are not stored)
     c64 xq[NSTEP][4], wq[NSTEP][4];
@@ -515,7 +519,7 @@ k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 
         for (int d = 0; d < 4; ++d) {
             const int c = c0 + 8 * i + 4 * g + d, cc = c < C_in ? c : 0;
             wq[i][d] = W[(long long)cc * C_out + o];
-            xq[i][d] = xsrc[cc * 128];
+            xq[i][d] = xsrc[(long long)cc * x_channel];
         }
     };
     floatx16 acc_re, acc_im;
@@ -562,11 +566,11 @@ k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 
     for (; c0 + 8 * NSTEP < C_in; c0 += 8 * NSTEP) block(std::true_type{}, c0);
     block(std::false_type{}, c0);
 
-    c64 *__restrict__ Yb = Yh + (long long)blockIdx.x * C_out * 128 + 32 * wave + col;
+    c64 *__restrict__ Yb = Yh + (ROWS ? blockIdx.x * rows.y_batch : (long long)blockIdx.x * C_out * 128) + 32 * wave + col;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int oo = o0 + 8 * (r / 4) + 4 * g + (r % 4);
-        if (oo < C_out) Yb[oo * 128] = make_float2(acc_re[r], acc_im[r]);
+        if (oo < C_out) Yb[(long long)oo * y_channel] = make_float2(acc_re[r], acc_im[r]);
     }
 }
 

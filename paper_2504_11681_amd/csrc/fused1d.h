@@ -34,6 +34,8 @@ hipError_t fused1d_launch(int N, int K, const Fused1dArgs &a, long long batch_ro
 bool contraction_forced_f32();
 // True when the environment asks for the four-wave double-buffered kernel everywhere (TFNO_KERNEL=generic).
 bool generic_kernels_forced();
+// True when it asks for nothing (TFNO_KERNEL, TFNO_CONTRACTION).
+bool default_kernels();
 
 // Wave-specialised variant (BF16x3 split contraction on the matrix pipe beside the VALU transforms).
 bool fused1d_ws_supported(int N, int K);

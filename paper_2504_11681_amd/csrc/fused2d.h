@@ -45,4 +45,8 @@ hipError_t cgemm_permode_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, 
 // Modes per batch element in the joint mode index of a spectrum that keeps `modes` of them: 64-byte rows.
 inline int spectrum_stride(int modes) { return (modes + 7) & ~7; }
 
+// The same with one W for spectra in rows of whole 32 modes, K <= 128 of them contracted: batch element b, channel c of X at b x_batch + c x_channel.
+hipError_t cgemm_rows_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, float scale, long long B, int K, long long x_batch, int x_channel,
+                             long long y_batch, int y_channel, hipStream_t s);
+
 }  // namespace tfno

@@ -17,6 +17,17 @@ size_t fused2d_workspace_bytes(long long B, int C_in, int C_out, int K1, int K2)
     return sizeof(c64) * (size_t)B * K1 * K2 * ((size_t)C_in + C_out);
 }
 
+hipError_t cgemm_rows_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, float scale, long long B, int K, long long x_batch, int x_channel,
+                             long long y_batch, int y_channel, hipStream_t s)
+{
+    if (B < 1 || B >= (1LL << 24) || K < 1 || K > 128) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)B, (unsigned)((C_out + 31) / 32)), block(64 * ((K + 31) / 32));
+    const ModeRows rows{x_batch, y_batch, x_channel, y_channel};
+    if (C_in <= 16) hipLaunchKernelGGL((k_cgemm_modes_direct<2, 8, true>), grid, block, 0, s, Xh, W, Yh, C_in, C_out, scale, rows);
+    else hipLaunchKernelGGL((k_cgemm_modes_direct<4, 6, true>), grid, block, 0, s, Xh, W, Yh, C_in, C_out, scale, rows);
+    return hipGetLastError();
+}
+
 hipError_t cgemm_modes_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, int C_out, float scale, long long tiles,
                               hipStream_t s, bool all_products)
 {
@@ -29,9 +40,9 @@ hipError_t cgemm_modes_launch(const c64 *Xh, const c64 *W, c64 *Yh, int C_in, in
     // A tile is a workgroup there, and a launch has fewer than 2^32 threads.
     if (!contraction_forced_f32() && (C_out <= 32 || tiles * ((C_out + 31) / 32) <= (C_in <= 128 ? 512 : 256)) && tiles < (1LL << 24)) {
         const dim3 gd((unsigned)tiles, (unsigned)((C_out + 31) / 32));
-        if (C_in <= 16 && all_products) hipLaunchKernelGGL((k_cgemm_modes_direct<2, 8>), gd, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, scale);
-        else if (C_in <= 16) hipLaunchKernelGGL((k_cgemm_modes_direct<2, 6>), gd, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, scale);
-        else hipLaunchKernelGGL((k_cgemm_modes_direct<4, 6>), gd, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, scale);
+        if (C_in <= 16 && all_products) hipLaunchKernelGGL((k_cgemm_modes_direct<2, 8>), gd, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, scale, ModeRows{});
+        else if (C_in <= 16) hipLaunchKernelGGL((k_cgemm_modes_direct<2, 6>), gd, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, scale, ModeRows{});
+        else hipLaunchKernelGGL((k_cgemm_modes_direct<4, 6>), gd, dim3(256), 0, s, Xh, W, Yh, C_in, C_out, scale, ModeRows{});
         return hipGetLastError();
     }
     if (!contraction_forced_f32() && C_in <= 64) {

@@ -43,4 +43,8 @@ bool pruned1d_permode_fused(long long B, int C_in, int C_out, int N, int K, int 
 hipError_t pruned1d_permode_inverse(bool real, const c64 *Xh, const c64 *W, c64 *y, long long B, int C_in, int C_out, int N, int K, int Ma,
                                     int Mp, float scale, hipStream_t s);
 
+// Layers of N = 1024 with up to 128 modes and few batch elements (shared W; real: x, y float32): three kernels whose spectra are held in y.
+bool pruned1d_in_y_supported(bool real, long long B, int C_in, int C_out, int N, int K_keep);
+hipError_t pruned1d_in_y(bool real, const void *x, const c64 *W, void *y, long long B, int C_in, int C_out, int N, int K_keep, hipStream_t s);
+
 }  // namespace tfno

@@ -88,7 +88,7 @@ static hipError_t launch_fwd(const c64 *x, c64 *Xh, int C, long long pencils, in
     // (measured: the forward kernels gain 2 - 4 % and the real-valued inverse 13 % from the balanced grid; the complex
     // inverse kernels, which write twice the bytes, lose 4 % and keep the fixed grid)
     const unsigned grid = balanced_grid<&k_fwd1d<N, K, REAL, FORM>>((pencils + Cf::PPS - 1) / Cf::PPS, 256);
-    hipLaunchKernelGGL((k_fwd1d<N, K, REAL, FORM>), dim3(grid), dim3(256), 0, s, x, Xh, C, pencils, K_keep, Mp);
+    hipLaunchKernelGGL((k_fwd1d<N, K, REAL, FORM>), dim3(grid), dim3(256), 0, s, x, Xh, C, pencils, K_keep, Mp, 0LL, 0LL);
     return hipGetLastError();
 }
 
@@ -98,7 +98,7 @@ static hipError_t launch_inv(const c64 *Yh, c64 *y, int C, long long pencils, in
     using Cf = CfgP1<N, K>;
     const long long sweeps = (pencils + Cf::PPS - 1) / Cf::PPS;
     const unsigned grid = REAL ? balanced_grid<&k_inv1d<N, K, REAL, FORM>>(sweeps, 256) : (unsigned)(sweeps < 1024 ? sweeps : 1024);
-    hipLaunchKernelGGL((k_inv1d<N, K, REAL, FORM>), dim3(grid), dim3(256), 0, s, Yh, y, C, pencils, K_keep, Mp);
+    hipLaunchKernelGGL((k_inv1d<N, K, REAL, FORM>), dim3(grid), dim3(256), 0, s, Yh, y, C, pencils, K_keep, Mp, 0LL);
     return hipGetLastError();
 }
 
@@ -288,6 +288,51 @@ hipError_t pruned1d_permode_inverse(bool real, const c64 *Xh, const c64 *W, c64 
 {
     if (Ma < 1 || Ma > K || Mp < Ma || !pruned1d_permode_fused(B, C_in, C_out, N, K, Ma)) return hipErrorInvalidValue;
     return real ? permode_n<true>(Xh, W, y, B, C_in, C_out, N, K, Ma, Mp, scale, s) : permode_n<false>(Xh, W, y, B, C_in, C_out, N, K, Ma, Mp, scale, s);
+}
+
+// Input pencils whose bins an output pencil has room for beside its own: rows of 128 bins, two of them for every part.
+static int channels_per_pencil(bool real, int C_in, int C_out)
+{
+    const int pitch = real ? 512 : 1024;                    // complex numbers in an output pencil
+    int g = 1;
+    while (g * (long long)C_out < C_in) g *= 2;
+    return pitch / g >= 256 ? g : 0;
+}
+
+// A fused workgroup takes its row's channels 8 at a time, 0.42 us per channel however few rows there are; the three kernels take about as long as their
+// bytes at 4 TB/s, and both some 9 us besides (fused and three kernels, us: B 4, C 32, K 64 23 and 12; B 48, C 128 56 and 33; B 48, 200 -> 100 91 and 44; B 100,
+// C 32 23 and 20, 16 -> 64 18.7 and 20.9; real rows, C 128, B 90 65 and 41, B 180, on the symmetric kernel, 73 and 83).
+bool pruned1d_in_y_supported(bool real, long long B, int C_in, int C_out, int N, int K_keep)
+{
+    if (N != 1024 || K_keep < 1 || K_keep > 128 || B >= (1LL << 24) || !channels_per_pencil(real, C_in, C_out)) return false;
+    const double bytes = (real ? 4.0 : 8.0) * N * (double)B * ((double)C_in + C_out);
+    return bytes <= (real ? 1.2e6 : 1.6e6) * C_in;
+}
+
+template <int K, bool REAL>
+static hipError_t rows_in_y(const void *x, const c64 *W, void *y, long long B, int C_in, int C_out, int K_keep, hipStream_t s)
+{
+    constexpr int N = 1024, pitch = REAL ? N / 2 : N;
+    using Cf = CfgP1<N, K>;
+    const int g = channels_per_pencil(REAL, C_in, C_out), channel = pitch / g;
+    const long long batch = (long long)C_out * pitch, pin = B * C_in, pout = B * C_out;
+    c64 *Yh = reinterpret_cast<c64 *>(y), *Xh = Yh + 128;
+    const unsigned gin = balanced_grid<&k_fwd1d<N, K, REAL, P1_ROWS>>((pin + Cf::PPS - 1) / Cf::PPS, 256);
+    const unsigned gout = balanced_grid<&k_inv1d<N, K, REAL, P1_ROWS>>((pout + Cf::PPS - 1) / Cf::PPS, 256);
+    hipLaunchKernelGGL((k_fwd1d<N, K, REAL, P1_ROWS>), dim3(gin), dim3(256), 0, s, (const c64 *)x, Xh, C_in, pin, K_keep, K_keep, batch, (long long)channel);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    e = cgemm_rows_launch(Xh, W, Yh, C_in, C_out, (REAL ? 2.0f : 1.0f) / (float)N, B, K_keep, batch, channel, batch, pitch, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_inv1d<N, K, REAL, P1_ROWS>), dim3(gout), dim3(256), 0, s, (const c64 *)nullptr, Yh, C_out, pout, K_keep, K_keep, (long long)pitch);
+    return hipGetLastError();
+}
+
+hipError_t pruned1d_in_y(bool real, const void *x, const c64 *W, void *y, long long B, int C_in, int C_out, int N, int K_keep, hipStream_t s)
+{
+    if (!pruned1d_in_y_supported(real, B, C_in, C_out, N, K_keep)) return hipErrorInvalidValue;
+    if (K_keep <= 64) return real ? rows_in_y<64, true>(x, W, y, B, C_in, C_out, K_keep, s) : rows_in_y<64, false>(x, W, y, B, C_in, C_out, K_keep, s);
+    return real ? rows_in_y<128, true>(x, W, y, B, C_in, C_out, K_keep, s) : rows_in_y<128, false>(x, W, y, B, C_in, C_out, K_keep, s);
 }
 
 }  // namespace tfno

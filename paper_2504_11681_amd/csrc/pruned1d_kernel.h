@@ -103,12 +103,16 @@ __device__ __forceinline__ int p1_slot(int c, int p)
 // modes: 128 channels 117 -> 108 us, 64 channels 59.8 -> 56.7 us with P1_ALL and the inverse's zeros moved to their use.
 // With 127 modes kept: 118 -> 113 us with P1_FULL; CGEMM + iFFT variant, B 256, 128 channels, 128 points, 57 modes: 33.9 -> 31.7 us.
 // The inverse kernel knows P1_ALL and P1_CUT: a full spectrum holds zeros in the bins that are not kept.
-enum { P1_CUT = 0, P1_FULL = 1, P1_ALL = 2 };               // any Mp; Mp = K; K_keep = Mp = K
+// P1_ROWS: the K_keep kept bins of a pencil in a row of their own, row (b, c) at b batch + c channel (inverse: of pencil q at q channel, in y itself).
+enum { P1_CUT = 0, P1_FULL = 1, P1_ALL = 2, P1_ROWS = 3 };  // any Mp; Mp = K; K_keep = Mp = K
 template <int N, int K, bool REAL, int FORM>
 __global__ void __launch_bounds__(256)
-k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npencils, int K_keep_, int Mp_)
+k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npencils, int K_keep_, int Mp_, long long batch, long long channel)
 {
-    const int K_keep = FORM == P1_ALL ? K : K_keep_, Mp = FORM != P1_CUT ? K : Mp_;
+    const int K_keep = FORM == P1_ALL ? K : K_keep_, Mp = FORM == P1_ROWS ? K_keep_ : FORM != P1_CUT ? K : Mp_;
+    auto place = [&](long long b, int ch, int k) __attribute__((always_inline)) {
+        return FORM == P1_ROWS ? b * batch + ch * channel + k : spec1d_index(b * Mp + k, ch, C);
+    };
     using Cf = CfgP1<N, K>;
     constexpr int LPR = Cf::LPR, PPS = Cf::PPS, KH = Cf::KH, CPL = Cf::CPL, OPL = Cf::OPL;
     constexpr bool WIDE = Cf::WIDE;
@@ -176,7 +180,7 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
                         if constexpr (REAL) {
                             if (kl + 16 * kh == 0) val = make_float2(0.5f * val.x, 0.5f * val.y);
                         }
-                        if (kl + 16 * kh < Mp) Xh[spec1d_index(b * Mp + kl + 16 * kh, ch, C)] = val;
+                        if (kl + 16 * kh < Mp) Xh[place(b, ch, kl + 16 * kh)] = val;
                     }
                 }
             }
@@ -215,7 +219,7 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
                     if constexpr (REAL) {
                         if (k == 0) val = make_float2(0.5f * val.x, 0.5f * val.y);
                     }
-                    if (k < Mp) Xh[spec1d_index(b * Mp + k, ch, C)] = val;
+                    if (k < Mp) Xh[place(b, ch, k)] = val;
                 }
             }
         }
@@ -308,7 +312,7 @@ __device__ __forceinline__ void p1_inverse(const LdsP1<N, K> &L, int tid, Kept k
 // as zeros where there are any).  y: [npencils, N] contiguous (pencil q = b * C + o).
 template <int N, int K, bool REAL, int FORM>
 __global__ void __launch_bounds__(256)
-k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npencils, int K_keep_, int Mp_)
+k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npencils, int K_keep_, int Mp_, long long channel)
 {
     static_assert(FORM != P1_FULL, "a full spectrum is read as it is");
     constexpr bool ALL = FORM == P1_ALL;
@@ -327,6 +331,13 @@ k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npenci
     auto load_spectrum = [&](long long sweep) __attribute__((always_inline)) {
         long long q = sweep * PPS + g;
         if (q >= npencils) q = npencils - 1;
+        if constexpr (FORM == P1_ROWS) {                    // (the pencil itself, before anything is written to it)
+            static_assert(WIDE || CPL == 1, "one column to a lane");
+            const c64 *src = y + q * channel + (WIDE ? kl_w : p);
+#pragma unroll
+            for (int kh = 0; kh < KH; ++kh) yin[kh] = src[(WIDE ? kl_w : p) + 16 * kh < K_keep ? 16 * kh : 0];
+            return;
+        }
         const long long b = q / C;
         const int ch = (int)(q % C);
 #pragma unroll

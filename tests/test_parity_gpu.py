@@ -433,6 +433,39 @@ def test_waves_that_own_their_slab(gpu, oracle_mod, case):
     close(yd.cpu().numpy().astype(np.float64), oracle_mod.spectral_conv1d_real(xr, W, K)[0], case)
 
 
+# 1024 points and few rows, spectra held in y: one, two and four input pencils to an output pencil, the last of them full and not, mode counts around
+# the tiles of 32 and both built sizes, channels around the steps of 8 and 32, a last slab with one output; the limits of the rule (rows, modes, no
+# room) on both sides.  (real, B, C_in, C_out, K)
+ROWS_IN_Y = [(False, 1, 1, 1, 1), (False, 2, 33, 33, 64), (False, 3, 9, 5, 65), (False, 2, 20, 5, 17), (False, 2, 21, 5, 17), (False, 3, 40, 20, 128), (False, 2, 17, 64, 32),
+             (False, 3, 130, 129, 100), (False, 97, 64, 64, 33), (False, 98, 64, 64, 33), (False, 2, 16, 16, 129), (True, 1, 1, 1, 1), (True, 2, 33, 33, 64), (True, 3, 9, 5, 65),
+             (True, 3, 10, 5, 128), (True, 3, 11, 5, 128), (True, 2, 40, 70, 97), (True, 146, 64, 64, 128), (True, 147, 64, 64, 128)]
+
+
+@pytest.mark.parametrize("case", ROWS_IN_Y, ids=lambda c: "%s_B%d_Ci%d_Co%d_K%d" % (("real" if c[0] else "complex",) + c[1:]))
+def test_few_rows_of_1024_points(gpu, oracle_mod, case):
+    """Bound: 10 steps of butterflies each way of about 0.7 units of 2^-24, and the contraction with 3 and one per 32 channels (130: 7 units):
+    sqrt(20 0.5 + 49) 2^-24 = 4.5e-7."""
+    torch, binding = gpu
+    real, B, Ci, Co, K = case
+    say(f"[case] rows in y {case}")
+    x = inputs.make_x(1650 + Ci, B, Ci, (1024,))
+    W = inputs.make_W(1650 + Ci, Ci, Co)
+    dtype, call, want = torch.complex64, binding.spectral_conv1d_auto, None
+    if real:
+        x, dtype, call = np.ascontiguousarray(x.real), torch.float32, binding.spectral_conv1d_real
+    want = (oracle_mod.spectral_conv1d_real if real else oracle_mod.spectral_conv1d)(x, W, K)[0]
+    n, pad = B * Co * 1024, 2 if real else 1                # y begins 8 bytes past a line
+    whole = torch.full((n + 2 * pad,), float("nan"), dtype=dtype, device="cuda")
+    y = whole[pad:pad + n].view(B, Co, 1024)
+    xd, Wd = torch.from_numpy(x).cuda(), torch.from_numpy(W).cuda()
+    for turn in range(2):                                   # (y holds the first call's result in the second)
+        call(xd, Wd, y, K)
+        got = y.cpu().numpy()
+        check(got.astype(np.float64 if real else np.complex128), want, "rows in y", rel_l2=4.5e-7)
+    guards = torch.view_as_real(whole)[..., 0] if not real else whole
+    assert bool(torch.isnan(guards[:pad]).all()) and bool(torch.isnan(guards[n + pad:]).all())
+
+
 # Every form of the matrix transform, by the sides it reads and writes.  (B, C_in, C_out, N1, N2, K1, K2); N1 = 1: 1-D
 MATDFT_FORMS = {
     "1-D, two output tiles per wave": (328, 100, 2, 1, 140, 1, 40), "1-D, three": (328, 100, 2, 1, 141, 1, 70), "1-D, four": (328, 100, 2, 1, 140, 1, 100),
