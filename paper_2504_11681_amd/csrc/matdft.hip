@@ -53,7 +53,11 @@ static hipError_t pick_fwd(const MatdftArgs &a, hipStream_t s)
     case 3: return launch_fwd<3, 1, IN, OUT, VEC>(a, s);
     case 2: return launch_fwd<2, 1, IN, OUT, VEC>(a, s);
     default:
-        return parts == 8 ? launch_fwd<1, 8, IN, OUT, VEC>(a, s) : parts == 4 ? launch_fwd<1, 4, IN, OUT, VEC>(a, s) : launch_fwd<1, 1, IN, OUT, VEC>(a, s);
+        // (1-D layers with so few pencils and 256 points or more run k_matrow_fwd)
+        if constexpr (!(IN == MD_ROWS && OUT == MD_SPEC)) {
+            if (parts == 8) return launch_fwd<1, 8, IN, OUT, VEC>(a, s);
+        }
+        return parts >= 4 ? launch_fwd<1, 4, IN, OUT, VEC>(a, s) : launch_fwd<1, 1, IN, OUT, VEC>(a, s);
     }
 }
 
