@@ -62,7 +62,11 @@ bool matgrid_supported(int dir, long long images, int N1, int N2, int K1, int K2
     if (images < 1 || images >= (1LL << 31)) return false;
     const Plan p = plan(dir, images, N1, N2, K1, K2);
     if (p.lds > MOST_LDS) return false;
-    if (images >= 256) return true;
+    // Two sixteens of rows take a wave's registers twice: with seven and eight waves to a workgroup one fits a CU (40 x 250, K 20 x 20, 600 fields: forward
+    // 19.4 -> 29.2 us, inverse 24.1 -> 28.9; 200 x 200, K 25 x 25, 400 fields: 52.1 -> 40.6, 56.0 -> 49.5), and its inverse stays a question of the
+    // chain up to two workgroups for every CU (220 x 56, K 25 x 8, 400 fields: 17.4 -> 21.2; 348 x 82, K 17 x 13, 486 fields: 45 -> 34).
+    if (K1 > 16 && N2 > 224) return false;
+    if (images >= (dir > 0 && K1 > 16 ? 512 : 256)) return true;
     const long long bytes = images * N1 * N2 * (long long)sizeof(c64);
     if (dir < 0) {
         const int turns = (N1 / 32 + p.parts) / p.parts;

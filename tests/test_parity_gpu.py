@@ -313,7 +313,7 @@ def test_2d_sides_with_odd_factors(gpu, oracle_mod, shape):
 # column, with two; sides of equal length (one root table); long sums on either axis; and one step outside (the kernel per axis)
 FIELD_2D = [(32, 8, 8, 30, 30, 1, 1), (32, 8, 8, 31, 33, 15, 16), (32, 8, 9, 33, 34, 16, 17), (16, 17, 16, 33, 65, 17, 16), (32, 8, 8, 50, 66, 32, 32),
             (2, 3, 5, 85, 85, 12, 12), (8, 9, 40, 85, 85, 12, 12), (1, 2, 3, 60, 50, 9, 9), (1, 3, 2, 45, 97, 10, 11), (33, 32, 32, 40, 96, 8, 9),
-            (8, 32, 33, 97, 129, 16, 20), (8, 32, 33, 63, 160, 17, 9), (4, 64, 65, 62, 255, 30, 31), (4, 64, 64, 36, 249, 9, 12), (16, 16, 16, 511, 41, 13, 9),
+            (8, 32, 33, 97, 129, 16, 20), (8, 32, 33, 63, 160, 17, 9), (4, 64, 65, 62, 255, 30, 31), (4, 128, 129, 62, 224, 30, 31), (4, 128, 128, 62, 225, 30, 31), (8, 32, 64, 220, 56, 25, 8), (8, 32, 63, 220, 56, 25, 8), (4, 64, 64, 36, 249, 9, 12), (16, 16, 16, 511, 41, 13, 9),
             (2, 128, 128, 500, 33, 32, 8), (2, 130, 128, 300, 130, 20, 21), (4, 33, 2, 194, 67, 16, 13),
             (32, 8, 8, 29, 33, 9, 9), (32, 8, 8, 33, 29, 9, 9), (32, 8, 8, 45, 45, 33, 9), (32, 8, 8, 45, 45, 9, 33), (16, 16, 16, 33, 257, 9, 9), (16, 16, 16, 513, 33, 9, 9),
             # (the inverse rows kernel in whole pencils by one and two waves, which odd grids of these sizes no longer run)
