@@ -65,7 +65,9 @@ bool matgrid_supported(int dir, long long images, int N1, int N2, int K1, int K2
     // Two sixteens of rows take a wave's registers twice: with seven and eight waves to a workgroup one fits a CU (40 x 250, K 20 x 20, 600 fields: forward
     // 19.4 -> 29.2 us, inverse 24.1 -> 28.9; 200 x 200, K 25 x 25, 400 fields: 52.1 -> 40.6, 56.0 -> 49.5), and its inverse stays a question of the
     // chain up to two workgroups for every CU (220 x 56, K 25 x 8, 400 fields: 17.4 -> 21.2; 348 x 82, K 17 x 13, 486 fields: 45 -> 34).
-    if (K1 > 16 && N2 > 224) return false;
+    // Four waves and more and fewer than two fields for every CU only pay with larger fields (132 x 160, K 19 x 20, 300 fields: 24.3 -> 31.0, 30.8 -> 35.0;
+    // 600 fields of 132 x 192 50.7 -> 49.0, 54.7 -> 54.0).
+    if (K1 > 16 && (N2 > 224 || (N2 > 128 && images < 512 && N1 * N2 < 32768))) return false;
     if (images >= (dir > 0 && K1 > 16 ? 512 : 256)) return true;
     const long long bytes = images * N1 * N2 * (long long)sizeof(c64);
     if (dir < 0) {
