@@ -232,7 +232,7 @@ k_fused1d(Fused1dArgs a)
     };
 
     // The last block with channels missing: what a wave or a step of the contraction has none for is left out (complex rows, N 256: B 300, 100 -> 250,
-    // 128 modes 178 -> 126 us; N 128: B 300, 130 -> 130, 64 modes 72.6 -> 62.5, B 163, 86 -> 10, 16 modes 10.0 -> 8.7; real rows, whose small layers
+    // 128 modes 169 -> 134 us; N 128: B 300, 130 -> 130, 64 modes 73.1 -> 56.6, B 163, 86 -> 10, 16 modes 10.0 -> 8.7; real rows, whose small layers
     // wait for one workgroup's chain, 3 to 7 % slower: only the steps are left out there).
     constexpr bool SKIP = !EVEN && BF && !REAL;
     auto load_pencil = [&](int c0) __attribute__((always_inline)) {
@@ -242,13 +242,10 @@ k_fused1d(Fused1dArgs a)
 #pragma unroll
             for (int jj = 0; jj < P; ++jj) v[jj] = widen(fetch(src + T * jj));
         } else if constexpr (SKIP) {
-            // Channels past C_in meet zero weights: the lanes of a wave that has some of both read channel 0 (finite wherever the result
-            // is), a wave that has none loads nothing.
-            if (c0 + wave_u * PPW < a.C_in) {
-                const XT *src = xb + (long long)(c < a.C_in ? c : 0) * a.x_chan_stride + t;
+            // (channels past C_in meet zero weights: their lanes read channel 0, finite wherever the result is)
+            const XT *src = xb + (long long)(c < a.C_in ? c : 0) * a.x_chan_stride + t;
 #pragma unroll
-                for (int jj = 0; jj < P; ++jj) v[jj] = widen(fetch(src + T * jj));
-            }
+            for (int jj = 0; jj < P; ++jj) v[jj] = widen(fetch(src + T * jj));
         } else {
             const bool ok = c < a.C_in;
             const XT *src = xb + (long long)(ok ? c : 0) * a.x_chan_stride + t;
@@ -292,25 +289,31 @@ k_fused1d(Fused1dArgs a)
     };
     // stage A: P-point transform of the slice in v, written transposed into the wave's Z tile
     // (with channels that leave a wave without any in the last block, that wave skips its transforms and puts zeros into the operand tile)
-    auto has_pencils = [&](int blk) __attribute__((always_inline)) { return !SKIP || blk * PPI + wave_u * PPW < a.C_in; };
-    auto stage_a = [&](int blk) __attribute__((always_inline)) {
-        if (!has_pencils(blk)) return;
+    // (only asked where the block may be the last: a branch in the loop would part the transforms from the matrix products that they run under,
+    // N 256, 148 -> 61 channels, 128 modes, B 173 37.5 -> 39.7 us)
+    auto has_pencils = [&](int blk) __attribute__((always_inline)) { return blk * PPI + wave_u * PPW < a.C_in; };
+    auto stage_a = [&](auto last, int blk) __attribute__((always_inline)) {
+        if constexpr (SKIP && decltype(last)::value) {
+            if (!has_pencils(blk)) return;
+        }
         c64 z[P];
         RegFFT<P, -1, 1>::run(v, z);
 #pragma unroll
         for (int p = 0; p < P; ++p) Zw[jw * ZS + p * ZROW + t] = z[p];
     };
     // stage B: twiddle, T-point transform pruned to the Q retained outputs of each column, into XH[buf]
-    auto stage_b = [&](int buf, int blk) __attribute__((always_inline)) {
+    auto stage_b = [&](auto last, int buf, int blk) __attribute__((always_inline)) {
         float *XHb = XH + buf * C::XH_BUF;
-        if (!has_pencils(blk)) {
+        if constexpr (SKIP && decltype(last)::value) {
+            if (!has_pencils(blk)) {
 #pragma unroll
-            for (int cc = 0; cc < CPL; ++cc) {
-                const int item = lane + 64 * cc;
+                for (int cc = 0; cc < CPL; ++cc) {
+                    const int item = lane + 64 * cc;
 #pragma unroll
-                for (int q = 0; q < Q; ++q) put_operand(XHb, wave * PPW + item / P, item % P + P * q, make_float2(0.f, 0.f));
+                    for (int q = 0; q < Q; ++q) put_operand(XHb, wave * PPW + item / P, item % P + P * q, make_float2(0.f, 0.f));
+                }
+                return;
             }
-            return;
         }
 #pragma unroll
         for (int cc = 0; cc < CPL; ++cc) {
@@ -459,10 +462,10 @@ k_fused1d(Fused1dArgs a)
         // (scheduling fences: left alone, the compiler sinks stage A into the MFMA sequence and the pencil loads
         // behind the closing barrier, which leaves them one stage B to arrive instead of a whole contraction)
         load_w(wv, it * PPI);
-        stage_b(0, it);
+        stage_b(std::integral_constant<bool, !DO_A>{}, 0, it);
         wave_sync();
         __syncthreads();
-        if constexpr (DO_A) { stage_a(it + 1); wave_sync(); }
+        if constexpr (DO_A) { stage_a(std::integral_constant<bool, !DO_LOAD>{}, it + 1); wave_sync(); }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (DO_LOAD) load_pencil((it + 2) * PPI);
         __builtin_amdgcn_sched_barrier(0);
@@ -484,8 +487,8 @@ k_fused1d(Fused1dArgs a)
         constexpr std::integral_constant<bool, !DO_B> last{};
         if constexpr (ALLT) mfma_block(cur, last, it);
         else if (has_tiles) mfma_block(cur, last, it);
-        if constexpr (DO_B) { stage_b(cur ^ 1, it + 1); wave_sync(); }
-        if constexpr (DO_A) { stage_a(it + 2); wave_sync(); }
+        if constexpr (DO_B) { stage_b(std::integral_constant<bool, !DO_A>{}, cur ^ 1, it + 1); wave_sync(); }
+        if constexpr (DO_A) { stage_a(std::integral_constant<bool, !DO_LOAD>{}, it + 2); wave_sync(); }
         if constexpr (DO_LOAD) load_pencil((it + 3) * PPI);
         if constexpr (DO_B) {
 #pragma unroll
@@ -500,7 +503,7 @@ k_fused1d(Fused1dArgs a)
     if constexpr (C::WIDE) {
         load_pencil(0);
         build_twiddles();
-        stage_a(0);
+        stage_a(yes, 0);
         wave_sync();
         if (n_it > 1) load_pencil(PPI);
         int it = 0;
@@ -511,13 +514,13 @@ k_fused1d(Fused1dArgs a)
         load_pencil(0);
         load_w(wv, 0);
         build_twiddles();
-        stage_a(0);
+        stage_a(yes, 0);
         wave_sync();
         if (n_it > 1) load_pencil(PPI);
-        stage_b(0, 0);
+        stage_b(yes, 0, 0);
         wave_sync();
         if (n_it > 1) {
-            stage_a(1);
+            stage_a(yes, 1);
             wave_sync();
             if (n_it > 2) load_pencil(2 * PPI);
         }
