@@ -506,6 +506,8 @@ template <int NSTEP, int NP, bool ROWS = false>
 __global__ void __launch_bounds__(256, 2)
 k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__restrict__ Yh, int C_in, int C_out, float scale, ModeRows rows)
 {
+    // (tiles: 32-bit offsets)
+    using Offset = std::conditional_t<ROWS, long long, int>;
     const int x_channel = ROWS ? rows.x_channel : 128, y_channel = ROWS ? rows.y_channel : 128;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, g = lane >> 5;
@@ -519,7 +521,7 @@ k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 
         for (int d = 0; d < 4; ++d) {
             const int c = c0 + 8 * i + 4 * g + d, cc = c < C_in ? c : 0;
             wq[i][d] = W[(long long)cc * C_out + o];
-            xq[i][d] = xsrc[(long long)cc * x_channel];
+            xq[i][d] = xsrc[(Offset)cc * x_channel];
         }
     };
     floatx16 acc_re, acc_im;
@@ -570,7 +572,7 @@ k_cgemm_modes_direct(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int oo = o0 + 8 * (r / 4) + 4 * g + (r % 4);
-        if (oo < C_out) Yb[(long long)oo * y_channel] = make_float2(acc_re[r], acc_im[r]);
+        if (oo < C_out) Yb[(Offset)oo * y_channel] = make_float2(acc_re[r], acc_im[r]);
     }
 }
 
