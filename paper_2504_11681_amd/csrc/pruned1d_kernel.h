@@ -72,14 +72,22 @@ __device__ __forceinline__ LdsP1<N, K> p1_setup(unsigned char *raw, int tid)
     return l;
 }
 
-// The twiddle tables, to be built while the first loads are on their way (about 1 us for 1024 points).
+// The twiddle tables.
 template <int N, int K>
 __device__ __forceinline__ void p1_tables(const LdsP1<N, K> &l, int tid)
 {
     using C = CfgP1<N, K>;
-    __builtin_amdgcn_sched_barrier(0);
     for (int i = tid; i < N; i += C::NT) l.tw[i] = cis2pi(-(float)((i / C::LPR) * (i % C::LPR)), (float)N);
     if (C::WIDE && tid < 64) l.tw64[tid] = cis2pi(-(float)tid, 64.f);
+}
+// The same while loads are on their way.  In the transform kernels up to 256 points (B 200, 30 -> 60 channels, real rows of 256, own weights, 32 modes: 19.9 -> 19.5 us the layer);
+// 1024 points take about 1 us for their tables, under which the kernel's arguments arrive as well when these come first (40 x 95 -> 96 channels, 8 modes: 23.5 us, behind
+// the loads 24.1; B 32, C 64, real rows, own weights, 16 modes 10.7 and 11.1).
+template <int N, int K>
+__device__ __forceinline__ void p1_tables_behind_loads(const LdsP1<N, K> &l, int tid)
+{
+    __builtin_amdgcn_sched_barrier(0);
+    p1_tables(l, tid);
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -119,6 +127,7 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
     __shared__ __align__(16) unsigned char raw[Cf::LDS_BYTES];
     const int tid = threadIdx.x;
     const LdsP1<N, K> L = p1_setup<N, K>(raw, tid);
+    if constexpr (WIDE) p1_tables(L, tid);
     const int g = tid / LPR, p = tid % LPR;
     const int kl_w = (tid & 63) >> 2, qa = tid & 3;         // wide path: column and quad position
 
@@ -162,8 +171,9 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
         wave_sync();
         const long long q = sweep * PPS + g;
         const bool ok = q < npencils;
-        const long long b = q / C;
-        const int ch = (int)(q % C);
+        // (fewer than 2^31 pencils: 32-bit division)
+        const unsigned b = (unsigned)q / (unsigned)C;
+        const int ch = (int)((unsigned)q - b * (unsigned)C);
         if constexpr (!WIDE) {
 #pragma unroll
             for (int i = 0; i < CPL; ++i) {
@@ -227,8 +237,8 @@ k_fwd1d(const c64 *__restrict__ x, c64 *__restrict__ Xh, int C, long long npenci
 
     if ((long long)blockIdx.x >= nsweeps) return;           // uniform per workgroup; no barrier has been reached
     load_pencil(blockIdx.x);
-    p1_tables(L, tid);
-    __syncthreads();
+    if constexpr (!WIDE) p1_tables_behind_loads(L, tid);
+    __syncthreads();                                        // twiddle tables are ready
     long long sweep = blockIdx.x;
     for (; sweep + gridDim.x < nsweeps; sweep += gridDim.x) stage(sweep, std::true_type{}, sweep + gridDim.x);
     stage(sweep, std::false_type{}, 0);
@@ -323,6 +333,7 @@ k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npenci
     __shared__ __align__(16) unsigned char raw[Cf::LDS_BYTES];
     const int tid = threadIdx.x;
     const LdsP1<N, K> L = p1_setup<N, K>(raw, tid);
+    if constexpr (WIDE) p1_tables(L, tid);
     const int g = tid / LPR, p = tid % LPR;
     const int kl_w = (tid & 63) >> 2, qa = tid & 3;
 
@@ -338,15 +349,16 @@ k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npenci
             for (int kh = 0; kh < KH; ++kh) yin[kh] = src[(WIDE ? kl_w : p) + 16 * kh < K_keep ? 16 * kh : 0];
             return;
         }
-        const long long b = q / C;
-        const int ch = (int)(q % C);
+        // (fewer than 2^31 pencils: 32-bit division)
+        const unsigned b = (unsigned)q / (unsigned)C;
+        const int ch = (int)((unsigned)q - b * (unsigned)C);
 #pragma unroll
         for (int i = 0; i < CPL; ++i)
 #pragma unroll
             for (int kh = 0; kh < KH; ++kh) {
                 const int kl = WIDE ? kl_w : p + LPR * i;
                 const int k = kl + 16 * kh;
-                yin[i * KH + kh] = Yh[spec1d_index(b * Mp + (ALL || k < K_keep ? k : 0), ch, C)];
+                yin[i * KH + kh] = Yh[spec1d_index((long long)b * Mp + (ALL || k < K_keep ? k : 0), ch, C)];
             }
     };
     // Bins that are not kept become zeros where the loaded values are used, a sweep later: done beside the load, the select
@@ -365,8 +377,8 @@ k_inv1d(const c64 *__restrict__ Yh, c64 *__restrict__ y, int C, long long npenci
 
     if ((long long)blockIdx.x >= nsweeps) return;
     load_spectrum(blockIdx.x);
-    p1_tables(L, tid);
-    __syncthreads();
+    if constexpr (!WIDE) p1_tables_behind_loads(L, tid);
+    __syncthreads();                                        // twiddle tables are ready
     long long sweep = blockIdx.x;
     for (; sweep + gridDim.x < nsweeps; sweep += gridDim.x) stage(sweep, std::true_type{}, sweep + gridDim.x);
     stage(sweep, std::false_type{}, 0);
@@ -421,7 +433,7 @@ k_inv1d_permode(const c64 *__restrict__ Xh, const c64 *__restrict__ W, c64 *__re
                 }
             __builtin_amdgcn_sched_barrier(0);
             if (!tables) {
-                p1_tables(L, tid);
+                p1_tables_behind_loads(L, tid);
                 tables = true;
             }
             c64 sum[R];

@@ -31,3 +31,17 @@ def test_the_direct_contraction_of_tiles_addresses_with_32_bits(tmp_path):
                                    "template __global__ void k_cgemm_modes_direct<2, 8>(const c64 *, const c64 *, c64 *, int, int, float, ModeRows);").items():
         assert "v_mfma_f32_32x32x16_bf16" in code, name
         assert code.count("v_lshlrev_b64") == 0, (name, code.count("v_lshlrev_b64"))
+
+
+def test_pruned_kernels_of_1024_points_build_their_tables_first_and_divide_in_32_bits(tmp_path):
+    """The pencil of a lane is taken apart into batch element and channel with a 32-bit division (a 64-bit one is some 120 instructions
+    before the first load; its estimate is a v_rcp_f32), and the twiddle tables are under way before the first load of the field: behind the loads
+    both kernels of an 1024-point layer were 0.2 - 0.6 us slower."""
+    code = instructions(tmp_path, "pruned1d_kernel.h", "".join(
+        f"template __global__ void k_fwd1d<1024, 64, {real}, 0>(const c64 *, c64 *, int, long long, int, int, long long, long long);\n"
+        f"template __global__ void k_inv1d<1024, 64, {real}, 0>(const c64 *, c64 *, int, long long, int, int, long long);\n" for real in ("true", "false")))
+    assert len(code) == 4
+    for name, ins in code.items():
+        assert not [i for i in ins if i.startswith("v_rcp_f32")], name
+        first = {kind: next(k for k, i in enumerate(ins) if i.startswith(kind)) for kind in ("ds_write", "global_load")}
+        assert first["ds_write"] < first["global_load"], (name, first)
