@@ -302,9 +302,12 @@ static int channels_per_pencil(bool real, int C_in, int C_out)
 // A fused workgroup takes its row's channels 8 at a time, 0.42 us per channel however few rows there are; the three kernels take about as long as their
 // bytes at 4 TB/s, and both some 9 us besides (fused and three kernels, us: B 4, C 32, K 64 23 and 12; B 48, C 128 56 and 33; B 48, 200 -> 100 91 and 44; B 100,
 // C 32 23 and 20, 16 -> 64 18.7 and 20.9; real rows, C 128, B 90 65 and 41, B 180, on the symmetric kernel, 73 and 83).
+// Up to 8 channels are one step of a fused workgroup, and three launches cost more than what its few slabs of outputs wait for (1 -> 1 channels, B 13, K 5, real
+// rows 8.8 and 11.6; 8 -> 2, B 5, K 43 10.4 and 11.6; 8 -> 13, B 3, K 5 13.0 and 11.9).
 bool pruned1d_in_y_supported(bool real, long long B, int C_in, int C_out, int N, int K_keep)
 {
     if (N != 1024 || K_keep < 1 || K_keep > 128 || B >= (1LL << 24) || !channels_per_pencil(real, C_in, C_out)) return false;
+    if (C_in <= 8 && C_out <= (real ? 16 : 8)) return false;
     const double bytes = (real ? 4.0 : 8.0) * N * (double)B * ((double)C_in + C_out);
     return bytes <= (real ? 1.2e6 : 1.6e6) * C_in;
 }
