@@ -241,12 +241,17 @@ static int permode_outputs(long long B, int C_out, int N, int Ma)
 // launch and the latency that are saved weigh more (whole layers, two kernels after the forward transform against one: B 32, 64 x 64 channels, N 1024, 16
 // modes, 16.8 MB, 512 workgroups 13.6 and 10.9 us; B 15, 22 -> 41, N 64, 13 modes 11.6 and 8.7; B 11, 82 -> 72, N 128, 39 modes, 20.3 MB 11.9 and 13.1; B 8,
 // 15 -> 98, N 256, 79 modes, 784 workgroups 11.5 and 11.9; B 182, 13 -> 32, N 128, 16 modes, 728 workgroups 11.5 and 8.8; B 54, 62 -> 96, N 256, 45 modes, 116 MB 19.9 and 31.4).
+// A wave walks a quarter of the channels, 16 at a time, or 8 with results for two lanes each, where a contraction of its own spreads them over the chip: up to two steps
+// of the latter, three of the former, eight where no workgroup waits for a CU (in a graph, two kernels and one: B 3, 186 -> 2, N 256, 90 modes 13.0 and 16.4; B 10, 95 -> 11, N 256,
+// 103 modes, 110 workgroups 14.3 and 13.5; B 8, 636 -> 45, N 64, 3 modes, 360 workgroups 19.1 and 26.3; B 9, 373 -> 76, N 128, 7 modes, 342 workgroups 15.5 and 18.7; B 20, 166 -> 10, N 64,
+// 15 modes, 200 workgroups 11.9 and 9.9; B 7, 365 -> 31, N 128, 7 modes, 217 workgroups 14.9 and 13.1; 2000 channels up to 2.1 times as slow).
 bool pruned1d_permode_fused(long long B, int C_in, int C_out, int N, int K, int Ma)
 {
     if (N > 1024 || !pruned1d_supported(N, K) || Ma > 256) return false;
     if (B > 768 || B * C_out > (1LL << 24) || B * C_in * C_out * (long long)Ma * (long long)sizeof(c64) > 20000000) return false;
     const int G = permode_outputs(B, C_out, N, Ma);
-    return B * ((C_out + G - 1) / G) <= 768;
+    const long long workgroups = B * ((C_out + G - 1) / G);
+    return workgroups <= 768 && C_in <= (G * Ma > 64 ? 64 : workgroups > 256 ? 192 : 512);
 }
 
 template <int N, int K, bool REAL>

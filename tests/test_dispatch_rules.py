@@ -23,3 +23,13 @@ def rule(name, *types, result=cb):
 def test_rows_of_1024_points_held_in_y(case, on):
     real, B, Ci, Co, K = case
     assert rule("_ZN4tfno23pruned1d_in_y_supportedEbxiiii", cb, ll, ci, ci, ci, ci)(real, B, Ci, Co, 1024, K) == on
+
+
+# (B, C_in, C_out, N, kernels' K, modes): own weights per mode, contraction and inverse in one kernel
+@pytest.mark.parametrize("case,on", [((3, 186, 2, 256, 128, 90), False), ((5, 106, 12, 256, 128, 90), False), ((25, 89, 29, 128, 64, 37), False), ((8, 636, 45, 64, 16, 3), False),
+                                     ((9, 373, 76, 128, 16, 7), False), ((2, 1800, 3, 256, 16, 12), False),
+                                     ((6, 64, 25, 256, 128, 69), True), ((20, 166, 10, 64, 16, 15), True), ((7, 365, 31, 128, 16, 7), True), ((32, 64, 64, 1024, 64, 16), True),
+                                     ((6, 65, 25, 256, 128, 69), False), ((30, 192, 16, 128, 16, 1), True), ((30, 193, 16, 128, 16, 1), False),
+                                     ((7, 512, 31, 128, 16, 7), True), ((7, 513, 31, 128, 16, 7), False)], ids=str)
+def test_small_layers_with_own_weights_in_one_kernel(case, on):
+    assert rule("_ZN4tfno22pruned1d_permode_fusedExiiiii", ll, ci, ci, ci, ci, ci)(*case) == on
