@@ -34,6 +34,8 @@ hipError_t fused1d_launch(int N, int K, const Fused1dArgs &a, long long batch_ro
 bool contraction_forced_f32();
 // True when the environment asks for the four-wave double-buffered kernel everywhere (TFNO_KERNEL=generic).
 bool generic_kernels_forced();
+// Slabs of 32 outputs to a workgroup of eight waves for real rows of 256 points where there are few workgroups; 0: four waves.
+int fused1d_real_eight_waves(int K, long long rows, int C_in, int C_out);
 // True when it asks for nothing (TFNO_KERNEL, TFNO_CONTRACTION).
 bool default_kernels();
 

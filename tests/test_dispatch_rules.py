@@ -33,3 +33,11 @@ def test_rows_of_1024_points_held_in_y(case, on):
                                      ((7, 512, 31, 128, 16, 7), True), ((7, 513, 31, 128, 16, 7), False)], ids=str)
 def test_small_layers_with_own_weights_in_one_kernel(case, on):
     assert rule("_ZN4tfno22pruned1d_permode_fusedExiiiii", ll, ci, ci, ci, ci, ci)(*case) == on
+
+
+# (K, rows, C_in, C_out): real rows of 256 points, slabs of a workgroup of eight waves (0: four waves)
+@pytest.mark.parametrize("case,slabs", [((64, 14, 2, 1), 0), ((64, 2, 16, 32), 0), ((128, 1, 7, 2), 0), ((128, 8, 8, 33), 0),
+                                        ((64, 23, 17, 7), 1), ((128, 8, 9, 33), 1), ((32, 2, 3, 2), 1), ((64, 64, 64, 64), 1), ((64, 200, 9, 64), 2), ((128, 200, 64, 64), 0),
+                                        ((64, 257, 64, 64), 0), ((16, 4, 64, 64), 0)], ids=str)
+def test_eight_waves_for_few_real_rows_of_256_points(case, slabs):
+    assert rule("_ZN4tfno24fused1d_real_eight_wavesEixii", ci, ll, ci, ci, result=ci)(*case) == slabs
