@@ -53,7 +53,8 @@ static hipError_t pick_fwd(const MatdftArgs &a, hipStream_t s)
     case 3: return launch_fwd<3, 1, IN, OUT, VEC>(a, s);
     case 2: return launch_fwd<2, 1, IN, OUT, VEC>(a, s);
     default:
-        // (1-D layers with so few pencils and 256 points or more run k_matrow_fwd)
+        // (1-D layers with so few pencils and 256 points or more run k_matrow_fwd, but for 1025 to 1632 pencils with more than 128 modes, for which four
+        // parts measured level with eight: 11 x 99 pencils, 200 modes, 398 to 2411 points 34.1 against 33.7 to 53.8 against 54.8 us the layer)
         if constexpr (!(IN == MD_ROWS && OUT == MD_SPEC)) {
             if (parts == 8) return launch_fwd<1, 8, IN, OUT, VEC>(a, s);
         }

@@ -15,6 +15,7 @@ int forward_tiles(long long P, int K)
     const int all = (K + 15) / 16, most = (P + 15) / 16 * ((all + 1) / 2) <= 128 ? 2 : 4, groups = (all + most - 1) / most;
     return (all + groups - 1) / groups;
 }
+int forward_groups(long long P, int K) { return ((K + 15) / 16 + forward_tiles(P, K) - 1) / forward_tiles(P, K); }
 size_t forward_lds(long long P, int N, int K) { return MG_ROOT * (size_t)N + sizeof(c64) * forward_parts(N) * 256 * forward_tiles(P, K); }
 
 struct Inverse { int waves, parts, groups; size_t lds; };
@@ -46,13 +47,19 @@ Kernel pick_fwd(int KT)
 
 bool matrow_forward_supported(long long B, int C_in, int N, int K)
 {
+    const long long P = B * C_in;
+    if (N < 32 || N > 4096 || P < 1 || P > 16383 || forward_lds(P, N, K) > MOST_LDS) return false;
     // (few pencils: with 16384 of them and more the transform of one sum per wave has the chip full, 256 x 64 pencils of 500 points, 60 modes
     // 25 against 30 us; 64 x 128 of 500 points, 64 modes 16.0 -> 15.4, 64 x 40 of 1000, 50 modes 12.7 -> 11.1, 5 x 71 of 162, 9 modes 5.9 -> 4.0)
-    // Short sums, which a wave gets through by itself, lose earlier (700 x 20 pencils of 130 points, 60 modes: the layer 45.6 -> 52.2; 64 x 128 of 50
-    // points, 12 modes 22.6 -> 11.8), and earlier still with more than 64 modes: those are several groups of waves, each of which fetches and folds
-    // the pencils again (33 x 128 of 130 points, 96 modes: 31.4 -> 35.9).
-    const long long most = N >= 256 ? 16383 : K <= 64 ? 8192 : 4096;
-    return N >= 32 && N <= 4096 && B * C_in <= most && forward_lds(B * C_in, N, K) <= MOST_LDS;
+    // More than 64 modes are several workgroups to a tile of pencils, each of which fetches and folds them again, one to a CU: ahead while all
+    // are there at once, or from 512 points on nearly fill a second round (whole layers: 33 x 33 pencils of 398 points, 195 modes, 276 workgroups 29.2 against 33.3;
+    // 76 x 166 of 581, 241 modes 88 against 119; 67 x 34 of 977, 152 modes, 429 workgroups 61.3 -> 57.8).
+    const long long workgroups = (P + 15) / 16 * forward_groups(P, K);
+    if (forward_groups(P, K) > 1) return workgroups <= 256 || (N >= 512 && workgroups > 384 && workgroups <= 512);
+    // Short sums, which a wave gets through by itself, lose earlier, with more modes sooner (whole layers: 103 x 43 of 203 points, 35 modes 14.5 against 16.6;
+    // 29 x 163 of 130, 55 modes 18.5 and 21.8; 189 x 52 of 304, 50 modes 25.7 and 27.3; 64 x 128 of 50, 12 modes 22.6 -> 11.8).
+    if (N < 256) return P <= (K <= 16 ? 8192 : 4096);
+    return N >= 512 || K <= 32 || P <= 8192;
 }
 
 hipError_t matrow_forward(const MatrowArgs &args, hipStream_t s)

@@ -41,3 +41,13 @@ def test_small_layers_with_own_weights_in_one_kernel(case, on):
                                         ((64, 257, 64, 64), 0), ((16, 4, 64, 64), 0)], ids=str)
 def test_eight_waves_for_few_real_rows_of_256_points(case, slabs):
     assert rule("_ZN4tfno24fused1d_real_eight_wavesEixii", ci, ll, ci, ci, result=ci)(*case) == slabs
+
+
+# (B, C_in, N, K): lengths that are no powers of two, forward kernel of 16 pencils per workgroup
+@pytest.mark.parametrize("case,on", [((76, 166, 581, 241), False), ((83, 73, 1026, 262), False), ((139, 89, 434, 179), False), ((459, 33, 476, 133), False), ((33, 33, 398, 195), False),
+                                     ((11, 99, 2411, 200), False), ((103, 43, 203, 35), False), ((29, 163, 130, 55), False), ((189, 52, 304, 50), False),
+                                     ((67, 34, 977, 152), True), ((67, 34, 400, 152), False), ((64, 128, 500, 64), True), ((64, 40, 1000, 50), True), ((5, 71, 162, 9), True),
+                                     ((64, 128, 50, 12), True), ((64, 64, 300, 128), False), ((32, 64, 300, 128), True), ((64, 64, 130, 60), True), ((65, 64, 130, 60), False),
+                                     ((128, 64, 130, 16), True), ((129, 64, 130, 16), False), ((256, 64, 600, 50), False), ((255, 64, 600, 50), True)], ids=str)
+def test_forward_transform_of_few_pencils_of_odd_length(case, on):
+    assert rule("_ZN4tfno24matrow_forward_supportedExiii", ll, ci, ci, ci)(*case) == on
