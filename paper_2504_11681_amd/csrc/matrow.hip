@@ -85,15 +85,22 @@ bool matrow_inverse_supported(long long B, int C_in, int C_out, int N, int K)
 {
     if (N < 32 || N > 4096 || K > 32 * MR_WAVES) return false;
     if ((long long)C_in * C_out >= (1LL << 28) || (long long)C_in * 128 >= (1LL << 28) || B * C_out >= (1LL << 31) / 32) return false;
-    // Many modes leave two waves or one to a sum over the channels, and one workgroup to a CU: with many channels then a contraction for
-    // all workgroups is ahead (B 64, C 128, N 1000, K 100: 51.5 against 58 us; B 16, C 200, N 500, K 200: 37 against 42; but 16 -> 128
-    // channels, N 700, K 90: 34 against 29)
-    if (K > 64 && C_in > 64 && (C_in > 128 || B * ((C_out + 31) / 32) > 128)) return false;
-    // Slabs of 32 outputs that are a quarter padding and more, four to a CU and more (B 2048, C 16, N 200, K 20: the layer 37.2 -> 42.6; B 512,
-    // C 64, N 100, K 20: 29.8 -> 26.0)
-    const long long slabs = (C_out + 31) / 32;
-    if (B * slabs >= 1024 && 4 * C_out < 3 * 32 * slabs) return false;
-    return inverse_plan(B, C_in, C_out, N, K).lds <= MOST_LDS;
+    const Inverse p = inverse_plan(B, C_in, C_out, N, K);
+    if (p.lds > MOST_LDS) return false;
+    // A wave's share of the channels is one chain: with many modes, two waves or one to a sum, a contraction for all workgroups is ahead past 128 channels
+    // (3 x 257 -> 13 channels, N 551, K 169: 42.3 and 45.6 us the layer).
+    const long long slabs = (C_out + 31) / 32, steps = (C_in + 7) / 8;
+    if (steps > 16 * p.parts) return false;
+    // What is done beside the layer, for every CU.  The slab of a batch element is 32 outputs and whole tiles of 32 modes; separate kernels lay the outputs
+    // (modes) of all batch elements side by side, and contract once where here every group of workgroups does.  In tiles of 32 outputs x 64 points x 16 modes (0.16 us)
+    // and of 8 channels x 32 modes x 32 outputs (0.1 us), against some 4 us for the launch and the pass over memory that go: 617 batch elements, 1 -> 1 channels, N 1713,
+    // K 121, 504 tiles beside the layer, 34.8 and 114 us; 282, 3 -> 10, N 1307, K 153 44.0 and 83.6; 547, 224 -> 269, N 77, K 4 71 and 112; 42, 44 -> 1,
+    // N 1954, K 74, 24 tiles 30.5 and 26.6; 453, 2 -> 17, N 273, K 50, 17 tiles 25.2 and 21.5.  Less where they come in several rounds, the last of them short: 571, 1 -> 5, N 291,
+    // K 2, 9 tiles 14.5 and 18.6; 140, 90 -> 44, N 235, K 105, 10 tiles 40.6 and 47.0.
+    const long long pairs = (long long)(N / 64 + 1) * mr_steps(K), mt = (K + 31) / 32, workgroups = B * slabs * p.groups;
+    const double tiles = (double)(B * slabs - (B * C_out + 31) / 32) * pairs / 256;
+    const double sums = (double)(workgroups * mt - (B * K + 127) / 128 * 4 * slabs) * steps / 256;
+    return workgroups * p.waves > 256 * MR_WAVES ? tiles <= 5 && sums <= 40 : tiles <= 25 && sums <= 80;
 }
 
 hipError_t matrow_inverse(const MatrowArgs &args, hipStream_t s)
