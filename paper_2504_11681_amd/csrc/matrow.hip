@@ -93,14 +93,16 @@ bool matrow_inverse_supported(long long B, int C_in, int C_out, int N, int K)
     if (steps > 16 * p.parts) return false;
     // What is done beside the layer, for every CU.  The slab of a batch element is 32 outputs and whole tiles of 32 modes; separate kernels lay the outputs
     // (modes) of all batch elements side by side, and contract once where here every group of workgroups does.  In tiles of 32 outputs x 64 points x 16 modes (0.16 us)
-    // and of 8 channels x 32 modes x 32 outputs (0.1 us), against some 4 us for the launch and the pass over memory that go: 617 batch elements, 1 -> 1 channels, N 1713,
-    // K 121, 504 tiles beside the layer, 34.8 and 114 us; 282, 3 -> 10, N 1307, K 153 44.0 and 83.6; 547, 224 -> 269, N 77, K 4 71 and 112; 42, 44 -> 1,
-    // N 1954, K 74, 24 tiles 30.5 and 26.6; 453, 2 -> 17, N 273, K 50, 17 tiles 25.2 and 21.5.  Less where they come in several rounds, the last of them short: 571, 1 -> 5, N 291,
-    // K 2, 9 tiles 14.5 and 18.6; 140, 90 -> 44, N 235, K 105, 10 tiles 40.6 and 47.0.
+    // and of 8 channels x 32 modes x 32 outputs (0.1 us), against some 4.5 us for a launch and the pass over the contracted spectrum that go: 617 batch elements, 1 -> 1 channels,
+    // N 1713, K 121, 504 tiles beside the layer, 34.8 and 114 us; 282, 3 -> 10, N 1307, K 153 44.0 and 83.6; 547, 224 -> 269, N 77, K 4, 468 sums 71 and 112; 42, 44 -> 1,
+    // N 1954, K 74, 24 tiles 30.5 and 26.6.  Several rounds of workgroups cost their latency besides (571, 1 -> 5, N 291, K 2, 9 tiles, two rounds 14.5 and 18.6; 453, 2 -> 17, N 273, K 50,
+    // 17 tiles 25.2 and 21.5; 145, 3 -> 244, N 447, K 98, 10 tiles, five rounds 98.6 and 62.5).  Of 2400 drawn layers 21 are more than 3 % slower than with kernels of their own.
     const long long pairs = (long long)(N / 64 + 1) * mr_steps(K), mt = (K + 31) / 32, workgroups = B * slabs * p.groups;
-    const double tiles = (double)(B * slabs - (B * C_out + 31) / 32) * pairs / 256;
-    const double sums = (double)(workgroups * mt - (B * K + 127) / 128 * 4 * slabs) * steps / 256;
-    return workgroups * p.waves > 256 * MR_WAVES ? tiles <= 5 && sums <= 40 : tiles <= 25 && sums <= 80;
+    const double tiles = (double)(B * slabs - (B * C_out + 31) / 32) * pairs / 256, sums = (double)(workgroups * mt - (B * K + 127) / 128 * 4 * slabs) * steps / 256;
+    const int by_waves = 12 / p.waves, by_lds = (int)(MOST_LDS / p.lds), resident = 256 * (by_waves < 1 ? 1 : by_waves < by_lds ? by_waves : by_lds);
+    const double rounds = (double)((workgroups + resident - 1) / resident);
+    const double out_us = (double)B * C_out * N * sizeof(c64) / 5e6, spectrum_us = (double)B * C_out * K * 2 * sizeof(c64) / 5e6;
+    return sums <= 80 && (rounds > 1.0 ? 2.0 + rounds : 0.0) + 0.16 * tiles <= 4.5 + 1.5 * spectrum_us + 0.1 * out_us;
 }
 
 hipError_t matrow_inverse(const MatrowArgs &args, hipStream_t s)

@@ -56,8 +56,8 @@ def test_forward_transform_of_few_pencils_of_odd_length(case, on):
 # (B, C_in, C_out, N, K): lengths that are no powers of two, contraction and inverse in one kernel
 @pytest.mark.parametrize("case,on", [((617, 1, 1, 1713, 121), False), ((208, 1, 2, 3169, 117), False), ((282, 3, 10, 1307, 153), False), ((88, 1, 33, 1286, 184), False),
                                      ((895, 7, 3, 338, 116), False), ((547, 224, 269, 77, 4), False), ((985, 111, 221, 46, 1), False),
-                                     ((571, 1, 5, 291, 2), False), ((140, 90, 44, 235, 105), False), ((3, 257, 13, 551, 169), False), ((1, 129, 32, 551, 169), False), ((2, 1100, 32, 1000, 20), False),
-                                     ((42, 44, 1, 1954, 74), True), ((453, 2, 17, 273, 50), False), ((64, 40, 56, 1000, 50), True), ((8, 69, 72, 116, 12), True), ((2, 3, 5, 600, 192), True),
+                                     ((571, 1, 5, 291, 2), False), ((3, 257, 13, 551, 169), False), ((1, 129, 32, 551, 169), False), ((2, 1100, 32, 1000, 20), False),
+                                     ((42, 44, 1, 1954, 74), True), ((145, 3, 244, 447, 98), True), ((228, 68, 172, 215, 34), True), ((453, 2, 17, 273, 50), True), ((64, 40, 56, 1000, 50), True), ((8, 69, 72, 116, 12), True), ((2, 3, 5, 600, 192), True),
                                      ((1, 128, 32, 551, 169), True), ((2, 1024, 32, 1000, 20), True), ((2, 3, 5, 600, 257), False), ((2, 4, 5, 31, 9), False)], ids=str)
 def test_contraction_and_inverse_of_odd_lengths_in_one_kernel(case, on):
     assert rule("_ZN4tfno24matrow_inverse_supportedExiiii", ll, ci, ci, ci, ci)(*case) == on
