@@ -31,6 +31,8 @@ Plan plan(int dir, long long images, int N1, int N2, int K1, int K2)
     return p;
 }
 
+bool forward_long(int N1, int N2, const Plan &p) { return N1 / 32 + 1 > 3 * p.parts || N2 / 32 + 1 > 3 * p.parts2; }
+
 typedef void (*Kernel)(MatgridArgs);
 template <bool LONG>
 Kernel pick_fwd(int K1, int K2)
@@ -44,17 +46,25 @@ Kernel pick(int dir, int N1, int N2, int K1, int K2, const Plan &p)
         if (K1 <= 16) return N2 > 128 ? k_matgrid_inv<2, 1, 4> : k_matgrid_inv<2, 1, 3>;
         return p.RG == 2 ? k_matgrid_inv<2, 2, 3> : k_matgrid_inv<1, 2, 3>;
     }
-    const bool LONG = N1 / 32 + 1 > 3 * p.parts || N2 / 32 + 1 > 3 * p.parts2;
-    return LONG ? pick_fwd<true>(K1, K2) : pick_fwd<false>(K1, K2);
+    return forward_long(N1, N2, p) ? pick_fwd<true>(K1, K2) : pick_fwd<false>(K1, K2);
 }
 }  // namespace
 
-// From a workgroup for every CU on the field kernels are ahead of a kernel per axis (85 x 85, K 12 x 12, 1024 fields each way: forward
-// 25.2 -> 14.5 us, inverse 29.9 -> 18.7; 158 x 131, 594 and 342 fields: 46.6 -> 34.1, 31.2 -> 19.8; the worst of 47 drawn shapes 71 x 149: inverse
-// 20.8 -> 22.9).  Fewer fields are a question of the longest chain: a kernel per axis spreads one field over many workgroups and
-// takes about 9 us and what its bytes cost, a field's workgroup takes its blocks of 32 rows (forward) or its tiles of 32
-// output pairs (inverse) in turn.  In tenths of a microsecond, from the same measurements: 300 x 300, 8 fields 13.0 against 37 us, 85 x 85,
-// 8 fields 9.0 against 7.1, 200 x 120, K 32 x 17, 32 fields 11.6 against 12.2, 126 fields 16.7 against 13.3.
+// Waves of the chosen kernel that a SIMD holds, from its registers.
+static int waves_per_simd(int dir, int N1, int N2, int K1, const Plan &p)
+{
+    if (dir > 0) return K1 <= 16 && N2 > 128 ? 4 : 3;
+    const bool LONG = forward_long(N1, N2, p);
+    return LONG ? (K1 > 16 ? 2 : 3) : K1 > 16 ? 3 : 4;
+}
+
+// Which is faster for a direction, these kernels or a kernel per axis, is a question of rounds and of the longest chain: a field's workgroup takes its blocks of 32 rows
+// (forward) or its tiles of 32 output pairs (inverse) in turn, and what a last short round leaves idle is lost, while a kernel per axis spreads each field over
+// many workgroups and takes a launch more and what its bytes cost.  In microseconds, fitted to whole layers with both kinds of kernels for either direction (3350 drawn shapes of 30 to
+// 512 x 30 to 480 points, 1 to 4500 fields): chosen like this they take 0.838 of the time of kernels per axis (the best of the four combinations 0.833), and 20 of them are more than
+// 3 % slower, at most 12 %.  85 x 85, K 12 x 12, 1024 fields each way: forward 25.2 -> 14.5 us, inverse 29.9 -> 18.7; 158 x 131, 594 and 342
+// fields: 46.6 -> 34.1, 31.2 -> 19.8; 300 x 300, 8 fields 13.0 against 37 us; whole layers with an inverse by these kernels at 320 fields of 273 x 133, K 28 x 8, two rounds, the second
+// a quarter full, 55.1 and 77.3, and a forward transform at 1805 of 77 x 141, K 18 x 10, 66.7 and 93.8.
 // More than 256 columns go to a kernel per axis: two column tiles to a wave measured 13 % slower to 25 % faster, without a clear line.
 bool matgrid_supported(int dir, long long images, int N1, int N2, int K1, int K2)
 {
@@ -62,20 +72,19 @@ bool matgrid_supported(int dir, long long images, int N1, int N2, int K1, int K2
     if (images < 1 || images >= (1LL << 31)) return false;
     const Plan p = plan(dir, images, N1, N2, K1, K2);
     if (p.lds > MOST_LDS) return false;
-    // Two sixteens of rows take a wave's registers twice: with seven and eight waves to a workgroup one fits a CU (40 x 250, K 20 x 20, 600 fields: forward
-    // 19.4 -> 29.2 us, inverse 24.1 -> 28.9; 200 x 200, K 25 x 25, 400 fields: 52.1 -> 40.6, 56.0 -> 49.5), and its inverse stays a question of the
-    // chain up to two workgroups for every CU (220 x 56, K 25 x 8, 400 fields: 17.4 -> 21.2; 348 x 82, K 17 x 13, 486 fields: 45 -> 34).
-    // Four waves and more and fewer than two fields for every CU only pay with larger fields (132 x 160, K 19 x 20, 300 fields: 24.3 -> 31.0, 30.8 -> 35.0;
-    // 600 fields of 132 x 192 50.7 -> 49.0, 54.7 -> 54.0).
-    if (K1 > 16 && (N2 > 224 || (N2 > 128 && images < 512 && N1 * N2 < 32768))) return false;
-    if (images >= (dir > 0 && K1 > 16 ? 512 : 256)) return true;
-    const long long bytes = images * N1 * N2 * (long long)sizeof(c64);
+    // (workgroups of up to four waves fill the SIMDs' places one by one; of a larger one some SIMD holds two waves, always the same: 273 x 133, K 28 x 8, five waves at three to a
+    // SIMD, 256, 270, 512 and 530 fields 46.5, 74.1, 74.6 and 101.7 us the layer)
+    const int simd = waves_per_simd(dir, N1, N2, K1, p), by_waves = p.waves <= 4 ? 4 * simd / p.waves : simd / ((p.waves + 3) / 4), by_lds = (int)(MOST_LDS / p.lds);
+    const long long resident = 256LL * (by_waves < 1 ? 1 : by_waves < by_lds ? by_waves : by_lds);
+    const double rounds = (double)((images + resident - 1) / resident);
+    const double field_us = (double)images * N1 * N2 * sizeof(c64) / 5e6, half_us = (double)images * N1 * K2 * 2 * sizeof(c64) / 5e6;
+    const int two1 = K1 > 16 ? 2 : 1, two2 = K2 > 16 ? 2 : 1;
     if (dir < 0) {
-        const int turns = (N1 / 32 + p.parts) / p.parts;
-        return turns * (K1 > 16 ? 21 : 16) <= 45 + bytes / 260000;
+        const int columns = (N1 / 32 + p.parts) / p.parts, rows = (N2 / 32 + p.parts2) / p.parts2 * ((two1 * p.parts2 + p.waves - 1) / p.waves);
+        return rounds * (3.5 + 0.45 * columns * (1 + two1) + 0.35 * rows * (1 + two2)) <= 8.0 + 0.9 * field_us + half_us;
     }
     const int turns = (N1 / 64 + p.parts) / p.parts;
-    return 55 + turns * (K1 > 16 ? 48 : 34) <= 90 + bytes / 350000;
+    return rounds * (2.5 + turns * (2.0 + 0.8 * two1)) <= 6.5 + 0.7 * field_us + 1.2 * half_us;
 }
 
 hipError_t matgrid_launch(int dir, const c64 *in, c64 *out, long long images, int C, int N1, int N2, int K1, int K2, hipStream_t s)
