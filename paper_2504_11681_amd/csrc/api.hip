@@ -188,11 +188,15 @@ Fused1dArgs strip_rows(const c64 *T1, const c64 *W, c64 *T2, int B, int C_in, in
 // writes to them; the K1 rows of `g` input images follow in the g parts of an output image.  Returns g; 0: image kernels.
 // Whole layers, image kernels and strips (us): 256 x 256, K 64 x 64, B 1, C 16 64.8 and 16.3; B 4, C 32 70 and 50; B 4, C 64 77 and 83; 256 x 64, K 32 x 16,
 // B 4, C 64 38 and 22; 128 x 128, K 16 x 16, B 4, C 64 30 and 24, B 8 37 and 41; 64 x 64, K 16 x 16, B 8, C 64 22 and 18; 64 x 256, K 16 x 64, B 4, C 32 24 and 19,
-// C 64 27 and 31: up to about 72000 rows' worth of images x N2, 100000 with the longer walk of 256 rows.
+// C 64 27 and 31: up to about 72000 rows' worth of images x N2, 100000 with the longer walk of 256 rows.  Less with many retained rows, which are written, contracted and read
+// twice (B 45, 2 -> 10 channels, 64 x 128, K 21 x 3 19.3 and 23.1; B 61, 2 -> 15, 128 x 64, K 27 x 8 27.2 and 29.2; B 59, 9 -> 15, 256 x 64, K 59 x 2 47.1 and 59.1; B 25, 4 -> 26, 256 x 128, K 46 x 19 59.2 and 62.6; B 14, 8 -> 18,
+// 256 x 256, K 52 x 3 55.9 and 63.6; but B 19, 3 -> 18, 64 x 128, K 16 x 6 18.5 and 16.1, B 26, 47 -> 13, 256 x 64, K 22 x 23 57.6 and 51.1), and not where they are more than three for every CU beside the short walk of 64 rows (B 58, 2 -> 2, 64 x 256, K 19 x 24 20.4 and 25.9).
 int strip_channels_per_field(const Shape &req, int B, int C_in, int C_out)
 {
     if (!colfft_supported(req.N1, req.K1) || !round_modes(req.N2, req.K2, fused1d_supported) || generic_kernels_forced() || contraction_forced_f32()) return 0;
-    if ((double)B * ((double)C_in + C_out) * req.N2 > (req.N1 >= 256 ? 100000.0 : 72000.0)) return 0;
+    const double rows = (double)B * ((double)C_in + C_out) * req.N2;
+    if (rows > (req.N1 >= 256 ? 100000.0 : 72000.0) || rows * (1.0 + 4.0 * req.K1 / req.N1) > (req.N1 == 128 ? 120000.0 : 140000.0)) return 0;
+    if (req.N1 == 64 && (double)B * req.K1 * ((C_out + 31) / 32) > 768.0) return 0;
     int g = 1;
     while (g * (long long)C_out < C_in) g *= 2;
     return 2 * req.K1 * g <= req.N1 ? g : 0;

@@ -47,6 +47,17 @@ def close(got, want, what):
     assert mx <= MAX_ABS, f"{what}: max abs {mx:.3e}"
 
 
+def writes_workspace(gpu, nbytes, call):
+    """Whether call() writes to a registered workspace of nbytes: the kernels that keep their spectra there do, layers whose
+    intermediates are held in y do not."""
+    torch, binding = gpu
+    ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device="cuda")
+    binding.set_workspace(ws)
+    call()
+    torch.cuda.synchronize()
+    return bool((ws != 0x5A).any())
+
+
 def run_gpu(gpu, fn_name, x, W, K):
     torch, binding = gpu
     xd = torch.from_numpy(x).cuda()
@@ -405,6 +416,24 @@ def test_2d_few_and_many_images(gpu, shape):
         say(f"   rel {rel:.2e}, max {worst:.2e}")
         assert rel <= 3.0e-7 and worst <= 3e-6, shape
     assert bool(torch.isnan(whole[:1].real).all()) and bool(torch.isnan(whole[n + 1:].real).all())
+
+
+# (B, C_in, C_out, N1, N2, K1, K2), strips: layers that strips made slower (many retained rows) and layers that they serve
+STRIPS_OR_IMAGES = [((45, 2, 10, 64, 128, 21, 3), False), ((59, 9, 15, 256, 64, 59, 2), False), ((25, 4, 26, 256, 128, 46, 19), False), ((14, 8, 18, 256, 256, 52, 3), False),
+                    ((58, 2, 2, 64, 256, 19, 24), False), ((38, 2, 12, 64, 128, 23, 62), False), ((61, 2, 15, 128, 64, 27, 8), False),
+                    ((19, 3, 18, 64, 128, 16, 6), True), ((26, 47, 13, 256, 64, 22, 23), True), ((1, 16, 16, 256, 256, 64, 64), True), ((8, 64, 64, 64, 64, 16, 16), True),
+                    ((4, 64, 64, 64, 64, 33, 16), False), ((4, 32, 32, 256, 256, 64, 64), True)]
+
+
+@pytest.mark.parametrize("shape,strips", STRIPS_OR_IMAGES, ids=str)
+def test_2d_layers_of_few_images_by_strips_or_image_kernels(gpu, shape, strips):
+    torch, binding = gpu
+    B, Ci, Co, N1, N2, K1, K2 = shape
+    say(f"[case] strips or images {shape}")
+    x = torch.zeros((B, Ci, N1, N2), dtype=torch.complex64, device="cuda")
+    W = torch.zeros((Ci, Co), dtype=torch.complex64, device="cuda")
+    y = torch.empty((B, Co, N1, N2), dtype=torch.complex64, device="cuda")
+    assert writes_workspace(gpu, binding.workspace_bytes_2d(0, *shape), lambda: binding.spectral_conv2d_rect(x, W, y, K1, K2)) == (not strips)
 
 
 # Fused layers whose waves invert the slab they have accumulated without the workgroup's LDS (every wave a slab of 32 outputs and all modes): N 128
