@@ -265,15 +265,14 @@ def test_staged_lengths_that_are_not_powers_of_two(gpu, oracle_mod):
     check(run_gpu(gpu, "spectral_conv1d_auto", x, W, 40), want, "auto, N = 300")
 
 
-# the matrix transform that serves lengths with odd factors: remainders of its 16-element blocks, edges of its 32-output
-# tiles, pencil counts around 32, sums dealt out to 1, 4 and 8 waves, the direct sums of fields that do not fit (its other
-# forms: MATDFT_FORMS below).
+# the transforms that serve lengths with odd factors: remainders of their blocks of 16 pairs, edges of their tiles of 32 outputs, pencil
+# counts around 32, sums dealt out to several waves, the direct sums of fields that do not fit (single kernels: MATDFT_FORMS,
+# ROW_1D below).
 # (B, C_in, C_out, N, K)
 ODD_1D = [(1, 1, 1, 17, 17), (1, 2, 3, 127, 3), (2, 31, 33, 129, 31), (3, 11, 32, 144, 32), (1, 33, 1, 145, 33), (2, 5, 7, 257, 97),
           (1, 40, 24, 271, 128), (2, 17, 9, 390, 129), (700, 16, 48, 136, 72), (1100, 32, 30, 40, 40), (1, 3, 2, 3000, 65),
           (90, 3, 128, 100, 99), (2, 4, 4, 123, 123), (3, 20, 7, 64 + 1, 40), (2, 3, 3, 63, 63), (4, 300, 5, 56, 8), (3, 5, 6, 39, 39), (3, 5, 6, 41, 20),
-          # outputs of 32 MB and more, stored as whole pencils by one, two or four waves (from 65 points; odd pencil counts, rows
-          # that start anywhere in a line), and one length past the range on either side
+          # many outputs (those of the matrix transform that store whole pencils: MATDFT_FORMS), lengths around 64, 128, 256 and 512
           (700, 2, 97, 65, 9), (700, 2, 97, 63, 9), (513, 2, 73, 127, 20), (300, 2, 91, 129, 17), (257, 2, 65, 255, 30),
           (200, 2, 91, 257, 12), (131, 2, 97, 511, 33), (131, 2, 97, 510, 33), (100, 2, 91, 513, 8)]
 
@@ -319,15 +318,15 @@ def test_2d_sides_with_odd_factors(gpu, oracle_mod, shape):
     check(run_gpu_rect(gpu, "spectral_conv2d_rect_staged", x, W, K1, K2), want, "odd sides")
 
 
-# Both sides odd: a workgroup per field.  (B, C_in, C_out, N1, N2, K1, K2), with 256 fields and more each way unless noted: the shortest
-# sides, both parities, one and two sixteens of modes on either axis, all parts of a sum and sets of waves, the last columns' tile full, with one
-# column, with two; sides of equal length (one root table); long sums on either axis; and one step outside (the kernel per axis)
+# Both sides odd: a workgroup per field, or a kernel per axis, by the rule on rounds and chains (tests/test_dispatch_rules.py).  (B, C_in, C_out, N1, N2,
+# K1, K2): the shortest sides, both parities, one and two sixteens of modes on either axis, all parts of a sum and sets of waves, the last columns' tile
+# full, with one column, with two; sides of equal length (one root table); long sums on either axis; and one step outside the kernel's sizes
 FIELD_2D = [(32, 8, 8, 30, 30, 1, 1), (32, 8, 8, 31, 33, 15, 16), (32, 8, 9, 33, 34, 16, 17), (16, 17, 16, 33, 65, 17, 16), (32, 8, 8, 50, 66, 32, 32),
             (2, 3, 5, 85, 85, 12, 12), (8, 9, 40, 85, 85, 12, 12), (1, 2, 3, 60, 50, 9, 9), (1, 3, 2, 45, 97, 10, 11), (33, 32, 32, 40, 96, 8, 9),
             (8, 32, 33, 97, 129, 16, 20), (8, 32, 33, 63, 160, 17, 9), (4, 64, 65, 62, 255, 30, 31), (4, 128, 129, 62, 224, 30, 31), (4, 128, 128, 62, 225, 30, 31), (8, 32, 64, 220, 56, 25, 8), (8, 32, 63, 220, 56, 25, 8), (4, 64, 64, 36, 249, 9, 12), (16, 16, 16, 511, 41, 13, 9),
             (2, 128, 128, 500, 33, 32, 8), (2, 130, 128, 300, 130, 20, 21), (4, 33, 2, 194, 67, 16, 13),
             (32, 8, 8, 29, 33, 9, 9), (32, 8, 8, 33, 29, 9, 9), (32, 8, 8, 45, 45, 33, 9), (32, 8, 8, 45, 45, 9, 33), (16, 16, 16, 33, 257, 9, 9), (16, 16, 16, 513, 33, 9, 9),
-            # (the inverse rows kernel in whole pencils by one and two waves, which odd grids of these sizes no longer run)
+            # (one side a power of two)
             (8, 2, 61, 128, 85, 12, 12), (8, 2, 61, 64, 200, 9, 10), (8, 2, 61, 64, 130, 9, 10)]
 
 
@@ -354,7 +353,7 @@ def test_fields_with_odd_sides(gpu, shape):
 # 1-D, few pencils: the forward kernel with 1 to 4 sixteens of modes per wave and several groups of them, one to eight waves to a sum, long sums,
 # a last tile of pencils with one; the kernel that contracts and transforms back: channels past a step of eight, modes past a tile, one to eight
 # tiles of modes (and shares of the channels), last slabs with one output and none missing, outputs in one group of workgroups and in
-# several, as many waves as tiles of outputs (512 slabs and more); and one step outside each.  (B, C_in, C_out, N, K)
+# several, as many waves as tiles of outputs (512 slabs and more); and shapes outside the rules.  (B, C_in, C_out, N, K)
 ROW_1D = [(2, 3, 4, 33, 1), (3, 5, 33, 33, 33), (1, 17, 32, 34, 16), (3, 16, 31, 47, 17), (2, 9, 64, 63, 32), (5, 8, 65, 65, 33), (1, 1, 1, 66, 48), (3, 24, 40, 95, 49),
           (2, 40, 33, 97, 64), (2, 64, 32, 129, 65), (1, 65, 5, 255, 96), (2, 33, 40, 257, 97), (2, 64, 7, 300, 128), (1, 20, 12, 511, 160), (2, 3, 5, 600, 256), (2, 3, 5, 600, 257),
           (64, 40, 56, 1000, 50), (2, 15, 70, 1025, 12), (1, 128, 128, 1900, 20), (1, 4, 6, 4095, 7), (1, 4, 6, 3000, 200), (255, 64, 4, 90, 10), (256, 64, 4, 90, 10),
@@ -495,22 +494,46 @@ def test_few_rows_of_1024_points(gpu, oracle_mod, case):
     assert bool(torch.isnan(guards[:pad]).all()) and bool(torch.isnan(guards[n + pad:]).all())
 
 
-# Every form of the matrix transform, by the sides it reads and writes.  (B, C_in, C_out, N1, N2, K1, K2); N1 = 1: 1-D
+# Every form of the matrix transform, by the sides it reads and writes.  (B, C_in, C_out, N1, N2, K1, K2); N1 = 1: 1-D.  A form's direction is
+# the inverse where its name says inverse or whole pencils, else the forward one; the test asserts that it is this kernel that runs, and
+# not those of few pencils or of whole fields, which the last entries name.
 MATDFT_FORMS = {
     "1-D, two output tiles per wave": (328, 100, 2, 1, 140, 1, 40), "1-D, three": (328, 100, 2, 1, 141, 1, 70), "1-D, four": (328, 100, 2, 1, 140, 1, 100),
     "1-D, long, two": (330, 100, 2, 1, 1030, 1, 64), "1-D, long, three": (330, 100, 2, 1, 1031, 1, 96), "1-D, long, four": (330, 100, 2, 1, 1030, 1, 128),
-    "1-D, few points, two": (330, 100, 2, 1, 39, 1, 39), "1-D, inverse with two tiles": (330, 2, 100, 1, 100, 1, 30),
-    "1-D, long, inverse with two tiles": (28, 2, 100, 1, 1500, 1, 40), "1-D, long, four waves": (8, 40, 8, 1, 1500, 1, 40), "1-D, long, eight waves": (1, 40, 8, 1, 1500, 1, 40),
+    "1-D, few points, two": (330, 100, 2, 1, 39, 1, 39), "1-D, four waves": (330, 50, 1, 1, 300, 1, 20), "1-D, long, four waves": (330, 50, 1, 1, 1030, 1, 20),
+    "1-D, inverse": (3000, 1, 1, 1, 100, 1, 30), "1-D, inverse, two tiles": (33100, 1, 1, 1, 65, 1, 9), "1-D, long, inverse": (300, 1, 1, 1, 1410, 1, 40),
+    "1-D, long, inverse, two tiles": (2800, 1, 1, 1, 1500, 1, 40), "1-D, whole pencils by one wave": (33100, 1, 1, 1, 127, 1, 20),
+    "1-D, whole pencils by two waves": (33100, 1, 1, 1, 255, 1, 30), "1-D, whole pencils by four waves": (16600, 1, 1, 1, 511, 1, 33),
     "rows, two": (8, 63, 2, 66, 140, 5, 40), "rows, three": (8, 63, 2, 66, 141, 5, 70), "rows, four": (8, 63, 2, 66, 140, 5, 100),
-    "rows, four waves": (2, 40, 3, 90, 140, 5, 20), "rows, eight waves": (2, 3, 4, 90, 300, 5, 20), "rows, few points, two": (8, 63, 2, 66, 39, 5, 39),
+    "rows, four waves": (2, 40, 3, 64, 140, 5, 20), "rows, eight waves": (2, 3, 4, 90, 300, 5, 20), "rows, few points, two": (8, 63, 2, 66, 39, 5, 39),
     "rows, long": (8, 49, 3, 21, 1500, 9, 20), "rows, long, two": (33, 100, 2, 10, 1100, 3, 50), "rows, long, four waves": (4, 49, 3, 21, 1500, 9, 20), "rows, long, eight waves": (1, 4, 3, 21, 1500, 9, 20),
-    "rows, inverse in pieces, two tiles": (8, 2, 64, 65, 100, 7, 30), "rows, long, inverse, two tiles": (8, 2, 49, 9, 1500, 4, 20), "rows, long, inverse": (1, 2, 3, 9, 1500, 4, 20),
-    "rows, inverse in whole pencils by one wave": (8, 2, 73, 85, 85, 12, 12), "by two waves": (8, 2, 61, 61, 200, 9, 10), "by two waves, just past 128": (8, 2, 61, 90, 130, 9, 10),
-    "by four waves": (4, 2, 61, 61, 300, 9, 10), "by four waves, just past 256": (4, 2, 61, 70, 257, 9, 10), "by four waves, odd counts": (5, 2, 33, 67, 499, 5, 33),
+    "rows, inverse in pieces, two tiles": (8, 2, 64, 64, 100, 7, 30), "rows, long, inverse, two tiles": (8, 2, 49, 9, 1500, 4, 20), "rows, long, inverse": (1, 2, 3, 9, 1500, 4, 20),
+    "rows, whole pencils by one wave": (8, 2, 61, 128, 85, 12, 12), "rows, whole pencils by two waves": (8, 2, 61, 64, 200, 9, 10), "rows, whole pencils by two waves, just past 128": (8, 2, 130, 64, 130, 9, 10),
+    "rows, whole pencils by four waves": (4, 2, 120, 61, 300, 9, 10), "rows, whole pencils by four waves, just past 256": (4, 2, 125, 70, 257, 9, 10),
+    "rows, inverse in pieces, 300 points": (4, 2, 61, 61, 300, 9, 10), "rows, inverse in pieces, 257 points": (4, 2, 61, 70, 257, 9, 10),
+    "rows, whole pencils by four waves, odd counts": (5, 2, 33, 67, 499, 5, 33),
     "columns, two": (28, 100, 2, 141, 13, 40, 12), "columns, three": (28, 100, 2, 141, 13, 70, 12), "columns, four": (28, 100, 2, 140, 13, 100, 12),
-    "columns, four waves": (4, 50, 3, 141, 50, 20, 10), "columns, eight waves": (2, 3, 3, 301, 13, 20, 12), "columns, long": (33, 90, 3, 1050, 13, 20, 11),
+    "columns, four waves": (4, 50, 3, 141, 64, 20, 10), "columns, eight waves": (2, 3, 3, 301, 13, 20, 12), "columns, long": (33, 90, 3, 1050, 13, 20, 11),
     "columns, long, two": (33, 90, 2, 1050, 13, 50, 12), "columns, long, four waves": (8, 60, 3, 1500, 13, 20, 11), "columns, long, eight waves": (1, 6, 3, 1500, 13, 20, 11),
-    "columns, inverse with two tiles": (28, 2, 100, 100, 12, 30, 12), "columns, long, inverse, two tiles": (8, 2, 49, 1500, 9, 20, 9)}
+    "columns, inverse with two tiles": (28, 2, 100, 100, 12, 30, 12), "columns, long, inverse, two tiles": (8, 2, 49, 1500, 9, 20, 9),
+    # the kernels of few pencils and of whole fields at the shapes of such forms
+    "few pencils, 100 points": (330, 2, 100, 1, 100, 1, 30), "few pencils, 1500 points": (28, 2, 100, 1, 1500, 1, 40), "few pencils, a sum over eight waves": (8, 40, 8, 1, 1500, 1, 40),
+    "few pencils, 40": (1, 40, 8, 1, 1500, 1, 40), "fields, 90 x 140": (2, 40, 40, 90, 140, 5, 20), "fields, 65 x 100": (8, 2, 64, 65, 100, 7, 30), "fields, 85 x 85": (8, 2, 73, 85, 85, 12, 12),
+    "fields, 61 x 200": (8, 2, 61, 61, 200, 9, 10), "fields, 90 x 130": (8, 2, 61, 90, 130, 9, 10), "fields, 141 x 50": (4, 50, 60, 141, 50, 20, 10)}
+
+
+def by_kernels_of_few_pencils_or_fields(binding, shape, inverse):
+    """The library's own rules (internal functions, so by their mangled names)."""
+    import ctypes
+    B, Ci, Co, N1, N2, K1, K2 = shape
+    name, args = (("_ZN4tfno17matgrid_supportedEixiiii", (+1 if inverse else -1, ctypes.c_longlong(B * (Co if inverse else Ci)), N1, N2, K1, K2)) if N1 > 1 else
+                  ("_ZN4tfno24matrow_inverse_supportedExiiii", (ctypes.c_longlong(B), Ci, Co, N2, K2)) if inverse else
+                  ("_ZN4tfno24matrow_forward_supportedExiii", (ctypes.c_longlong(B), Ci, N2, K2)))
+    if N1 > 1 and (N1 & (N1 - 1) == 0 or N2 & (N2 - 1) == 0):
+        return False                                        # (fields: both sides odd)
+    fn = getattr(binding.lib(), name)
+    fn.restype = ctypes.c_bool
+    return fn(*args)
 
 
 def exact_layer(torch, x, W, K1, K2):
@@ -532,6 +555,10 @@ def test_forms_of_the_matrix_transform(gpu, form):
     torch, binding = gpu
     B, Ci, Co, N1, N2, K1, K2 = MATDFT_FORMS[form]
     say(f"[case] matrix transform: {form} {MATDFT_FORMS[form]}")
+    if form.startswith(("few pencils", "fields")):
+        assert by_kernels_of_few_pencils_or_fields(binding, MATDFT_FORMS[form], False) and by_kernels_of_few_pencils_or_fields(binding, MATDFT_FORMS[form], True)
+    else:
+        assert not by_kernels_of_few_pencils_or_fields(binding, MATDFT_FORMS[form], "inverse" in form or "whole pencils" in form)
     gen = torch.Generator(device="cuda").manual_seed(1800 + N1 + N2)
     x = torch.view_as_complex(torch.randn((B, Ci, N1, N2, 2), generator=gen, device="cuda"))
     W = torch.view_as_complex(torch.randn((Ci, Co, 2), generator=gen, device="cuda")) / Ci ** 0.5
