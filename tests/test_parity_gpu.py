@@ -234,7 +234,8 @@ def test_1d_staged_general_shapes(gpu, oracle_mod, shape):
     check(run_gpu(gpu, "spectral_conv1d_staged", x, W, K), want, "staged")
 
 
-# image kernels (N in {64,128,256}, K in {16,32,64}) and, for the other shapes, the strip pipeline
+# grids of the image kernels (N in {64,128,256}, K in {16,32,64}), which few images go through as strips (the image kernels themselves: RECT_IMAGE
+# and IMAGES_2D below), and other shapes of the strip pipeline
 SMALL_2D = [(2, 3, 5, 64, 16), (1, 8, 8, 64, 8), (2, 5, 33, 128, 32), (1, 4, 3, 256, 64), (1, 2, 2, 64, 64),
             (1, 3, 2, 64, 32), (1, 3, 2, 128, 16), (2, 2, 2, 128, 64), (1, 2, 3, 256, 16), (1, 2, 2, 256, 32),
             (3, 7, 70, 256, 64), (1, 2, 2, 128, 128), (1, 2, 2, 512, 64)]
@@ -629,6 +630,16 @@ def test_2d_staged_general_shape(gpu, oracle_mod):
     check(run_gpu(gpu, "spectral_conv2d_staged", x, W, K), want, "staged2d")
 
 
+def run_image_kernels(gpu, x, W, K1, K2):
+    """spectral_conv2d_rect, asserted to run the image kernels: few images go by strips held in y, which leave the workspace alone."""
+    torch, binding = gpu
+    B, Ci, N1, N2 = x.shape
+    got = []
+    need = binding.workspace_bytes_2d(0, B, Ci, W.shape[1], N1, N2, K1, K2)
+    assert writes_workspace(gpu, need, lambda: got.append(run_gpu_rect(gpu, "spectral_conv2d_rect", x, W, K1, K2))), "not the image kernels"
+    return got[0]
+
+
 def run_gpu_rect(gpu, fn_name, x, W, K1, K2):
     torch, binding = gpu
     xd = torch.from_numpy(x).cuda()
@@ -639,7 +650,8 @@ def run_gpu_rect(gpu, fn_name, x, W, K1, K2):
     return yd.cpu().numpy()
 
 
-# every (N1, N2, K1, K2) instantiation of the image kernels
+# every (N1, N2, K1, K2) instantiation of the image kernels: with nine input channels to one output there is no room for the
+# strips of the input in y.  The same grids with 3 -> 2 channels go by strips where they fit.
 RECT_IMAGE = [(n1, n2, k1, k2) for n1 in (64, 128, 256) for n2 in (64, 128, 256) for k1 in (16, 32, 64)
               for k2 in (16, 32, 64)]
 
@@ -647,15 +659,31 @@ RECT_IMAGE = [(n1, n2, k1, k2) for n1 in (64, 128, 256) for n2 in (64, 128, 256)
 @pytest.mark.parametrize("shape", RECT_IMAGE, ids=lambda s: "N%dx%d_K%dx%d" % s)
 def test_2d_rect_image_kernels(gpu, oracle_mod, shape):
     N1, N2, K1, K2 = shape
-    B, Ci, Co = 2, 3, 2
-    say(f"[case] spectral_conv2d_rect {shape}")
-    x = inputs.make_x(300 + N1 + 2 * N2 + K1 + 3 * K2, B, Ci, (N1, N2))
-    W = inputs.make_W(300 + N1 + 2 * N2 + K1 + 3 * K2, Ci, Co)
+    for B, Ci, Co in ((2, 3, 2), (2, 9, 1)):
+        say(f"[case] spectral_conv2d_rect {shape} {(B, Ci, Co)}")
+        x = inputs.make_x(300 + N1 + 2 * N2 + K1 + 3 * K2, B, Ci, (N1, N2))
+        W = inputs.make_W(300 + N1 + 2 * N2 + K1 + 3 * K2, Ci, Co)
+        want, _ = oracle_mod.spectral_conv2d_rect(x, W, K1, K2)
+        check(run_image_kernels(gpu, x, W, K1, K2) if Ci == 9 else run_gpu_rect(gpu, "spectral_conv2d_rect", x, W, K1, K2), want, "rect")
+
+
+# (B, C_in, C_out, N1, N2, K1, K2): the image kernels with ragged channels on every contraction kernel, with many images, with mode counts
+# between the built sizes, and with more retained rows than strips have room for
+IMAGES_2D = [(2, 9, 1, 64, 64, 12, 12), (1, 9, 2, 128, 256, 20, 48), (2, 9, 1, 256, 128, 64, 33), (40, 4, 4, 64, 256, 1, 5), (2, 33, 5, 256, 64, 64, 16), (4, 7, 70, 64, 256, 16, 64),
+             (2, 66, 130, 128, 256, 32, 16), (6, 7, 70, 256, 256, 64, 64), (1, 1, 1, 64, 64, 33, 1), (2, 40, 33, 64, 64, 32, 32), (1, 130, 70, 128, 64, 64, 50), (1, 257, 9, 64, 64, 40, 9)]
+
+
+@pytest.mark.parametrize("shape", IMAGES_2D, ids=lambda s: "B%d_Ci%d_Co%d_N%dx%d_K%dx%d" % s)
+def test_2d_image_kernels(gpu, oracle_mod, shape):
+    B, Ci, Co, N1, N2, K1, K2 = shape
+    say(f"[case] image kernels {shape}")
+    x = inputs.make_x(350 + N1 + K2, B, Ci, (N1, N2))
+    W = inputs.make_W(350 + N1 + K2, Ci, Co)
     want, _ = oracle_mod.spectral_conv2d_rect(x, W, K1, K2)
-    check(run_gpu_rect(gpu, "spectral_conv2d_rect", x, W, K1, K2), want, "rect")
+    check(run_image_kernels(gpu, x, W, K1, K2), want, "image kernels")
 
 
-# (B, C_in, C_out, N1, N2, K1, K2): ragged channels on the image kernels, strip-pipeline shapes (first axis or mode
+# (B, C_in, C_out, N1, N2, K1, K2): ragged channels on grids of the image kernels, strip-pipeline shapes (first axis or mode
 # count outside the image kernels' set), and shapes only the staged twin takes
 RECT_MIXED = [(3, 7, 70, 64, 256, 16, 64), (2, 33, 5, 256, 64, 64, 16), (1, 66, 130, 128, 256, 32, 16),
               (2, 3, 4, 32, 256, 8, 64), (1, 2, 3, 512, 64, 100, 16), (2, 3, 2, 16, 1024, 16, 128),
@@ -737,11 +765,12 @@ def test_2d_rect_staged_general_shapes(gpu, oracle_mod, shape):
 
 
 def test_2d_rect_square_case_is_bitwise_the_square_entry_point(gpu):
-    x = inputs.make_x(77, 2, 5, (128, 128))
-    W = inputs.make_W(77, 5, 6)
-    a = run_gpu_rect(gpu, "spectral_conv2d_rect", x, W, 32, 32)
-    b = run_gpu(gpu, "spectral_conv2d", x, W, 32)
-    assert np.array_equal(a.view(np.float32), b.view(np.float32))
+    for Ci, Co in ((5, 6), (9, 1)):                         # strips held in y, image kernels
+        x = inputs.make_x(77, 2, Ci, (128, 128))
+        W = inputs.make_W(77, Ci, Co)
+        a = run_image_kernels(gpu, x, W, 32, 32) if Ci == 9 else run_gpu_rect(gpu, "spectral_conv2d_rect", x, W, 32, 32)
+        b = run_gpu(gpu, "spectral_conv2d", x, W, 32)
+        assert np.array_equal(a.view(np.float32), b.view(np.float32))
 
 
 # per-mode weights (B, C_in, C_out, N, K): several batch groups, ragged channels, K below / equal / above one tile
@@ -935,36 +964,46 @@ def test_many_small_images_2d(gpu, oracle_mod):
 
 def test_entry_points_replay_from_a_hip_graph(gpu):
     """The entry points only enqueue kernels on the caller's stream, so they can be captured once their first (eager)
-    call has been made: three replays, with eager work and synchronisation in between, each bitwise equal to eager."""
+    call has been made: three replays, with eager work and synchronisation in between, each bitwise equal to eager.  The fused 1-D
+    layer; the 2-D layer by image kernels and by strips held in y; rows of 1024 points, complex and real, whose spectra are held in y."""
     torch, binding = gpu
-    say("[case] HIP graph capture of the fused 1-D and the three-kernel 2-D entry points")
-    x1 = torch.from_numpy(inputs.make_x(11, 8, 24, (256,))).cuda()
-    W1 = torch.from_numpy(inputs.make_W(11, 24, 40)).cuda()
-    y1 = torch.zeros((8, 40, 256), dtype=torch.complex64, device="cuda")
-    x2 = torch.from_numpy(inputs.make_x(12, 2, 5, (64, 128))).cuda()
-    W2 = torch.from_numpy(inputs.make_W(12, 5, 6)).cuda()
-    y2 = torch.zeros((2, 6, 64, 128), dtype=torch.complex64, device="cuda")
-    binding.spectral_conv1d(x1, W1, y1, 64)
-    binding.spectral_conv2d_rect(x2, W2, y2, 16, 32)
-    torch.cuda.synchronize()
-    want1, want2 = y1.clone(), y2.clone()
+    say("[case] HIP graph capture of the fused 1-D, the 2-D and the few-rows entry points")
+    layers = []
+    for call, B, Ci, Co, dims, K in ((binding.spectral_conv1d, 8, 24, 40, (256,), (64,)), (binding.spectral_conv2d_rect, 2, 9, 1, (64, 128), (40, 32)),
+                                     (binding.spectral_conv2d_rect, 2, 5, 6, (64, 128), (16, 32)), (binding.spectral_conv1d_auto, 4, 24, 40, (1024,), (50,)),
+                                     (binding.spectral_conv1d_real, 4, 24, 40, (1024,), (50,))):
+        x = inputs.make_x(11 + len(layers), B, Ci, dims)
+        if call is binding.spectral_conv1d_real:
+            x = np.ascontiguousarray(x.real)
+        x = torch.from_numpy(x).cuda()
+        layers.append((call, x, torch.from_numpy(inputs.make_W(11 + len(layers), Ci, Co)).cuda(), torch.zeros((B, Co) + dims, dtype=x.dtype, device="cuda"), K))
+
+    def run(layer, *stream):
+        call, x, W, y, K = layer
+        call(x, W, y, *K, *stream)
+
+    # (which of them use the workspace: the image kernels alone.  One buffer for all, registered before the capture)
+    need = binding.workspace_bytes_2d(0, 2, 9, 1, 64, 128, 40, 32) + binding.workspace_bytes_2d(0, 2, 5, 6, 64, 128, 16, 32)
+    assert [writes_workspace(gpu, need, lambda: run(layer)) for layer in layers] == [False, True, False, False, False]
+    want = [y.clone() for _, _, _, y, _ in layers]
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     g = torch.cuda.CUDAGraph()
     with torch.cuda.stream(side):
         with torch.cuda.graph(g, stream=side):
-            st = torch.cuda.current_stream().cuda_stream
-            binding.spectral_conv1d(x1, W1, y1, 64, st)
-            binding.spectral_conv2d_rect(x2, W2, y2, 16, 32, st)
+            for layer in layers:
+                run(layer, torch.cuda.current_stream().cuda_stream)
     torch.cuda.current_stream().wait_stream(side)
     for _ in range(3):
-        y1.zero_()
-        y2.zero_()
+        for layer in layers:
+            layer[3].zero_()
+        run(layers[1])                                      # (eager work between the replays)
+        layers[1][3].zero_()
         torch.cuda.synchronize()
         g.replay()
         torch.cuda.synchronize()
-        assert torch.equal(torch.view_as_real(y1), torch.view_as_real(want1))
-        assert torch.equal(torch.view_as_real(y2), torch.view_as_real(want2))
+        for layer, w in zip(layers, want):
+            assert torch.equal(layer[3], w)
 
 
 def test_general_layers_replay_from_a_hip_graph(gpu):
@@ -1073,8 +1112,8 @@ def test_1d_any_mode_count(gpu, oracle_mod, shape):
         assert np.max(np.abs(got - wantr)) / np.max(np.abs(wantr)) <= MAX_ABS
 
 
-# (B, C_in, C_out, N1, N2, K1, K2): image kernels with rounded mode counts, strip pipeline with a rounded last axis,
-# long pencils
+# (B, C_in, C_out, N1, N2, K1, K2): few images on grids of the image kernels with rounded mode counts (the kernels themselves: IMAGES_2D), strip
+# pipeline with a rounded last axis, long pencils
 ANY_K_2D = [(2, 3, 5, 64, 64, 12, 12), (1, 5, 33, 128, 256, 20, 48), (2, 4, 3, 256, 128, 64, 33), (1, 2, 2, 64, 256, 1, 5),
             (2, 3, 4, 32, 256, 8, 40), (1, 2, 3, 512, 64, 100, 12)]
 
@@ -1354,8 +1393,10 @@ def test_channel_count_sweep(gpu, oracle_mod):
         torch.cuda.synchronize()
         got = yd.cpu().numpy().astype(np.float64)
         close(got, wantr, ("real", Ci, Co, N))
-        # 2-D image kernels, mode CGEMM and per-mode contraction with the same channel counts
+        # 2-D: strips of few images or, with more than half of the rows retained, image kernels and mode CGEMM; per-mode contraction
         x2 = inputs.make_x(1900 + idx, 1, Ci, (64, 64))
+        want2, _ = oracle_mod.spectral_conv2d_rect(x2, W, 33, 16)
+        close(run_image_kernels(gpu, x2, W, 33, 16).astype(np.complex128), want2, ("2d images", Ci, Co))
         want2, _ = oracle_mod.spectral_conv2d(x2, W, 16)
         got = run_gpu(gpu, "spectral_conv2d", x2, W, 16).astype(np.complex128)
         close(got, want2, ("2d", Ci, Co))
@@ -1365,7 +1406,7 @@ def test_channel_count_sweep(gpu, oracle_mod):
         torch.cuda.synchronize()
         got = yd.cpu().numpy().astype(np.complex128)
         close(got, want2, ("2d permode", Ci, Co))
-    say(f"   {len(pairs)} channel-count pairs on 8-9 entry points each")
+    say(f"   {len(pairs)} channel-count pairs on 9-10 layers each")
 
 
 def test_batch_size_sweep(gpu, oracle_mod):
@@ -1525,8 +1566,8 @@ def test_empty_batch_and_error_paths(gpu):
 # path that mixed scaled and unscaled quantities, would show here.
 @pytest.mark.parametrize("entry,shape", [("spectral_conv1d", (3, 24, 40, 1024, 128)), ("spectral_conv1d", (5, 32, 64, 256, 128)),
                                          ("spectral_conv1d", (4, 64, 256, 256, 64)), ("spectral_conv1d_pruned", (3, 70, 65, 256, 64)),
-                                         ("spectral_conv2d", (2, 8, 8, 64, 16)), ("spectral_conv2d", (1, 4, 3, 512, 40)),
-                                         ("spectral_conv1d_auto", (3, 24, 40, 1000, 50)), ("spectral_conv1d_auto", (9, 5, 40, 39, 20)),
+                                         ("spectral_conv2d", (2, 8, 8, 64, 16)), ("spectral_conv2d", (2, 9, 1, 64, 16)), ("spectral_conv2d", (1, 4, 3, 512, 40)),
+                                         ("spectral_conv1d_auto", (3, 24, 40, 1024, 50)), ("spectral_conv1d_auto", (3, 24, 40, 1000, 50)), ("spectral_conv1d_auto", (9, 5, 40, 39, 20)),
                                          ("spectral_conv2d_staged", (2, 8, 8, 85, 12)),
                                          ("spectral_conv1d_permode", (16, 24, 33, 256, 100)), ("spectral_conv1d_permode", (64, 40, 64, 256, 100)),
                                          ("spectral_conv1d_permode", (3, 20, 7, 64, 12))],

@@ -1,5 +1,6 @@
 """The entry point that allocates nothing (tfno_spectral_conv2d_noalloc) against tfno_spectral_conv2d, through the
-C ABI: two calls in a row, the second on a smaller input, both sharing the library's static scratch array."""
+C ABI: calls in a row, the second on a smaller input, that share the library's static scratch array, and calls that hold their
+intermediates in y."""
 import sys
 
 import numpy as np
@@ -23,8 +24,10 @@ def test_noalloc_entry_point_matches_the_workspace_one_on_two_calls_in_a_row(ora
     assert torch.cuda.is_available(), "this test needs the MI355X"
     L = binding.lib()
     stream = torch.cuda.current_stream().cuda_stream
-    # (B, C_in, C_out, N, K): image kernels with a rounded mode count, then a smaller call, then the strip pipeline
-    for (B, Ci, Co, N, K) in [(6, 24, 40, 128, 32), (2, 5, 7, 64, 12), (1, 3, 4, 512, 32)]:
+    # (B, C_in, C_out, N, K), scratch: image kernels with a rounded mode count, a smaller call of theirs, few images by strips in y, the
+    # strip pipeline in the scratch array, image kernels once more
+    for (B, Ci, Co, N, K), scratch in [((26, 22, 23, 64, 12), True), ((1, 2, 2, 64, 33), True), ((6, 24, 40, 128, 32), False), ((2, 5, 7, 64, 12), False),
+                                       ((1, 3, 4, 512, 32), True), ((2, 9, 1, 128, 32), True)]:
         say(f"[case] tfno_spectral_conv2d_noalloc {(B, Ci, Co, N, K)}")
         x = inputs.make_x(2600 + N, B, Ci, (N, N))
         W = inputs.make_W(2600 + N, Ci, Co)
@@ -36,8 +39,12 @@ def test_noalloc_entry_point_matches_the_workspace_one_on_two_calls_in_a_row(ora
         assert st == binding.OK, binding.status_string(st)
         torch.cuda.synchronize()
         y_old = torch.full((B, Co, N, N), float("nan"), dtype=torch.complex64, device="cuda")
+        ws = torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda")
+        binding.set_workspace(ws)
         binding.spectral_conv2d(xd, Wd, y_old, K)              # the existing entry point, registered workspace
         torch.cuda.synchronize()
+        # (the same kernels run on the scratch array: what writes to the one writes to the other)
+        assert bool((ws != 0x5A).any()) == scratch
         got, ref = y_new.cpu().numpy().astype(np.complex128), y_old.cpu().numpy().astype(np.complex128)
         assert not np.isnan(got.view(np.float64)).any(), "some outputs were never written"
         rel = np.linalg.norm((got - ref).ravel()) / np.linalg.norm(ref.ravel())
