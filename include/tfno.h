@@ -27,7 +27,9 @@
  *  - Ownership: the caller owns every buffer (including the workspace) and must
  *    keep it alive and unmodified until the stream has passed the call.
  *  - y must not overlap x or W (checked on address ranges: TFNO_ERR_ALIAS).
- *  - y may hold intermediates of a call before its result.
+ *  - y may hold intermediates of a call before its result, and is read back then: the 2-D calls with image kernels for
+ *    few images (half-transformed rows), tfno_spectral_conv1d_auto and tfno_spectral_conv1d_real for few rows of N = 1024
+ *    (truncated spectra).  A y that the device reaches slowly (memory of a peer or of the host) pays for both directions.
  *  - x, W and y must be aligned to 8 bytes (TFNO_ERR_ALIGN), the float32 tensors of the real-valued entry points
  *    included: complex64 elements move as 8-byte words, and kernels for real fields move up to four floats at a time.
  *  - Argument errors are detected on the host before anything is launched, so a
@@ -49,8 +51,9 @@
  *  - Two environment variables, read once per process, select alternative kernels for A/B measurements and tests:
  *    TFNO_CONTRACTION=f32 (FP32-MFMA contractions instead of the exact-split BF16 ones) and, for N = 1024,
  *    TFNO_KERNEL=ws | generic | sym (the wave-specialised, the four-wave or the symmetric-wave kernel whatever the
- *    batch size, instead of the per-shape default).  Results stay within the same tolerance; production callers
- *    leave both unset.
+ *    batch size, instead of the per-shape default).  TFNO_CONTRACTION=f32 and TFNO_KERNEL=generic also keep small
+ *    layers on the general kernels: 2-D layers of few images on the image kernels, N = 256 on workgroups of four waves;
+ *    any of the settings keeps N = 1024 on one kernel.  Results stay within the same tolerance; production callers leave both unset.
  */
 #ifndef TFNO_H
 #define TFNO_H
@@ -97,7 +100,9 @@ tfno_status tfno_spectral_conv1d(const void *x, const void *W, void *y,
  *
  * N in {64,128,256}, K <= 64 (built sizes 16, 32, 64): three launches -- a per-image truncated forward transform, the
  * CGEMM over the K*K retained modes, a per-image zero-padded inverse -- whose only intermediates are the
- * truncated spectra (tfno_workspace_bytes(2, 0, ...) = 8 B K^2 (C_in + C_out) bytes of workspace).
+ * truncated spectra (tfno_workspace_bytes(2, 0, ...) = 8 B K^2 (C_in + C_out) bytes of workspace).  Few images, whose
+ * workgroups would leave most of the chip idle, run the pipeline below instead, its two strips held in y; the workspace is
+ * asked for (TFNO_ERR_WORKSPACE) but not used then.
  * Other shapes that the 1-D fused kernel supports run the paper's 2-D pipeline instead: truncated forward
  * FFT along the first axis, the fused 1-D kernel along the last axis on the K retained rows, zero-padded
  * inverse along the first axis, with two [B, C, K, N] strips in the workspace.  Shapes neither path covers:
@@ -109,9 +114,9 @@ tfno_status tfno_spectral_conv2d(const void *x, const void *W, void *y,
 /*
  * tfno_spectral_conv2d for callers that cannot allocate device memory or register a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, result and kernels as
- * tfno_spectral_conv2d, but the intermediates (the truncated spectra, or the strips of the strip pipeline) live in
- * a scratch array of TFNO_NOALLOC_SCRATCH_BYTES that is part of the library image: every GPU the library runs on
- * holds its own copy until the process ends, and the call allocates and frees nothing and ignores
+ * tfno_spectral_conv2d, but the intermediates that would go through the workspace (the truncated spectra, or the strips of
+ * the strip pipeline) live in a scratch array of TFNO_NOALLOC_SCRATCH_BYTES that is part of the library image; few images hold
+ * theirs in y here as well.  Every GPU the library runs on holds its own copy until the process ends, and the call allocates and frees nothing and ignores
  * tfno_set_workspace.  A shape whose tfno_workspace_bytes(2, 0, ...) exceeds TFNO_NOALLOC_SCRATCH_BYTES returns
  * TFNO_ERR_WORKSPACE before anything is launched.  The first call on a device looks up the array's address there
  * (hipGetSymbolAddress); a failure of that lookup is TFNO_ERR_HIP.  All calls on one GPU share that GPU's array:
@@ -132,7 +137,7 @@ tfno_status tfno_spectral_conv2d_noalloc(const void *x, const void *W, void *y,
  * tfno_workspace_bytes(dims, 1, ...) bytes of workspace.
  *
  * With a side that is no power of two these entry points are the way to run the layer, not a baseline: they run
- * pruned transforms around the mode CGEMM (three launches in 1-D, five in 2-D) inside the same workspace, along that side
+ * pruned transforms around the mode CGEMM (two or three launches in 1-D, three to five in 2-D) inside the same workspace, along that side
  * as contractions with the kept columns of the DFT matrix, along a side that is a power of two by butterflies.  Calls for
  * which this does not fit the workspace keep the five stages with direct sums.  In complex elements it takes
  *   ceil(B K1 K / 128) 128 (C_in + C_out) + B N1 K max(C_in, C_out)        (1-D: K1 = 1, without the second term)
@@ -153,8 +158,8 @@ tfno_status tfno_spectral_conv2d_staged(const void *x, const void *W, void *y,
  *
  * x is [B, C_in, N1, N2] and y [B, C_out, N1, N2], row-major with N2 contiguous; the modes kept are k1 < K1 along
  * the first spatial axis and k2 < K2 along the last.  N1, N2 powers of two in [2, 4096], 1 <= K1 <= N1,
- * 1 <= K2 <= N2.  N1, N2 in {64,128,256} with K1, K2 in {16,32,64} run the image kernels of
- * tfno_spectral_conv2d (workspace 8 B K1 K2 (C_in + C_out) bytes); other shapes whose last axis (N2, K2) the fused
+ * 1 <= K2 <= N2.  N1, N2 in {64,128,256} with K1, K2 in {16,32,64} run the kernels of
+ * tfno_spectral_conv2d (image kernels, or strips in y for few images; workspace 8 B K1 K2 (C_in + C_out) bytes); other shapes whose last axis (N2, K2) the fused
  * 1-D kernel supports run the strip pipeline (workspace 8 B K1 N2 (C_in + C_out) bytes); the rest return
  * TFNO_ERR_UNSUPPORTED from the fused entry point.  The staged twin accepts every valid shape.  Pointer, aliasing,
  * stream and error rules as for tfno_spectral_conv2d; with N1 = N2 and K1 = K2 the calls are identical to
@@ -172,7 +177,8 @@ tfno_status tfno_spectral_conv2d_rect_staged(const void *x, const void *W, void 
  * zero-padded inverse FFT along the first axis; the two [B, C, K1, N2] strips go through the workspace
  * (tfno_workspace_bytes_2d(7, ...) = 8 B K1 N2 (C_in + C_out) bytes).  Same arguments, contract and result as
  * tfno_spectral_conv2d_rect.  It exists for comparison (the 2-D ablation of the paper): on this machine the image
- * kernels, which keep both axes of an image on chip, are several times faster.  Shapes: N1 a power of two in
+ * kernels, which keep both axes of an image on chip, are up to several times faster once there are images enough to
+ * fill it (for fewer tfno_spectral_conv2d_rect takes strips by itself).  Shapes: N1 a power of two in
  * [2, 4096] with any K1 <= N1, (N2, K2) a shape of the fused 1-D kernel; others TFNO_ERR_UNSUPPORTED.
  */
 tfno_status tfno_spectral_conv2d_strips(const void *x, const void *W, void *y, int B, int C_in, int C_out,
@@ -190,7 +196,8 @@ tfno_status tfno_spectral_conv2d_strips(const void *x, const void *W, void *y, i
  * W is a device pointer to a contiguous row-major c64 tensor [C_in, C_out, K] (1-D) or [C_in, C_out, K1, K2]
  * (2-D), modes innermost; x, y, stream, aliasing and error rules as for the other entry points.  Three launches:
  * pruned forward transform with built-in truncation, per-mode contraction on the truncated spectra, pruned inverse
- * with built-in zero padding (the transform kernels of tfno_spectral_conv1d_pruned and tfno_spectral_conv2d_rect).
+ * with built-in zero padding (the transform kernels of tfno_spectral_conv1d_pruned and tfno_spectral_conv2d_rect); small
+ * 1-D layers run the last two in one.
  * Shapes: 1-D those of tfno_spectral_conv1d_pruned with N <= 1024; 2-D N1, N2 in {64,128,256}, K1, K2 <= 64
  * (W holds exactly the K, or K1 x K2, matrices of the modes kept, whatever built size the transforms run);
  * others TFNO_ERR_UNSUPPORTED.  Workspace: tfno_workspace_bytes(1, 6, ...) and
@@ -208,7 +215,8 @@ tfno_status tfno_spectral_conv2d_permode(const void *x, const void *W, void *y, 
  *   y[b,o,:] = C2R_N( pad( sum_c R2C_N(x[b,c,:])[k] * W[c,o],  k < K ) )
  *
  * x [B, C_in, N] and y [B, C_out, N] are device pointers to contiguous float32 tensors, W [C_in, C_out] to c64;
- * K <= N/2.  One launch of the fully fused kernel: the pencils are read as 4-byte reals, bin 0 enters the
+ * K <= N/2.  One launch of the fully fused kernel, or for few rows of N = 1024 with K <= 128 three launches whose truncated spectra
+ * are held in y: the pencils are read as 4-byte reals, bin 0 enters the
  * contraction with weight 1/2 and the epilogue stores 2/N times the real part of the zero-padded inverse -- the
  * C2R transform of the Hermitian extension -- so the layer moves half the bytes of the complex one.  Shapes: N in
  * {64,128,256,512,1024}, K <= N/2 (built sizes: powers of two from 8 (N = 64), 16 (N = 128, 256), 32 (N = 512,
@@ -240,7 +248,7 @@ size_t tfno_fno2d_real_workspace_bytes(int B, int C_in, int C_out, int N1, int N
 /*
  * The 1-D counterpart:  y = irfft( pad( sum_c rfft(x[b,c])[k] * W[c, o, k] ) ),  0 <= k < M,  2 M <= N.
  * x [B, C_in, N], y [B, C_out, N] float32, W [C_in, C_out, M] c64.  Three launches (pruned forward transform of the
- * real pencils, per-mode contraction, pruned inverse storing the real part).  Shapes: N in {64, 128, 256} with
+ * real pencils, per-mode contraction, pruned inverse storing the real part), small layers two (the last two in one).  Shapes: N in {64, 128, 256} with
  * M <= N/2, or N = 1024 with M <= 128; others TFNO_ERR_UNSUPPORTED.  Workspace:
  * tfno_fno1d_real_workspace_bytes(...) bytes.
  */
@@ -283,9 +291,10 @@ tfno_status tfno_spectral_conv1d_gemm_ifft(const void *x, const void *W, void *y
  * Per-shape dispatch (variant "E" of Table 2, Sec. 5: the best of the variants for each shape), with the rule
  * measured on MI355X: the CGEMM + iFFT variant when C_out > 128, N = 128 and K <= 32 (the fully fused kernel
  * repeats the forward transform for every 128-output slab, which only there costs more than the detour of the
- * truncated spectrum; at N = 256 it covers 256 outputs per workgroup), else the fully fused kernel where one exists, else the three pruned kernels of tfno_spectral_conv1d_pruned where they exist (N = 2048, 4096), else the
- * staged path.  Accepts every valid 1-D shape; same contract and same result as
- * tfno_spectral_conv1d.  Workspace: tfno_workspace_bytes(1, 5, ...) bytes (0 when the fused kernel is chosen).
+ * truncated spectrum; at N = 256 it covers 256 outputs per workgroup), else three kernels with their spectra in y for few rows of
+ * N = 1024 with K <= 128, else the fully fused kernel where one exists, else the three pruned kernels of tfno_spectral_conv1d_pruned
+ * where they exist (N = 2048, 4096), else the staged path.  Accepts every valid 1-D shape; same contract and same result as
+ * tfno_spectral_conv1d.  Workspace: tfno_workspace_bytes(1, 5, ...) bytes (0 when the fused kernel or the spectra in y are chosen).
  */
 tfno_status tfno_spectral_conv1d_auto(const void *x, const void *W, void *y,
                                       int B, int C_in, int C_out, int N, int K, void *stream);

@@ -4,12 +4,12 @@
 // operands split exactly into three BF16 terms), with a workgroup per field and the field transformed along its first axis
 // kept in LDS.  As one kernel per axis, the last axis came first: a lane read (or wrote) a contiguous pencil of its own, so that
 // every load of a wave touched 64 lines, and the half-transformed fields went through memory.  Here the columns of the field are
-// the pencils of the first axis: 32 neighbouring lanes read 256 contiguous bytes of a row.
+// the pencils of the first axis: 16 neighbouring lanes read 256 contiguous bytes of a row, two columns each.
 //
 //   forward  wave = 32 columns (and a share of the rows): T[k1][n2] = sum_{n1} x[n1][n2] w1^(-n1 k1), n1 folded, into LDS;
 //            then the kept rows k1 are 32 pencils of the last axis, whose sum is dealt out to the waves; partial sums meet in LDS
 //   inverse  U[k1][n2] = sum_{k2} Y[k1][k2] w2^(k2 n2) by tiles of 32 output pairs, into LDS; then wave = 32 columns,
-//            y[n1][n2] = sum_{k1} U[k1][n2] w1^(n1 k1), rows n1 and N1 - n1 together, put together in LDS eight or sixteen rows at a time
+//            y[n1][n2] = sum_{k1} U[k1][n2] w1^(n1 k1), rows n1 and N1 - n1 together, put together in LDS sixteen or 32 rows at a time
 //            and stored as whole lines past the caches (pieces of lines stay dirty in the last-level cache, and the
 //            next kernel's reads wait for their write-back)
 //
@@ -212,7 +212,7 @@ k_matgrid_fwd(MatgridArgs a)
         const unsigned place = 8u * (unsigned)first;
         MgSums<2, KT1> acc;
         mg_sum<2, KT1, true, LONG>(acc, tab1, N1, K1, part, a.parts, [&](c64 (*u)[4], c64 (*v)[4], int n) __attribute__((always_inline)) {
-            // (a field has at most 2 MB: 32-bit offsets from a uniform address.  Slots go up to N1 / 2 + 15, rows of the field from 30
+            // (a field has at most 1 MB: 32-bit offsets from a uniform address.  Slots go up to N1 / 2 + 15, rows of the field from 30
             // points on; only slot 0 has no partner)
             const unsigned lo = __umul24((unsigned)n, pitch) + place, hi = __umul24((unsigned)(N1 - n), pitch) + place;
 #pragma unroll
