@@ -61,7 +61,7 @@ static int waves_per_simd(int dir, int N1, int N2, int K1, const Plan &p)
 // Which is faster for a direction, these kernels or a kernel per axis, is a question of rounds and of the longest chain: a field's workgroup takes its blocks of 32 rows
 // (forward) or its tiles of 32 output pairs (inverse) in turn, and what a last short round leaves idle is lost, while a kernel per axis spreads each field over
 // many workgroups and takes a launch more and what its bytes cost.  In microseconds, fitted to whole layers with both kinds of kernels for either direction (3350 drawn shapes of 30 to
-// 512 x 30 to 480 points, 1 to 4500 fields): chosen like this they take 0.838 of the time of kernels per axis (the best of the four combinations 0.833), and 20 of them are more than
+// 512 x 30 to 480 points, 1 to 4500 fields): chosen like this they take 0.837 of the time of kernels per axis (the best of the four combinations 0.833), and 22 of them are more than
 // 3 % slower, at most 12 %.  85 x 85, K 12 x 12, 1024 fields each way: forward 25.2 -> 14.5 us, inverse 29.9 -> 18.7; 158 x 131, 594 and 342
 // fields: 46.6 -> 34.1, 31.2 -> 19.8; 300 x 300, 8 fields 13.0 against 37 us; whole layers with an inverse by these kernels at 320 fields of 273 x 133, K 28 x 8, two rounds, the second
 // a quarter full, 55.1 and 77.3, and a forward transform at 1805 of 77 x 141, K 18 x 10, 66.7 and 93.8.
@@ -77,14 +77,15 @@ bool matgrid_supported(int dir, long long images, int N1, int N2, int K1, int K2
     const int simd = waves_per_simd(dir, N1, N2, K1, p), by_waves = p.waves <= 4 ? 4 * simd / p.waves : simd / ((p.waves + 3) / 4), by_lds = (int)(MOST_LDS / p.lds);
     const long long resident = 256LL * (by_waves < 1 ? 1 : by_waves < by_lds ? by_waves : by_lds);
     const double rounds = (double)((images + resident - 1) / resident);
-    const double field_us = (double)images * N1 * N2 * sizeof(c64) / 5e6, half_us = (double)images * N1 * K2 * 2 * sizeof(c64) / 5e6;
+    const double field_us = (double)images * N1 * N2 * sizeof(c64) / 5e6, half_us = (double)images * N1 * 2 * sizeof(c64) / 5e6;
     const int two1 = K1 > 16 ? 2 : 1, two2 = K2 > 16 ? 2 : 1;
     if (dir < 0) {
         const int columns = (N1 / 32 + p.parts) / p.parts, rows = (N2 / 32 + p.parts2) / p.parts2 * ((two1 * p.parts2 + p.waves - 1) / p.waves);
-        return rounds * (3.5 + 0.45 * columns * (1 + two1) + 0.35 * rows * (1 + two2)) <= 8.0 + 0.9 * field_us + half_us;
+        // (fewer than 16 kept columns cost a kernel per axis what 16 do, the width of its products: 3250 fields of 54 x 39, K 2 x 2 37.5 and 54.2 us the layer)
+        return rounds * (4.0 + 0.45 * columns * (1 + two1) + 0.35 * rows * (1 + two2)) <= 8.5 + 0.9 * field_us + half_us * (K2 > 16 ? K2 : 16);
     }
     const int turns = (N1 / 64 + p.parts) / p.parts;
-    return rounds * (2.5 + turns * (2.0 + 0.8 * two1)) <= 6.5 + 0.7 * field_us + 1.2 * half_us;
+    return rounds * (2.5 + turns * (2.0 + 0.8 * two1)) <= 6.5 + 0.7 * field_us + 1.2 * half_us * K2;
 }
 
 hipError_t matgrid_launch(int dir, const c64 *in, c64 *out, long long images, int C, int N1, int N2, int K1, int K2, hipStream_t s)

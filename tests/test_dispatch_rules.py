@@ -63,11 +63,11 @@ def test_contraction_and_inverse_of_odd_lengths_in_one_kernel(case, on):
     assert rule("_ZN4tfno24matrow_inverse_supportedExiiii", ll, ci, ci, ci, ci)(*case) == on
 
 
-# (direction, fields, N1, N2, K1, K2): both sides odd, both axes of a field in one kernel
+# (direction, fields, N1, N2, K1, K2): both sides odd, both axes of a field in one kernel; many narrow fields with few kept columns as well
 @pytest.mark.parametrize("case,on", [((-1, 1805, 77, 141, 18, 10), False), ((-1, 585, 99, 147, 23, 2), False), ((-1, 3270, 33, 136, 3, 18), False), ((-1, 3780, 45, 51, 19, 2), False),
                                      ((+1, 320, 273, 133, 28, 8), False), ((+1, 640, 93, 142, 32, 7), False), ((+1, 1040, 240, 52, 31, 9), False), ((+1, 1525, 272, 37, 29, 1), False),
                                      ((+1, 1142, 71, 149, 20, 12), False), ((-1, 8, 300, 300, 12, 12), False), ((-1, 100, 40, 40, 33, 9), False), ((-1, 100, 29, 40, 9, 9), False),
                                      ((-1, 1024, 85, 85, 12, 12), True), ((+1, 1024, 85, 85, 12, 12), True), ((-1, 8, 85, 85, 12, 12), True), ((-1, 594, 158, 131, 12, 12), True),
-                                     ((+1, 342, 158, 131, 12, 12), True), ((-1, 126, 200, 120, 32, 17), True)], ids=str)
+                                     ((+1, 342, 158, 131, 12, 12), True), ((-1, 126, 200, 120, 32, 17), True), ((-1, 3250, 54, 39, 2, 2), True), ((-1, 3320, 198, 38, 26, 3), True)], ids=str)
 def test_fields_with_odd_sides_in_one_kernel(case, on):
     assert rule("_ZN4tfno17matgrid_supportedEixiiii", ci, ll, ci, ci, ci, ci)(*case) == on
